@@ -175,7 +175,10 @@ int vlut_mpgemm_token_outer(const uint8_t* packed, float w_scale, const float* a
  *                 NULL when that size is 0
  * For a few tokens (streamed tables, no plan override: always for N <= 2, up to N = 32 while one workgroup per
  * row tile and token pair fits the device at once) a kernel specialised for that case runs instead and needs no
- * workspace; the results are the same numbers.
+ * workspace; the results are the same numbers.  For more tokens (no table given, no plan override) the product runs
+ * on the INT8 matrix cores, the packed bytes taken apart in registers: the same INT32 sums without tables (and without
+ * the workspace, whose size stays that of the lookup plan).  The lookup kernel runs where a plan is forced or a
+ * materialised table is given.
  */
 int vlut_mpgemm(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale,
                 const int16_t* lut_or_null, int64_t M, int64_t K, int64_t N, float* y, int64_t ldy,
@@ -256,7 +259,8 @@ int vlut_pack_weights_g5(const int8_t* w_ternary, int64_t M, int64_t K, uint8_t*
                          void* stream);
 /*
  * As vlut_mpgemm (streamed tables only: there is no materialised-table variant), on a blob written by
- * vlut_pack_weights_g5.  a_q (8-byte aligned) and a_scale as written by vlut_quantize_act for the same K, N.
+ * vlut_pack_weights_g5 (on the matrix cores when K % 4 == 0, packed and a_q are 16-byte aligned and no plan is forced; else
+ * the 243-row lookup kernel).  a_q (8-byte aligned) and a_scale as written by vlut_quantize_act for the same K, N.
  */
 int vlut_mpgemm_g5(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K,
                    int64_t N, float* y, int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes,
@@ -273,9 +277,9 @@ int vlut_query_plan_g5(int64_t M, int64_t K, int64_t N, int* out3);
  * of 4, as the quantiser's K % 4 == 0 demands) four per byte; K5 = 0 or K - K5 = 0 leave one part empty.
  *   blob = [vlut_pack_weights_g5 blob of W[:, :K5]] [vlut_pack_weights blob of W[:, K5:]]
  *   vlut_mixed_k5(K)            K5, or -1 if K is not a positive multiple of 4
- * vlut_mpgemm_mixed runs each part through its kernel in partial-sum mode (a_q: the part's range of activation rows)
- * and adds the parts with the split-K parts in one exact INT32 pass before the scale step: the same numbers as
- * vlut_mpgemm.  The workspace (vlut_workspace_bytes_mixed, never 0) is required; other arguments and errors as in
+ * vlut_mpgemm_mixed runs both parts in one launch on the matrix cores (with a plan override: each part through its
+ * lookup kernel in partial-sum mode, a_q: the part's range of activation rows, and one exact INT32 pass that adds
+ * the parts before the scale step): the same numbers as vlut_mpgemm.  The workspace (vlut_workspace_bytes_mixed, never 0) is required; other arguments and errors as in
  * vlut_mpgemm (streamed tables only).
  */
 int64_t vlut_mixed_k5(int64_t K);
@@ -319,8 +323,8 @@ int vlut_mpgemm_mfma(const uint8_t* packed, float w_scale, const int8_t* a_q, co
 int vlut_set_plan(int J, int R, int waves, int split_k);
 
 /*
- * Reports the launch plan vlut_mpgemm would use for this shape (after any vlut_set_plan override of the
- * calling thread): out4 (host, 4 ints) = { J, R, split_k, number of workgroup tiles }.  (The launch itself has at
+ * Reports the launch plan of the lookup kernel for this shape (after any vlut_set_plan override of the calling
+ * thread; without an override and beyond a few tokens vlut_mpgemm runs on the matrix cores instead): out4 (host, 4 ints) = { J, R, split_k, number of workgroup tiles }.  (The launch itself has at
  * most one workgroup per compute unit; each walks through its share of the tiles.)
  * With few tokens and no override (N <= 2 always; 3 <= N <= 32 when ceil(N/2) copies of the row tiles are at most
  * 256 workgroups and a cost estimate favours it: few rows per workgroup, or a short K), vlut_mpgemm uses a kernel

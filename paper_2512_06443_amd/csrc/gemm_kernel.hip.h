@@ -1,0 +1,395 @@
+// The mpGeMM as a contraction on the INT8 matrix cores: the packed bytes are taken apart in registers, next to the
+// matrix instruction that uses them.  Serves the 2-bit, the 1.60-bit and the mixed packing.
+// Part of the single translation unit vlut.hip (included there, in this order).
+#pragma once
+
+namespace {
+
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
+
+// ---------------------------------------------------------------------------------------------
+// Workgroup = WM x WK waves; tile = 32*RT*WM output rows x 32*CT tokens.  The WK groups of WM waves take every WK-th
+// macro step of K (two packed tile columns: 128 values of K at four weights per byte, 160 at five) and their INT32
+// sums meet in LDS at the end, so that a tile keeps eight waves busy without partial sums in device memory.
+//
+// Weights.  v_mfma_i32_32x32x32_i8 wants, per lane, 16 values of K of one row: a lane loads the 16 packed bytes of
+// its row and tile column (one 16-byte load per macro step, whole 128-byte lines per four rows) and unpacks four bytes
+// at a time into "planes": plane j holds digit j of the four bytes.  That is a fixed permutation of K inside the 16
+// (20) values of a dword, which the activations follow, so no byte is ever moved to its natural place.  Four bytes
+// cost 24 VALU instructions: as 8-bit fractions F of 3^g in 16-bit halves, the next digit is the integer part of 3 F
+// (v_pk_mad_u16 adds the -1 of the digit to the high byte on the way), one byte permute gathers a plane.
+//
+// Activations.  The token-chunked layout [N/8][K][8] goes through LDS as it is, 16 bytes (two k of eight tokens) per
+// lane, and ds_read_b64_tr_b8 transposes it on the way to the registers: 16 lanes point at 8 rows (k) x 16 tokens, lane
+// i receives the eight values of token i.  Which k a row pointer names is free, so the plane order costs nothing.
+// Chunks of eight tokens are pitched so that the 16 eight-byte rows of a read lie in distinct banks.
+//
+// What bounds it (rates of this chip, measured): 16 ns per v_mfma_i32_32x32x32_i8 and SIMD (4.1 POP/s in all), about
+// five VALU instructions fit beside one of them; LDS serves transposing reads at 183 and writes at 71 bytes per clock.
+// With RT x CT = 2 x 4 a wave spends six unpacking instructions per matrix instruction, hence the wide token tile.
+// ---------------------------------------------------------------------------------------------
+struct GemmParams {
+    const uint8_t* packed;
+    const uint8_t* packed4;   // mixed packing: the 2-bit blob of the last K - K5 < 20 values of K, else null
+    const int8_t* a_q;
+    const float* a_scale;
+    const float* w_rows;
+    float* y;
+    int32_t* acc;
+    float w_scale;
+    int M, N, Ka;             // Ka: activation rows per token chunk
+    int Kmain;                // values of K in `packed`
+    int KCn, KCn4, RGtotal, ldy, chunks;
+    int macros;               // macro steps of `packed`
+    int tiles_n, tiles, per_xcd;
+};
+
+template <int GW>
+struct GemmShape {
+    static constexpr int kCol = 16 * GW;                   // values of K per packed tile column
+    static constexpr int kUnits = kCol;                    // 16-byte units of a chunk per macro step: 2 kCol * 8 / 16
+    static constexpr int kP1 = kUnits * 16 + 16;           // second chunk of a pair: half an eight-row bank window further
+    static constexpr int kP2 = (2 * kUnits * 16 + 16 - 128 + 255) / 256 * 256 + 128;   // pairs alternate between the halves of the banks
+};
+
+// Four packed bytes -> GW planes of four INT8 weights, in GW + 1 steps (so that the caller can place matrix instructions
+// between them): start() makes the fractions, plane() the next plane, first weight first.
+// The fraction x / 3^GW in 1/256, rounded up far enough that GW multiplications by three give exactly the GW digits of
+// every x < 3^GW: (809 x + 255) >> 8 for 81 values, x + ((55 x + 1008) >> 10) for 243.
+template <int GW>
+struct Unpack {
+    u16x2 e, o;                                            // bytes 0 and 2, bytes 1 and 3
+    __device__ __forceinline__ void start(unsigned w) {
+        e = __builtin_bit_cast(u16x2, w & 0x00ff00ffu);
+        o = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(0u, w, 0x0c030c01u));
+        if constexpr (GW == 4) {
+            e = (e * u16x2{809, 809} + u16x2{255, 255}) >> (unsigned short)8;
+            o = (o * u16x2{809, 809} + u16x2{255, 255}) >> (unsigned short)8;
+        } else {
+            e += (e * u16x2{55, 55} + u16x2{1008, 1008}) >> (unsigned short)10;
+            o += (o * u16x2{55, 55} + u16x2{1008, 1008}) >> (unsigned short)10;
+        }
+    }
+    __device__ __forceinline__ int plane(u16x2 minus1) {
+        const u16x2 three = {3, 3}, low = {0xff, 0xff};
+        e = e * three + minus1;                            // digit - 1 in the high byte, the next fraction in the low one
+        o = o * three + minus1;
+        const int pl = (int)__builtin_amdgcn_perm(__builtin_bit_cast(unsigned, o), __builtin_bit_cast(unsigned, e), 0x07030501u);
+        e &= low;
+        o &= low;
+        return pl;
+    }
+};
+
+// 0xff00 in both halves, opaque to the compiler: knowing the constant it would multiply a second time, without the
+// addend, for the low bytes.
+__device__ __forceinline__ u16x2 opaque_minus1() {
+    unsigned v = 0xff00ff00u;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("" : "+s"(v));
+#endif
+    return __builtin_bit_cast(u16x2, v);
+}
+
+__device__ __forceinline__ i32x2 lds_read_tr8(unsigned addr) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2*)addr);
+#else
+    (void)addr;
+    return i32x2{0, 0};
+#endif
+}
+
+// LDS bytes of one workgroup: the double-buffered activation tiles of the WK groups, later the sums they exchange;
+// behind them the scales of the tile's tokens and rows.
+template <int GW, int RT, int CT, int WM, int WK>
+constexpr int gemm_lds_bytes() {
+    const int stage = WK * 2 * CT * 2 * GemmShape<GW>::kP2, sums = WM * RT * CT * 4 * (WK - 1) * 1024;
+    return (stage > sums ? stage : sums) + 32 * (CT + RT * WM) * 4;
+}
+
+template <int GW, int RT, int CT, int WM, int WK>
+__global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) {
+    using S = GemmShape<GW>;
+    constexpr int NQ = GW;                                 // matrix instructions per macro step and 32 x 32 tile
+    constexpr int BN = 32 * CT;
+    constexpr int kBuf = CT * 2 * S::kP2;                  // one activation tile
+    constexpr int kGroupThreads = 64 * WM;
+    constexpr int kUnitsTile = BN / 8 * S::kUnits;
+    constexpr int kPer = (kUnitsTile + kGroupThreads - 1) / kGroupThreads;
+    constexpr int BM = 32 * RT * WM;
+    constexpr unsigned kZero = GW == 4 ? kZeroIdx4 : 0x79797979u;      // four bytes of the all-zero pattern
+    constexpr int kScales = gemm_lds_bytes<GW, RT, CT, WM, WK>() - (BN + BM) * 4;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WM, wk = wave / WM;
+    const int i = lane & 31, kb = lane >> 5;
+
+    // tiles in a list with the token tiles of a row tile next to each other; each XCD takes a contiguous range of it, so
+    // that the workgroups that unpack the same weights share an L2
+    const int tile = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
+    if (tile >= p.tiles) return;
+    const int mt = tile / p.tiles_n, nt = tile - mt * p.tiles_n;
+    const int m_wave = (mt * WM + wm) * 32 * RT;
+    const int chunk0 = nt * (BN / 8);
+
+    // Loads: 32-bit offsets from the uniform bases of the tile (a tile spans less than 2^31 bytes of either operand).
+    // ---- weights: this lane's row of each row tile (rows past the padded matrix read data that is never stored; tile
+    //      columns past the end of K are clamped and replaced by the all-zero pattern when they are unpacked)
+    const int rg0 = mt * (BM / 4);
+    const uint8_t* wbase = p.packed + (size_t)rg0 * p.KCn * 64;
+    unsigned woff[RT], wend[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        const int rgl = min((wm * RT + rt) * 8 + (i >> 2), p.RGtotal - 1 - rg0);
+        const unsigned row = (unsigned)rgl * (unsigned)p.KCn * 64u + (unsigned)((i & 3) * 16);
+        woff[rt] = row + (unsigned)(kb * 64);
+        wend[rt] = row + (unsigned)(p.KCn - 1) * 64u;
+    }
+    auto load_weights = [&](int macro, i32x4 (&w)[RT]) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) w[rt] = *(const i32x4*)(wbase + min(woff[rt] + (unsigned)macro * 128u, wend[rt]));
+    };
+    auto keep_mask = [&](int macro) { return 2 * macro + kb < p.KCn ? 0xffffffffu : 0u; };
+    // ---- activations: thread of the group -> 16-byte units of the tile; chunks past the last and rows past K are
+    //      clamped (such tokens are not stored, such rows meet zero weights)
+    const int gt = tid - wk * kGroupThreads;
+    const int8_t* abase = p.a_q + (size_t)chunk0 * p.Ka * 8;
+    unsigned aoff[kPer], aend[kPer], adst[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int idx = min(gt + u * kGroupThreads, kUnitsTile - 1);
+        const int c = idx / S::kUnits, unit = idx - c * S::kUnits;
+        const unsigned row = (unsigned)min(c, p.chunks - 1 - chunk0) * (unsigned)p.Ka * 8u;
+        aoff[u] = row + (unsigned)unit * 16u;
+        aend[u] = row + (unsigned)(p.Kmain / 2 - 1) * 16u;
+        adst[u] = (unsigned)((wk * 2) * kBuf + (c >> 1) * S::kP2 + (c & 1) * S::kP1 + unit * 16);
+    }
+    auto load_acts = [&](int macro, i32x4 (&a)[kPer]) {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) a[u] = *(const i32x4*)(abase + min(aoff[u] + (unsigned)macro * (S::kUnits * 16u), aend[u]));
+    };
+    auto store_acts = [&](int buf, const i32x4 (&a)[kPer]) {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)
+            if (kUnitsTile % kGroupThreads == 0 || u + 1 < kPer || gt + u * kGroupThreads < kUnitsTile)
+                *(lds_i32x4*)(adst[u] + buf * kBuf) = a[u];
+    };
+    // ---- transposing reads: lane of a group of 16 -> row r of the eight, chunk half; the four groups are tokens 0-15
+    //      and 16-31 of K block 0, then of K block 1
+    const int r8 = (lane & 15) >> 1;
+    const unsigned rd = (unsigned)((wk * 2) * kBuf + ((lane >> 4) & 1) * S::kP2 + (lane & 1) * S::kP1 + kb * S::kCol * 8 + (r8 & 3) * GW * 8);
+    const unsigned rd_a = rd + (r8 >> 2) * 8;              // planes j and j + 1 of one dword
+    const unsigned rd_b = rd + (r8 >> 2) * 5 * 4 * 8;      // (five weights per byte) plane 4 of two neighbouring dwords
+
+    i32x16 acc[RT][CT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = i32x16{};
+
+    // half (0 or 1) of the activation operand ct of matrix instructions q
+    auto read_half = [&](int buf, int q, int ct, int half) {
+        const unsigned at = (unsigned)(buf * kBuf + ct * 2 * S::kP2);
+        if (GW == 4 || q < 4) return lds_read_tr8(rd_a + at + (4 * GW * q + 2 * half) * 8);      // planes 0..3 of dword q
+        return lds_read_tr8(rd_b + at + (half * 2 * 4 * GW + 4) * 8);                             // plane 4 of the four dwords
+    };
+    unsigned left[RT][4];                                  // plane 4 of the dwords of the current macro step
+
+    // ---- the K loop: macro steps wk, wk + WK, ... of this group (the groups run the same number of passes; a step past
+    //      the end has zero weights).  Loads run two steps ahead of their use.
+    const int passes = (p.macros + WK - 1) / WK;
+    i32x4 w0[RT], w1[RT], a0[kPer];
+    load_weights(wk, w0);
+    load_acts(wk, a0);
+    // (mixed packing) the last < 20 values of K: at most four packed bytes per row, 16 activation rows per chunk
+    i32x4 at4 = {0, 0, 0, 0};
+    unsigned w4[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) w4[rt] = kZeroIdx4;
+    if (GW == 5 && p.packed4) {
+        if (tid < BN) {
+            const int row2 = min((p.Kmain >> 1) + (tid & 7), (p.Ka >> 1) - 1);
+            at4 = *(const i32x4*)(p.a_q + (size_t)min(chunk0 + (tid >> 3), p.chunks - 1) * p.Ka * 8 + (size_t)row2 * 16);
+        }
+        if (wk == 0 && kb == 0) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const int row = m_wave + 32 * rt + i;
+                w4[rt] = *(const unsigned*)(p.packed4 + (size_t)min(row >> 2, p.RGtotal - 1) * p.KCn4 * 64 + (row & 3) * 16);
+            }
+        }
+    }
+    for (int j = tid; j < BN + BM; j += 64 * WM * WK)
+        *(lds_i32*)(unsigned)(kScales + j * 4) = __builtin_bit_cast(
+            int, j < BN ? p.a_scale[min(nt * BN + j, p.N - 1)] : (p.w_rows ? p.w_rows[min(mt * BM + j - BN, p.M - 1)] : p.w_scale));
+    store_acts(0, a0);
+    load_acts(wk + WK, a0);
+    load_weights(wk + WK, w1);                             // (requested after them, as in the loop: loads return in order)
+    i32x4 a[CT], b[RT];
+    Unpack<GW> un[RT];
+    const u16x2 minus1 = opaque_minus1();
+    // step st of making the weight operands of matrix instructions q from the raw dwords w
+    auto unpack_step = [&](const i32x4 (&w)[RT], unsigned keep, int q, int st, i32x4 (&o)[RT]) {
+        const int rt = st / (GW + 1), j = st % (GW + 1);
+        if (q >= 4) {
+            if (j == 0) o[rt] = i32x4{(int)left[rt][0], (int)left[rt][1], (int)left[rt][2], (int)left[rt][3]};
+        } else if (j == 0) {
+            un[rt].start(((unsigned)w[rt][q] & keep) | (kZero & ~keep));
+        } else {
+            const int pl = un[rt].plane(minus1);
+            if (j <= 4) o[rt][j - 1] = pl;
+            else left[rt][q] = (unsigned)pl;
+        }
+    };
+#pragma unroll
+    for (int st = 0; st < RT * (GW + 1); ++st) unpack_step(w0, keep_mask(wk), 0, st, b);
+    wg_barrier_lds();
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+        const i32x2 lo = read_half(0, 0, ct, 0), hi = read_half(0, 0, ct, 1);
+        a[ct] = i32x4{lo.x, lo.y, hi.x, hi.y};
+    }
+    // One macro step.  The operands of matrix instructions q + 1 are read and unpacked between the matrix instructions q, a
+    // few vector instructions behind each of them: the matrix core works 32 cycles on one, the vector unit is free for
+    // 28 of them.  (The order is pinned: left to itself the compiler gathers the vector instructions in blocks.)  The
+    // one barrier stands before the last group: by then every wave holds the last operands of this tile, so the other
+    // buffer (filled during this step) may be read and this one overwritten.
+    auto macro_step = [&](int buf, int macro, i32x4 (&w)[RT], const i32x4 (&w_next)[RT]) {
+        const unsigned keep = keep_mask(macro), keep_next = keep_mask(macro + WK);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const bool last = q + 1 == NQ;
+            if (q == 0) {
+                store_acts(buf ^ 1, a0);
+                load_acts(macro + 2 * WK, a0);
+            }
+            if (last) {
+                wg_barrier_lds();
+                load_weights(macro + 2 * WK, w);
+            }
+            i32x4 an[CT], bn[RT];
+            constexpr int G = CT * RT, NS = RT * (GW + 1), NR = 2 * CT;
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                __builtin_amdgcn_sched_barrier(0);
+                acc[g % RT][g / RT] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[g / RT], b[g % RT], acc[g % RT][g / RT], 0, 0, 0);
+#pragma unroll
+                for (int r = g * NR / G; r < (g + 1) * NR / G; ++r) {
+                    const i32x2 v = read_half(last ? buf ^ 1 : buf, last ? 0 : q + 1, r >> 1, r & 1);
+                    an[r >> 1][2 * (r & 1)] = v.x;
+                    an[r >> 1][2 * (r & 1) + 1] = v.y;
+                }
+#pragma unroll
+                for (int st = g * NS / G; st < (g + 1) * NS / G; ++st) {
+                    if (last) unpack_step(w_next, keep_next, 0, st, bn);
+                    else unpack_step(w, keep, q + 1, st, bn);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) a[ct] = an[ct];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) b[rt] = bn[rt];
+        }
+    };
+    for (int t = 0; t < passes; t += 2) {
+        macro_step(0, wk + t * WK, w0, w1);
+        if (t + 1 < passes) macro_step(1, wk + (t + 1) * WK, w1, w0);
+    }
+    wg_barrier_lds();
+    if (GW == 5 && p.packed4) {                            // its planes are those of four weights per byte
+        if (tid < BN) *(lds_i32x4*)(unsigned)((tid >> 4) * S::kP2 + ((tid >> 3) & 1) * S::kP1 + (tid & 7) * 16) = at4;
+        wg_barrier_lds();
+        if (wk == 0) {
+            const unsigned rd4 = (unsigned)(((lane >> 4) & 1) * S::kP2 + (lane & 1) * S::kP1 + (r8 & 3) * 4 * 8 + (r8 >> 2) * 8);
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                Unpack<4> u;
+                u.start(w4[rt]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) b[rt][j] = u.plane(minus1);
+            }
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const i32x2 lo = lds_read_tr8(rd4 + ct * 2 * S::kP2), hi = lds_read_tr8(rd4 + ct * 2 * S::kP2 + 16);
+                a[ct] = i32x4{lo.x, lo.y, hi.x, hi.y};
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) acc[rt][ct] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ct], b[rt], acc[rt][ct], 0, 0, 0);
+            }
+        }
+        wg_barrier_lds();
+    }
+
+    // ---- epilogue.  A lane holds, of each 32 x 32 product, output row i and the tokens 8 g + 4 kb + 0..3 in registers 4 g
+    //      .. 4 g + 3: "quad" g.  The quads are dealt out over the WK groups, which add the other groups' sums and store.
+    constexpr int Q = RT * CT * 4;
+    constexpr int kOwn = (Q + WK - 1) / WK;                // quads per group
+    if (WK > 1) {
+#pragma unroll
+        for (int qd = 0; qd < Q; ++qd) {
+            const int owner = qd / kOwn;
+            if (owner != wk) {
+                const i32x16& v = acc[qd / 4 / CT][qd / 4 % CT];
+                const int g = qd & 3;
+                const int slot = wk - (wk > owner ? 1 : 0);
+                *(lds_i32x4*)(unsigned)((((wm * Q + qd) * (WK - 1)) + slot) * 1024 + lane * 16) = i32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+            }
+        }
+        wg_barrier_lds();
+    }
+#pragma unroll
+    for (int qd = 0; qd < Q; ++qd) {
+        if (qd / kOwn != wk) continue;
+        const int rt = qd / 4 / CT, ct = qd / 4 % CT, g = qd & 3;
+        int v[4] = {acc[rt][ct][4 * g], acc[rt][ct][4 * g + 1], acc[rt][ct][4 * g + 2], acc[rt][ct][4 * g + 3]};
+#pragma unroll
+        for (int s = 0; s < WK - 1; ++s) {
+            const i32x4 o = *(const lds_i32x4*)(unsigned)((((wm * Q + qd) * (WK - 1)) + s) * 1024 + lane * 16);
+            v[0] += o.x; v[1] += o.y; v[2] += o.z; v[3] += o.w;
+        }
+        const int ml = (wm * RT + rt) * 32 + i, nl = 32 * ct + 8 * g + 4 * kb;
+        const int m = mt * BM + ml, n = nt * BN + nl;
+        if (m >= p.M) continue;
+        if (p.y) {
+            const i32x4 sc = *(const lds_i32x4*)(unsigned)(kScales + nl * 4);
+            const float ws = __builtin_bit_cast(float, *(const lds_i32*)(unsigned)(kScales + (BN + ml) * 4));
+            float* dst = p.y + (size_t)n * p.ldy + m;
+#pragma unroll
+            for (int e = 0; e < 4; ++e, dst += p.ldy)
+                if (n + e < p.N) *dst = (float)v[e] * (ws * __builtin_bit_cast(float, (int)sc[e]));
+        }
+        if (p.acc) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (n + e < p.N) p.acc[(size_t)m * p.N + n + e] = v[e];
+        }
+    }
+}
+
+// The tile shapes that are built and what a launch costs with them, in us, fitted to launches of 1 to 8 workgroups per
+// compute unit n at K = 1280 and 5120: base + n * fixed + passes of the K loop * (lat + n * pass).  First value four, second
+// five weights per byte.  `fixed` is the store of the tile (4.5 to 5 TB/s over all compute units, not overlapped: the
+// workgroups of a round end together), `pass` one macro step of every K group.
+struct GemmTile {
+    int rt, ct, wm, wk;
+    double base[2], fixed[2], lat[2], pass[2];
+    constexpr int rows() const { return 32 * rt * wm; }
+    constexpr int tokens() const { return 32 * ct; }
+};
+constexpr GemmTile kGemmTiles[] = {
+    {2, 4, 4, 2, {4.2, 4.2}, {6.5, 7.0}, {0.00, 0.10}, {1.43, 1.90}},
+    {1, 4, 4, 2, {3.0, 3.0}, {3.8, 4.0}, {0.00, 0.03}, {0.90, 1.14}},
+    {1, 4, 2, 4, {1.9, 0.0}, {4.1, 0.0}, {0.00, 0.00}, {1.13, 0.00}},      // long K; (five weights: more LDS than there is)
+    {1, 2, 2, 4, {2.9, 2.2}, {1.3, 2.4}, {0.08, 0.00}, {0.64, 0.95}},
+    {1, 1, 2, 4, {2.8, 2.8}, {0.75, 1.1}, {0.13, 0.08}, {0.45, 0.60}},
+    {1, 1, 1, 8, {2.6, 1.5}, {1.0, 2.2}, {0.11, 0.00}, {0.54, 0.88}},
+};
+constexpr int kGemmTileCount = (int)(sizeof(kGemmTiles) / sizeof(kGemmTiles[0]));
+constexpr bool gemm_tile_built(int gw, int tile) { return gw == 4 || kGemmTiles[tile].pass[1] > 0.0; }
+
+}  // namespace

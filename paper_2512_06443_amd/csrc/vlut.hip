@@ -33,6 +33,7 @@
 #include "lookup_kernel.hip.h"
 #include "mfma_kernel.hip.h"
 #include "lookup5_kernel.hip.h"
+#include "gemm_kernel.hip.h"
 #include "narrow_kernel.hip.h"
 #include "small_kernels.hip.h"
 
@@ -566,6 +567,75 @@ int launch_lookup5_r(int R, const Lookup5Params& p, int grid, hipStream_t stream
     return launch_lookup5_by_r<NEED32>(R, p, grid, stream);
 }
 
+// ---- matrix-core path (gemm_kernel): every product with streamed tables, unless a plan of the lookup kernels is forced
+double gemm_cost(int gw, int tile, int64_t M, int64_t macros, int64_t N) {
+    const GemmTile& t = kGemmTiles[tile];
+    const int g = gw - 4;
+    const int64_t tiles = ((M + t.rows() - 1) / t.rows()) * ((N + t.tokens() - 1) / t.tokens());
+    const double n = (double)((tiles + 255) / 256), passes = (double)((macros + t.wk - 1) / t.wk);
+    return t.base[g] + n * t.fixed[g] + passes * (t.lat[g] + n * t.pass[g]);
+}
+
+int choose_gemm_tile(int gw, int64_t M, int64_t macros, int64_t N) {
+    int best = -1;
+    double best_cost = 1e300;
+    for (int i = 0; i < kGemmTileCount; ++i) {
+        if (!gemm_tile_built(gw, i)) continue;
+        const double c = gemm_cost(gw, i, M, macros, N);
+        if (c < best_cost) { best_cost = c; best = i; }
+    }
+    return best;
+}
+
+template <int GW, int I>
+int launch_gemm_t(const GemmParams& p, hipStream_t stream) {
+    constexpr GemmTile t = kGemmTiles[I];
+    auto kfn = gemm_kernel<GW, t.rt, t.ct, t.wm, t.wk>;
+    constexpr int lds = gemm_lds_bytes<GW, t.rt, t.ct, t.wm, t.wk>();
+    static_assert(lds <= 160 * 1024, "LDS of a workgroup");
+    static std::atomic<unsigned> attr_done{0};   // one bit per device: the attribute belongs to the device's copy
+    if (!allow_dynamic_lds((const void*)kfn, lds, attr_done)) return VLUT_ERR_DEVICE;
+    GemmParams q = p;
+    q.tiles_n = (q.N + t.tokens() - 1) / t.tokens();
+    q.tiles = (q.M + t.rows() - 1) / t.rows() * q.tiles_n;
+    q.per_xcd = (q.tiles + 7) / 8;
+    hipLaunchKernelGGL(kfn, dim3(8 * q.per_xcd), dim3(64 * t.wm * t.wk), lds, stream, q);
+    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+}
+
+template <int GW, int I = 0>
+int launch_gemm_tile(int tile, const GemmParams& p, hipStream_t stream) {
+    if constexpr (I >= kGemmTileCount) {
+        return VLUT_ERR_UNSUPPORTED;
+    } else {
+        if constexpr (gemm_tile_built(GW, I)) {
+            if (tile == I) return launch_gemm_t<GW, I>(p, stream);
+        }
+        return launch_gemm_tile<GW, I + 1>(tile, p, stream);
+    }
+}
+
+// K5 values of K five to a byte (0: none), the rest of K four to a byte behind them (at most 16 values if K5 > 0).
+int launch_gemm(const uint8_t* packed, float w_scale, const float* w_rows, const int8_t* a_q, const float* a_scale, int64_t M,
+                int64_t K, int64_t K5, int64_t N, float* y, int64_t ldy, int32_t* acc, hipStream_t stream) {
+    GemmParams p;
+    std::memset(&p, 0, sizeof(p));
+    const int gw = K5 > 0 ? 5 : 4;
+    p.packed = packed; p.a_q = a_q; p.a_scale = a_scale; p.w_rows = w_rows; p.y = y; p.acc = acc; p.w_scale = w_scale;
+    p.M = (int)M; p.N = (int)N; p.Ka = (int)K; p.ldy = (int)ldy; p.RGtotal = (int)((M + 3) / 4); p.chunks = (int)((N + 7) / 8);
+    p.Kmain = (int)(K5 > 0 ? K5 : K);
+    p.KCn = (p.Kmain / gw + 15) / 16;
+    p.macros = (p.KCn + 1) / 2;
+    if (K5 > 0 && K > K5) {
+        p.packed4 = packed + (size_t)p.RGtotal * p.KCn * 64;
+        p.KCn4 = (int)(((K - K5) / 4 + 15) / 16);
+    }
+    const int tile = choose_gemm_tile(gw, M, p.macros, N);
+    return gw == 5 ? launch_gemm_tile<5>(tile, p, stream) : launch_gemm_tile<4>(tile, p, stream);
+}
+
+bool lookup_plan_forced() { return t_forced.Jlog >= 0 || t_forced.R != 0 || t_forced.S != 0 || t_forced.BW != 0; }
+
 // ---- comparison path: tokens per workgroup from N, K split so that few tiles still give every CU a few workgroups
 struct MfmaPlan {
     int BN, tiles_m, tiles_n, S, steps_per_split, grid;
@@ -850,6 +920,8 @@ static int mpgemm_impl(const uint8_t* packed, float w_scale, const float* w_rows
         if (!workspace) return VLUT_ERR_NULL;
         if (workspace_bytes < ws_need) return VLUT_ERR_SMALL_BUFFER;
     }
+    if (!lut_or_null && !lookup_plan_forced())
+        return launch_gemm(packed, w_scale, w_rows, a_q, a_scale, M, K, 0, N, y, ldy, acc_or_null, (hipStream_t)stream);
     LookupParams p;
     std::memset(&p, 0, sizeof(p));
     p.packed = packed; p.a_q = a_q; p.a_scale = a_scale; p.lut = lut_or_null;
@@ -1067,6 +1139,10 @@ int vlut_mpgemm_g5(const uint8_t* packed, float w_scale, const int8_t* a_q, cons
         if (!workspace) return VLUT_ERR_NULL;
         if (workspace_bytes < ws_need) return VLUT_ERR_SMALL_BUFFER;
     }
+    // the matrix-core path reads both operands 16 bytes at a time, so it wants the alignment and K % 4 == 0 (two activation
+    // rows of a chunk are 16 bytes) that this call does not demand
+    if (t_forced5.R == 0 && t_forced5.S == 0 && K % 4 == 0 && (uintptr_t)packed % 16 == 0 && (uintptr_t)a_q % 16 == 0)
+        return launch_gemm(packed, w_scale, nullptr, a_q, a_scale, M, K, K, N, y, ldy, acc_or_null, (hipStream_t)stream);
     Lookup5Params p;
     std::memset(&p, 0, sizeof(p));
     p.packed = packed; p.a_q = a_q; p.a_scale = a_scale; p.y = y; p.acc = acc_or_null; p.ws = (int32_t*)workspace;
@@ -1167,6 +1243,8 @@ int vlut_mpgemm_mixed(const uint8_t* packed, float w_scale, const int8_t* a_q, c
     if (!workspace) return VLUT_ERR_NULL;
     if (workspace_bytes < need) return VLUT_ERR_SMALL_BUFFER;
     hipStream_t s = (hipStream_t)stream;
+    if (t_forced5.R == 0 && t_forced5.S == 0 && !lookup_plan_forced() && (uintptr_t)packed % 16 == 0)
+        return launch_gemm(packed, w_scale, nullptr, a_q, a_scale, M, K, K5, N, y, ldy, acc_or_null, s);
     if (K5 > 0) {
         const Derived5 d = derive5(pl5, M, K5, N);
         Lookup5Params p;

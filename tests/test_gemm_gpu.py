@@ -1,0 +1,78 @@
+"""The matrix-core path against the oracle at the edges of its tiles: every packed byte value, rows and tokens next to multiples
+of the tile shapes, K with an odd number of packed tile columns, fewer macro steps than groups, the 2-bit tail of the
+mixed packing at each of its lengths.  Integers are compared exactly; an output is one whole number below 2^24 times two
+fp32 scales, two roundings, hence 2 * 2^-24 < 1.2e-7 relative to the oracle's fp64 product."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2512_06443_amd import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+REL = 2.0 ** -23
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2512_06443_amd import binding
+    binding.lib()
+    binding.set_plan(0, 0, 0, 0)
+    binding.set_plan_g5(0, 0)
+    return binding
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def check(B, W, s, x, packings=("p4", "mixed"), tag=""):
+    M, K = W.shape
+    N = x.shape[0]
+    print(f"gemm case {tag} M={M} K={K} N={N}", flush=True)
+    _, _, acc_ref, y_ref = O.mpgemm(W, s, x)
+    a_q, a_s = B.quantize_act(dev(x))
+    calls = {"p4": (B.pack_weights, B.mpgemm), "g5": (B.pack_weights_g5, B.mpgemm_g5), "mixed": (B.pack_weights_mixed, B.mpgemm_mixed)}
+    for name in packings:
+        pack, mpgemm = calls[name]
+        ybig = torch.full((N + 1, M + 3), -7.0, device="cuda")
+        y, acc = mpgemm(pack(dev(W)), float(s), a_q, a_s, M, y=ybig[:N, :M], want_acc=True)
+        torch.cuda.synchronize()
+        assert np.array_equal(acc.cpu().numpy(), acc_ref), name
+        yy = y.cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(yy - y_ref) <= REL * np.abs(y_ref)), name
+        full = ybig.cpu().numpy()
+        assert np.all(full[:, M:] == -7.0) and np.all(full[N:] == -7.0), name
+
+
+@pytest.mark.parametrize("g,K", [(4, 324), (5, 1220)])
+def test_every_packed_byte(B, g, K):
+    # row r holds pattern r in its group r and zeros elsewhere; all patterns in one row as well
+    n = 3 ** g
+    digits = np.array([[(v // 3 ** (g - 1 - j)) % 3 - 1 for j in range(g)] for v in range(n)], np.int8)
+    W = np.zeros((n + 1, K), np.int8)
+    for v in range(n):
+        W[v, v * g:(v + 1) * g] = digits[v]
+    W[n, :n * g] = digits.reshape(-1)
+    check(B, W, np.float32(0.5), wl.activations(11, 40, K), ("p4",) if g == 4 else ("g5",), tag=f"all bytes g={g}")
+
+
+@pytest.mark.parametrize("M,K,N", [(31, 64, 33), (32, 128, 32), (65, 192, 31), (33, 4160, 65), (127, 516, 64), (129, 2564, 96),
+                                   (3840, 260, 1000), (4099, 1028, 1030), (8193, 132, 520), (513, 9220, 515), (7000, 2580, 127)])
+def test_tile_edges(B, M, K, N):
+    W, s, x = wl.small_case(1200 + M + N, M, K, N)
+    check(B, W, s, x, tag="edges")
+
+
+@pytest.mark.parametrize("K", [20, 24, 28, 32, 36, 176, 336, 2564, 2576])
+def test_tail_lengths_of_the_mixed_packing(B, K):
+    W, s, x = wl.small_case(1300 + K, 70, K, 37)
+    check(B, W, s, x, ("mixed", "g5") if K % 20 == 0 else ("mixed",), tag="tail")
+
+
+def test_extremes_of_the_accumulator(B):
+    W = np.ones((40, 8192), np.int8)
+    W[1::2] = -1
+    x = np.ones((35, 8192), np.float32)
+    x[::3] = -1.0
+    check(B, W, np.float32(1.0), x, tag="all +-127")
