@@ -34,6 +34,7 @@
 #include "mfma_kernel.hip.h"
 #include "lookup5_kernel.hip.h"
 #include "gemm_kernel.hip.h"
+#include "decode_kernel.hip.h"
 #include "narrow_kernel.hip.h"
 #include "small_kernels.hip.h"
 
@@ -634,6 +635,35 @@ int launch_gemm(const uint8_t* packed, float w_scale, const float* w_rows, const
     return gw == 5 ? launch_gemm_tile<5>(tile, p, stream) : launch_gemm_tile<4>(tile, p, stream);
 }
 
+// ---- up to sixteen tokens from fp32 (decode_kernel): one launch, every workgroup quantises all tokens.  Measured against
+//      quantiser + gemm_kernel (about 4 us more launches): 2560 x 2560 x 16 7.0 us, 13824 x 2560 x 16 8.8 us (10.5 us as two), but
+//      2560 x 6912 x 16 15.0 us (11.5 us): the rows of x are read by every workgroup, so N * K is bounded; beyond 128 rows for
+//      each of 256 workgroups that work is repeated, so more than two tokens bound M.
+constexpr int64_t kDecodeMaxValues = 65536;
+bool decode_applies(int64_t M, int64_t K, int64_t N) {
+    return N <= 16 && N * K <= kDecodeMaxValues && (M <= 256 * 128 || N <= 2);
+}
+
+template <int T, int MT>
+int launch_decode_t(const DecodeParams& p, hipStream_t stream) {
+    auto kfn = decode_kernel<T, MT>;
+    const int lds = decode_lds_bytes(T, p.macros);
+    if (lds > 160 * 1024) return VLUT_ERR_UNSUPPORTED;      // (cannot happen within decode_applies)
+    static std::atomic<unsigned> attr_done{0};   // one bit per device: the attribute belongs to the device's copy
+    if (!allow_dynamic_lds((const void*)kfn, 160 * 1024, attr_done)) return VLUT_ERR_DEVICE;
+    hipLaunchKernelGGL(kfn, dim3((unsigned)((p.M + 16 * MT - 1) / (16 * MT))), dim3(64 * kDecodeWaves), lds, stream, p);
+    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+}
+
+// Row tiles per workgroup: the fewest whose grid is one round of workgroups (more waves per row tile split K finer).
+template <int T>
+int launch_decode(const DecodeParams& p, hipStream_t stream) {
+    if (p.M <= 256 * 16) return launch_decode_t<T, 1>(p, stream);
+    if (p.M <= 256 * 32) return launch_decode_t<T, 2>(p, stream);
+    if (p.M <= 256 * 64) return launch_decode_t<T, 4>(p, stream);
+    return launch_decode_t<T, 8>(p, stream);
+}
+
 bool lookup_plan_forced() { return t_forced.Jlog >= 0 || t_forced.R != 0 || t_forced.S != 0 || t_forced.BW != 0; }
 
 // ---- comparison path: tokens per workgroup from N, K split so that few tiles still give every CU a few workgroups
@@ -1019,6 +1049,18 @@ int vlut_mpgemm_f32(const uint8_t* packed, float w_scale, const float* w_scale_r
     const float w_one = w_rows ? 1.0f : w_scale;
     char* ws = (char*)workspace;
 
+    if (!lookup_plan_forced() && decode_applies(M, K, N)) {
+        DecodeParams q;
+        std::memset(&q, 0, sizeof(q));
+        q.packed = packed; q.x = x; q.w_rows = w_rows; q.y = y; q.acc = acc_or_null; q.a_scale_out = a_scale_out_or_null;
+        q.ldx = ldx; q.w_scale = w_one; q.M = (int)M; q.N = (int)N; q.K = (int)K; q.KCn = (int)((K / 4 + 15) / 16);
+        q.RGtotal = (int)((M + 3) / 4); q.ldy = (int)ldy; q.macros = (q.KCn + 3) / 4; q.x_vec = x_vec;
+        if (N == 1) return launch_decode<1>(q, s);
+        if (N == 2) return launch_decode<2>(q, s);
+        if (N <= 4) return launch_decode<4>(q, s);
+        if (N <= 8) return launch_decode<8>(q, s);
+        return launch_decode<16>(q, s);
+    }
     if (L.kind == kF32Narrow) {
         const NarrowPlan np = narrow_plan(M, K, N);
         NarrowParams q;

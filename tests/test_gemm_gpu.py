@@ -76,3 +76,23 @@ def test_extremes_of_the_accumulator(B):
     x = np.ones((35, 8192), np.float32)
     x[::3] = -1.0
     check(B, W, np.float32(1.0), x, tag="all +-127")
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 8, 9, 15, 16])
+def test_few_tokens_from_fp32(B, N):
+    # one launch that quantises inside: every count of token slots, rows next to 16, 32, 64 and 128 per workgroup, K with
+    # one to more than twelve passes of 256 values per wave, the last ones ragged; unaligned rows of x
+    for M, K in ((1, 4), (17, 260), (4097, 1028), (8200, 512), (16400, 64), (130, 3844), (50, 65536 // N // 4 * 4)):
+        W, s, x = wl.small_case(1400 + M + N, M, K, N)
+        x[N // 2] *= 1e-3
+        _, s_ref, acc_ref, y_ref = O.mpgemm(W, s, x)
+        packed = B.pack_weights(dev(W))
+        odd = torch.full((N, K + 3), 9e9, device="cuda")
+        odd[:, 1:K + 1] = dev(x)
+        for xd in (dev(x), odd[:, 1:K + 1]):
+            print(f"decode case M={M} K={K} N={N}", flush=True)
+            y, acc, sc = B.mpgemm_f32(packed, float(s), xd, M, want_acc=True, want_scales=True)
+            torch.cuda.synchronize()
+            assert np.array_equal(acc.cpu().numpy(), acc_ref)
+            assert np.array_equal(sc.cpu().numpy().view(np.uint32), s_ref.view(np.uint32))
+            assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - y_ref) <= REL * np.abs(y_ref))
