@@ -102,8 +102,13 @@ def _check(status: int, where: str) -> None:
         raise VlutError(status, where)
 
 
+# The raw handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object around the same
+# handle, 2.7 us of a call that takes 8.7; asking for the handle itself takes 0.1.
+_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -276,22 +281,25 @@ def mpgemm_f32(packed: torch.Tensor, w_scale, x: torch.Tensor, M: int, y: Option
     """Runs vlut_mpgemm_f32 on fp32 activations x [N][K] (row stride >= K).  w_scale: a float, or an fp32 [M]
     tensor on the GPU with one weight scale per output row.  Returns (y [N][M], acc or None, a_scale or None)."""
     assert x.is_cuda and x.dtype == torch.float32 and x.dim() == 2 and x.stride(1) == 1
+    L = _lib or lib()
     N, K = x.shape
-    dev = x.device
     rows = w_scale if isinstance(w_scale, torch.Tensor) else None
     if rows is not None:
         assert rows.is_cuda and rows.dtype == torch.float32 and rows.numel() == M
     if y is None:
-        y = torch.empty((N, M), dtype=torch.float32, device=dev)
-    acc = torch.empty((M, N), dtype=torch.int32, device=dev) if want_acc else None
-    scales = torch.empty(N, dtype=torch.float32, device=dev) if want_scales else None
-    ws_bytes = lib().vlut_workspace_bytes_f32(M, K, N)
-    if workspace is None and ws_bytes:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
-    rc = lib().vlut_mpgemm_f32(_ptr(packed), 1.0 if rows is not None else float(w_scale), _ptr(rows), _ptr(x), x.stride(0),
-                               M, K, N, _ptr(y), y.stride(0), _ptr(acc), _ptr(scales), _ptr(workspace),
-                               0 if workspace is None else workspace.numel() * workspace.element_size(), _stream())
-    _check(rc, "vlut_mpgemm_f32")
+        y = torch.empty((N, M), dtype=torch.float32, device=x.device)
+    acc = torch.empty((M, N), dtype=torch.int32, device=x.device) if want_acc else None
+    scales = torch.empty(N, dtype=torch.float32, device=x.device) if want_scales else None
+    if workspace is None:
+        ws_bytes = L.vlut_workspace_bytes_f32(M, K, N)
+        if ws_bytes:
+            workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=x.device)
+    else:
+        ws_bytes = workspace.numel() * workspace.element_size()
+    rc = L.vlut_mpgemm_f32(packed.data_ptr(), 1.0 if rows is not None else float(w_scale), _ptr(rows), x.data_ptr(), x.stride(0),
+                           M, K, N, y.data_ptr(), y.stride(0), _ptr(acc), _ptr(scales), _ptr(workspace), ws_bytes, _stream())
+    if rc != VLUT_OK:
+        raise VlutError(rc, "vlut_mpgemm_f32")
     return y, acc, scales
 
 
