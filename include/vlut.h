@@ -16,10 +16,11 @@
  *   - The caller owns every buffer.  The library allocates no device memory.
  *     State it keeps between calls: (i) the per-thread tuning override of
  *     vlut_set_plan (and a per-thread cache of the launch plans chosen for the
- *     last few shapes, emptied by vlut_set_plan); (ii) one 4-byte device flag
- *     per GPU that the pack kernels raise for a non-ternary weight, reset and
- *     read back inside every vlut_pack_weights* call under a host mutex (the
- *     pack calls of one process are therefore serialised); (iii) one bit per
+ *     last few shapes, emptied by vlut_set_plan); (ii) one 4-byte flag in pinned
+ *     host memory (allocated by the first pack call) that the pack kernels raise
+ *     for a non-ternary weight, reset and read inside every vlut_pack_weights*
+ *     call under a host mutex (the pack calls of one process are therefore
+ *     serialised); (iii) one bit per
  *     kernel and device that records that the kernel's LDS limit was raised.
  *     None of it influences results.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).

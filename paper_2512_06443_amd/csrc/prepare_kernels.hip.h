@@ -6,37 +6,72 @@
 namespace {
 
 // ---------------------------------------------------------------------------------------------
-// Offline packing (Sec. 3.3): one thread per packed byte, including the padding bytes.
+// Offline packing (Sec. 3.3), padding bytes included.  A thread makes one dword of the blob: four groups of one row.
+// Threads in the order of the blob (4 dwords of a row, 4 rows, then the next tile column), so a wave stores 256
+// contiguous bytes and reads 4 * 64 * GW / 4 contiguous bytes of each of four rows.  A group is one signed dot product of
+// its bytes with the powers of three, plus the value of the all-zero pattern.
+// Bound by memory: 14336 x 4096 (58.7 MB in, 14.7 MB out) 14.2 us, 5.2 TB/s; 30.3 us with one thread per byte and byte loads.
 // ---------------------------------------------------------------------------------------------
-__device__ int g_pack_error;
+// Nonzero if a byte of w is outside {-1, 0, +1}: its bits 1..7 differ, or it is -2.
+__device__ __forceinline__ unsigned not_ternary(unsigned w) {
+    return ((w ^ (w << 1)) & 0xfcfcfcfcu) | ((w >> 1) & ~w & 0x01010101u);
+}
+__device__ __forceinline__ int dot4_i8(unsigned a, int b, int c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_sdot4((int)a, b, c, false);
+#else
+    (void)a; (void)b;
+    return c;
+#endif
+}
+
+// (weights and blob may start at any byte: global memory takes unaligned dwords)
+typedef unsigned unaligned_u32 __attribute__((aligned(1)));
+typedef int unaligned_i32x4 __attribute__((ext_vector_type(4), aligned(1)));
 
 template <int GW>   // GW = weights per byte: 4 (2.00 bits per weight) or 5 (1.60)
-__global__ void pack_kernel(const int8_t* __restrict__ w, int M, int64_t ldw, int G, int KCn, int RGtotal,
-                            uint8_t* __restrict__ packed) {
-    size_t total = (size_t)RGtotal * KCn * 64;
-    size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    int b = (int)(i & 15);
-    int r = (int)((i >> 4) & 3);
-    size_t tile = i >> 6;
-    int kc = (int)(tile % KCn);
-    int rg = (int)(tile / KCn);
-    int m = rg * 4 + r;
-    int kg = kc * 16 + b;
-    unsigned v = GW == 4 ? 40u : 121u;      // the all-zero pattern: every digit 1
+__global__ void __launch_bounds__(256) pack_kernel(const int8_t* __restrict__ w, int M, int64_t ldw, int G, int KCn, int RGtotal,
+                                                   unaligned_u32* __restrict__ packed, volatile int* error) {
+    const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+    const size_t tile = i >> 4;
+    if (tile >= (size_t)RGtotal * KCn) return;
+    const int rg = (int)(tile / KCn), kc = (int)(tile - (size_t)rg * KCn);
+    const int m = rg * 4 + (int)((i >> 2) & 3);
+    const int kg = kc * 16 + (int)(i & 3) * 4;             // first of the thread's four groups
+    constexpr unsigned kZero = GW == 4 ? 40u : 121u;       // the all-zero pattern: every digit 1
+    constexpr int kPow = GW == 4 ? 0x0103091b : 0x03091b51;   // 27, 9, 3, 1 or 81, 27, 9, 3: first weight in the low byte
+    unsigned out = kZero * 0x01010101u;
     if (m < M && kg < G) {
-        const int8_t* p = w + (size_t)m * (size_t)ldw + (size_t)kg * GW;
-        bool ok = true;
-        v = 0;
+        const int8_t* src = w + (size_t)m * (size_t)ldw + (size_t)kg * GW;
+        const int groups = min(4, G - kg);
+        unsigned d[GW] = {};                               // the 4 * GW weights, zeros past the last group
+        if (groups == 4) {
+            const unaligned_i32x4 v = *(const unaligned_i32x4*)src;
+            d[0] = (unsigned)v.x; d[1] = (unsigned)v.y; d[2] = (unsigned)v.z; d[3] = (unsigned)v.w;
+            if constexpr (GW == 5) d[4] = *(const unaligned_u32*)(src + 16);
+        } else {
 #pragma unroll
-        for (int j = 0; j < GW; ++j) {      // first weight = most significant base-3 digit
-            const int wj = p[j];
-            ok = ok && wj >= -1 && wj <= 1;
-            v = v * 3u + (unsigned)(wj + 1);
+            for (int j = 0; j < 4 * GW; ++j)
+                if (j < groups * GW) d[j >> 2] |= (unsigned)(unsigned char)src[j] << (8 * (j & 3));
         }
-        if (!ok) atomicOr(&g_pack_error, 1);
+        unsigned bad = 0;
+#pragma unroll
+        for (int j = 0; j < GW; ++j) bad |= not_ternary(d[j]);
+        if (bad) *error = 1;                               // (host memory; every writer writes the same value)
+        out = 0;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            int v;
+            if constexpr (GW == 4) {
+                v = dot4_i8(d[g], kPow, (int)kZero);
+            } else {                                       // bytes 5 g .. 5 g + 4 of the twenty
+                const unsigned first = g == 0 ? d[0] : __builtin_amdgcn_alignbyte(d[g + 1], d[g], (unsigned)g);
+                v = dot4_i8(first, kPow, (int)kZero + (int)(signed char)(d[g + 1] >> (8 * g)));
+            }
+            out |= (unsigned)(v & 0xff) << (8 * g);
+        }
     }
-    packed[i] = (uint8_t)v;
+    packed[i] = out;
 }
 
 // ---------------------------------------------------------------------------------------------

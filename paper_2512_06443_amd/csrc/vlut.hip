@@ -418,6 +418,36 @@ int launch_narrow(const NarrowPlan& np, const NarrowParams& p, hipStream_t strea
 }
 
 std::mutex g_pack_mutex;
+int* g_pack_flag = nullptr;                // pinned host memory, one int, kept until the process ends (guarded by the mutex)
+
+template <int GW>
+int launch_pack(const int8_t* w, int64_t M, int64_t ldw, int64_t K, uint8_t* packed, hipStream_t s) {
+    const int G = (int)(K / GW), KCn = (G + 15) / 16, RGtotal = (int)((M + 3) / 4);
+    const size_t threads = (size_t)RGtotal * KCn * 16;
+    hipLaunchKernelGGL(pack_kernel<GW>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, w, (int)M, ldw, G, KCn, RGtotal,
+                       (unaligned_u32*)packed, g_pack_flag);
+    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+}
+
+// The first K5 values of every row five to a byte, the others four to a byte behind them; then waits for the flag of the
+// value check.  The kernels raise it in pinned host memory, so that an ordinary call copies nothing (a device flag that is
+// cleared and read back by two copies of four bytes costs about 25 us).
+int pack_parts(const int8_t* w, int64_t M, int64_t K, int64_t K5, uint8_t* packed, void* stream) {
+    hipStream_t s = (hipStream_t)stream;
+    std::lock_guard<std::mutex> lock(g_pack_mutex);
+    if (!g_pack_flag && hipHostMalloc((void**)&g_pack_flag, sizeof(int), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        g_pack_flag = nullptr;
+        return VLUT_ERR_DEVICE;
+    }
+    volatile int* flag = g_pack_flag;
+    *flag = 0;
+    int rc = K5 > 0 ? launch_pack<5>(w, M, K, K5, packed, s) : VLUT_OK;
+    if (rc == VLUT_OK && K > K5)
+        rc = launch_pack<4>(w + K5, M, K, K - K5, packed + (K5 > 0 ? (size_t)((M + 3) / 4) * (size_t)((K5 / 5 + 15) / 16) * 64 : 0), s);
+    // (waits also when the second launch failed: the flag must not be raised into a later call)
+    if (hipStreamSynchronize(s) != hipSuccess) return VLUT_ERR_DEVICE;
+    return rc != VLUT_OK ? rc : (*flag ? VLUT_ERR_VALUE : VLUT_OK);
+}
 
 // ---- vlut_mpgemm_f32: which kernels run and how the caller's workspace is divided
 enum { kF32Narrow = 0, kF32Fused = 1, kF32TwoLaunches = 2 };
@@ -792,21 +822,7 @@ int vlut_pack_weights(const int8_t* w_ternary, int64_t M, int64_t K, uint8_t* pa
     if (!w_ternary || !packed) return VLUT_ERR_NULL;
     size_t need = vlut_packed_weight_bytes(M, K);
     if (packed_bytes < need) return VLUT_ERR_SMALL_BUFFER;
-    hipStream_t s = (hipStream_t)stream;
-    std::lock_guard<std::mutex> lock(g_pack_mutex);
-    int zero = 0;
-    if (hipMemcpyToSymbolAsync(HIP_SYMBOL(g_pack_error), &zero, sizeof(int), 0, hipMemcpyHostToDevice, s) != hipSuccess)
-        return VLUT_ERR_DEVICE;
-    int G = (int)(K / 4), KCn = (G + 15) / 16, RGtotal = (int)((M + 3) / 4);
-    size_t blocks = (need + 255) / 256;
-    hipLaunchKernelGGL(pack_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, s, w_ternary, (int)M, K, G, KCn, RGtotal,
-                       packed);
-    if (hipGetLastError() != hipSuccess) return VLUT_ERR_DEVICE;
-    int err = 0;
-    if (hipMemcpyFromSymbolAsync(&err, HIP_SYMBOL(g_pack_error), sizeof(int), 0, hipMemcpyDeviceToHost, s) != hipSuccess)
-        return VLUT_ERR_DEVICE;
-    if (hipStreamSynchronize(s) != hipSuccess) return VLUT_ERR_DEVICE;
-    return err ? VLUT_ERR_VALUE : VLUT_OK;
+    return pack_parts(w_ternary, M, K, 0, packed, stream);
 }
 
 #ifndef VLUT_QUANT_PER_TOKEN
@@ -1121,21 +1137,7 @@ int vlut_pack_weights_g5(const int8_t* w_ternary, int64_t M, int64_t K, uint8_t*
     if (!w_ternary || !packed) return VLUT_ERR_NULL;
     size_t need = vlut_packed_weight_bytes_g5(M, K);
     if (packed_bytes < need) return VLUT_ERR_SMALL_BUFFER;
-    hipStream_t s = (hipStream_t)stream;
-    std::lock_guard<std::mutex> lock(g_pack_mutex);
-    int zero = 0;
-    if (hipMemcpyToSymbolAsync(HIP_SYMBOL(g_pack_error), &zero, sizeof(int), 0, hipMemcpyHostToDevice, s) != hipSuccess)
-        return VLUT_ERR_DEVICE;
-    int G = (int)(K / 5), KCn = (G + 15) / 16, RGtotal = (int)((M + 3) / 4);
-    size_t blocks = (need + 255) / 256;
-    hipLaunchKernelGGL(pack_kernel<5>, dim3((unsigned)blocks), dim3(256), 0, s, w_ternary, (int)M, K, G, KCn, RGtotal,
-                       packed);
-    if (hipGetLastError() != hipSuccess) return VLUT_ERR_DEVICE;
-    int err = 0;
-    if (hipMemcpyFromSymbolAsync(&err, HIP_SYMBOL(g_pack_error), sizeof(int), 0, hipMemcpyDeviceToHost, s) != hipSuccess)
-        return VLUT_ERR_DEVICE;
-    if (hipStreamSynchronize(s) != hipSuccess) return VLUT_ERR_DEVICE;
-    return err ? VLUT_ERR_VALUE : VLUT_OK;
+    return pack_parts(w_ternary, M, K, K, packed, stream);
 }
 
 size_t vlut_workspace_bytes_g5(int64_t M, int64_t K, int64_t N) {
@@ -1220,32 +1222,7 @@ int vlut_pack_weights_mixed(const int8_t* w_ternary, int64_t M, int64_t K, uint8
     if (!shape_ok(M, K, 1)) return VLUT_ERR_SHAPE;
     if (!w_ternary || !packed) return VLUT_ERR_NULL;
     if (packed_bytes < vlut_packed_weight_bytes_mixed(M, K)) return VLUT_ERR_SMALL_BUFFER;
-    const int64_t K5 = vlut_mixed_k5(K), K4 = K - K5;
-    const size_t bytes5 = K5 > 0 ? vlut_packed_weight_bytes_g5(M, K5) : 0;
-    const size_t bytes4 = K4 > 0 ? vlut_packed_weight_bytes(M, K4) : 0;
-    hipStream_t s = (hipStream_t)stream;
-    std::lock_guard<std::mutex> lock(g_pack_mutex);
-    int zero = 0;
-    if (hipMemcpyToSymbolAsync(HIP_SYMBOL(g_pack_error), &zero, sizeof(int), 0, hipMemcpyHostToDevice, s) != hipSuccess)
-        return VLUT_ERR_DEVICE;
-    const int RGtotal = (int)((M + 3) / 4);
-    if (K5 > 0) {
-        const int G = (int)(K5 / 5), KCn = (G + 15) / 16;
-        hipLaunchKernelGGL(pack_kernel<5>, dim3((unsigned)((bytes5 + 255) / 256)), dim3(256), 0, s, w_ternary, (int)M, K, G,
-                           KCn, RGtotal, packed);
-        if (hipGetLastError() != hipSuccess) return VLUT_ERR_DEVICE;
-    }
-    if (K4 > 0) {
-        const int G = (int)(K4 / 4), KCn = (G + 15) / 16;
-        hipLaunchKernelGGL(pack_kernel<4>, dim3((unsigned)((bytes4 + 255) / 256)), dim3(256), 0, s, w_ternary + K5, (int)M, K,
-                           G, KCn, RGtotal, packed + bytes5);
-        if (hipGetLastError() != hipSuccess) return VLUT_ERR_DEVICE;
-    }
-    int err = 0;
-    if (hipMemcpyFromSymbolAsync(&err, HIP_SYMBOL(g_pack_error), sizeof(int), 0, hipMemcpyDeviceToHost, s) != hipSuccess)
-        return VLUT_ERR_DEVICE;
-    if (hipStreamSynchronize(s) != hipSuccess) return VLUT_ERR_DEVICE;
-    return err ? VLUT_ERR_VALUE : VLUT_OK;
+    return pack_parts(w_ternary, M, K, vlut_mixed_k5(K), packed, stream);
 }
 
 // The two parts as launches of the kernels above in partial-sum mode, then one exact INT32 sum + scale step.

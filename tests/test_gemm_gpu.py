@@ -96,3 +96,26 @@ def test_few_tokens_from_fp32(B, N):
             assert np.array_equal(acc.cpu().numpy(), acc_ref)
             assert np.array_equal(sc.cpu().numpy().view(np.uint32), s_ref.view(np.uint32))
             assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - y_ref) <= REL * np.abs(y_ref))
+
+
+def test_pack_unaligned_and_value_check(B):
+    # matrices and blobs that start at any byte, ragged tails; a bad value anywhere is reported and the next call is clean
+    M, K = 37, 340
+    W = wl.ternary(1600, M, K, 0.4)
+    L = B.lib()
+    calls = ((L.vlut_pack_weights, B.pack_weights), (L.vlut_pack_weights_g5, B.pack_weights_g5),
+             (L.vlut_pack_weights_mixed, B.pack_weights_mixed))
+    for raw, wrapped in calls:
+        want = wrapped(dev(W))
+        for off in (1, 2, 7):
+            src = torch.zeros(M * K + 16, dtype=torch.int8, device="cuda")
+            src[off:off + M * K] = dev(W).flatten()
+            blob = torch.full((want.numel() + 16,), 255, dtype=torch.uint8, device="cuda")
+            assert raw(src.data_ptr() + off, M, K, blob.data_ptr() + off, want.numel(), None) == 0
+            assert torch.equal(blob[off:off + want.numel()], want)
+            assert int((blob == 255).sum()) == 16
+        for pos, value in ((0, 2), (5 * K + 33, -2), (M * K - 1, 3), (M * K // 2, -128), (17, 127)):
+            bad = dev(W).flatten()
+            bad[pos] = value
+            assert raw(bad.data_ptr(), M, K, want.data_ptr(), want.numel(), None) == B.VLUT_ERR_VALUE
+            assert torch.equal(wrapped(dev(W)), wrapped(dev(W)))
