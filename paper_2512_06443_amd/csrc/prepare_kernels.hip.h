@@ -76,11 +76,12 @@ __global__ void __launch_bounds__(256) pack_kernel(const int8_t* __restrict__ w,
 
 // ---------------------------------------------------------------------------------------------
 // Activation quantisation + transposition (Sec. 3.4 first paragraph, Sec. 3.3).
-// One workgroup handles one chunk of 8 consecutive tokens over all K.  A wave reads 8 consecutive float4 of each
-// of the 8 tokens per pass (lane = token + 8 * quad): 128 contiguous bytes per token.  The four codes a lane makes
-// (4 consecutive k of one token) are transposed inside its quad of lanes, so that every lane leaves with one dword
-// of the chunk's [K][8] block (4 tokens of one k) and a wave's LDS store is 256 contiguous bytes, free of bank
-// conflicts; the block is contiguous in the token-chunked layout and leaves with 16-byte stores.
+// One workgroup handles four consecutive tokens (half a chunk) over all K, so that 1024 tokens are one workgroup per
+// compute unit and a row up to 14336 values stays in registers between the absmax and the rounding.  A wave reads 16
+// consecutive float4 of each of the four tokens (lane = token + 4 * quad): 256 contiguous bytes per token.  The four codes
+// a lane makes (4 consecutive k of one token) are transposed inside its quad of lanes, so that every lane leaves with
+// one dword of the chunk's [K][8] block (4 tokens of one k); the two halves of a chunk are blocks 8 apart (same XCD under
+// round-robin dispatch), so their half lines meet in one L2.
 //   NV  float4 values per thread kept in registers between the absmax pass and the rounding pass
 //       (0: x is read twice, for large K)
 //   VEC true when rows can be read as float4 (x and ldx 16-byte aligned)
@@ -119,85 +120,60 @@ __device__ __forceinline__ unsigned quad_transpose_codes(unsigned d, int tok) {
 
 template <int NV, bool VEC>
 __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(const float* __restrict__ x, int N, int K, int64_t ldx,
-                                                                 int8_t* __restrict__ a_q, float* __restrict__ a_scale) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char q_lds[];   // [K][8] codes
-    __shared__ float red[kQuantThreads / 64][8];
-    __shared__ float s_inv[8];
-    const int chunk = blockIdx.x;
+                                                                 int8_t* __restrict__ a_q, float* __restrict__ a_scale, int chunks) {
+    __shared__ __attribute__((aligned(16))) float red[4][kQuantThreads / 64];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    const int t = lane & 7;                    // token of the chunk
-    const int kq = wave * 8 + (lane >> 3);     // this thread handles k = 4*(kq + 128*i) .. +3
-    const int n = chunk * 8 + t;
+    const int b = blockIdx.x;
+    const int chunk = (b >> 4) * 8 + (b & 7), half = (b >> 3) & 1;
+    if (chunk >= chunks) return;
+    const int t = lane & 3;                    // token of the four
+    const int kq = wave * 16 + (lane >> 2);    // this thread handles k = 4*(kq + 256*i) .. +3
+    const int n = chunk * 8 + half * 4 + t;
     const bool live = n < N;
     const float* row = x + (size_t)(live ? n : 0) * ldx;
     const int nquad = K >> 2;                  // K % 4 == 0
-
-    auto load4 = [&](int qi) -> f32x4 {
-        if (VEC) return *(const f32x4*)(row + 4 * (size_t)qi);
-        return f32x4{row[4 * (size_t)qi], row[4 * (size_t)qi + 1], row[4 * (size_t)qi + 2], row[4 * (size_t)qi + 3]};
+    constexpr int NB = NV > 0 ? NV : 8;        // loads in flight per thread and pass
+    auto load_pass = [&](int q0, f32x4 (&v)[NB]) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int qi = q0 + kq + 256 * i;
+            const float* src = row + 4 * (size_t)qi;
+            if (!live || qi >= nquad) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            else if (VEC) v[i] = *(const f32x4*)src;
+            else v[i] = f32x4{src[0], src[1], src[2], src[3]};
+        }
     };
-
-    f32x4 xv[NV > 0 ? NV : 1];
+    f32x4 xv[NB];
     float amax = 0.0f;
-    if (NV > 0) {
+    for (int q0 = 0; q0 < (NV > 0 ? 1 : nquad); q0 += 256 * NB) {
+        load_pass(q0, xv);
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int qi = kq + 128 * i;
-            xv[i] = (live && qi < nquad) ? load4(qi) : f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < NB; ++i)
             amax = fmaxf(fmaxf(amax, fmaxf(fabsf(xv[i].x), fabsf(xv[i].y))), fmaxf(fabsf(xv[i].z), fabsf(xv[i].w)));
-        }
-    } else {
-        // eight loads in flight per thread and pass (a plain loop would wait for every load in turn)
-        for (int q0 = 0; q0 < nquad; q0 += 128 * 8) {
-            f32x4 tv[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int qi = q0 + kq + 128 * i;
-                tv[i] = (live && qi < nquad) ? load4(qi) : f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                amax = fmaxf(fmaxf(amax, fmaxf(fabsf(tv[i].x), fabsf(tv[i].y))), fmaxf(fabsf(tv[i].z), fabsf(tv[i].w)));
-        }
     }
-    for (int off = 32; off >= 8; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));   // lanes of the same token
-    if (lane < 8) red[wave][lane] = amax;
+    for (int off = 32; off >= 4; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));   // lanes of the same token
+    if (lane < 4) red[lane][wave] = amax;
     __syncthreads();
-    if (tid < 8) {
-        float v = 0.0f;
-        for (int w = 0; w < kQuantThreads / 64; ++w) v = fmaxf(v, red[w][tid]);
-        // IEEE-correct fp32 divisions (the default for HIP); no reciprocal approximation.
-        s_inv[tid] = (v > 0.0f) ? 127.0f / v : 0.0f;
-        if (chunk * 8 + tid < N) a_scale[chunk * 8 + tid] = v / 127.0f;
+    float v = 0.0f;
+#pragma unroll
+    for (int w4 = 0; w4 < kQuantThreads / 256; ++w4) {
+        const f32x4 r = *(const f32x4*)&red[t][4 * w4];
+        v = fmaxf(fmaxf(v, fmaxf(r.x, r.y)), fmaxf(r.z, r.w));
     }
-    __syncthreads();
-    const float inv = s_inv[t];
-    // The quad transpose uses all four lanes of a quad; they share qi, so the bounds test is uniform per quad.
-    auto emit = [&](int qi, const f32x4 v) {       // tokens past N: x = 0 -> code 0
-        const unsigned e = quad_transpose_codes(quant_codes4(v, inv), t);
-        if (qi < nquad) *(unsigned*)(q_lds + (size_t)qi * 32 + (t & 3) * 8 + (t >> 2) * 4) = e;
-    };
-    if (NV > 0) {
+    // IEEE-correct fp32 divisions (the default for HIP); no reciprocal approximation.
+    const float inv = (v > 0.0f) ? 127.0f / v : 0.0f;
+    if (tid < 4 && live) a_scale[n] = v / 127.0f;
+    unsigned* dst = (unsigned*)(a_q + (size_t)chunk * K * 8) + half;
+    for (int q0 = 0; q0 < (NV > 0 ? 1 : nquad); q0 += 256 * NB) {
+        if (NV == 0) load_pass(q0, xv);
 #pragma unroll
-        for (int i = 0; i < NV; ++i) emit(kq + 128 * i, xv[i]);
-    } else {
-        // every lane runs the same number of passes (the quad exchange needs its partner lanes)
-        for (int q0 = 0; q0 < nquad; q0 += 128 * 8) {
-            f32x4 tv[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int qi = q0 + kq + 128 * i;
-                tv[i] = (live && qi < nquad) ? load4(qi) : f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) emit(q0 + kq + 128 * i, tv[i]);
+        for (int i = 0; i < NB; ++i) {
+            const int qi = q0 + kq + 256 * i;  // uniform in a quad of lanes; tokens past N: x = 0 -> code 0
+            const unsigned e = quad_transpose_codes(quant_codes4(xv[i], inv), t);
+            if (qi < nquad) dst[(size_t)(4 * qi + t) * 2] = e;
         }
     }
-    __syncthreads();
-    i32x4* dst = (i32x4*)(a_q + (size_t)chunk * K * 8);
-    const i32x4* src = (const i32x4*)q_lds;
-    for (int i = tid; i < K / 2; i += kQuantThreads) dst[i] = src[i];   // 16 bytes = 2 k-rows of 8 codes
 }
 
 // The same quantiser with one workgroup (256 threads) per token, for long rows or many tokens: the chunk kernel above
@@ -274,99 +250,6 @@ __global__ void __launch_bounds__(kTokThreads) quantize_token_kernel(const float
             const int qi = q0 + tid + kTokThreads * i;
             if (qi < nquad) store4(qi, live ? quant_codes4(xv[i], inv) : 0u);
         }
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
-// The same quantiser as two kernels, for inputs of a few million values: reading x twice costs less than either the
-// single-byte stores of quantize_token_kernel or the few workgroups of quantize_kernel.
-//   absmax_token_kernel    one workgroup per token: amax[n] = max_k |x[n][k]|
-//   quantize_chunk_kernel  one workgroup per (chunk of 8 tokens, range of K): a thread reads the same four k of the 8
-//                          rows, quantises, transposes the bytes in registers and stores the 32 bytes [4 k][8 tokens]
-//                          of the token-chunked layout with two 16-byte stores (full lines per wave)
-// Same decisions in fp32 as the other two kernels (amax, IEEE divisions, rint, clamp), hence the same bits.
-// ---------------------------------------------------------------------------------------------
-template <bool VEC>
-__global__ void __launch_bounds__(kTokThreads) absmax_token_kernel(const float* __restrict__ x, int N, int K, int64_t ldx,
-                                                                   float* __restrict__ amax_out) {
-    __shared__ float red[kTokThreads / 64];
-    const int tid = threadIdx.x;
-    const int n = blockIdx.x;
-    if (n >= N) return;
-    const float* row = x + (size_t)n * ldx;
-    const int nquad = K >> 2;
-    float amax = 0.0f;
-    for (int q0 = 0; q0 < nquad; q0 += kTokThreads * 8) {       // eight loads in flight per thread and pass
-        f32x4 xv[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int qi = q0 + tid + kTokThreads * i;
-            const float* src = row + 4 * (size_t)(qi < nquad ? qi : 0);
-            xv[i] = qi < nquad ? (VEC ? *(const f32x4*)src : f32x4{src[0], src[1], src[2], src[3]}) : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            amax = fmaxf(fmaxf(amax, fmaxf(fabsf(xv[i].x), fabsf(xv[i].y))), fmaxf(fabsf(xv[i].z), fabsf(xv[i].w)));
-    }
-    amax = wave_max_f32(amax);
-    if ((tid & 63) == 0) red[tid >> 6] = amax;
-    __syncthreads();
-    if (tid == 0) {
-        float v = 0.0f;
-#pragma unroll
-        for (int w = 0; w < kTokThreads / 64; ++w) v = fmaxf(v, red[w]);
-        amax_out[n] = v;
-    }
-}
-
-// 4 x 4 byte transpose: in[r] holds bytes (r,0..3); out[c] holds bytes (0..3, c).
-__device__ __forceinline__ void transpose_bytes4(const unsigned (&in)[4], unsigned (&out)[4]) {
-    const unsigned t01l = __builtin_amdgcn_perm(in[1], in[0], 0x05010400u), t01h = __builtin_amdgcn_perm(in[1], in[0], 0x07030602u);
-    const unsigned t23l = __builtin_amdgcn_perm(in[3], in[2], 0x05010400u), t23h = __builtin_amdgcn_perm(in[3], in[2], 0x07030602u);
-    out[0] = __builtin_amdgcn_perm(t23l, t01l, 0x05040100u);
-    out[1] = __builtin_amdgcn_perm(t23l, t01l, 0x07060302u);
-    out[2] = __builtin_amdgcn_perm(t23h, t01h, 0x05040100u);
-    out[3] = __builtin_amdgcn_perm(t23h, t01h, 0x07060302u);
-}
-
-template <bool VEC>
-__global__ void __launch_bounds__(kTokThreads) quantize_chunk_kernel(const float* __restrict__ x, int N, int K, int64_t ldx,
-                                                                     const float* __restrict__ amax,
-                                                                     int8_t* __restrict__ a_q, float* __restrict__ a_scale,
-                                                                     int quads_per_block) {
-    __shared__ float s_inv[8];
-    const int tid = threadIdx.x;
-    const int chunk = blockIdx.x;
-    if (tid < 8) {
-        const int n = chunk * 8 + tid;
-        const float v = n < N ? amax[n] : 0.0f;
-        s_inv[tid] = (v > 0.0f) ? 127.0f / v : 0.0f;           // IEEE divisions, as in the other quantisers
-        if (n < N && blockIdx.y == 0) a_scale[n] = v / 127.0f;
-    }
-    __syncthreads();
-    float inv[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) inv[t] = s_inv[t];
-    const int nquad = K >> 2;
-    const int q_begin = blockIdx.y * quads_per_block;
-    const int q_end = min(nquad, q_begin + quads_per_block);
-    int8_t* dst = a_q + (size_t)chunk * K * 8;
-    for (int qi = q_begin + tid; qi < q_end; qi += kTokThreads) {
-        unsigned c[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int n = chunk * 8 + t;
-            const float* src = x + (size_t)(n < N ? n : 0) * ldx + 4 * (size_t)qi;
-            const f32x4 v = n < N ? (VEC ? *(const f32x4*)src : f32x4{src[0], src[1], src[2], src[3]}) : f32x4{0.f, 0.f, 0.f, 0.f};
-            c[t] = n < N ? quant_codes4(v, inv[t]) : 0u;         // tokens past N: zeros
-        }
-        unsigned lo[4], hi[4];                                   // lo[k] = tokens 0-3 of k, hi[k] = tokens 4-7
-        const unsigned c_lo[4] = {c[0], c[1], c[2], c[3]}, c_hi[4] = {c[4], c[5], c[6], c[7]};
-        transpose_bytes4(c_lo, lo);
-        transpose_bytes4(c_hi, hi);
-        i32x4* o = (i32x4*)(dst + (size_t)qi * 32);
-        o[0] = i32x4{(int)lo[0], (int)hi[0], (int)lo[1], (int)hi[1]};
-        o[1] = i32x4{(int)lo[2], (int)hi[2], (int)lo[3], (int)hi[3]};
     }
 }
 

@@ -454,15 +454,13 @@ enum { kF32Narrow = 0, kF32Fused = 1, kF32TwoLaunches = 2 };
 struct F32Layout {
     int kind;
     Plan plan;                                   // kF32Fused
-    size_t off_scale, off_amax, off_aq, off_ws, total;     // byte offsets into the workspace
+    size_t off_scale, off_aq, off_ws, total;     // byte offsets into the workspace
 };
 
 size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Inputs from which the two-kernel quantiser (absmax per token, then chunks of 8 tokens per K range) is the fastest
-// form (measured: 14.6 against 21.2 us at N = 512, K = 14336; a second launch costs more than it saves below about
-// four million values); it needs N floats of scratch, which only vlut_mpgemm_f32 has (its workspace).
-bool quantize_two_kernels(int64_t N, int64_t K) { return N * K >= ((int64_t)1 << 22) && N >= 64; }
+// From how many tokens the quantiser takes four tokens per workgroup instead of one.
+constexpr int64_t kQuantTokenMaxN = 256;
 
 F32Layout f32_layout(int64_t M, int64_t K, int64_t N) {
     F32Layout L;
@@ -487,8 +485,8 @@ F32Layout f32_layout(int64_t M, int64_t K, int64_t N) {
         return L;
     }
     L.kind = kF32TwoLaunches;                    // quantise into the workspace, then the ordinary path
-    L.off_amax = scale_bytes;                    // per-token absmax between the two kernels of the quantiser
-    L.off_aq = L.off_amax + (quantize_two_kernels(N, K) ? scale_bytes : 0);
+    // (N unused floats ahead of the codes of a large input: the workspace keeps the size callers know)
+    L.off_aq = scale_bytes + ((N * K >= ((int64_t)1 << 22) && N >= 64) ? scale_bytes : 0);
     L.off_ws = L.off_aq + round256((size_t)((N + 7) / 8) * (size_t)K * 8);
     const bool narrow = narrow_applies(M, K, N, nullptr, false);
     const Plan pl = narrow ? Plan{4, 1, 1, 4} : choose_plan(M, K, N);
@@ -825,58 +823,19 @@ int vlut_pack_weights(const int8_t* w_ternary, int64_t M, int64_t K, uint8_t* pa
     return pack_parts(w_ternary, M, K, 0, packed, stream);
 }
 
-#ifndef VLUT_QUANT_PER_TOKEN
-// measured: the per-token kernel is the faster one except for more than ~2M values in short rows, where its
-// single-byte stores cost more than the chunk kernel's serial reads
-#define VLUT_QUANT_PER_TOKEN(N, K) (!((N) * (K) >= 2000000 && (K) <= 4096))
-#endif
-static int quantize_impl(const float* x, int64_t N, int64_t K, int64_t ldx, int8_t* a_q, float* a_scale,
-                         float* amax_scratch_or_null, void* stream) {
+static int quantize_impl(const float* x, int64_t N, int64_t K, int64_t ldx, int8_t* a_q, float* a_scale, void* stream) {
     if (!shape_ok(1, K, N)) return VLUT_ERR_SHAPE;
     if (ldx < K) return VLUT_ERR_SHAPE;
     if (!x || !a_q || !a_scale) return VLUT_ERR_NULL;
     if (((uintptr_t)a_q) % 16 != 0) return VLUT_ERR_UNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
-    const unsigned chunks = (unsigned)((N + 7) / 8);
+    const int chunks = (int)((N + 7) / 8);
     const bool vec = (((uintptr_t)x) % 16 == 0) && (ldx % 4 == 0);
-    if (amax_scratch_or_null && quantize_two_kernels(N, K)) {
-        if (vec) hipLaunchKernelGGL(absmax_token_kernel<true>, dim3((unsigned)N), dim3(kTokThreads), 0, s, x, (int)N, (int)K, ldx,
-                                    amax_scratch_or_null);
-        else hipLaunchKernelGGL(absmax_token_kernel<false>, dim3((unsigned)N), dim3(kTokThreads), 0, s, x, (int)N, (int)K, ldx,
-                                amax_scratch_or_null);
-        if (hipGetLastError() != hipSuccess) return VLUT_ERR_DEVICE;
-        // K ranges per chunk: enough workgroups for about three per CU, each at least one pass of 256 quads
-        const int nquad = (int)(K / 4);
-        int ranges = (int)((768 + chunks - 1) / chunks);
-        const int max_ranges = (nquad + kTokThreads - 1) / kTokThreads;
-        if (ranges > max_ranges) ranges = max_ranges;
-        if (ranges < 1) ranges = 1;
-        int quads_per_block = (nquad + ranges - 1) / ranges;
-        quads_per_block = (quads_per_block + kTokThreads - 1) / kTokThreads * kTokThreads;
-        ranges = (nquad + quads_per_block - 1) / quads_per_block;
-        const dim3 grid(chunks, (unsigned)ranges);
-        if (vec) hipLaunchKernelGGL(quantize_chunk_kernel<true>, grid, dim3(kTokThreads), 0, s, x, (int)N, (int)K, ldx,
-                                    (const float*)amax_scratch_or_null, a_q, a_scale, quads_per_block);
-        else hipLaunchKernelGGL(quantize_chunk_kernel<false>, grid, dim3(kTokThreads), 0, s, x, (int)N, (int)K, ldx,
-                                (const float*)amax_scratch_or_null, a_q, a_scale, quads_per_block);
-        return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
-    }
-    const size_t lds = (size_t)K * 8;
-    const int nquad_per_thread = (int)((K / 4 + 127) / 128);
-    auto launch = [&](auto kfn) -> int {
-        if (lds > 160 * 1024 - 1024) return VLUT_ERR_UNSUPPORTED;   // the chunk's [K][8] block is staged in LDS
-        static std::atomic<unsigned> attr_done{0};   // per kernel instance (generic lambda), one bit per device
-        if (lds > 48 * 1024 && !allow_dynamic_lds((const void*)kfn, 160 * 1024 - 1024, attr_done, false))
-            return VLUT_ERR_DEVICE;
-        hipLaunchKernelGGL(kfn, dim3(chunks), dim3(kQuantThreads), lds, s, x, (int)N, (int)K, ldx, a_q, a_scale);
-        return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
-    };
-    // One workgroup per token (every CU reads one row once) unless the byte stores would dominate
-    if (VLUT_QUANT_PER_TOKEN(N, K)) {
-        const unsigned blocks = ((chunks + 7) / 8) * 64;
+    if (N < kQuantTokenMaxN) {                 // one workgroup per token
+        const unsigned blocks = (unsigned)((chunks + 7) / 8) * 64;
         const int per_thread = (int)((K / 4 + kTokThreads - 1) / kTokThreads);
         auto launch_tok = [&](auto kfn) -> int {
-            hipLaunchKernelGGL(kfn, dim3(blocks), dim3(kTokThreads), 0, s, x, (int)N, (int)K, ldx, a_q, a_scale, (int)chunks);
+            hipLaunchKernelGGL(kfn, dim3(blocks), dim3(kTokThreads), 0, s, x, (int)N, (int)K, ldx, a_q, a_scale, chunks);
             return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
         };
         if (!vec) return launch_tok(quantize_token_kernel<0, false>);
@@ -885,18 +844,22 @@ static int quantize_impl(const float* x, int64_t N, int64_t K, int64_t ldx, int8
         if (per_thread <= 16) return launch_tok(quantize_token_kernel<16, true>);
         return launch_tok(quantize_token_kernel<0, true>);
     }
-    if (vec) {
-        if (nquad_per_thread <= 5) return launch(quantize_kernel<5, true>);
-        if (nquad_per_thread <= 8) return launch(quantize_kernel<8, true>);
-        if (nquad_per_thread <= 16) return launch(quantize_kernel<16, true>);
-        return launch(quantize_kernel<0, true>);
-    }
-    return launch(quantize_kernel<0, false>);
+    const unsigned blocks = (unsigned)((chunks + 7) / 8) * 16;
+    const int per_thread = (int)((K / 4 + 255) / 256);
+    auto launch = [&](auto kfn) -> int {
+        hipLaunchKernelGGL(kfn, dim3(blocks), dim3(kQuantThreads), 0, s, x, (int)N, (int)K, ldx, a_q, a_scale, chunks);
+        return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+    };
+    if (!vec) return launch(quantize_kernel<0, false>);
+    if (per_thread <= 4) return launch(quantize_kernel<4, true>);
+    if (per_thread <= 8) return launch(quantize_kernel<8, true>);
+    if (per_thread <= 14) return launch(quantize_kernel<14, true>);
+    return launch(quantize_kernel<0, true>);
 }
 
 int vlut_quantize_act(const float* x, int64_t N, int64_t K, int64_t ldx, int8_t* a_q, float* a_scale,
                       void* stream) {
-    return quantize_impl(x, N, K, ldx, a_q, a_scale, nullptr, stream);
+    return quantize_impl(x, N, K, ldx, a_q, a_scale, stream);
 }
 
 int vlut_build_lut(const int8_t* a_q, int64_t K, int64_t N, int16_t* lut, size_t lut_bytes, void* stream) {
@@ -1090,8 +1053,7 @@ int vlut_mpgemm_f32(const uint8_t* packed, float w_scale, const float* w_scale_r
     if (L.kind == kF32TwoLaunches) {
         float* scales = a_scale_out_or_null ? a_scale_out_or_null : (float*)(ws + L.off_scale);
         int8_t* a_q = (int8_t*)(ws + L.off_aq);
-        int rc = quantize_impl(x, N, K, ldx, a_q, scales, quantize_two_kernels(N, K) ? (float*)(ws + L.off_amax) : nullptr,
-                               stream);
+        int rc = quantize_impl(x, N, K, ldx, a_q, scales, stream);
         if (rc != VLUT_OK) return rc;
         return mpgemm_impl(packed, w_one, w_rows, a_q, scales, nullptr, M, K, N, y, ldy, acc_or_null, ws + L.off_ws,
                            L.total - L.off_ws, stream);

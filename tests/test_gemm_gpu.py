@@ -98,6 +98,24 @@ def test_few_tokens_from_fp32(B, N):
             assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - y_ref) <= REL * np.abs(y_ref))
 
 
+@pytest.mark.parametrize("N", [255, 256, 259, 1030])
+def test_quantiser_with_four_tokens_per_workgroup(B, N):
+    # rows that fit 4, 8 and 14 registers of float4 per thread and longer ones, ragged K, unaligned rows, a zero row
+    for K in (4, 260, 4096, 4100, 8196, 14340):
+        x = wl.activations(1500 + K, N, K)
+        x[N - 2] = 0.0
+        q_ref, s_ref = O.quantize(x)
+        odd = torch.full((N, K + 3), 9e9, device="cuda")
+        odd[:, 1:K + 1] = dev(x)
+        for xd in (dev(x), odd[:, 1:K + 1]):
+            a_q, a_s = B.quantize_act(xd, torch.full(((N + 7) // 8, K, 8), 99, dtype=torch.int8, device="cuda"))
+            torch.cuda.synchronize()
+            assert np.array_equal(B.act_chunked_to_kn(a_q, N).cpu().numpy(), q_ref)
+            assert np.array_equal(a_s.cpu().numpy().view(np.uint32), s_ref.view(np.uint32))
+            if N % 8:
+                assert int(a_q[-1, :, N % 8:].abs().max()) == 0      # tokens past N hold zeros
+
+
 def test_pack_unaligned_and_value_check(B):
     # matrices and blobs that start at any byte, ragged tails; a bad value anywhere is reported and the next call is clean
     M, K = 37, 340
