@@ -44,6 +44,7 @@ struct GemmParams {
     int KCn, KCn4, RGtotal, ldy, chunks;
     int macros;               // macro steps of `packed`
     int tiles_n, tiles, per_xcd;
+    int stream_out;           // y is too large for the caches: store past them
 };
 
 template <int GW>
@@ -361,7 +362,11 @@ __global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) 
             float* dst = p.y + (size_t)n * p.ldy + m;
 #pragma unroll
             for (int e = 0; e < 4; ++e, dst += p.ldy)
-                if (n + e < p.N) *dst = (float)v[e] * (ws * __builtin_bit_cast(float, (int)sc[e]));
+                if (n + e < p.N) {
+                    const float out = (float)v[e] * (ws * __builtin_bit_cast(float, (int)sc[e]));
+                    if (p.stream_out) __builtin_nontemporal_store(out, dst);
+                    else *dst = out;
+                }
         }
         if (p.acc) {
 #pragma unroll
