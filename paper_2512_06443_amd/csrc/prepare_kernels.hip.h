@@ -76,8 +76,9 @@ __global__ void __launch_bounds__(256) pack_kernel(const int8_t* __restrict__ w,
 
 // ---------------------------------------------------------------------------------------------
 // Activation quantisation + transposition (Sec. 3.4 first paragraph, Sec. 3.3).
-// One workgroup handles four consecutive tokens (half a chunk) over all K, so that 1024 tokens are one workgroup per
-// compute unit and a row up to 14336 values stays in registers between the absmax and the rounding.  A wave reads 16
+// For about a thousand tokens and more: one workgroup handles four consecutive tokens (half a chunk) over all K, so that
+// 1024 tokens are one workgroup per compute unit, and a row up to 14336 values stays in registers between the absmax and
+// the rounding (N = 1024: 7.3 us at K = 6912, 14.8 us at K = 14336; one token per workgroup: 8.0 and 15.8 us).  A wave reads 16
 // consecutive float4 of each of the four tokens (lane = token + 4 * quad): 256 contiguous bytes per token.  The four codes
 // a lane makes (4 consecutive k of one token) are transposed inside its quad of lanes, so that every lane leaves with
 // one dword of the chunk's [K][8] block (4 tokens of one k); the two halves of a chunk are blocks 8 apart (same XCD under
@@ -91,18 +92,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Absmax quantiser of one token row, decided in fp32: inv = 127 / amax (IEEE division, 0 for an all-zero row),
 // code = clamp(rint(x * inv), -127, 127) with ties to even.
-// Four values at once, code of v[c] in byte c.  |v * inv| <= 127 (1 + 2^-23) for finite rows, so the rounded value r
-// is an integer of [-127, 127], r + 128 is exact and fits a byte: one saturating float -> byte conversion per value
-// writes it in place, and flipping the top bits afterwards subtracts the 128 again.  The lower clamp stays as an
-// instruction (an overflowing inv = 127 / amax for rows below 4e-37 can make r = -inf); the upper one is the
-// conversion's saturation.
+// Four values at once, code of v[c] in byte c.  Adding 1.5 * 2^23 to the product (rounded to fp32 first: there is no
+// contraction here) rounds it to an integer with ties to even and leaves that integer, two's complement, in the low byte of
+// the sum.  The clamp comes before the rounding, which gives the same code; it only matters where 127 / amax overflows
+// (rows below 4e-37): -inf and NaN become -127, +inf 127.
 __device__ __forceinline__ unsigned quant_codes4(const f32x4 v, float inv) {
-    unsigned d = 0u;
-    d = __builtin_amdgcn_cvt_pk_u8_f32(fmaxf(rintf(v.x * inv), -127.0f) + 128.0f, 0u, d);
-    d = __builtin_amdgcn_cvt_pk_u8_f32(fmaxf(rintf(v.y * inv), -127.0f) + 128.0f, 1u, d);
-    d = __builtin_amdgcn_cvt_pk_u8_f32(fmaxf(rintf(v.z * inv), -127.0f) + 128.0f, 2u, d);
-    d = __builtin_amdgcn_cvt_pk_u8_f32(fmaxf(rintf(v.w * inv), -127.0f) + 128.0f, 3u, d);
-    return d ^ 0x80808080u;
+    unsigned u[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) u[c] = __builtin_bit_cast(unsigned, __builtin_amdgcn_fmed3f(v[c] * inv, -127.0f, 127.0f) + 12582912.0f);
+    return __builtin_amdgcn_perm(u[1], u[0], 0x0c0c0400u) | __builtin_amdgcn_perm(u[3], u[2], 0x04000c0cu);
 }
 // The lane holds the codes of k = 4q .. 4q+3 of token `tok` (byte c = k offset c); the four lanes of a quad hold
 // four consecutive tokens of the same q.  Returns, for the lane with tok % 4 == c, the codes of those four tokens
@@ -176,20 +174,22 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(const float* __
     }
 }
 
-// The same quantiser with one workgroup (256 threads) per token, for long rows or many tokens: the chunk kernel above
-// lets one CU pull 8 whole rows twice, which takes 20 us at K = 8640, while here every CU reads one row once.  The
-// price is the store: a token owns one byte in every 8 of its chunk's [K][8] block, so the codes leave as single
-// bytes (distinct bytes written by different workgroups: no race).  Tokens past N (padding of the last chunk) are
-// written as zeros.  Blocks are numbered so that the 8 tokens of a chunk sit 8 blocks apart (same XCD under
+// The same quantiser with one workgroup per token: every CU reads one row once.  A token owns one byte in every 8 of its
+// chunk's [K][8] block, so the codes leave as single bytes (distinct bytes written by different workgroups: no race), and
+// the address unit takes a byte store line by line: the four codes of a lane (32 bytes apart in the block) first go
+// through the wave's 256 bytes of LDS, so that consecutive lanes store consecutive k and an instruction touches 4 lines
+// instead of 16.  N = 64: 5.2 -> 3.2 us at K = 6912; N = 512, K = 14336: 20.8 -> 8.4 us.  Tokens past N (padding of the last
+// chunk) are written as zeros.  Blocks are numbered so that the 8 tokens of a chunk sit 8 blocks apart (same XCD under
 // round-robin dispatch, so their partial lines meet in one L2); this is a matter of speed only.
 //   NV  float4 values per thread kept in registers between the two passes (0: x is read twice)
-constexpr int kTokThreads = 256;
+constexpr int kTokThreads = 512;               // 256: 0.7 to 2 us slower from K = 6912 on; 1024: the same
 
 template <int NV, bool VEC>
 __global__ void __launch_bounds__(kTokThreads) quantize_token_kernel(const float* __restrict__ x, int N, int K, int64_t ldx,
                                                                      int8_t* __restrict__ a_q,
                                                                      float* __restrict__ a_scale, int chunks) {
     __shared__ float red[kTokThreads / 64];
+    __shared__ unsigned codes[kTokThreads / 64][64];
     const int tid = threadIdx.x;
     const int b = blockIdx.x;
     const int chunk = (b >> 6) * 8 + (b & 7);
@@ -230,12 +230,17 @@ __global__ void __launch_bounds__(kTokThreads) quantize_token_kernel(const float
     const float inv = (v > 0.0f) ? 127.0f / v : 0.0f;      // IEEE divisions
     if (tid == 0 && live) a_scale[n] = v / 127.0f;
     int8_t* dst = a_q + (size_t)chunk * K * 8 + t;
-    auto store4 = [&](int qi, unsigned d) {
-        int8_t* o = dst + (size_t)qi * 32;
-        o[0] = (int8_t)(d & 0xffu);
-        o[8] = (int8_t)((d >> 8) & 0xffu);
-        o[16] = (int8_t)((d >> 16) & 0xffu);
-        o[24] = (int8_t)(d >> 24);
+    unsigned* const mine = codes[tid >> 6];
+    auto store4 = [&](int qi, unsigned d) {                // qi of the lane; every lane of the wave takes part
+        mine[tid & 63] = d;
+        __builtin_amdgcn_wave_barrier();
+        const int k0 = 4 * (qi - (tid & 63)) + (tid & 63);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = k0 + 64 * j;
+            if (k < K) dst[(size_t)k * 8] = ((const int8_t*)mine)[64 * j + (tid & 63)];
+        }
+        __builtin_amdgcn_wave_barrier();
     };
     for (int q0 = 0; q0 < (NV > 0 ? 1 : nquad); q0 += kTokThreads * NB) {
         if (NV == 0 && live) {
@@ -248,7 +253,7 @@ __global__ void __launch_bounds__(kTokThreads) quantize_token_kernel(const float
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             const int qi = q0 + tid + kTokThreads * i;
-            if (qi < nquad) store4(qi, live ? quant_codes4(xv[i], inv) : 0u);
+            if (qi - (tid & 63) < nquad) store4(qi, live ? quant_codes4(xv[i], inv) : 0u);      // (uniform per wave)
         }
     }
 }

@@ -459,8 +459,9 @@ struct F32Layout {
 
 size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// From how many tokens the quantiser takes four tokens per workgroup instead of one.
-constexpr int64_t kQuantTokenMaxN = 256;
+// From how many tokens the quantiser takes four tokens per workgroup instead of one.  Measured, one / four: N = 512 3.8 / 4.8 us
+// at K = 4096, 4.9 / 6.6 at 6912, 8.4 / 11.6 at 14336; N = 1024 5.6 / 5.3, 8.0 / 7.3, 15.8 / 14.8.
+constexpr int64_t kQuantTokenMaxN = 768;
 
 F32Layout f32_layout(int64_t M, int64_t K, int64_t N) {
     F32Layout L;
@@ -655,9 +656,9 @@ int launch_gemm(const uint8_t* packed, float w_scale, const float* w_rows, const
     p.Kmain = (int)(K5 > 0 ? K5 : K);
     p.KCn = (p.Kmain / gw + 15) / 16;
     p.macros = (p.KCn + 1) / 2;
-    if (K5 > 0 && K > K5) {
     // an output well beyond half of the L2s (32 MB) is not kept there: 14336 x 4096 x 512 37.4 -> 35.4 us
     p.stream_out = M * N * 4 >= ((int64_t)16 << 20);
+    if (K5 > 0 && K > K5) {
         p.packed4 = packed + (size_t)p.RGtotal * p.KCn * 64;
         p.KCn4 = (int)(((K - K5) / 4 + 15) / 16);
     }
@@ -835,15 +836,14 @@ static int quantize_impl(const float* x, int64_t N, int64_t K, int64_t ldx, int8
     const bool vec = (((uintptr_t)x) % 16 == 0) && (ldx % 4 == 0);
     if (N < kQuantTokenMaxN) {                 // one workgroup per token
         const unsigned blocks = (unsigned)((chunks + 7) / 8) * 64;
-        const int per_thread = (int)((K / 4 + kTokThreads - 1) / kTokThreads);
         auto launch_tok = [&](auto kfn) -> int {
             hipLaunchKernelGGL(kfn, dim3(blocks), dim3(kTokThreads), 0, s, x, (int)N, (int)K, ldx, a_q, a_scale, chunks);
             return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
         };
         if (!vec) return launch_tok(quantize_token_kernel<0, false>);
-        if (per_thread <= 4) return launch_tok(quantize_token_kernel<4, true>);
-        if (per_thread <= 10) return launch_tok(quantize_token_kernel<10, true>);
-        if (per_thread <= 16) return launch_tok(quantize_token_kernel<16, true>);
+        if (K <= 4096) return launch_tok(quantize_token_kernel<2, true>);
+        if (K <= 8192) return launch_tok(quantize_token_kernel<4, true>);
+        if (K <= 16384) return launch_tok(quantize_token_kernel<8, true>);
         return launch_tok(quantize_token_kernel<0, true>);
     }
     const unsigned blocks = (unsigned)((chunks + 7) / 8) * 16;

@@ -98,12 +98,15 @@ def test_few_tokens_from_fp32(B, N):
             assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - y_ref) <= REL * np.abs(y_ref))
 
 
-@pytest.mark.parametrize("N", [255, 256, 259, 1030])
-def test_quantiser_with_four_tokens_per_workgroup(B, N):
-    # rows that fit 4, 8 and 14 registers of float4 per thread and longer ones, ragged K, unaligned rows, a zero row
-    for K in (4, 260, 4096, 4100, 8196, 14340):
+@pytest.mark.parametrize("N", [1, 13, 259, 767, 768, 771, 1030])
+def test_quantiser_with_one_and_four_tokens_per_workgroup(B, N):
+    # rows that fit each count of registers per thread and longer ones, ragged K, unaligned rows, a zero row
+    for K in (4, 260, 4096, 4100, 8196, 14340, 16388):
         x = wl.activations(1500 + K, N, K)
         x[N - 2] = 0.0
+        # below 127 / FLT_MAX = 3.7e-37 the reciprocal overflows and every nonzero value becomes +-127; 0 * inf has no defined
+        # code, so the scale keeps nonzero values nonzero (FLT_TRUE_MIN = 1.4e-45)
+        x[N // 2] *= 1e-38
         q_ref, s_ref = O.quantize(x)
         odd = torch.full((N, K + 3), 9e9, device="cuda")
         odd[:, 1:K + 1] = dev(x)
