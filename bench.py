@@ -39,22 +39,11 @@ sys.path.insert(0, ROOT)
 
 # MI355X published peaks used for the roofline fractions
 HBM_PEAK_GBS = 8000.0
-CUS, CLOCK_GHZ = 256, 2.4
-# packed INT16 adds: 64 lanes x 2 per CU per clock; table reads: 256 B per CU per clock (2 B per add)
-ALU_PEAK_TADDS = CUS * 64 * 2 * CLOCK_GHZ / 1e3          # 78.64 T INT16 adds/s
-LDS_PEAK_GBS = CUS * 256 * CLOCK_GHZ                      # 157286 GB/s
-# what microbenchmarks reach on this device: 240 B/clk/CU of conflict-free 16-byte table reads at the ~2.1 GHz the
-# shader clock holds under this load
-LDS_MEASURED_PEAK_GBS = CUS * 240 * 2.1                   # 129024 GB/s
-MFMA_INT8_PEAK_TOPS = 5000.0                              # dense INT8 matrix-core peak (the comparison kernel's roof)
+MFMA_INT8_PEAK_TOPS = 5000.0                              # dense INT8 matrix-core peak
 
-# HBM bytes per launch of the lookup kernel measured with rocprofv3 --pmc (FETCH_SIZE, WRITE_SIZE), see profiles/
+# HBM bytes per launch of the product's kernel measured with rocprofv3 --pmc (FETCH_SIZE, WRITE_SIZE), see profiles/
 MEASURED_TRAFFIC_BYTES = {
-    "llama8b_linears/gateup/512": 75.8e6,  # profiles/lookup_kernel_llama8b_gateup_n512_stats_sq_counters_hbm_traffic.md
-    "bitnet3b_prefill/up/256": 22.6e6,     # profiles/lookup_kernel_bitnet3b_up_n256_stats_sq_counters_hbm_traffic.md
-    "bitnet2b_ffn_up/up/128": 10.85e6,     # profiles/lookup_kernel_bitnet2b_ffn_up_n128_stats_sq_counters_hbm_traffic.md
-    "layer2b4_nsweep/gate/16": 6.33e6,     # profiles/layer2b4_gate_n16_kernel_stats_hbm_traffic.md
-    "layer2b4_nsweep/gate/1": 4.66e6,      # profiles/narrow_kernel_layer2b4_gate_n1_stats_and_hbm_traffic.md
+    "llama8b_linears/gateup/512": 45.3e6,  # profiles/gemm_kernel_llama8b_gateup_n512_sq_counters_hbm_traffic.md
 }
 
 
@@ -231,7 +220,7 @@ def run_timed(torch, fn, count, warmup, use_graph=True):
 
 def time_case(B, torch, case, steps, warmup):
     """(wall ms per whole step through vlut_mpgemm_f32, GPU ms per launch of the dominant kernel, launch mode, wall ms
-    per step of the two-call form, GPU ms per vlut_mpgemm launch).  The dominant kernel is the lookup kernel: when
+    per step of the two-call form, GPU ms per vlut_mpgemm launch).  The dominant kernel is the product's: when
     the step is one fused launch its time is the step's own GPU time (HIP events on the launch stream), otherwise it
     comes from a timed region that holds only the vlut_mpgemm launches, after quantising once."""
     # The device clocks fall while the host prepares a case; whichever region is timed first would pay for the ramp.
@@ -272,7 +261,12 @@ def time_ablation(B, torch, case, steps, warmup):
 
     case.quantize(torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
+    J, R, S, _ = case.plan
+    if J:                                 # the streamed tables: without a forced plan the product runs on the matrix cores
+        B.set_plan(J, R, 0, S)
     _, t_stream, _ = run_timed(torch, case.gemm, steps, warmup)
+    if J:
+        B.set_plan(0, 0, 0, 0)
     y_streamed = case.y.clone()
     _, t_both, _ = run_timed(torch, both, steps, warmup)
     if not torch.equal(y_streamed, case.y):
@@ -322,24 +316,17 @@ def cpu_baseline(wl, W, w_scale, x):
 def roof(M, K, N, ms):
     """The roof that binds a shape and the fraction of it that `ms` (milliseconds) reaches.
 
-    N <= 16: HBM bandwidth on the algorithmic bytes (packed weights + INT8 activations + scales + fp32 output).
-    N >= 256: the table-lookup roof: one 2-byte LDS read (= one INT16 add) per (row, k-group, token) at 256 B/clk/CU.
-    In between: whichever of the two floors is the longer time.  frac = floor time / measured time."""
+    HBM bandwidth on the algorithmic bytes (packed weights + INT8 activations + scales + fp32 output) or the INT8 matrix
+    cores on 2 M K N operations, whichever of the two floors is the longer time.  frac = floor time / measured time."""
     alg = M * K // 4 + K * N + 4 * N + 4 * M * N
-    lds = 2 * M * (K // 4) * N
     t_hbm = alg / (HBM_PEAK_GBS * 1e9) * 1e3
-    t_lds = lds / (LDS_PEAK_GBS * 1e9) * 1e3
-    if N <= 16:
-        bound, floor = "hbm", t_hbm
-    elif N >= 256:
-        bound, floor = "lds", t_lds
-    else:
-        bound, floor = ("lds", t_lds) if t_lds >= t_hbm else ("hbm", t_hbm)
-    return {"bound": bound, "floor_ms": floor, "frac": floor / ms, "hbm_floor_ms": t_hbm, "lds_floor_ms": t_lds}
+    t_mfma = 2.0 * M * K * N / (MFMA_INT8_PEAK_TOPS * 1e12) * 1e3
+    bound, floor = ("mfma", t_mfma) if t_mfma >= t_hbm else ("hbm", t_hbm)
+    return {"bound": bound, "floor_ms": floor, "frac": floor / ms, "hbm_floor_ms": t_hbm, "mfma_floor_ms": t_mfma}
 
 
 def measure_entry(B, torch, wl, wname, lin, n, seed, rotate, steps, warmup, with_mfma=True):
-    """One (shape, N) of the sweep: the whole step through vlut_mpgemm_f32, the lookup kernel alone, the comparison
+    """One (shape, N) of the sweep: the whole step through vlut_mpgemm_f32, the product's kernel alone, the comparison
     path.  Returns (dict for the JSON line, Case, (W, w_scale, x))."""
     wk = wl.WORKLOADS[wname]
     W, w_scale, x = wl.make_case(wk, lin, n, seed)
@@ -386,10 +373,9 @@ def measure_layer(B, torch, wl, n, seed, rotate, steps, warmup):
     ms, ms_gpu, _ = run_timed(torch, fn, steps, warmup)
     shapes = [(lins[nm].M, lins[nm].K) for nm in ("q", "k", "v", "o", "gate", "up", "down")]
     alg = sum(m * k // 4 + 4 * m * n for m, k in shapes) + 3 * (2560 * n + 4 * n) + (6912 * n + 4 * n)
-    lds = sum(2 * m * (k // 4) * n for m, k in shapes)
-    t_hbm, t_lds = alg / (HBM_PEAK_GBS * 1e9) * 1e3, lds / (LDS_PEAK_GBS * 1e9) * 1e3
-    bound, floor = ("hbm", t_hbm) if n <= 16 else (("lds", t_lds) if (n >= 256 or t_lds >= t_hbm) else ("hbm", t_hbm))
     ops = sum(2.0 * m * k * n for m, k in shapes)
+    t_hbm, t_mfma = alg / (HBM_PEAK_GBS * 1e9) * 1e3, ops / (MFMA_INT8_PEAK_TOPS * 1e12) * 1e3
+    bound, floor = ("mfma", t_mfma) if t_mfma >= t_hbm else ("hbm", t_hbm)
     return {"N": n, "seed": seed, "launches": 4, "what": "q|k|v, o, gate|up, down through vlut_mpgemm_f32 (quantisation included)",
             "plans": [list(c.plan32) for c in cases],
             "ms": ms, "gpu_ms": ms_gpu, "GOPS": ops / (ms * 1e-3) / 1e9,
@@ -447,7 +433,7 @@ def main():
         if not torch.equal(y_ref, case.y):
             print("bench.py: the 1.60-bit path disagrees with the 2-bit path", file=sys.stderr)
             sys.exit(4)
-        g5 = {"what": "vlut_mpgemm_g5 on the same weights packed 5 per byte (1.60 bits per weight, 243-row tables)",
+        g5 = {"what": "vlut_mpgemm_g5 on the same weights packed 5 per byte (1.60 bits per weight)",
               "ms": ms_g5, "plan": {"R": case.plan5[0], "split_k": case.plan5[1], "workgroups": case.plan5[2]},
               "packed_weight_bytes": case.pool5[0].numel(), "time_over_2bit": ms_g5 / ms_gemm}
     else:
@@ -458,33 +444,23 @@ def main():
             sys.exit(4)
         g5 = {"what": "vlut_mpgemm_mixed on the same weights (first 20*floor(K/20) features 5 per byte, the rest 4 per byte)",
               "ms": ms_mx, "packed_weight_bytes": case.poolx[0].numel(), "time_over_2bit": ms_mx / ms_gemm}
-    if case.plan32[0] == 0:
-        kernel_name = "narrow_kernel (few tokens: quantisation, table build, lookups and scale in one launch)"
-    elif case.plan32[4] and case.plan32[2] == 1:
-        kernel_name = ("lookup_kernel, quantising variant (absmax + INT8 codes, LDS table build, lookup-accumulate, "
-                       "epilogue in one launch)")
+    if N <= 16 and N * K <= 65536:
+        kernel_name = "decode_kernel (few tokens: quantisation, unpacking, INT8 matrix cores and scale in one launch)"
     else:
-        kernel_name = "lookup_kernel (LDS table build + lookup-accumulate + epilogue)"
+        kernel_name = "gemm_kernel (packed bytes unpacked in registers, INT8 matrix cores, scale)"
     ops = 2.0 * M * K * N
-    adds = M * (K // 4) * N                      # one INT16 add (= 2 table bytes) per (row, group, token)
     gops = ops / (ms_step * 1e-3) / 1e9
-    achieved_tadds = adds / (ms_kernel * 1e-3) / 1e12
-    lds_gbs = 2.0 * adds / (ms_kernel * 1e-3) / 1e9
     alg = wl.algorithmic_bytes(M, K, N)
     rk = roof(M, K, N, ms_kernel)
     traffic_key = f"{w.name}/{lin.name}/{N}"
     roofline = {
         "kernel": kernel_name, "kernel_ms": ms_kernel,
         "bound": rk["bound"],
-        "achieved": lds_gbs if rk["bound"] == "lds" else alg / (ms_kernel * 1e-3) / 1e9,
-        "peak": LDS_PEAK_GBS if rk["bound"] == "lds" else HBM_PEAK_GBS, "unit": "GB/s",
+        "achieved": ops / (ms_kernel * 1e-3) / 1e12 if rk["bound"] == "mfma" else alg / (ms_kernel * 1e-3) / 1e9,
+        "peak": MFMA_INT8_PEAK_TOPS if rk["bound"] == "mfma" else HBM_PEAK_GBS,
+        "unit": "TOPS" if rk["bound"] == "mfma" else "GB/s",
         "frac": rk["frac"],
-        "what": ("lds: table bytes the lookups read, 2 per (row, k-group, token), against 256 CUs x 256 B/clk x 2.4 GHz; "
-                 "hbm: algorithmic bytes against 8 TB/s"),
-        "alu_equivalent": {"achieved_TADDs": achieved_tadds, "peak_TADDs": ALU_PEAK_TADDS,
-                           "frac": achieved_tadds / ALU_PEAK_TADDS},
-        "lds_frac": lds_gbs / LDS_PEAK_GBS,
-        "lds_frac_of_measured_peak": lds_gbs / LDS_MEASURED_PEAK_GBS,
+        "what": "mfma: 2 M K N operations against 5 POP/s dense INT8; hbm: algorithmic bytes against 8 TB/s",
         "hbm_frac": alg / (ms_kernel * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "traffic": MEASURED_TRAFFIC_BYTES.get(traffic_key),
         "traffic_source": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE summary under profiles/ (a stored figure: this run "
@@ -494,10 +470,10 @@ def main():
         "metric": "ternary mpGeMM GOPS (2*M*K*N) + weight-stream GB/s at N=1..1024 tokens",
         "value": gops, "unit": "GOPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": ms_step, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "int16/int32 (INT8 activations, ternary weights)", "data": "synthetic",
+        "dtype": "int8/int32 (INT8 activations, ternary weights)", "data": "synthetic",
         "config": {"workload": f"{w.name}/{lin.name}: M={M} K={K} N={N}, ternary P(0)={w.p_zero}, INT8 per-token absmax "
                                f"activations from N(0,1)" + (f" with {w.outlier_frac:.0%} outlier channels x20" if w.outlier_frac else "") +
-                               "; step = vlut_mpgemm_f32 (quantise + table build + lookup + scale)",
+                               "; step = vlut_mpgemm_f32 (quantise + product + scale)",
                    "plan": head["plan"], "weight_pool_buffers": len(case.pool), "launch": mode,
                    "timing": f"median of {REPS} replays of a graph of {args.steps} steps"},
         "weight_stream_GBs": (M * K / 4) / (ms_step * 1e-3) / 1e9,
@@ -506,7 +482,7 @@ def main():
                                      "ms_per_step": ms_step_stream},
         "two_call_form": {"what": "vlut_quantize_act + vlut_mpgemm on the same inputs", "ms_per_step": ms_two_call,
                           "mpgemm_kernel_ms": ms_gemm},
-        "mfma_comparison": {"what": "vlut_mpgemm_mfma on the same inputs (unpack to INT8 + v_mfma_i32_16x16x64_i8), "
+        "mfma_comparison": {"what": "vlut_mpgemm_mfma on the same inputs (weights unpacked through LDS + v_mfma_i32_16x16x64_i8), "
                                     "GPU ms per call incl. its activation re-layout kernel",
                             "ms": head.get("mfma_ms"), "lut_over_mfma_time": head.get("lut_over_mfma_time"),
                             "mfma_frac_of_int8_peak": head.get("mfma_frac_of_int8_peak")},
