@@ -179,7 +179,7 @@ int vlut_mpgemm_token_outer(const uint8_t* packed, float w_scale, const float* a
  * workspace; the results are the same numbers.  For more tokens (no table given, no plan override) the product runs
  * on the INT8 matrix cores, the packed bytes taken apart in registers: the same INT32 sums without tables (and without
  * the workspace, whose size stays that of the lookup plan).  The lookup kernel runs where a plan is forced or a
- * materialised table is given.
+ * materialised table is given, and where few rows and tokens with a long K leave the matrix cores too few workgroups.
  */
 int vlut_mpgemm(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale,
                 const int16_t* lut_or_null, int64_t M, int64_t K, int64_t N, float* y, int64_t ldy,
@@ -219,7 +219,7 @@ int vlut_mpgemm_rows(const uint8_t* packed, const float* w_scale_rows, const int
 /*
  * Quantisation and mpGeMM in one call, from fp32 activations: the steps of vlut_quantize_act (Sec. 3.4 first
  * paragraph: per-token absmax INT8) and of vlut_mpgemm / vlut_mpgemm_rows (Alg. 1, Eq. 2) with the same readings and
- * the same numbers.  Up to 16 tokens with N * K <= 65536 (and M <= 32768 for more than two tokens) it is one launch: every
+ * the same numbers.  Up to 16 tokens with N * K <= 65536 and M <= 32768 it is one launch: every
  * workgroup quantises all tokens itself and multiplies on the matrix cores, no INT8 activations in memory.  Beyond
  * that, the few-token kernel where it applies from fp32 (reported by vlut_query_plan_f32 with J = 0, also where the
  * former takes the call; K <= 35840 for one token, 39936 for more), else the quantiser as a kernel of its own into the

@@ -617,6 +617,11 @@ int choose_gemm_tile(int gw, int64_t M, int64_t macros, int64_t N) {
     return best;
 }
 
+double gemm_best_cost(int gw, int64_t M, int64_t K, int64_t N) {
+    const int64_t macros = ((K / gw + 15) / 16 + 1) / 2;
+    return gemm_cost(gw, choose_gemm_tile(gw, M, macros, N), M, macros, N);
+}
+
 template <int GW, int I>
 int launch_gemm_t(const GemmParams& p, hipStream_t stream) {
     constexpr GemmTile t = kGemmTiles[I];
@@ -669,10 +674,10 @@ int launch_gemm(const uint8_t* packed, float w_scale, const float* w_rows, const
 // ---- up to sixteen tokens from fp32 (decode_kernel): one launch, every workgroup quantises all tokens.  Measured against
 //      quantiser + gemm_kernel (about 4 us more launches): 2560 x 2560 x 16 7.0 us, 13824 x 2560 x 16 8.8 us (10.5 us as two), but
 //      2560 x 6912 x 16 15.0 us (11.5 us): the rows of x are read by every workgroup, so N * K is bounded; beyond 128 rows for
-//      each of 256 workgroups that work is repeated, so more than two tokens bound M.
+//      each of 256 workgroups that work is repeated (128256 x 4096 x 1 45 us, the table kernel 30 us), so M is bounded too.
 constexpr int64_t kDecodeMaxValues = 65536;
 bool decode_applies(int64_t M, int64_t K, int64_t N) {
-    return N <= 16 && N * K <= kDecodeMaxValues && (M <= 256 * 128 || N <= 2);
+    return N <= 16 && N * K <= kDecodeMaxValues && M <= 256 * 128;
 }
 
 template <int T, int MT>
@@ -931,7 +936,10 @@ static int mpgemm_impl(const uint8_t* packed, float w_scale, const float* w_rows
         if (!workspace) return VLUT_ERR_NULL;
         if (workspace_bytes < ws_need) return VLUT_ERR_SMALL_BUFFER;
     }
-    if (!lut_or_null && !lookup_plan_forced())
+    // Few rows and tokens with a long K leave the matrix-core path a handful of workgroups, while the lookup kernel can
+    // split K over many (with the partial sums in the workspace): the cheaper of the two fitted costs.  Measured, lookup / matrix
+    // cores: 64 x 16384 x 40 10.8 / 14.0 us, 16 x 65532 x 33 23.8 / 45 us, but 200 x 14336 x 64 14.1 / 12.9, 640 x 2560 x 40 8.4 / 5.9.
+    if (!lut_or_null && !lookup_plan_forced() && plan_cost(pl, M, K, N) * 1e-3 >= gemm_best_cost(4, M, K, N))
         return launch_gemm(packed, w_scale, w_rows, a_q, a_scale, M, K, 0, N, y, ldy, acc_or_null, (hipStream_t)stream);
     LookupParams p;
     std::memset(&p, 0, sizeof(p));

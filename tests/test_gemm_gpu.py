@@ -58,8 +58,10 @@ def test_every_packed_byte(B, g, K):
 
 
 @pytest.mark.parametrize("M,K,N", [(31, 64, 33), (32, 128, 32), (65, 192, 31), (33, 4160, 65), (127, 516, 64), (129, 2564, 96),
-                                   (3840, 260, 1000), (4099, 1028, 1030), (8193, 132, 520), (513, 9220, 515), (7000, 2580, 127)])
+                                   (3840, 260, 1000), (4099, 1028, 1030), (8193, 132, 520), (513, 9220, 515), (7000, 2580, 127), (16, 32768, 33), (64, 16384, 40),
+                                   (200, 14336, 64)])
 def test_tile_edges(B, M, K, N):
+    # (the last three: next to the rule that leaves few rows with a long K to the lookup kernel)
     W, s, x = wl.small_case(1200 + M + N, M, K, N)
     check(B, W, s, x, tag="edges")
 
