@@ -460,7 +460,7 @@ struct F32Layout {
 size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 // From how many tokens the quantiser takes four tokens per workgroup instead of one.  Measured, one / four: N = 512 3.8 / 4.8 us
-// at K = 4096, 4.9 / 6.6 at 6912, 8.4 / 11.6 at 14336; N = 1024 5.6 / 5.3, 8.0 / 7.3, 15.8 / 14.8.
+// at K = 4096, 4.9 / 6.6 at 6912, 8.4 / 11.6 at 14336; N = 1024 5.6 / 5.3, 8.0 / 7.3, 15.8 / 14.8, but 4.0 / 4.1 at K = 2560 (short rows stay with one).
 constexpr int64_t kQuantTokenMaxN = 768;
 
 F32Layout f32_layout(int64_t M, int64_t K, int64_t N) {
@@ -839,7 +839,7 @@ static int quantize_impl(const float* x, int64_t N, int64_t K, int64_t ldx, int8
     hipStream_t s = (hipStream_t)stream;
     const int chunks = (int)((N + 7) / 8);
     const bool vec = (((uintptr_t)x) % 16 == 0) && (ldx % 4 == 0);
-    if (N < kQuantTokenMaxN) {                 // one workgroup per token
+    if (N < kQuantTokenMaxN || K <= 3072) {    // one workgroup per token
         const unsigned blocks = (unsigned)((chunks + 7) / 8) * 64;
         auto launch_tok = [&](auto kfn) -> int {
             hipLaunchKernelGGL(kfn, dim3(blocks), dim3(kTokThreads), 0, s, x, (int)N, (int)K, ldx, a_q, a_scale, chunks);
