@@ -937,9 +937,9 @@ static int mpgemm_impl(const uint8_t* packed, float w_scale, const float* w_rows
         if (workspace_bytes < ws_need) return VLUT_ERR_SMALL_BUFFER;
     }
     // Few rows and tokens with a long K leave the matrix-core path a handful of workgroups, while the lookup kernel can
-    // split K over many (with the partial sums in the workspace): the cheaper of the two fitted costs.  Measured, lookup / matrix
+    // split K over many (with the partial sums in the workspace): the cheaper of the two fitted costs (the lookup kernel's overstates so few outputs by a third).  Measured, lookup / matrix
     // cores: 64 x 16384 x 40 10.8 / 14.0 us, 16 x 65532 x 33 23.8 / 45 us, but 200 x 14336 x 64 14.1 / 12.9, 640 x 2560 x 40 8.4 / 5.9.
-    if (!lut_or_null && !lookup_plan_forced() && plan_cost(pl, M, K, N) * 1e-3 >= gemm_best_cost(4, M, K, N))
+    if (!lut_or_null && !lookup_plan_forced() && plan_cost(pl, M, K, N) * (M * N <= 4096 ? 0.75e-3 : 1e-3) >= gemm_best_cost(4, M, K, N))
         return launch_gemm(packed, w_scale, w_rows, a_q, a_scale, M, K, 0, N, y, ldy, acc_or_null, (hipStream_t)stream);
     LookupParams p;
     std::memset(&p, 0, sizeof(p));
