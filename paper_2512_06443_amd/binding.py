@@ -103,12 +103,16 @@ def _check(status: int, where: str) -> None:
 
 
 # The raw handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object around the same
-# handle, 2.7 us of a call that takes 8.7; asking for the handle itself takes 0.1.
-_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+# handle, 2.7 us of a call that takes 8.7; asking for the handle itself takes 0.1.  The two functions are private names of torch:
+# where a build does not have them (one without a GPU, on which the size helpers still work) the public call serves.
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    _raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 
-
-def _stream() -> int:
-    return _raw_stream(_device())
+    def _stream() -> int:
+        return _raw_stream(_device())
+else:
+    def _stream() -> int:
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

@@ -340,3 +340,20 @@ def test_mixed_packing_host_logic(L):
     assert L.vlut_mpgemm_mixed(d, 1.0, d, d, 8, 36, 4, d, 7, None, d, 1 << 20, None) == -2
     assert L.vlut_mpgemm_mixed(d, 1.0, d, d, 8, 36, 4, d, 8, None, None, 0, None) == -1        # the workspace is required
     assert L.vlut_mpgemm_mixed(d, 1.0, d, d, 8, 36, 4, d, 8, None, d, 16, None) == -3
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_binding_imports_without_the_private_stream_functions(monkeypatch, missing):
+    """A torch without a GPU build has neither of the two functions the stream handle is taken from; the module still
+    imports there and its size helpers work."""
+    import importlib.util
+
+    import torch
+    from paper_2512_06443_amd import binding
+    monkeypatch.delattr(torch._C, missing)
+    spec = importlib.util.spec_from_file_location("binding_without_gpu_build", binding.__file__)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    assert mod.packed_weight_bytes(256, 256) == 16384
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 77})())
+    assert mod._stream() == 77
