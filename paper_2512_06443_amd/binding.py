@@ -300,7 +300,7 @@ def mpgemm_f32(packed: torch.Tensor, w_scale, x: torch.Tensor, M: int, y: Option
             workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=x.device)
     else:
         ws_bytes = workspace.numel() * workspace.element_size()
-    rc = L.vlut_mpgemm_f32(packed.data_ptr(), 1.0 if rows is not None else float(w_scale), _ptr(rows), x.data_ptr(), x.stride(0),
+    rc = L.vlut_mpgemm_f32(_ptr(packed), 1.0 if rows is not None else float(w_scale), _ptr(rows), x.data_ptr(), x.stride(0),
                            M, K, N, y.data_ptr(), y.stride(0), _ptr(acc), _ptr(scales), _ptr(workspace), ws_bytes, _stream())
     if rc != VLUT_OK:
         raise VlutError(rc, "vlut_mpgemm_f32")

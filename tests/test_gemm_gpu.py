@@ -142,3 +142,9 @@ def test_pack_unaligned_and_value_check(B):
             bad[pos] = value
             assert raw(bad.data_ptr(), M, K, want.data_ptr(), want.numel(), None) == B.VLUT_ERR_VALUE
             assert torch.equal(wrapped(dev(W)), wrapped(dev(W)))
+
+
+def test_missing_matrix_is_a_status_code(B):
+    with pytest.raises(B.VlutError) as e:
+        B.mpgemm_f32(None, 1.0, torch.zeros((4, 64), device="cuda"), 64)
+    assert e.value.status == B.VLUT_ERR_NULL
