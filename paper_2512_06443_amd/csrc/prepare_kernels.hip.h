@@ -76,13 +76,16 @@ __global__ void __launch_bounds__(256) pack_kernel(const int8_t* __restrict__ w,
 
 // ---------------------------------------------------------------------------------------------
 // Activation quantisation + transposition (Sec. 3.4 first paragraph, Sec. 3.3).
-// For about a thousand tokens and more: one workgroup handles four consecutive tokens (half a chunk) over all K, so that
-// 1024 tokens are one workgroup per compute unit, and a row up to 14336 values stays in registers between the absmax and
-// the rounding (N = 1024: 7.3 us at K = 6912, 14.8 us at K = 14336; one token per workgroup: 8.0 and 15.8 us).  A wave reads 16
-// consecutive float4 of each of the four tokens (lane = token + 4 * quad): 256 contiguous bytes per token.  The four codes
+// For many tokens: one workgroup handles four consecutive tokens (half a chunk) or all eight of a chunk over all K, and a
+// row stays in registers between the absmax and the rounding (four tokens: up to 14336 values, eight: up to 3072).  Four tokens
+// are for about a thousand tokens and more, so that 1024 tokens are one workgroup per compute unit (N = 1024: 8.4 us at K = 6912,
+// 15.9 us at K = 14336; one token per workgroup: 8.9 and 17.0 us).  Eight are for several thousand tokens of short rows, where the stores
+// bound it: a wave then writes whole lines of the chunk instead of every second dword of them (N = 4096: 5.6 / 8.8 / 11.2 us at K = 1028 /
+// 2048 / 2560; four tokens: 7.1 / 10.2 / 12.1).  A wave reads 64 / TOK consecutive float4 of each of its tokens (lane = token + TOK * quad).  The four codes
 // a lane makes (4 consecutive k of one token) are transposed inside its quad of lanes, so that every lane leaves with
 // one dword of the chunk's [K][8] block (4 tokens of one k); the two halves of a chunk are blocks 8 apart (same XCD under
 // round-robin dispatch), so their half lines meet in one L2.
+//   TOK tokens per workgroup: 4 or 8
 //   NV  float4 values per thread kept in registers between the absmax pass and the rounding pass
 //       (0: x is read twice, for large K)
 //   VEC true when rows can be read as float4 (x and ldx 16-byte aligned)
@@ -116,17 +119,19 @@ __device__ __forceinline__ unsigned quad_transpose_codes(unsigned d, int tok) {
     return lo | hi;
 }
 
-template <int NV, bool VEC>
+template <int TOK, int NV, bool VEC>
 __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(const float* __restrict__ x, int N, int K, int64_t ldx,
                                                                  int8_t* __restrict__ a_q, float* __restrict__ a_scale, int chunks) {
-    __shared__ __attribute__((aligned(16))) float red[4][kQuantThreads / 64];
+    constexpr int QW = 64 / TOK;               // quads of each token that a wave handles per pass
+    constexpr int QP = kQuantThreads / TOK;    // and the workgroup
+    __shared__ __attribute__((aligned(16))) float red[TOK][kQuantThreads / 64];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int b = blockIdx.x;
-    const int chunk = (b >> 4) * 8 + (b & 7), half = (b >> 3) & 1;
+    const int chunk = TOK == 8 ? b : (b >> 4) * 8 + (b & 7), half = TOK == 8 ? 0 : (b >> 3) & 1;
     if (chunk >= chunks) return;
-    const int t = lane & 3;                    // token of the four
-    const int kq = wave * 16 + (lane >> 2);    // this thread handles k = 4*(kq + 256*i) .. +3
+    const int t = lane & (TOK - 1);            // token of the four or eight
+    const int kq = wave * QW + lane / TOK;     // this thread handles k = 4*(kq + QP*i) .. +3
     const int n = chunk * 8 + half * 4 + t;
     const bool live = n < N;
     const float* row = x + (size_t)(live ? n : 0) * ldx;
@@ -135,7 +140,7 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(const float* __
     auto load_pass = [&](int q0, f32x4 (&v)[NB]) {
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            const int qi = q0 + kq + 256 * i;
+            const int qi = q0 + kq + QP * i;
             const float* src = row + 4 * (size_t)qi;
             if (!live || qi >= nquad) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
             else if (VEC) v[i] = *(const f32x4*)src;
@@ -144,14 +149,14 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(const float* __
     };
     f32x4 xv[NB];
     float amax = 0.0f;
-    for (int q0 = 0; q0 < (NV > 0 ? 1 : nquad); q0 += 256 * NB) {
+    for (int q0 = 0; q0 < (NV > 0 ? 1 : nquad); q0 += QP * NB) {
         load_pass(q0, xv);
 #pragma unroll
         for (int i = 0; i < NB; ++i)
             amax = fmaxf(fmaxf(amax, fmaxf(fabsf(xv[i].x), fabsf(xv[i].y))), fmaxf(fabsf(xv[i].z), fabsf(xv[i].w)));
     }
-    for (int off = 32; off >= 4; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));   // lanes of the same token
-    if (lane < 4) red[lane][wave] = amax;
+    for (int off = 32; off >= TOK; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));   // lanes of the same token
+    if (lane < TOK) red[lane][wave] = amax;
     __syncthreads();
     float v = 0.0f;
 #pragma unroll
@@ -161,15 +166,15 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(const float* __
     }
     // IEEE-correct fp32 divisions (the default for HIP); no reciprocal approximation.
     const float inv = (v > 0.0f) ? 127.0f / v : 0.0f;
-    if (tid < 4 && live) a_scale[n] = v / 127.0f;
-    unsigned* dst = (unsigned*)(a_q + (size_t)chunk * K * 8) + half;
-    for (int q0 = 0; q0 < (NV > 0 ? 1 : nquad); q0 += 256 * NB) {
+    if (tid < TOK && live) a_scale[n] = v / 127.0f;
+    unsigned* dst = (unsigned*)(a_q + (size_t)chunk * K * 8) + (TOK == 8 ? t >> 2 : half);
+    for (int q0 = 0; q0 < (NV > 0 ? 1 : nquad); q0 += QP * NB) {
         if (NV == 0) load_pass(q0, xv);
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            const int qi = q0 + kq + 256 * i;  // uniform in a quad of lanes; tokens past N: x = 0 -> code 0
+            const int qi = q0 + kq + QP * i;   // uniform in a quad of lanes; tokens past N: x = 0 -> code 0
             const unsigned e = quad_transpose_codes(quant_codes4(xv[i], inv), t);
-            if (qi < nquad) dst[(size_t)(4 * qi + t) * 2] = e;
+            if (qi < nquad) dst[(size_t)(4 * qi + (t & 3)) * 2] = e;
         }
     }
 }
@@ -181,15 +186,17 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(const float* __
 // instead of 16.  N = 64: 5.2 -> 3.2 us at K = 6912; N = 512, K = 14336: 20.8 -> 8.4 us.  Tokens past N (padding of the last
 // chunk) are written as zeros.  Blocks are numbered so that the 8 tokens of a chunk sit 8 blocks apart (same XCD under
 // round-robin dispatch, so their partial lines meet in one L2); this is a matter of speed only.
+//   THREADS  by the length of the rows: a wave without a value to load costs its launch and its part of the barriers all the
+//            same.  N = 4096: 3.6 us at K = 64 with one wave, 5.8 us at K = 1024 with four (512 threads: 6.5 and 7.8)
 //   NV  float4 values per thread kept in registers between the two passes (0: x is read twice)
-constexpr int kTokThreads = 512;               // 256: 0.7 to 2 us slower from K = 6912 on; 1024: the same
+constexpr int kTokThreads = 512;               // longer rows.  256: 0.7 to 2 us slower from K = 6912 on; 1024: 0.9 us slower at K = 2560, N = 1024
 
-template <int NV, bool VEC>
-__global__ void __launch_bounds__(kTokThreads) quantize_token_kernel(const float* __restrict__ x, int N, int K, int64_t ldx,
+template <int THREADS, int NV, bool VEC>
+__global__ void __launch_bounds__(THREADS) quantize_token_kernel(const float* __restrict__ x, int N, int K, int64_t ldx,
                                                                      int8_t* __restrict__ a_q,
                                                                      float* __restrict__ a_scale, int chunks) {
-    __shared__ float red[kTokThreads / 64];
-    __shared__ unsigned codes[kTokThreads / 64][64];
+    __shared__ float red[THREADS / 64];
+    __shared__ unsigned codes[THREADS / 64][64];
     const int tid = threadIdx.x;
     const int b = blockIdx.x;
     const int chunk = (b >> 6) * 8 + (b & 7);
@@ -211,10 +218,10 @@ __global__ void __launch_bounds__(kTokThreads) quantize_token_kernel(const float
     f32x4 xv[NB];
     float amax = 0.0f;
     if (live) {
-        for (int q0 = 0; q0 < (NV > 0 ? 1 : nquad); q0 += kTokThreads * NB) {
+        for (int q0 = 0; q0 < (NV > 0 ? 1 : nquad); q0 += THREADS * NB) {
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
-                const int qi = q0 + tid + kTokThreads * i;
+                const int qi = q0 + tid + THREADS * i;
                 xv[i] = qi < nquad ? load4(qi) : f32x4{0.f, 0.f, 0.f, 0.f};
             }
 #pragma unroll
@@ -226,7 +233,7 @@ __global__ void __launch_bounds__(kTokThreads) quantize_token_kernel(const float
     __syncthreads();
     float v = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kTokThreads / 64; ++w) v = fmaxf(v, red[w]);
+    for (int w = 0; w < THREADS / 64; ++w) v = fmaxf(v, red[w]);
     const float inv = (v > 0.0f) ? 127.0f / v : 0.0f;      // IEEE divisions
     if (tid == 0 && live) a_scale[n] = v / 127.0f;
     int8_t* dst = a_q + (size_t)chunk * K * 8 + t;
@@ -242,17 +249,17 @@ __global__ void __launch_bounds__(kTokThreads) quantize_token_kernel(const float
         }
         __builtin_amdgcn_wave_barrier();
     };
-    for (int q0 = 0; q0 < (NV > 0 ? 1 : nquad); q0 += kTokThreads * NB) {
+    for (int q0 = 0; q0 < (NV > 0 ? 1 : nquad); q0 += THREADS * NB) {
         if (NV == 0 && live) {
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
-                const int qi = q0 + tid + kTokThreads * i;
+                const int qi = q0 + tid + THREADS * i;
                 xv[i] = qi < nquad ? load4(qi) : f32x4{0.f, 0.f, 0.f, 0.f};
             }
         }
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            const int qi = q0 + tid + kTokThreads * i;
+            const int qi = q0 + tid + THREADS * i;
             if (qi - (tid & 63) < nquad) store4(qi, live ? quant_codes4(xv[i], inv) : 0u);      // (uniform per wave)
         }
     }

@@ -459,10 +459,6 @@ struct F32Layout {
 
 size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// From how many tokens the quantiser takes four tokens per workgroup instead of one.  Measured, one / four: N = 512 3.8 / 4.8 us
-// at K = 4096, 4.9 / 6.6 at 6912, 8.4 / 11.6 at 14336; N = 1024 5.6 / 5.3, 8.0 / 7.3, 15.8 / 14.8, but 4.0 / 4.1 at K = 2560 (short rows stay with one).
-constexpr int64_t kQuantTokenMaxN = 768;
-
 F32Layout f32_layout(int64_t M, int64_t K, int64_t N) {
     F32Layout L;
     std::memset(&L, 0, sizeof(L));
@@ -595,6 +591,40 @@ int launch_lookup5_by_r(int r, const Lookup5Params& p, int grid, hipStream_t str
 template <bool NEED32>
 int launch_lookup5_r(int R, const Lookup5Params& p, int grid, hipStream_t stream) {
     return launch_lookup5_by_r<NEED32>(R, p, grid, stream);
+}
+
+// ---- quantiser: tokens per workgroup and threads by the shape, rows in registers whether they are aligned or not (reading
+//      unaligned ones twice, eight loads at a time, costs 21 us instead of 5.6 at N = 4096, K = 1024).  Measured, us:
+//        one token per workgroup up to K = 1024 (K = 768, N = 4096: 5.2; four tokens 6.7), up to N = 1536 while K <= 3072 (K = 2560,
+//        N = 1024 / 2000: 4.7 / 7.0; four tokens 4.9 / 6.5), up to N = 768 beyond (K = 6912, N = 512 / 1024: 5.7 / 8.9; four tokens 7.4 / 8.4)
+//        eight tokens from N = 3584 on while K <= 3072 (K = 2560, N = 3000 / 4096: 9.6 / 11.2; four tokens 9.3 / 12.1)
+template <bool VEC>
+int launch_quantize(const float* x, int64_t N, int64_t K, int64_t ldx, int8_t* a_q, float* a_scale, int chunks, hipStream_t s) {
+    const unsigned blocks8 = (unsigned)((chunks + 7) / 8);       // groups of eight chunks, one per XCD
+    auto launch = [&](auto kfn, unsigned grid, int threads) -> int {
+        hipLaunchKernelGGL(kfn, dim3(grid), dim3(threads), 0, s, x, (int)N, (int)K, ldx, a_q, a_scale, chunks);
+        return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+    };
+    if (K <= 256) return launch(quantize_token_kernel<64, 1, VEC>, blocks8 * 64, 64);
+    if (K <= 1024) return launch(quantize_token_kernel<256, 1, VEC>, blocks8 * 64, 256);
+    if (N < (K <= 3072 ? 1536 : 768)) {
+        constexpr int T = kTokThreads;
+        if (K <= 4096) return launch(quantize_token_kernel<T, 2, VEC>, blocks8 * 64, T);
+        if (K <= 8192) return launch(quantize_token_kernel<T, 4, VEC>, blocks8 * 64, T);
+        if (K <= 16384) return launch(quantize_token_kernel<T, 8, VEC>, blocks8 * 64, T);
+        return launch(quantize_token_kernel<T, 0, VEC>, blocks8 * 64, T);
+    }
+    if (N >= 3584 && K <= 3072) {
+        if (K <= 1536) return launch(quantize_kernel<8, 3, VEC>, (unsigned)chunks, kQuantThreads);
+        if (K <= 2048) return launch(quantize_kernel<8, 4, VEC>, (unsigned)chunks, kQuantThreads);
+        return launch(quantize_kernel<8, 6, VEC>, (unsigned)chunks, kQuantThreads);
+    }
+    if (K <= 2048) return launch(quantize_kernel<4, 2, VEC>, blocks8 * 16, kQuantThreads);
+    if (K <= 3072) return launch(quantize_kernel<4, 3, VEC>, blocks8 * 16, kQuantThreads);
+    if (K <= 4096) return launch(quantize_kernel<4, 4, VEC>, blocks8 * 16, kQuantThreads);
+    if (K <= 8192) return launch(quantize_kernel<4, 8, VEC>, blocks8 * 16, kQuantThreads);
+    if (K <= 14336) return launch(quantize_kernel<4, 14, VEC>, blocks8 * 16, kQuantThreads);
+    return launch(quantize_kernel<4, 0, VEC>, blocks8 * 16, kQuantThreads);
 }
 
 // ---- matrix-core path (gemm_kernel): every product with streamed tables, unless a plan of the lookup kernels is forced
@@ -839,29 +869,7 @@ static int quantize_impl(const float* x, int64_t N, int64_t K, int64_t ldx, int8
     hipStream_t s = (hipStream_t)stream;
     const int chunks = (int)((N + 7) / 8);
     const bool vec = (((uintptr_t)x) % 16 == 0) && (ldx % 4 == 0);
-    if (N < kQuantTokenMaxN || K <= 3072) {    // one workgroup per token
-        const unsigned blocks = (unsigned)((chunks + 7) / 8) * 64;
-        auto launch_tok = [&](auto kfn) -> int {
-            hipLaunchKernelGGL(kfn, dim3(blocks), dim3(kTokThreads), 0, s, x, (int)N, (int)K, ldx, a_q, a_scale, chunks);
-            return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
-        };
-        if (!vec) return launch_tok(quantize_token_kernel<0, false>);
-        if (K <= 4096) return launch_tok(quantize_token_kernel<2, true>);
-        if (K <= 8192) return launch_tok(quantize_token_kernel<4, true>);
-        if (K <= 16384) return launch_tok(quantize_token_kernel<8, true>);
-        return launch_tok(quantize_token_kernel<0, true>);
-    }
-    const unsigned blocks = (unsigned)((chunks + 7) / 8) * 16;
-    const int per_thread = (int)((K / 4 + 255) / 256);
-    auto launch = [&](auto kfn) -> int {
-        hipLaunchKernelGGL(kfn, dim3(blocks), dim3(kQuantThreads), 0, s, x, (int)N, (int)K, ldx, a_q, a_scale, chunks);
-        return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
-    };
-    if (!vec) return launch(quantize_kernel<0, false>);
-    if (per_thread <= 4) return launch(quantize_kernel<4, true>);
-    if (per_thread <= 8) return launch(quantize_kernel<8, true>);
-    if (per_thread <= 14) return launch(quantize_kernel<14, true>);
-    return launch(quantize_kernel<0, true>);
+    return vec ? launch_quantize<true>(x, N, K, ldx, a_q, a_scale, chunks, s) : launch_quantize<false>(x, N, K, ldx, a_q, a_scale, chunks, s);
 }
 
 int vlut_quantize_act(const float* x, int64_t N, int64_t K, int64_t ldx, int8_t* a_q, float* a_scale,

@@ -148,3 +148,45 @@ def test_missing_matrix_is_a_status_code(B):
     with pytest.raises(B.VlutError) as e:
         B.mpgemm_f32(None, 1.0, torch.zeros((4, 64), device="cuda"), 64)
     assert e.value.status == B.VLUT_ERR_NULL
+
+
+@pytest.mark.parametrize("N", [1535, 1541, 3583, 3590])
+def test_quantiser_at_its_switch_over_points(B, N):
+    # one, four and eight tokens per workgroup, one, four and eight waves; rows at the limits of what each keeps in registers
+    for K in (4, 252, 256, 260, 1024, 1028, 1536, 1540, 2048, 2052, 3072, 3076):
+        x = wl.activations(1700 + K, N, K)
+        x[N - 2] = 0.0
+        q_ref, s_ref = O.quantize(x)
+        odd = torch.full((N, K + 3), 9e9, device="cuda")
+        odd[:, 1:K + 1] = dev(x)
+        for xd in (dev(x), odd[:, 1:K + 1]):
+            print(f"quantiser case K={K} N={N} stride={xd.stride(0)}", flush=True)
+            a_q, a_s = B.quantize_act(xd, torch.full(((N + 7) // 8, K, 8), 99, dtype=torch.int8, device="cuda"))
+            torch.cuda.synchronize()
+            assert np.array_equal(B.act_chunked_to_kn(a_q, N).cpu().numpy(), q_ref)
+            assert np.array_equal(a_s.cpu().numpy().view(np.uint32), s_ref.view(np.uint32))
+            if N % 8:
+                assert int(a_q[-1, :, N % 8:].abs().max()) == 0
+
+
+@pytest.mark.parametrize("N,K", [(4096, 64), (4096, 1024), (2000, 2560), (1000, 6912)])
+def test_unaligned_rows_cost_the_quantiser_about_what_aligned_ones_do(B, N, K):
+    # they were read twice, eight loads at a time: 2 to 3 times as long.  The same bytes, so the same time but for the
+    # narrower loads (0.9 to 1.05 measured); half of it is left for a busy machine, the best of several runs is taken
+    x = torch.randn((N, K + 1), device="cuda")
+    out = B.quantize_act(x[:, 1:])
+    sides = {"unaligned": x[:, 1:], "aligned": x[:, 1:].contiguous()}
+    best = {}
+    for rep in range(8):
+        for name, xd in sides.items():
+            B.quantize_act(xd, *out)
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda._sleep(200000)                       # the launches queue up behind it: their own time, not the host's
+            e0.record()
+            for _ in range(20):
+                B.quantize_act(xd, *out)
+            e1.record()
+            torch.cuda.synchronize()
+            best[name] = min(best.get(name, 1e9), e0.elapsed_time(e1))
+    print(best)
+    assert best["unaligned"] < 1.5 * best["aligned"]
