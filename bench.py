@@ -115,6 +115,7 @@ class Case:
         self._f32 = L.vlut_mpgemm_f32
         self.ws32 = torch.empty(max(L.vlut_workspace_bytes_f32(self.M, self.K, self.N), 16), dtype=torch.uint8, device="cuda")
         self.plan32 = B.query_plan_f32(self.M, self.K, self.N)
+        self.kernel32 = B.query_kernel("f32", self.M, self.K, self.N)
         rows_ptr = None if self.w_rows is None else self.w_rows.data_ptr()
         self._fargs = [(pk.data_ptr(), self.w_scale, rows_ptr, self.x.data_ptr(), self.x.stride(0), self.M, self.K, self.N,
                         self.y.data_ptr(), self.y.stride(0), None, None, self.ws32.data_ptr(), self.ws32.numel())
@@ -131,7 +132,6 @@ class Case:
         self.pool5 = [packed] + [packed.clone() for _ in range(n_pool - 1)]
         ws = L.vlut_workspace_bytes_g5(self.M, self.K, self.N)
         self.ws5 = torch.empty(max(ws, 16), dtype=torch.uint8, device="cuda")
-        self.plan5 = B.query_plan_g5(self.M, self.K, self.N)
         self._gemm5 = L.vlut_mpgemm_g5
         self._g5args = [(pk.data_ptr(), self.w_scale, self.a_q.data_ptr(), self.a_s.data_ptr(), self.M, self.K, self.N,
                          self.y.data_ptr(), self.y.stride(0), None, self.ws5.data_ptr(), self.ws5.numel())
@@ -335,8 +335,7 @@ def measure_entry(B, torch, wl, wname, lin, n, seed, rotate, steps, warmup, with
     ms_step, ms_kernel, mode, ms_two, ms_gemm = time_case(B, torch, c, steps, warmup)
     r_step, r_kernel = roof(M, K, n, ms_step), roof(M, K, n, ms_kernel)
     e = {"workload": wname, "linear": lin.name, "M": M, "K": K, "N": n, "seed": seed,
-         "plan": {"J": c.plan32[0], "R": c.plan32[1], "split_k": c.plan32[2], "workgroups": c.plan32[3],
-                  "one_launch_from_fp32": bool(c.plan32[4])},
+         "kernel": c.kernel32, "one_launch_from_fp32": bool(c.plan32[4]),
          "ms": ms_step, "kernel_ms": ms_kernel, "two_call_ms": ms_two, "mpgemm_ms": ms_gemm,
          "GOPS": 2.0 * M * K * n / (ms_step * 1e-3) / 1e9,
          "weight_stream_GBs": (M * K / 4) / (ms_step * 1e-3) / 1e9,
@@ -377,7 +376,7 @@ def measure_layer(B, torch, wl, n, seed, rotate, steps, warmup):
     t_hbm, t_mfma = alg / (HBM_PEAK_GBS * 1e9) * 1e3, ops / (MFMA_INT8_PEAK_TOPS * 1e12) * 1e3
     bound, floor = ("mfma", t_mfma) if t_mfma >= t_hbm else ("hbm", t_hbm)
     return {"N": n, "seed": seed, "launches": 4, "what": "q|k|v, o, gate|up, down through vlut_mpgemm_f32 (quantisation included)",
-            "plans": [list(c.plan32) for c in cases],
+            "kernels": [c.kernel32 for c in cases],
             "ms": ms, "gpu_ms": ms_gpu, "GOPS": ops / (ms * 1e-3) / 1e9,
             "weight_stream_GBs": sum(m * k // 4 for m, k in shapes) / (ms * 1e-3) / 1e9,
             "bound": bound, "floor_ms": floor, "frac": floor / ms}
@@ -434,7 +433,7 @@ def main():
             print("bench.py: the 1.60-bit path disagrees with the 2-bit path", file=sys.stderr)
             sys.exit(4)
         g5 = {"what": "vlut_mpgemm_g5 on the same weights packed 5 per byte (1.60 bits per weight)",
-              "ms": ms_g5, "plan": {"R": case.plan5[0], "split_k": case.plan5[1], "workgroups": case.plan5[2]},
+              "ms": ms_g5, "kernel": B.query_kernel("g5", M, K, N),
               "packed_weight_bytes": case.pool5[0].numel(), "time_over_2bit": ms_g5 / ms_gemm}
     else:
         case.enable_mixed(B, torch, W, rotate)
@@ -444,10 +443,10 @@ def main():
             sys.exit(4)
         g5 = {"what": "vlut_mpgemm_mixed on the same weights (first 20*floor(K/20) features 5 per byte, the rest 4 per byte)",
               "ms": ms_mx, "packed_weight_bytes": case.poolx[0].numel(), "time_over_2bit": ms_mx / ms_gemm}
-    if N <= 16 and N * K <= 65536:
-        kernel_name = "decode_kernel (few tokens: quantisation, unpacking, INT8 matrix cores and scale in one launch)"
-    else:
-        kernel_name = "gemm_kernel (packed bytes unpacked in registers, INT8 matrix cores, scale)"
+    kernel_name = {"matrix_few_tokens": "decode_kernel (few tokens: quantisation, unpacking, INT8 matrix cores and scale in one launch)",
+                   "matrix": "gemm_kernel (packed bytes unpacked in registers, INT8 matrix cores, scale)",
+                   "few_tokens": "narrow_kernel (few tokens: table build, lookups and scale)",
+                   "lookup": "lookup_kernel (LDS table build, lookup-accumulate, scale)"}[head["kernel"]]
     ops = 2.0 * M * K * N
     gops = ops / (ms_step * 1e-3) / 1e9
     alg = wl.algorithmic_bytes(M, K, N)
@@ -474,7 +473,7 @@ def main():
         "config": {"workload": f"{w.name}/{lin.name}: M={M} K={K} N={N}, ternary P(0)={w.p_zero}, INT8 per-token absmax "
                                f"activations from N(0,1)" + (f" with {w.outlier_frac:.0%} outlier channels x20" if w.outlier_frac else "") +
                                "; step = vlut_mpgemm_f32 (quantise + product + scale)",
-                   "plan": head["plan"], "weight_pool_buffers": len(case.pool), "launch": mode,
+                   "kernel": head["kernel"], "weight_pool_buffers": len(case.pool), "launch": mode,
                    "timing": f"median of {REPS} replays of a graph of {args.steps} steps"},
         "weight_stream_GBs": (M * K / 4) / (ms_step * 1e-3) / 1e9,
         "algorithmic_GBs": alg / (ms_step * 1e-3) / 1e9,
@@ -519,13 +518,12 @@ def main():
         wk = wl.WORKLOADS["layer2b4_nsweep"]
         out["layer"] = [measure_layer(B, torch, wl, n, wk.seeds[wk.N.index(n)], rotate, args.steps, args.warmup)
                         for n in wk.N]
-        print(f"{'workload':18s} {'lin':7s} {'M':>6s} {'K':>6s} {'N':>5s} {'plan(J,R,S,WG)':>20s} {'step us':>9s} "
+        print(f"{'workload':18s} {'lin':7s} {'M':>6s} {'K':>6s} {'N':>5s} {'kernel':>17s} {'step us':>9s} "
               f"{'kernel us':>9s} {'TOPS':>7s} {'W GB/s':>8s} {'bound':>5s} {'frac':>6s} {'k.frac':>6s} {'mfma us':>8s}",
               file=sys.stderr)
         for e in sweep:
-            pl = e["plan"]
             print(f"{e['workload']:18s} {e['linear']:7s} {e['M']:6d} {e['K']:6d} {e['N']:5d} "
-                  f"{str((pl['J'], pl['R'], pl['split_k'], pl['workgroups'])):>20s} {e['ms'] * 1e3:9.1f} "
+                  f"{e['kernel']:>17s} {e['ms'] * 1e3:9.1f} "
                   f"{e['kernel_ms'] * 1e3:9.1f} {e['GOPS'] / 1e3:7.1f} {e['weight_stream_GBs']:8.1f} {e['bound']:>5s} "
                   f"{e['frac']:6.3f} {e['kernel_frac']:6.3f} {e.get('mfma_ms', float('nan')) * 1e3:8.1f}", file=sys.stderr)
         for e in out["layer"]:

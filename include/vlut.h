@@ -233,7 +233,9 @@ int vlut_mpgemm_rows(const uint8_t* packed, const float* w_scale_rows, const int
  *   workspace     dev, 16-byte aligned, workspace_bytes >= vlut_workspace_bytes_f32(M, K, N); may be NULL when that
  *                 size is 0
  * vlut_query_plan_f32 tells which form a shape takes:
- *   out5 = {J, R, split_k, workgroups, fused (1) or two launches (0)}  (J, R as in vlut_query_plan)
+ *   out5 = {J, R, split_k, workgroups, fused (1) or two launches (0)}  (J, R as in vlut_query_plan; one launch on the
+ *   matrix cores: {0, rows per workgroup, 1, workgroups, 1}, or the few-token kernel's figures where that one applies too)
+ * and vlut_query_kernel (below) names the kernel.
  * Errors as in vlut_mpgemm; VLUT_ERR_SHAPE also for ldx < K.
  */
 size_t vlut_workspace_bytes_f32(int64_t M, int64_t K, int64_t N);            /* 0 if the shape is invalid      */
@@ -324,9 +326,25 @@ int vlut_mpgemm_mfma(const uint8_t* packed, float w_scale, const int8_t* a_q, co
 int vlut_set_plan(int J, int R, int waves, int split_k);
 
 /*
- * Reports the launch plan of the lookup kernel for this shape (after any vlut_set_plan override of the calling
- * thread; without an override and beyond a few tokens vlut_mpgemm runs on the matrix cores instead): out4 (host, 4 ints) = { J, R, split_k, number of workgroup tiles }.  (The launch itself has at
- * most one workgroup per compute unit; each walks through its share of the tiles.)
+ * Which kernel computes the product of a call of one of the four forms (after any override of the calling thread; operands
+ * aligned to 16 bytes, no materialised table): one of VLUT_KERNEL_*, or a negative VLUT_ERR_* code where the call would
+ * report it.
+ */
+#define VLUT_FORM_CODES 0    /* vlut_mpgemm, vlut_mpgemm_rows, vlut_mpgemm_static                              */
+#define VLUT_FORM_F32 1      /* vlut_mpgemm_f32                                                                */
+#define VLUT_FORM_G5 2       /* vlut_mpgemm_g5                                                                 */
+#define VLUT_FORM_MIXED 3    /* vlut_mpgemm_mixed                                                              */
+#define VLUT_KERNEL_LOOKUP 1            /* tables in LDS, the plan that vlut_query_plan or vlut_query_plan_g5 reports */
+#define VLUT_KERNEL_FEW_TOKENS 2        /* tables in LDS, one or two tokens per workgroup                      */
+#define VLUT_KERNEL_MATRIX 3            /* INT8 matrix cores                                                   */
+#define VLUT_KERNEL_MATRIX_FEW_TOKENS 4 /* INT8 matrix cores, from fp32 in one launch                          */
+int vlut_query_kernel(int form, int64_t M, int64_t K, int64_t N);
+
+/*
+ * Reports the launch plan of the lookup kernel for this shape, after any vlut_set_plan override of the calling
+ * thread: out4 (host, 4 ints) = { J, R, split_k, number of workgroup tiles }.  (The launch itself has at most one
+ * workgroup per compute unit; each walks through its share of the tiles.)  Without an override and beyond a few tokens
+ * vlut_mpgemm mostly runs on the matrix cores instead: vlut_query_kernel tells.
  * With few tokens and no override (N <= 2 always; 3 <= N <= 32 when ceil(N/2) copies of the row tiles are at most
  * 256 workgroups and a cost estimate favours it: few rows per workgroup, or a short K), vlut_mpgemm uses a kernel
  * of its own (two tokens per
@@ -337,7 +355,7 @@ int vlut_query_plan(int64_t M, int64_t K, int64_t N, int* out4);
 
 /*
  * Lookup waves per workgroup of the plan vlut_query_plan reports (12 or 14: a workgroup tile holds 4 * waves * R output
- * rows); 0 when the few-token kernel runs; a negative VLUT_ERR_* code for an invalid shape or an override that does
+ * rows), whichever kernel runs; 0 where vlut_query_plan reports the few-token kernel; a negative VLUT_ERR_* code for an invalid shape or an override that does
  * not fit it.
  */
 int vlut_query_lookup_waves(int64_t M, int64_t K, int64_t N);

@@ -31,6 +31,7 @@ EXPORTS = [
     "vlut_build_lut_token_outer", "vlut_mpgemm_token_outer",
     "vlut_mixed_k5", "vlut_packed_weight_bytes_mixed", "vlut_workspace_bytes_mixed", "vlut_pack_weights_mixed",
     "vlut_mpgemm_mixed", "vlut_static_scratch_bytes", "vlut_mpgemm_static", "vlut_query_lookup_waves",
+    "vlut_query_kernel",
 ]
 
 _lib = None
@@ -85,6 +86,7 @@ def lib() -> ctypes.CDLL:
         L.vlut_mpgemm_f32.argtypes = [p, cf, p, p, i64, i64, i64, i64, p, i64, p, p, p, sz, p]
         L.vlut_mpgemm_f32.restype = ci
         L.vlut_query_lookup_waves.argtypes, L.vlut_query_lookup_waves.restype = [i64, i64, i64], ci
+        L.vlut_query_kernel.argtypes, L.vlut_query_kernel.restype = [ci, i64, i64, i64], ci
         L.vlut_static_scratch_bytes.argtypes, L.vlut_static_scratch_bytes.restype = [], sz
         L.vlut_mpgemm_static.argtypes, L.vlut_mpgemm_static.restype = [p, cf, p, p, i64, i64, i64, p, i64, p, p], ci
         L.vlut_set_plan.argtypes, L.vlut_set_plan.restype = [ci, ci, ci, ci], ci
@@ -211,11 +213,24 @@ def mpgemm(packed: torch.Tensor, w_scale: float, a_q: torch.Tensor, a_scale: tor
 
 
 def query_lookup_waves(M: int, K: int, N: int) -> int:
-    """Lookup waves per workgroup (12 or 14) of the plan vlut_mpgemm would use; 0 for the few-token kernel."""
+    """Lookup waves per workgroup (12 or 14) of the plan query_plan reports; 0 for the few-token kernel."""
     w = lib().vlut_query_lookup_waves(M, K, N)
     if w < 0:
         raise VlutError(w, "vlut_query_lookup_waves")
     return w
+
+
+_FORMS = {"codes": 0, "f32": 1, "g5": 2, "mixed": 3}
+_KERNELS = {1: "lookup", 2: "few_tokens", 3: "matrix", 4: "matrix_few_tokens"}
+
+
+def query_kernel(form: str, M: int, K: int, N: int) -> str:
+    """The kernel that computes the product of `mpgemm` ("codes"), `mpgemm_f32` ("f32"), `mpgemm_g5` ("g5") or
+    `mpgemm_mixed` ("mixed"): "lookup", "few_tokens", "matrix" or "matrix_few_tokens" (VLUT_KERNEL_* of the header)."""
+    k = lib().vlut_query_kernel(_FORMS[form], M, K, N)
+    if k < 0:
+        raise VlutError(k, "vlut_query_kernel")
+    return _KERNELS[k]
 
 
 def static_scratch_bytes() -> int:
@@ -274,7 +289,7 @@ def mpgemm_token_outer(packed: torch.Tensor, w_scale: float, a_scale: torch.Tens
 
 
 def query_plan_f32(M: int, K: int, N: int) -> Tuple[int, int, int, int, bool]:
-    """(J, R, split_k, workgroups, fused) that vlut_mpgemm_f32 uses for this shape."""
+    """(J, R, split_k, workgroups, one launch) of vlut_mpgemm_f32 for this shape; query_kernel names the kernel."""
     out = (ctypes.c_int * 5)()
     _check(lib().vlut_query_plan_f32(M, K, N, out), "vlut_query_plan_f32")
     return out[0], out[1], out[2], out[3], bool(out[4])

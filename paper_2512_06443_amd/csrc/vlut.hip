@@ -88,6 +88,7 @@ struct Plan {
 };
 
 thread_local Plan t_forced = {-1, 0, 0, 0};
+bool lookup_plan_forced() { return t_forced.Jlog >= 0 || t_forced.R != 0 || t_forced.S != 0 || t_forced.BW != 0; }
 
 const int kSupportedR[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16};
 
@@ -377,7 +378,7 @@ NarrowPlan narrow_plan(int64_t M, int64_t K, int64_t N) {
 //                 per workgroup;
 //   general path  5.8 + 0.94 c + 0.41 x M N / 10^4 for lookup kernel + split-K sum, + 3.5 for the quantiser from fp32.
 bool narrow_applies(int64_t M, int64_t K, int64_t N, const void* lut, bool from_f32) {
-    if (N > kNarrowMaxN || lut != nullptr || t_forced.Jlog >= 0 || t_forced.R != 0 || t_forced.S != 0 || t_forced.BW != 0) return false;
+    if (N > kNarrowMaxN || lut != nullptr || lookup_plan_forced()) return false;
     if (N <= 2) return true;
     const NarrowPlan np = narrow_plan(M, K, N);
     if (np.grid > 256) return false;
@@ -449,10 +450,22 @@ int pack_parts(const int8_t* w, int64_t M, int64_t K, int64_t K5, uint8_t* packe
     return rc != VLUT_OK ? rc : (*flag ? VLUT_ERR_VALUE : VLUT_OK);
 }
 
+// ---- up to sixteen tokens from fp32 (decode_kernel): one launch, every workgroup quantises all tokens.  Measured against
+//      quantiser + gemm_kernel (about 4 us more launches): 2560 x 2560 x 16 7.0 us, 13824 x 2560 x 16 8.8 us (10.5 us as two), but
+//      2560 x 6912 x 16 15.0 us (11.5 us): the rows of x are read by every workgroup, so N * K is bounded; beyond 128 rows for
+//      each of 256 workgroups that work is repeated (128256 x 4096 x 1 45 us, the table kernel 30 us), so M is bounded too.
+constexpr int64_t kDecodeMaxValues = 65536;
+bool decode_applies(int64_t M, int64_t K, int64_t N) {
+    return !lookup_plan_forced() && N <= 16 && N * K <= kDecodeMaxValues && M <= 256 * 128;
+}
+// Row tiles of 16 per workgroup: the fewest whose grid is one round of workgroups (more waves per row tile split K finer).
+int decode_row_tiles(int64_t M) { return M <= 256 * 16 ? 1 : (M <= 256 * 32 ? 2 : (M <= 256 * 64 ? 4 : 8)); }
+
 // ---- vlut_mpgemm_f32: which kernels run and how the caller's workspace is divided
 enum { kF32Narrow = 0, kF32Fused = 1, kF32TwoLaunches = 2 };
 struct F32Layout {
-    int kind;
+    int kind;                                    // also the division of the workspace where decode_kernel takes the call
+    bool decode;                                 // decode_kernel takes the call (and leaves the workspace alone)
     Plan plan;                                   // kF32Fused
     size_t off_scale, off_aq, off_ws, total;     // byte offsets into the workspace
 };
@@ -462,6 +475,7 @@ size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 F32Layout f32_layout(int64_t M, int64_t K, int64_t N) {
     F32Layout L;
     std::memset(&L, 0, sizeof(L));
+    L.decode = decode_applies(M, K, N);
     const size_t scale_bytes = round256((size_t)N * sizeof(float));
     if (narrow_applies(M, K, N, nullptr, true) && narrow_plan(M, K, N).chunks <= narrow_fused_max_chunks(N == 1 ? 1 : 2)) {
         L.kind = kF32Narrow;
@@ -471,8 +485,7 @@ F32Layout f32_layout(int64_t M, int64_t K, int64_t N) {
     // it (every workgroup reads the whole rows of its 8 tokens and 16 row tiles repeat the work: +5.6 us on the
     // lookup kernel at M = 6912, K = 2560, N = 128, against 3.2 us + the gap between two kernels).  The fused form
     // is therefore only taken when a launch plan is forced (an override selects the kernel too).
-    const bool forced = t_forced.Jlog >= 0 || t_forced.R > 0 || t_forced.S > 0 || t_forced.BW > 0;
-    const bool fused = forced && choose_fused_plan(M, K, N, &L.plan);
+    const bool fused = lookup_plan_forced() && choose_fused_plan(M, K, N, &L.plan);
     if (fused) {
         L.kind = kF32Fused;
         if (L.plan.S > 1) {                      // the second kernel reads the scales from memory
@@ -652,6 +665,15 @@ double gemm_best_cost(int gw, int64_t M, int64_t K, int64_t N) {
     return gemm_cost(gw, choose_gemm_tile(gw, M, macros, N), M, macros, N);
 }
 
+// Few rows and tokens with a long K leave the matrix-core path a handful of workgroups, while the lookup kernel can
+// split K over many (with the partial sums in the workspace): the cheaper of the two fitted costs (the lookup kernel's overstates so few outputs by a third).  Measured, lookup / matrix
+// cores: 64 x 16384 x 40 10.8 / 14.0 us, 16 x 65532 x 33 23.8 / 45 us, but 200 x 14336 x 64 14.1 / 12.9, 640 x 2560 x 40 8.4 / 5.9.
+bool matrix_cores_take(const Plan& pl, int64_t M, int64_t K, int64_t N) {
+    return !lookup_plan_forced() && plan_cost(pl, M, K, N) * (M * N <= 4096 ? 0.75e-3 : 1e-3) >= gemm_best_cost(4, M, K, N);
+}
+bool matrix_cores_take_g5(int64_t K) { return t_forced5.R == 0 && t_forced5.S == 0 && K % 4 == 0; }
+bool matrix_cores_take_mixed() { return t_forced5.R == 0 && t_forced5.S == 0 && !lookup_plan_forced(); }
+
 template <int GW, int I>
 int launch_gemm_t(const GemmParams& p, hipStream_t stream) {
     constexpr GemmTile t = kGemmTiles[I];
@@ -701,15 +723,6 @@ int launch_gemm(const uint8_t* packed, float w_scale, const float* w_rows, const
     return gw == 5 ? launch_gemm_tile<5>(tile, p, stream) : launch_gemm_tile<4>(tile, p, stream);
 }
 
-// ---- up to sixteen tokens from fp32 (decode_kernel): one launch, every workgroup quantises all tokens.  Measured against
-//      quantiser + gemm_kernel (about 4 us more launches): 2560 x 2560 x 16 7.0 us, 13824 x 2560 x 16 8.8 us (10.5 us as two), but
-//      2560 x 6912 x 16 15.0 us (11.5 us): the rows of x are read by every workgroup, so N * K is bounded; beyond 128 rows for
-//      each of 256 workgroups that work is repeated (128256 x 4096 x 1 45 us, the table kernel 30 us), so M is bounded too.
-constexpr int64_t kDecodeMaxValues = 65536;
-bool decode_applies(int64_t M, int64_t K, int64_t N) {
-    return N <= 16 && N * K <= kDecodeMaxValues && M <= 256 * 128;
-}
-
 template <int T, int MT>
 int launch_decode_t(const DecodeParams& p, hipStream_t stream) {
     auto kfn = decode_kernel<T, MT>;
@@ -721,16 +734,15 @@ int launch_decode_t(const DecodeParams& p, hipStream_t stream) {
     return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
 }
 
-// Row tiles per workgroup: the fewest whose grid is one round of workgroups (more waves per row tile split K finer).
 template <int T>
 int launch_decode(const DecodeParams& p, hipStream_t stream) {
-    if (p.M <= 256 * 16) return launch_decode_t<T, 1>(p, stream);
-    if (p.M <= 256 * 32) return launch_decode_t<T, 2>(p, stream);
-    if (p.M <= 256 * 64) return launch_decode_t<T, 4>(p, stream);
-    return launch_decode_t<T, 8>(p, stream);
+    switch (decode_row_tiles(p.M)) {
+    case 1: return launch_decode_t<T, 1>(p, stream);
+    case 2: return launch_decode_t<T, 2>(p, stream);
+    case 4: return launch_decode_t<T, 4>(p, stream);
+    default: return launch_decode_t<T, 8>(p, stream);
+    }
 }
-
-bool lookup_plan_forced() { return t_forced.Jlog >= 0 || t_forced.R != 0 || t_forced.S != 0 || t_forced.BW != 0; }
 
 // ---- comparison path: tokens per workgroup from N, K split so that few tiles still give every CU a few workgroups
 struct MfmaPlan {
@@ -944,10 +956,7 @@ static int mpgemm_impl(const uint8_t* packed, float w_scale, const float* w_rows
         if (!workspace) return VLUT_ERR_NULL;
         if (workspace_bytes < ws_need) return VLUT_ERR_SMALL_BUFFER;
     }
-    // Few rows and tokens with a long K leave the matrix-core path a handful of workgroups, while the lookup kernel can
-    // split K over many (with the partial sums in the workspace): the cheaper of the two fitted costs (the lookup kernel's overstates so few outputs by a third).  Measured, lookup / matrix
-    // cores: 64 x 16384 x 40 10.8 / 14.0 us, 16 x 65532 x 33 23.8 / 45 us, but 200 x 14336 x 64 14.1 / 12.9, 640 x 2560 x 40 8.4 / 5.9.
-    if (!lut_or_null && !lookup_plan_forced() && plan_cost(pl, M, K, N) * (M * N <= 4096 ? 0.75e-3 : 1e-3) >= gemm_best_cost(4, M, K, N))
+    if (!lut_or_null && matrix_cores_take(pl, M, K, N))
         return launch_gemm(packed, w_scale, w_rows, a_q, a_scale, M, K, 0, N, y, ldy, acc_or_null, (hipStream_t)stream);
     LookupParams p;
     std::memset(&p, 0, sizeof(p));
@@ -1010,7 +1019,7 @@ int vlut_query_plan_f32(int64_t M, int64_t K, int64_t N, int* out5) {
     if (!out5) return VLUT_ERR_NULL;
     if (!shape_ok(M, K, N)) return VLUT_ERR_SHAPE;
     const F32Layout L = f32_layout(M, K, N);
-    out5[4] = L.kind == kF32TwoLaunches ? 0 : 1;
+    out5[4] = L.kind == kF32TwoLaunches && !L.decode ? 0 : 1;
     if (L.kind == kF32Fused) {
         const Derived d = derive(L.plan, M, K, N);
         out5[0] = 1 << L.plan.Jlog; out5[1] = L.plan.R; out5[2] = L.plan.S; out5[3] = d.total;
@@ -1019,6 +1028,11 @@ int vlut_query_plan_f32(int64_t M, int64_t K, int64_t N, int* out5) {
     if (L.kind == kF32Narrow) {                // reported as vlut_query_plan reports the few-token kernel
         const NarrowPlan np = narrow_plan(M, K, N);
         out5[0] = 0; out5[1] = np.rows; out5[2] = 1; out5[3] = np.gridx * np.pairs;
+        return VLUT_OK;
+    }
+    if (L.decode) {
+        const int rows = 16 * decode_row_tiles(M);
+        out5[0] = 0; out5[1] = rows; out5[2] = 1; out5[3] = (int)((M + rows - 1) / rows);
         return VLUT_OK;
     }
     return vlut_query_plan(M, K, N, out5);
@@ -1046,7 +1060,7 @@ int vlut_mpgemm_f32(const uint8_t* packed, float w_scale, const float* w_scale_r
     const float w_one = w_rows ? 1.0f : w_scale;
     char* ws = (char*)workspace;
 
-    if (!lookup_plan_forced() && decode_applies(M, K, N)) {
+    if (L.decode) {
         DecodeParams q;
         std::memset(&q, 0, sizeof(q));
         q.packed = packed; q.x = x; q.w_rows = w_rows; q.y = y; q.acc = acc_or_null; q.a_scale_out = a_scale_out_or_null;
@@ -1165,7 +1179,7 @@ int vlut_mpgemm_g5(const uint8_t* packed, float w_scale, const int8_t* a_q, cons
     }
     // the matrix-core path reads both operands 16 bytes at a time, so it wants the alignment and K % 4 == 0 (two activation
     // rows of a chunk are 16 bytes) that this call does not demand
-    if (t_forced5.R == 0 && t_forced5.S == 0 && K % 4 == 0 && (uintptr_t)packed % 16 == 0 && (uintptr_t)a_q % 16 == 0)
+    if (matrix_cores_take_g5(K) && (uintptr_t)packed % 16 == 0 && (uintptr_t)a_q % 16 == 0)
         return launch_gemm(packed, w_scale, nullptr, a_q, a_scale, M, K, K, N, y, ldy, acc_or_null, (hipStream_t)stream);
     Lookup5Params p;
     std::memset(&p, 0, sizeof(p));
@@ -1242,7 +1256,7 @@ int vlut_mpgemm_mixed(const uint8_t* packed, float w_scale, const int8_t* a_q, c
     if (!workspace) return VLUT_ERR_NULL;
     if (workspace_bytes < need) return VLUT_ERR_SMALL_BUFFER;
     hipStream_t s = (hipStream_t)stream;
-    if (t_forced5.R == 0 && t_forced5.S == 0 && !lookup_plan_forced() && (uintptr_t)packed % 16 == 0)
+    if (matrix_cores_take_mixed() && (uintptr_t)packed % 16 == 0)
         return launch_gemm(packed, w_scale, nullptr, a_q, a_scale, M, K, K5, N, y, ldy, acc_or_null, s);
     if (K5 > 0) {
         const Derived5 d = derive5(pl5, M, K5, N);
@@ -1275,6 +1289,34 @@ int vlut_mpgemm_mixed(const uint8_t* packed, float w_scale, const int8_t* a_q, c
     }
     return launch_splitk_reduce((const int32_t*)workspace, pl5.S + pl4.S, M, N, w_scale, nullptr, a_scale, y, ldy,
                                 acc_or_null, s);
+}
+
+static int codes_kernel(int64_t M, int64_t K, int64_t N) {
+    if (narrow_applies(M, K, N, nullptr, false)) return VLUT_KERNEL_FEW_TOKENS;
+    const Plan pl = choose_plan(M, K, N);
+    if (pl.R == 0) return VLUT_ERR_UNSUPPORTED;
+    return matrix_cores_take(pl, M, K, N) ? VLUT_KERNEL_MATRIX : VLUT_KERNEL_LOOKUP;
+}
+
+int vlut_query_kernel(int form, int64_t M, int64_t K, int64_t N) {
+    if (form == VLUT_FORM_G5) {
+        if (!shape5_ok(M, K, N)) return VLUT_ERR_SHAPE;
+        if (!plan5_valid(choose_plan5(M, K, N), M, K, N)) return VLUT_ERR_UNSUPPORTED;
+        return matrix_cores_take_g5(K) ? VLUT_KERNEL_MATRIX : VLUT_KERNEL_LOOKUP;
+    }
+    if (form != VLUT_FORM_CODES && form != VLUT_FORM_F32 && form != VLUT_FORM_MIXED) return VLUT_ERR_UNSUPPORTED;
+    if (!shape_ok(M, K, N)) return VLUT_ERR_SHAPE;
+    if (form == VLUT_FORM_CODES) return codes_kernel(M, K, N);
+    if (form == VLUT_FORM_F32) {
+        const F32Layout L = f32_layout(M, K, N);
+        if (L.decode) return VLUT_KERNEL_MATRIX_FEW_TOKENS;
+        if (L.kind == kF32Narrow) return VLUT_KERNEL_FEW_TOKENS;
+        return L.kind == kF32Fused ? VLUT_KERNEL_LOOKUP : codes_kernel(M, K, N);
+    }
+    Plan5 p5;
+    Plan p4;
+    if (!mixed_plans(M, K, N, &p5, &p4)) return VLUT_ERR_UNSUPPORTED;
+    return matrix_cores_take_mixed() ? VLUT_KERNEL_MATRIX : VLUT_KERNEL_LOOKUP;
 }
 
 size_t vlut_mfma_workspace_bytes(int64_t M, int64_t K, int64_t N) {

@@ -357,3 +357,39 @@ def test_binding_imports_without_the_private_stream_functions(monkeypatch, missi
     assert mod.packed_weight_bytes(256, 256) == 16384
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 77})())
     assert mod._stream() == 77
+
+
+def test_queries_name_the_kernel_that_runs(L):
+    """vlut_query_plan_f32 tells one launch from two also where the matrix cores take a few tokens from fp32, and
+    vlut_query_kernel names the kernel of every form of the call, with and without an override."""
+    L.vlut_query_kernel.argtypes = [ci, i64, i64, i64]
+    codes, f32, g5, mixed = range(4)
+    lookup, few, matrix, matrix_few = 1, 2, 3, 4
+    out = (ci * 5)()
+    for (M, K, N, rows) in [(4096, 6552, 10, 16), (4097, 2560, 16, 32), (13824, 2560, 16, 64), (32768, 2560, 16, 128)]:
+        assert L.vlut_query_kernel(f32, M, K, N) == matrix_few                 # one launch, 16 to 128 rows per workgroup
+        assert L.vlut_query_plan_f32(M, K, N, out) == 0
+        assert tuple(out) == (0, rows, 1, -(-M // rows), 1)
+    assert L.vlut_query_plan_f32(2560, 6912, 16, out) == 0 and out[4] == 0     # N * K beyond 65536: two launches
+    assert L.vlut_query_plan_f32(32769, 2560, 16, out) == 0 and out[4] == 0
+    assert L.vlut_query_kernel(f32, 2560, 6912, 16) == L.vlut_query_kernel(codes, 2560, 6912, 16)
+    for (M, K, N) in [(14336, 4096, 512), (4096, 14336, 512), (3203, 3116, 77), (6912, 2560, 128)]:
+        assert L.vlut_query_kernel(codes, M, K, N) == L.vlut_query_kernel(f32, M, K, N) == matrix
+        assert L.vlut_query_kernel(mixed, M, K, N) == matrix
+    assert L.vlut_query_kernel(codes, 640, 2560, 4) == few
+    assert L.vlut_query_kernel(g5, 640, 2560, 4) == matrix and L.vlut_query_kernel(g5, 640, 2555, 4) == lookup   # 4 does not divide K
+    assert L.vlut_query_kernel(mixed, 64, 16, 8) == matrix
+    try:
+        assert L.vlut_set_plan(16, 2, 0, 1) == 0
+        for form in (codes, f32, mixed):
+            assert L.vlut_query_kernel(form, 300, 2560, 40) == lookup
+        assert L.vlut_query_kernel(g5, 300, 2560, 40) == matrix                # the other packing has an override of its own
+        assert L.vlut_set_plan(16, 2, 0, 4) == 0
+        assert L.vlut_query_kernel(codes, 300, 256, 40) == -6                  # more K splits than stages
+        assert L.vlut_set_plan(0, 0, 0, 0) == 0 and L.vlut_set_plan_g5(2, 1) == 0
+        assert L.vlut_query_kernel(g5, 300, 2560, 40) == L.vlut_query_kernel(mixed, 300, 2560, 40) == lookup
+        assert L.vlut_query_kernel(codes, 300, 2560, 40) == matrix
+    finally:
+        assert L.vlut_set_plan(0, 0, 0, 0) == 0 and L.vlut_set_plan_g5(0, 0) == 0
+    assert L.vlut_query_kernel(codes, 8, 6, 8) == -2 and L.vlut_query_kernel(g5, 8, 64, 8) == -2
+    assert L.vlut_query_kernel(4, 8, 64, 8) == -6
