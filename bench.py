@@ -2,17 +2,16 @@
 """Benchmark of the vector-LUT ternary x INT8 mpGeMM hot path on one MI355X.
 
 One step = one pass of the whole hot path over one batch of synthetic input that is already
-resident in HBM: per-token INT8 quantisation of the fp32 activations, streamed LDS table build,
-lookup-accumulate and scale epilogue, through vlut_mpgemm_f32 (which runs the quantisation inside the
-lookup kernel or as a kernel of its own ahead of it, whichever its cost model prefers for the shape; the
-two-call form vlut_quantize_act + vlut_mpgemm is timed next to it).  Weight packing is the paper's
+resident in HBM: per-token INT8 quantisation of the fp32 activations, product and scale, through
+vlut_mpgemm_f32 (which quantises inside the product's kernel for a few tokens and in a kernel of its own
+ahead of it for more; the two-call form vlut_quantize_act + vlut_mpgemm is timed next to it).  Weight packing is the paper's
 offline stage and is not timed.  The packed weights rotate through a pool larger than the last-level
 cache, so every step streams its weights from HBM.
 
 Default run (`python bench.py [--gpus 1 --steps K --warmup W]`): every benchmark shape is timed -- the
 2B FFN up projection at N = 128, the 3B up/down projections at N = 256, the 8B linears at N = 512 and the
 seven linears of one 2.4B-style decoder layer at N in {1, 16, 64, 256, 1024} (plus the layer as four stacked
-launches from fp32 inputs) -- and reported under `sweep` / `layer`, one entry per (shape, N) with its time, GOPS,
+launches from fp32 inputs) -- and reported under `sweep` / `layer`, one row per (shape, N) with its kernel, time, GOPS,
 weight-stream GB/s, the roof that binds it and the fraction of that roof.  The headline (`value`,
 `ms_per_step`, `roofline`, `cpu_baseline`) is the largest single-GPU shape, the 8B gate/up projection
 M = 14336, K = 4096, N = 512.  `--workload/--linear/--tokens` pick another headline; `--no-sweep` times the
@@ -382,6 +381,23 @@ def measure_layer(B, torch, wl, n, seed, rotate, steps, warmup):
             "bound": bound, "floor_ms": floor, "frac": floor / ms}
 
 
+def json_line(out):
+    """The JSON line: floats to six digits, the sweep as rows under one list of column names.  Whoever keeps only the last
+    part of the output still has the whole line (with a dict of 17-digit floats per shape it was 21 kB)."""
+    def short(v):
+        if isinstance(v, float):
+            return float(f"{v:.6g}")
+        if isinstance(v, dict):
+            return {k: short(x) for k, x in v.items()}
+        return [short(x) for x in v] if isinstance(v, (list, tuple)) else v
+
+    out = dict(out)
+    if "sweep" in out:
+        columns = [k for k in out["sweep"][0] if k not in ("floor_ms", "mpgemm_ms", "lut_over_mfma_time", "mfma_frac_of_int8_peak")]
+        out["sweep"] = {"columns": columns, "rows": [[e.get(k) for k in columns] for e in out["sweep"]]}
+    return json.dumps(short(out), separators=(",", ":"))
+
+
 def main():
     global REPS
     args = parse_args()
@@ -609,7 +625,7 @@ def main():
                   f"{r['stacked_from_fp32_two_call_ms'] * 1e3:20.1f} {r['packed_weight_MB']:11.2f} "
                   f"{r['weight_stream_GBs_stacked']:13.1f} {r['hbm_frac_stacked']:9.3f}", file=sys.stderr)
 
-    print(json.dumps(out))
+    print(json_line(out))
 
 
 if __name__ == "__main__":

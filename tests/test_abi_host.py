@@ -393,3 +393,26 @@ def test_queries_name_the_kernel_that_runs(L):
         assert L.vlut_set_plan(0, 0, 0, 0) == 0 and L.vlut_set_plan_g5(0, 0) == 0
     assert L.vlut_query_kernel(codes, 8, 6, 8) == -2 and L.vlut_query_kernel(g5, 8, 64, 8) == -2
     assert L.vlut_query_kernel(4, 8, 64, 8) == -6
+
+
+def test_bench_line_is_one_line_that_fits(L):
+    """The line of the default run (41 shapes, five layers) is complete within the last 12 kB of the output."""
+    import json
+
+    import bench
+    f = 0.12345678901234567
+    entry = {"workload": "layer2b4_nsweep", "linear": "gateup", "M": 14336, "K": 14336, "N": 1024, "seed": 4,
+             "kernel": "matrix_few_tokens", "one_launch_from_fp32": True, "bound": "mfma"}
+    entry.update({k: f for k in ("ms", "kernel_ms", "two_call_ms", "mpgemm_ms", "floor_ms", "frac", "kernel_frac", "mfma_ms",
+                                 "lut_over_mfma_time", "mfma_frac_of_int8_peak")}, GOPS=123456.78901234567, weight_stream_GBs=1234.5678901234567)
+    layer = {"N": 1024, "seed": 4, "launches": 4, "what": "w" * 80, "kernels": ["matrix_few_tokens"] * 4, "ms": f, "gpu_ms": f, "GOPS": 123456.78901234567,
+             "weight_stream_GBs": 1234.5678901234567, "bound": "mfma", "floor_ms": f, "frac": f}
+    out = {"metric": "m", "value": 723456.78901234567, "config": {"workload": "x" * 600}, "roofline": {"what": "x" * 900},
+           "sweep": [dict(entry) for _ in range(41)], "layer": [dict(layer) for _ in range(5)]}
+    line = bench.json_line(out)
+    assert "\n" not in line and len(line) < 12000
+    back = json.loads(line)
+    assert back["value"] == 723457.0 and len(back["sweep"]["rows"]) == 41
+    row = dict(zip(back["sweep"]["columns"], back["sweep"]["rows"][0]))
+    assert row["ms"] == 0.123457 and row["kernel"] == "matrix_few_tokens"
+    assert len(out["sweep"]) == 41 and isinstance(out["sweep"][0], dict)       # the caller's table is left alone
