@@ -665,11 +665,26 @@ double gemm_best_cost(int gw, int64_t M, int64_t K, int64_t N) {
     return gemm_cost(gw, choose_gemm_tile(gw, M, macros, N), M, macros, N);
 }
 
+// Time of a lookup plan (with its split-K sum) in us, in the units of gemm_cost: least squares over 869 shapes of 4 to 4096 rows,
+// K = 1024 to 65532 and 3 to 400 tokens, launches back to back (standard deviation 2.6 %, worst 12 % at 4 rows).  plan_cost above ranks plans
+// and overstates the time, by 6 % where a workgroup has several tiles and by 20 to 57 % where it has one.
+double lookup_us(const Plan& pl, int64_t M, int64_t K, int64_t N) {
+    const Derived d = derive(pl, M, K, N);
+    const int lookup_waves = kWaves - pl.BW;
+    const double rw = (double)((d.RGW + lookup_waves - 1) / lookup_waves);   // row groups of the slowest lookup wave
+    double stage = pl.BW == 4 ? 0.99 + 0.07 * rw : std::max(1.32, 0.72 + 0.102 * rw);
+    if (d.need32) stage *= 1.05;
+    double t = 3.8 + (double)((d.total + 255) / 256) * (d.stages_per_split * stage + 0.058 * rw);
+    if (pl.S > 1) t += 1.65 + 0.07 * pl.S + 3.8e-6 * (double)pl.S * (double)M * (double)N;
+    return std::max(t, (double)d.tiles_n * (double)d.RGtotal * d.KCn * 64.0 / (256.0 * 24.0 * 2100.0));   // weights from L2
+}
+
 // Few rows and tokens with a long K leave the matrix-core path a handful of workgroups, while the lookup kernel can
-// split K over many (with the partial sums in the workspace): the cheaper of the two fitted costs (the lookup kernel's overstates so few outputs by a third).  Measured, lookup / matrix
-// cores: 64 x 16384 x 40 10.8 / 14.0 us, 16 x 65532 x 33 23.8 / 45 us, but 200 x 14336 x 64 14.1 / 12.9, 640 x 2560 x 40 8.4 / 5.9.
+// split K over many (with the partial sums in the workspace): the cheaper of the two fitted times.  Measured, us, lookup / matrix
+// cores: 64 x 16384 x 128 10.9 / 14.1, 100 x 24000 x 72 13.9 / 19.4, 640 x 30000 x 33 18.9 / 23.7, 2560 x 30000 x 16 20.2 / 23.9, but
+// 256 x 14336 x 72 13.4 / 12.8, 640 x 16384 x 128 20.0 / 14.8, 2048 x 14336 x 16 15.4 / 12.9.
 bool matrix_cores_take(const Plan& pl, int64_t M, int64_t K, int64_t N) {
-    return !lookup_plan_forced() && plan_cost(pl, M, K, N) * (M * N <= 4096 ? 0.75e-3 : 1e-3) >= gemm_best_cost(4, M, K, N);
+    return !lookup_plan_forced() && lookup_us(pl, M, K, N) >= gemm_best_cost(4, M, K, N);
 }
 bool matrix_cores_take_g5(int64_t K) { return t_forced5.R == 0 && t_forced5.S == 0 && K % 4 == 0; }
 bool matrix_cores_take_mixed() { return t_forced5.R == 0 && t_forced5.S == 0 && !lookup_plan_forced(); }

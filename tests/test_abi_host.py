@@ -416,3 +416,18 @@ def test_bench_line_is_one_line_that_fits(L):
     row = dict(zip(back["sweep"]["columns"], back["sweep"]["rows"][0]))
     assert row["ms"] == 0.123457 and row["kernel"] == "matrix_few_tokens"
     assert len(out["sweep"]) == 41 and isinstance(out["sweep"][0], dict)       # the caller's table is left alone
+
+
+def test_long_rows_of_few_outputs_take_the_faster_kernel(L):
+    """INT8 codes with a long K: the side of the rule on which the measured times (us, lookup kernel with split-K / matrix
+    cores) put a shape, on both sides of 4096 outputs."""
+    L.vlut_query_kernel.argtypes = [ci, i64, i64, i64]
+    lookup, matrix = 1, 3
+    measured = [((16, 65532, 33), 23.8, 45.0), ((64, 16384, 40), 10.8, 14.0), ((64, 16384, 128), 10.85, 14.06), ((200, 16384, 48), 11.94, 14.15),
+                ((100, 24000, 72), 13.87, 19.37), ((256, 20480, 40), 12.85, 16.78), ((512, 45000, 72), 28.74, 34.41), ((640, 30000, 64), 20.5, 23.83),
+                ((1280, 65532, 64), 42.62, 48.48), ((2048, 36000, 20), 23.14, 27.72), ((2560, 20480, 16), 16.4, 17.4), ((2560, 30000, 16), 20.19, 23.87),
+                ((4096, 45000, 16), 30.26, 35.91),
+                ((256, 14336, 72), 13.39, 12.79), ((640, 16384, 128), 19.99, 14.83), ((640, 30000, 128), 26.82, 25.57), ((1280, 30000, 64), 28.12, 23.87),
+                ((2048, 14336, 16), 15.39, 12.91), ((640, 2560, 40), 8.4, 5.9)]
+    for shape, t_lookup, t_matrix in measured:
+        assert L.vlut_query_kernel(0, *shape) == (lookup if t_lookup < t_matrix else matrix), shape
