@@ -454,9 +454,14 @@ int pack_parts(const int8_t* w, int64_t M, int64_t K, int64_t K5, uint8_t* packe
 //      quantiser + gemm_kernel (about 4 us more launches): 2560 x 2560 x 16 7.0 us, 13824 x 2560 x 16 8.8 us (10.5 us as two), but
 //      2560 x 6912 x 16 15.0 us (11.5 us): the rows of x are read by every workgroup, so N * K is bounded; beyond 128 rows for
 //      each of 256 workgroups that work is repeated (128256 x 4096 x 1 45 us, the table kernel 30 us), so M is bounded too.
+//      One token and more than 64 rows for each of 256 workgroups: unpacking twice as many bytes per workgroup costs more than the
+//      table kernel's lookups, where its one launch from fp32 covers K (decode / table: 32768 x 4096 11.7 / 9.9 us, 32768 x 14336
+//      30.1 / 24.9; 16384 x 4096 8.2 / 8.0, 16384 x 6912 10.3 / 10.7; below K = 1024 level; two tokens, 32768 x 4096 12.0 / 12.6).
 constexpr int64_t kDecodeMaxValues = 65536;
 bool decode_applies(int64_t M, int64_t K, int64_t N) {
-    return !lookup_plan_forced() && N <= 16 && N * K <= kDecodeMaxValues && M <= 256 * 128;
+    if (lookup_plan_forced() || N > 16 || N * K > kDecodeMaxValues || M > 256 * 128) return false;
+    if (N == 1 && M > 256 * 64 && K >= 1024 && narrow_plan(M, K, N).chunks <= narrow_fused_max_chunks(1)) return false;
+    return true;
 }
 // Row tiles of 16 per workgroup: the fewest whose grid is one round of workgroups (more waves per row tile split K finer).
 int decode_row_tiles(int64_t M) { return M <= 256 * 16 ? 1 : (M <= 256 * 32 ? 2 : (M <= 256 * 64 ? 4 : 8)); }

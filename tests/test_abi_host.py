@@ -431,3 +431,14 @@ def test_long_rows_of_few_outputs_take_the_faster_kernel(L):
                 ((2048, 14336, 16), 15.39, 12.91), ((640, 2560, 40), 8.4, 5.9)]
     for shape, t_lookup, t_matrix in measured:
         assert L.vlut_query_kernel(0, *shape) == (lookup if t_lookup < t_matrix else matrix), shape
+
+
+def test_one_token_on_many_rows_takes_the_table_kernel(L):
+    """From fp32, one token: above 16384 rows the table kernel is the faster one while its one launch covers K."""
+    L.vlut_query_kernel.argtypes = [ci, i64, i64, i64]
+    few, matrix_few = 2, 4
+    for M, K, want in [(16384, 4096, matrix_few), (16385, 4096, few), (32768, 1024, few), (32768, 1020, matrix_few), (20000, 14336, few),
+                       (32768, 35840, few), (32768, 35844, matrix_few), (32768, 65536, matrix_few), (32769, 64, few), (13824, 2560, matrix_few)]:
+        assert L.vlut_query_kernel(1, M, K, 1) == want, (M, K)
+        assert L.vlut_workspace_bytes_f32(M, K, 1) == (0 if K <= 35840 else 256 + (8 * K + 255) // 256 * 256)
+    assert L.vlut_query_kernel(1, 32768, 4096, 2) == matrix_few

@@ -190,3 +190,27 @@ def test_unaligned_rows_cost_the_quantiser_about_what_aligned_ones_do(B, N, K):
             best[name] = min(best.get(name, 1e9), e0.elapsed_time(e1))
     print(best)
     assert best["unaligned"] < 1.5 * best["aligned"]
+
+
+def check_f32(B, W, s, x, kernel):
+    """mpgemm_f32 on aligned and on unaligned rows against the oracle; `kernel` is the one the library must take."""
+    M, K = W.shape
+    N = x.shape[0]
+    assert B.query_kernel("f32", M, K, N) == kernel
+    _, s_ref, acc_ref, y_ref = O.mpgemm(W, s, x)
+    packed = B.pack_weights(dev(W))
+    odd = torch.full((N, K + 3), 9e9, device="cuda")
+    odd[:, 1:K + 1] = dev(x)
+    for xd in (dev(x), odd[:, 1:K + 1]):
+        print(f"f32 case {kernel} M={M} K={K} N={N} stride={xd.stride(0)}", flush=True)
+        y, acc, sc = B.mpgemm_f32(packed, float(s), xd, M, want_acc=True, want_scales=True)
+        torch.cuda.synchronize()
+        assert np.array_equal(acc.cpu().numpy(), acc_ref)
+        assert np.array_equal(sc.cpu().numpy().view(np.uint32), s_ref.view(np.uint32))
+        assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - y_ref) <= REL * np.abs(y_ref))
+
+
+@pytest.mark.parametrize("M,K,kernel", [(16384, 1024, "matrix_few_tokens"), (16385, 1024, "few_tokens"), (16385, 1020, "matrix_few_tokens"),
+                                        (16401, 9220, "few_tokens"), (32768, 1028, "few_tokens"), (32769, 260, "few_tokens")])
+def test_one_token_on_many_rows(B, M, K, kernel):
+    check_f32(B, *wl.small_case(1800 + M + K, M, K, 1), kernel)
