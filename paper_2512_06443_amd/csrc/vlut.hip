@@ -457,10 +457,15 @@ int pack_parts(const int8_t* w, int64_t M, int64_t K, int64_t K5, uint8_t* packe
 //      One token and more than 64 rows for each of 256 workgroups: unpacking twice as many bytes per workgroup costs more than the
 //      table kernel's lookups, where its one launch from fp32 covers K (decode / table: 32768 x 4096 11.7 / 9.9 us, 32768 x 14336
 //      30.1 / 24.9; 16384 x 4096 8.2 / 8.0, 16384 x 6912 10.3 / 10.7; below K = 1024 level; two tokens, 32768 x 4096 12.0 / 12.6).
+//      9 to 16 tokens: a wave quantises a whole row, so the time grows with N * K, while the table kernel with 32 rows per workgroup
+//      spreads the tokens over workgroups; its time grows with their number, hence with M.  The line between them is fitted to
+//      M = 4 to 1000 (decode / table: 100 x 4096 x 12 8.2 / 8.7 us, 100 x 4680 x 14 10.3 / 9.5, 4 x 6552 x 9 11.5 / 10.6; 1000 x 4096 x 16
+//      level): within 3 % of the faster one, 5 % at M = 4.
 constexpr int64_t kDecodeMaxValues = 65536;
 bool decode_applies(int64_t M, int64_t K, int64_t N) {
     if (lookup_plan_forced() || N > 16 || N * K > kDecodeMaxValues || M > 256 * 128) return false;
     if (N == 1 && M > 256 * 64 && K >= 1024 && narrow_plan(M, K, N).chunks <= narrow_fused_max_chunks(1)) return false;
+    if (N > 8 && N * K >= 49152 + 12 * M && narrow_applies(M, K, N, nullptr, true) && narrow_plan(M, K, N).rows == 32) return false;
     return true;
 }
 // Row tiles of 16 per workgroup: the fewest whose grid is one round of workgroups (more waves per row tile split K finer).

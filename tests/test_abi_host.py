@@ -442,3 +442,14 @@ def test_one_token_on_many_rows_takes_the_table_kernel(L):
         assert L.vlut_query_kernel(1, M, K, 1) == want, (M, K)
         assert L.vlut_workspace_bytes_f32(M, K, 1) == (0 if K <= 35840 else 256 + (8 * K + 255) // 256 * 256)
     assert L.vlut_query_kernel(1, 32768, 4096, 2) == matrix_few
+
+
+def test_nine_to_sixteen_tokens_on_few_rows_take_the_faster_kernel(L):
+    """From fp32: the side of the rule on which the measured times (us, table kernel / matrix cores) put a shape."""
+    L.vlut_query_kernel.argtypes = [ci, i64, i64, i64]
+    few, matrix_few = 2, 4
+    measured = [((4, 6552, 9), 10.57, 11.52), ((100, 4680, 14), 9.52, 10.3), ((100, 4096, 16), 8.79, 9.15), ((640, 4680, 14), 9.65, 10.39),
+                ((1000, 4680, 14), 9.85, 10.44), ((100, 4096, 12), 8.70, 8.24), ((640, 2560, 16), 7.42, 6.93), ((2560, 2560, 16), 9.59, 7.17)]
+    for shape, t_table, t_matrix in measured:
+        assert L.vlut_query_kernel(1, *shape) == (few if t_table < t_matrix else matrix_few), shape
+    assert L.vlut_query_kernel(1, 4, 8188, 8) == matrix_few                    # up to eight tokens two waves share a row: never

@@ -214,3 +214,9 @@ def check_f32(B, W, s, x, kernel):
                                         (16401, 9220, "few_tokens"), (32768, 1028, "few_tokens"), (32769, 260, "few_tokens")])
 def test_one_token_on_many_rows(B, M, K, kernel):
     check_f32(B, *wl.small_case(1800 + M + K, M, K, 1), kernel)
+
+
+@pytest.mark.parametrize("M,K,N,kernel", [(4, 6552, 10, "few_tokens"), (33, 4096, 16, "few_tokens"), (100, 5040, 13, "few_tokens"),
+                                          (1000, 4680, 14, "few_tokens"), (1000, 4096, 14, "matrix_few_tokens"), (33, 3072, 16, "matrix_few_tokens")])
+def test_nine_to_sixteen_tokens_on_few_rows(B, M, K, N, kernel):
+    check_f32(B, *wl.small_case(1900 + M + N, M, K, N), kernel)
