@@ -61,7 +61,8 @@ def test_every_packed_byte(B, g, K):
                                    (3840, 260, 1000), (4099, 1028, 1030), (8193, 132, 520), (513, 9220, 515), (7000, 2580, 127), (16, 32768, 33), (64, 16384, 40),
                                    (200, 14336, 64)])
 def test_tile_edges(B, M, K, N):
-    # (the last three: next to the rule that leaves few rows with a long K to the lookup kernel)
+    # (the last three: next to the rule that leaves few rows with a long K to the lookup kernel, tested with the route asked for
+    # in test_routes_gpu.py)
     W, s, x = wl.small_case(1200 + M + N, M, K, N)
     check(B, W, s, x, tag="edges")
 
@@ -137,11 +138,12 @@ def test_pack_unaligned_and_value_check(B):
             assert raw(src.data_ptr() + off, M, K, blob.data_ptr() + off, want.numel(), None) == 0
             assert torch.equal(blob[off:off + want.numel()], want)
             assert int((blob == 255).sum()) == 16
+        good = want.clone()                                 # (the calls with a bad value overwrite the blob they are given)
         for pos, value in ((0, 2), (5 * K + 33, -2), (M * K - 1, 3), (M * K // 2, -128), (17, 127)):
             bad = dev(W).flatten()
             bad[pos] = value
             assert raw(bad.data_ptr(), M, K, want.data_ptr(), want.numel(), None) == B.VLUT_ERR_VALUE
-            assert torch.equal(wrapped(dev(W)), wrapped(dev(W)))
+            assert torch.equal(wrapped(dev(W)), good)
 
 
 def test_missing_matrix_is_a_status_code(B):

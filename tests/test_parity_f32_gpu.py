@@ -134,19 +134,19 @@ def test_row_stride_and_unaligned_rows(B):
     run_f32(B, W1, s1, x1, x_dev=dev(odd)[:, 3:1031], tag="unaligned rows, two tokens")
 
 
-def test_two_kernel_quantiser_for_large_inputs(B):
-    """More than about four million activation values: the quantiser inside vlut_mpgemm_f32 runs as two kernels
-    (absmax per token, then chunks of 8 tokens per K range); same codes and scales, bit for bit.  Ragged last chunk,
-    K ranges that do not divide K, rows that cannot be read as float4."""
-    for (M, K, N, pad) in [(64, 8192, 520, 0), (40, 14336, 300, 0), (33, 8200, 515, 3)]:
+def test_quantiser_of_large_inputs(B):
+    """More than about four million activation values through vlut_mpgemm_f32: one token per workgroup below 768 tokens, four
+    from there on; same codes and scales, bit for bit.  Ragged last chunk, rows longer than what is kept in registers,
+    rows that cannot be read as float4."""
+    for (M, K, N, pad) in [(64, 8192, 520, 0), (40, 14336, 300, 0), (33, 8200, 515, 3), (33, 4100, 1030, 3), (20, 14340, 771, 0)]:
         W, s, x = wl.small_case(480 + N, M, K, N)
         assert N * K >= 1 << 22
         if pad:                                              # rows start at addresses that are no multiple of 16
             big = np.full((N, K + pad + 1), 1e9, np.float32)
             big[:, 1:K + 1] = x
-            run_f32(B, W, s, x, tag="two-kernel quantiser, unaligned", x_dev=dev(big)[:, 1:K + 1])
+            run_f32(B, W, s, x, tag="large input, unaligned", x_dev=dev(big)[:, 1:K + 1])
         else:
-            run_f32(B, W, s, x, tag="two-kernel quantiser")
+            run_f32(B, W, s, x, tag="large input")
 
 
 @pytest.mark.parametrize("M", [100, 5000, 10000, 20000, 40000])
@@ -154,7 +154,7 @@ def test_one_or_two_tokens_every_tile_shape(B, M):
     for N, K in ((1, 260), (2, 1028)):
         W, s, x = wl.small_case(470 + M % 97 + N, M, K, N)
         qp = run_f32(B, W, s, x, fused=True, tag=f"narrow M{M} N{N}")
-        assert qp[0] == 0                                   # the one-or-two-token kernel
+        assert qp[0] == 0                                   # one launch of a kernel for few tokens
 
 
 def test_one_or_two_tokens_long_rows(B):
@@ -173,8 +173,9 @@ def test_one_or_two_tokens_long_rows(B):
 
 @pytest.mark.parametrize("N", [3, 4, 5, 6, 7, 8, 11, 16, 23, 32])
 def test_few_tokens_one_launch_per_token_pair(B, N):
-    # 3..32 tokens: the few-token kernel with a copy of its row tiles per token pair, while that grid is one round of
-    # workgroups with few rows each; M picks the rows per workgroup, the odd N leave the last pair with one token
+    # 3..32 tokens in one launch, while a copy of the row tiles per token pair is one round of workgroups with few rows each
+    # (up to 16 tokens with N * K <= 65536 the matrix-core kernel mostly takes the call); the reported rows per workgroup are
+    # the table kernel's, the odd N leave the last pair with one token
     for M, K in ((100, 260), (3000, 1028), (9000, 516), (130, 6912)):
         if N > 8 and M > 1000:
             continue
