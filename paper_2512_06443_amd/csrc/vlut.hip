@@ -70,13 +70,13 @@ int static_scratch_ptr(void** out) {
 // The table kernels form LDS addresses as idx*256 + slice*16 and so need their dynamic LDS segment to start at LDS
 // address 0, i.e. a kernel without static LDS: checked here, once per device, before the first launch (a kernel
 // that fails the check is never launched and the call returns VLUT_ERR_DEVICE).
-bool allow_dynamic_lds(const void* kfn, int bytes, std::atomic<unsigned>& done_mask, bool needs_lds_base0 = true) {
+bool allow_dynamic_lds(const void* kfn, int bytes, std::atomic<unsigned>& done_mask) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return false;
     const unsigned bit = (dev >= 0 && dev < 32) ? (1u << dev) : 0u;
     if (bit && (done_mask.load(std::memory_order_relaxed) & bit)) return true;
     hipFuncAttributes attr;
-    if (needs_lds_base0 && (hipFuncGetAttributes(&attr, kfn) != hipSuccess || attr.sharedSizeBytes != 0)) return false;
+    if (hipFuncGetAttributes(&attr, kfn) != hipSuccess || attr.sharedSizeBytes != 0) return false;
     if (hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return false;
     done_mask.fetch_or(bit, std::memory_order_relaxed);
     return true;
@@ -403,8 +403,12 @@ int launch_narrow_t(const NarrowParams& p, int grid, hipStream_t stream) {
 
 template <int NTOK, bool FUSED>
 int launch_narrow_n(const NarrowPlan& np, const NarrowParams& p, hipStream_t stream) {
-    if (np.parts == 2) return launch_narrow_t<NTOK, 2, 1, FUSED>(p, np.grid, stream);
-    if (np.rr == 1) return launch_narrow_t<NTOK, 1, 1, FUSED>(p, np.grid, stream);
+    if constexpr (NTOK == 1 && FUSED) {          // fewer rows are decode_kernel's: not built
+        if (np.rows < 128) return VLUT_ERR_UNSUPPORTED;
+    } else {
+        if (np.parts == 2) return launch_narrow_t<NTOK, 2, 1, FUSED>(p, np.grid, stream);
+        if (np.rr == 1) return launch_narrow_t<NTOK, 1, 1, FUSED>(p, np.grid, stream);
+    }
     if (np.rr == 2) return launch_narrow_t<NTOK, 1, 2, FUSED>(p, np.grid, stream);
     return launch_narrow_t<NTOK, 1, 4, FUSED>(p, np.grid, stream);
 }
