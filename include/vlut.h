@@ -177,8 +177,8 @@ int vlut_mpgemm_token_outer(const uint8_t* packed, float w_scale, const float* a
  * For a few tokens (streamed tables, no plan override: always for N <= 2, up to N = 32 while one workgroup per
  * row tile and token pair fits the device at once) a kernel specialised for that case runs instead and needs no
  * workspace; the results are the same numbers.  For more tokens (no table given, no plan override) the product runs
- * on the INT8 matrix cores, the packed bytes taken apart in registers: the same INT32 sums without tables (and without
- * the workspace, whose size stays that of the lookup plan).  The lookup kernel runs where a plan is forced or a
+ * on the INT8 matrix cores, the packed bytes taken apart in registers: the same INT32 sums without tables (the workspace
+ * is demanded, with the lookup plan's size, and left alone).  The lookup kernel runs where a plan is forced or a
  * materialised table is given, and where few rows and tokens with a long K leave the matrix cores too few workgroups.
  */
 int vlut_mpgemm(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale,
@@ -219,10 +219,10 @@ int vlut_mpgemm_rows(const uint8_t* packed, const float* w_scale_rows, const int
 /*
  * Quantisation and mpGeMM in one call, from fp32 activations: the steps of vlut_quantize_act (Sec. 3.4 first
  * paragraph: per-token absmax INT8) and of vlut_mpgemm / vlut_mpgemm_rows (Alg. 1, Eq. 2) with the same readings and
- * the same numbers.  Up to 16 tokens with N * K <= 65536 and M <= 32768 it is one launch: every
+ * the same numbers.  Up to 16 tokens with N * K <= 65536 and M <= 32768 it is mostly one launch: every
  * workgroup quantises all tokens itself and multiplies on the matrix cores, no INT8 activations in memory.  Beyond
- * that, the few-token kernel where it applies from fp32 (reported by vlut_query_plan_f32 with J = 0, also where the
- * former takes the call; K <= 35840 for one token, 39936 for more), else the quantiser as a kernel of its own into the
+ * that, and for one token on more than 16384 rows and nine to sixteen long ones on few rows, the few-token kernel where it
+ * applies from fp32 (K <= 35840 for one token, 39936 for more), else the quantiser as a kernel of its own into the
  * workspace, ahead of the kernel vlut_mpgemm takes.  A lookup kernel that quantises the 8 tokens of its tile itself
  * exists as well and is taken when vlut_set_plan forces a plan with J = 16 whose K range per workgroup is at most 8704.
  *   x             dev, fp32 [N][ldx], ldx >= K (16-byte aligned rows are read as float4)
@@ -280,10 +280,10 @@ int vlut_query_plan_g5(int64_t M, int64_t K, int64_t N, int* out3);
  * of 4, as the quantiser's K % 4 == 0 demands) four per byte; K5 = 0 or K - K5 = 0 leave one part empty.
  *   blob = [vlut_pack_weights_g5 blob of W[:, :K5]] [vlut_pack_weights blob of W[:, K5:]]
  *   vlut_mixed_k5(K)            K5, or -1 if K is not a positive multiple of 4
- * vlut_mpgemm_mixed runs both parts in one launch on the matrix cores (with a plan override: each part through its
- * lookup kernel in partial-sum mode, a_q: the part's range of activation rows, and one exact INT32 pass that adds
- * the parts before the scale step): the same numbers as vlut_mpgemm.  The workspace (vlut_workspace_bytes_mixed, never 0) is required; other arguments and errors as in
- * vlut_mpgemm (streamed tables only).
+ * vlut_mpgemm_mixed runs both parts in one launch on the matrix cores (with a plan override, or where packed is not
+ * 16-byte aligned: each part through its lookup kernel in partial-sum mode, a_q: the part's range of activation rows,
+ * and one exact INT32 pass that adds the parts before the scale step): the same numbers as vlut_mpgemm.  The workspace
+ * (vlut_workspace_bytes_mixed, never 0) is required; other arguments and errors as in vlut_mpgemm (streamed tables only).
  */
 int64_t vlut_mixed_k5(int64_t K);
 size_t vlut_packed_weight_bytes_mixed(int64_t M, int64_t K);                 /* 0 if the shape is invalid      */

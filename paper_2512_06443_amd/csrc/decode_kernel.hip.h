@@ -7,7 +7,7 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // A workgroup (16 waves) owns 16 * MT output rows and all of K for all tokens.  It quantises the tokens itself (every
 // workgroup repeats that: N * K floats from L2, while its weights are on their way from HBM), so that a linear is one
-// launch and needs no workspace; the waves then split the row tiles and K, and their INT32 sums meet in LDS.
+// launch and touches no workspace (the call still wants one of vlut_workspace_bytes_f32); the waves then split the row tiles and K, and their INT32 sums meet in LDS.
 //
 // v_mfma_i32_16x16x64_i8: tokens x rows.  Weights as in gemm_kernel (lane = row and tile column, 16 packed bytes per
 // load, planes instead of the natural order of K); a macro step is four tile columns = 256 values of K.  The codes are

@@ -373,10 +373,14 @@ NarrowPlan narrow_plan(int64_t M, int64_t K, int64_t N) {
 }
 
 // One or two tokens always take this kernel; more tokens while its workgroups fit the device at once and a cost
-// estimate fitted to measurements at N <= 32 (2B-model shapes) favours it by 10 %.  In us, with c = K / 1024:
+// estimate fitted to measurements at N <= 32 (2B-model shapes) favours it by 10 % over the lookup kernel.  In us, with c = K / 1024:
 //   this kernel   4.6 from fp32 activations (3.6 from INT8 ones) + c x {0.9, 1.35, 2.0, 3.4} for 32, 64, 128, 256 rows
 //                 per workgroup;
-//   general path  5.8 + 0.94 c + 0.41 x M N / 10^4 for lookup kernel + split-K sum, + 3.5 for the quantiser from fp32.
+//   lookup kernel 5.8 + 0.94 c + 0.41 x M N / 10^4 with its split-K sum, + 3.5 for the quantiser from fp32.
+// The estimate is older than gemm_kernel, which serves most calls that this rule declines.  Against that one the line is right for
+// short rows only; from INT8 codes, this kernel / the matrix cores: 640 x 1024 x 8 4.0 / 4.6 us, 640 x 2560 x 4 5.5 / 5.8, 6912 x 2560 x 1
+// 5.1 / 6.0, but 2560 x 2560 x 16 8.1 / 5.9, 100 x 8192 x 16 11.0 / 8.9, 4096 x 14336 x 4 17.9 / 13.3, 2560 x 30000 x 2 33.0 / 17.7.  Workspace sizes
+// and reported plans follow the rule, so callers know where it lies.
 bool narrow_applies(int64_t M, int64_t K, int64_t N, const void* lut, bool from_f32) {
     if (N > kNarrowMaxN || lut != nullptr || lookup_plan_forced()) return false;
     if (N <= 2) return true;
@@ -455,8 +459,8 @@ int pack_parts(const int8_t* w, int64_t M, int64_t K, int64_t K5, uint8_t* packe
 }
 
 // ---- up to sixteen tokens from fp32 (decode_kernel): one launch, every workgroup quantises all tokens.  Measured against
-//      quantiser + gemm_kernel (about 4 us more launches): 2560 x 2560 x 16 7.0 us, 13824 x 2560 x 16 8.8 us (10.5 us as two), but
-//      2560 x 6912 x 16 15.0 us (11.5 us): the rows of x are read by every workgroup, so N * K is bounded; beyond 128 rows for
+//      quantiser + gemm_kernel, launches back to back: 13824 x 2560 x 16 8.8 us (3.3 + 6.9 us as two), but 2560 x 6912 x 16 13.9 us
+//      (11.6 us): the rows of x are read by every workgroup, so N * K is bounded; beyond 128 rows for
 //      each of 256 workgroups that work is repeated (128256 x 4096 x 1 45 us, the table kernel 30 us), so M is bounded too.
 //      One token and more than 64 rows for each of 256 workgroups: unpacking twice as many bytes per workgroup costs more than the
 //      table kernel's lookups, where its one launch from fp32 covers K (decode / table: 32768 x 4096 11.7 / 9.9 us, 32768 x 14336
@@ -509,7 +513,7 @@ F32Layout f32_layout(int64_t M, int64_t K, int64_t N) {
         return L;
     }
     L.kind = kF32TwoLaunches;                    // quantise into the workspace, then the ordinary path
-    // (N unused floats ahead of the codes of a large input: the workspace keeps the size callers know)
+    // (N unused floats ahead of the codes of a large input: callers may hold a workspace of the size this call has always had)
     L.off_aq = scale_bytes + ((N * K >= ((int64_t)1 << 22) && N >= 64) ? scale_bytes : 0);
     L.off_ws = L.off_aq + round256((size_t)((N + 7) / 8) * (size_t)K * 8);
     const bool narrow = narrow_applies(M, K, N, nullptr, false);
@@ -654,7 +658,7 @@ int launch_quantize(const float* x, int64_t N, int64_t K, int64_t ldx, int8_t* a
     return launch(quantize_kernel<4, 0, VEC>, blocks8 * 16, kQuantThreads);
 }
 
-// ---- matrix-core path (gemm_kernel): every product with streamed tables, unless a plan of the lookup kernels is forced
+// ---- matrix-core path (gemm_kernel): products with streamed tables, unless a plan of the lookup kernels is forced or a rule below says otherwise
 double gemm_cost(int gw, int tile, int64_t M, int64_t macros, int64_t N) {
     const GemmTile& t = kGemmTiles[tile];
     const int g = gw - 4;
@@ -742,7 +746,9 @@ int launch_gemm(const uint8_t* packed, float w_scale, const float* w_rows, const
     p.Kmain = (int)(K5 > 0 ? K5 : K);
     p.KCn = (p.Kmain / gw + 15) / 16;
     p.macros = (p.KCn + 1) / 2;
-    // an output well beyond half of the L2s (32 MB) is not kept there: 14336 x 4096 x 512 37.4 -> 35.4 us
+    // an output beyond half of the L2s (32 MB) is not kept there: 14336 x 4096 x 512 37.4 -> 35.4 us.  Who reads y next pays about what
+    // the store saves: with quantise, clamp or sigmoid behind it 47.5, 48.0, 54.1 us, 47.5, 47.9, 53.8 with ordinary stores; nine
+    // shapes from 17 to 84 MB with a reader are within 2 % either way
     p.stream_out = M * N * 4 >= ((int64_t)16 << 20);
     if (K5 > 0 && K > K5) {
         p.packed4 = packed + (size_t)p.RGtotal * p.KCn * 64;
