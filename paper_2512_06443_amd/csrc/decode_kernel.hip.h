@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeP
     unsigned rd[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) rd[q] = (unsigned)(((kb * 4 + q) * T + ((i + ((kb * 4 + q) >> kShift)) & (T - 1))) * 16);
-    const u16x2 minus1 = opaque_minus1();
+    const UnpackConst uc(4);
     i32x4 acc = {0, 0, 0, 0};
     for (int m0 = part; m0 < p.macros; m0 += KP * PF) {
 #pragma unroll
@@ -142,10 +142,11 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeP
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     Unpack<4> un;
-                    un.start(((unsigned)w[j][q] & keep) | (kZeroIdx4 & ~keep));
                     i32x4 b;
+                    unsigned none;
+                    un.w = ((unsigned)w[j][q] & keep) | (kZeroIdx4 & ~keep);
 #pragma unroll
-                    for (int d = 0; d < 4; ++d) b[d] = un.plane(minus1);
+                    for (int st = 0; st < Unpack<4>::kOps; ++st) un.op(st, uc, b, none);
                     acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[q], b, acc, 0, 0, 0);
                 }
                 w[j] = load_w(macro + KP * PF);
@@ -160,7 +161,7 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeP
         const unsigned src = sums + (unsigned)((ml >> 4) * 1024 + ((n >> 2) * 16 + (ml & 15)) * 16 + (n & 3) * 4);
         int v = 0;
 #pragma unroll
-        for (int k = 0; k < KP; ++k) v += *(const lds_i32*)(src + (unsigned)(k * MT * 1024));
+        for (int k = 0; k < KP; ++k) v -= *(const lds_i32*)(src + (unsigned)(k * MT * 1024));
         const int m = blockIdx.x * 16 * MT + ml;
         if (m < p.M) {
             const float ws = p.w_rows ? p.w_rows[m] : p.w_scale;

@@ -55,44 +55,83 @@ struct GemmShape {
     static constexpr int kP2 = (2 * kUnits * 16 + 16 - 128 + 255) / 256 * 256 + 128;   // pairs alternate between the halves of the banks
 };
 
-// Four packed bytes -> GW planes of four INT8 weights, in GW + 1 steps (so that the caller can place matrix instructions
-// between them): start() makes the fractions, plane() the next plane, first weight first.
-// The fraction x / 3^GW in 1/256, rounded up far enough that GW multiplications by three give exactly the GW digits of
-// every x < 3^GW: (809 x + 255) >> 8 for 81 values, x + ((55 x + 1008) >> 10) for 243.
-template <int GW>
-struct Unpack {
-    u16x2 e, o;                                            // bytes 0 and 2, bytes 1 and 3
-    __device__ __forceinline__ void start(unsigned w) {
-        e = __builtin_bit_cast(u16x2, w & 0x00ff00ffu);
-        o = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(0u, w, 0x0c030c01u));
-        if constexpr (GW == 4) {
-            e = (e * u16x2{809, 809} + u16x2{255, 255}) >> (unsigned short)8;
-            o = (o * u16x2{809, 809} + u16x2{255, 255}) >> (unsigned short)8;
-        } else {
-            e += (e * u16x2{55, 55} + u16x2{1008, 1008}) >> (unsigned short)10;
-            o += (o * u16x2{55, 55} + u16x2{1008, 1008}) >> (unsigned short)10;
-        }
-    }
-    __device__ __forceinline__ int plane(u16x2 minus1) {
-        const u16x2 three = {3, 3}, low = {0xff, 0xff};
-        e = e * three + minus1;                            // digit - 1 in the high byte, the next fraction in the low one
-        o = o * three + minus1;
-        const int pl = (int)__builtin_amdgcn_perm(__builtin_bit_cast(unsigned, o), __builtin_bit_cast(unsigned, e), 0x07030501u);
-        e &= low;
-        o &= low;
-        return pl;
+// Four packed bytes -> GW planes of four INT8 values -w (negated: see below), in kOps single instructions so that the caller
+// can place matrix instructions between them.  A byte is two base-3 numbers of two digits, 9 H + L (five weights: 27 H + 3 L + d),
+// and v_perm_b32 looks four such numbers up in the eight bytes of a register pair at once.  Of the nine values 0..8 the
+// ninth has no byte: its selector is made 13 or more, which the instruction answers with 0xff, the -1 of the largest digit where
+// planes hold -w.  H comes from one rounding of a 16-bit float: with 0x64 above it a byte b is the number 1024 + b, and
+// (1024 + b) * m + c with m just below -1/9 rounds to 1024 + 15 - H, whose low byte is taken.  Checked for every byte by the tests.
+// Four weights: 13 instructions per four bytes (24 with a multiplication and a mask per digit).
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ f16x2 as_f16x2(unsigned v) { return __builtin_bit_cast(f16x2, v); }
+
+// What the instructions take from vector registers (one scalar operand each is all they may have), opaque so that the
+// compiler keeps it there.
+struct UnpackConst {
+    unsigned high, mul, table_a, table_b;
+    __device__ __forceinline__ explicit UnpackConst(int gw) {
+        high = gw == 4 ? 0x64646464u : 0x67676767u;
+        mul = gw == 4 ? 0xaf19af19u : 0xb556b556u;
+        table_a = 0x01010100u;                             // first digit of 7 - i in byte i
+        table_b = 0x0100ff01u;                             // second digit
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm("" : "+v"(high), "+v"(mul), "+v"(table_a), "+v"(table_b));
+#endif
     }
 };
 
-// 0xff00 in both halves, opaque to the compiler: knowing the constant it would multiply a second time, without the
-// addend, for the low bytes.
-__device__ __forceinline__ u16x2 opaque_minus1() {
-    unsigned v = 0xff00ff00u;
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm("" : "+s"(v));
-#endif
-    return __builtin_bit_cast(u16x2, v);
-}
+template <int GW>
+struct Unpack {
+    static constexpr int kOps = GW == 4 ? 13 : 19;
+    unsigned w, e, o, hi, lo;
+    // instruction st; planes into out[0..3], the fifth into out4
+    __device__ __forceinline__ void op(int st, const UnpackConst& c, i32x4& out, unsigned& out4) {
+        const auto fma = [](unsigned x, unsigned m, unsigned a) {
+            return __builtin_bit_cast(unsigned, __builtin_elementwise_fma(as_f16x2(x), as_f16x2(m), as_f16x2(a)));
+        };
+        const auto plane_a = [&](unsigned index) { return (int)__builtin_amdgcn_perm(c.table_a, 0x0000ffffu, index); };
+        const auto plane_b = [&](unsigned index) { return (int)__builtin_amdgcn_perm(c.table_b, 0x00ff0100u, index); };
+        if (GW == 4) {
+            switch (st) {
+            case 0: e = __builtin_amdgcn_perm(w, c.high, 0x00060004u); break;     // 1024 + bytes 0 and 2
+            case 1: o = __builtin_amdgcn_perm(w, c.high, 0x00070005u); break;     // bytes 1 and 3
+            case 2: e = fma(e, c.mul, 0x64816481u); break;                        // 1024 + 15 - H
+            case 3: o = fma(o, c.mul, 0x64816481u); break;
+            case 4: hi = __builtin_amdgcn_perm(o, e, 0x06020400u); break;         // 15 - H
+            case 5: lo = (hi << 3) + hi; break;
+            case 6: lo = lo + w - 0x87878787u; break;                             // 9 * (15 - H) + b - 135 = L
+            case 7: hi ^= 0x08080808u; break;                                     // 7 - H, 15 for H = 8
+            case 8: out[0] = plane_a(hi); break;
+            case 9: out[1] = plane_b(hi); break;
+            case 10: lo ^= 0x07070707u; break;                                    // 7 - L, 15 for L = 8
+            case 11: out[2] = plane_a(lo); break;
+            case 12: out[3] = plane_b(lo); break;
+            }
+        } else {
+            switch (st) {
+            case 0: e = __builtin_amdgcn_perm(w, c.high, 0x00060004u); break;     // 1792 + b
+            case 1: o = __builtin_amdgcn_perm(w, c.high, 0x00070005u); break;
+            case 2: e = fma(e, c.mul, 0x66d566d5u); break;                        // 1024 + 127 - b / 3
+            case 3: o = fma(o, c.mul, 0x66d566d5u); break;
+            case 4: lo = __builtin_amdgcn_perm(o, e, 0x06020400u); break;         // 127 - b / 3
+            case 5: e = fma(e, 0x2f1d2f1du, 0x631f631fu); break;                  // 1024 + 15 - b / 27
+            case 6: o = fma(o, 0x2f1d2f1du, 0x631f631fu); break;
+            case 7: hi = __builtin_amdgcn_perm(o, e, 0x06020400u); break;         // 15 - H
+            case 8: e = (lo << 1) + lo; break;
+            case 9: e = e + w - 0x7e7e7e7du; break;                               // b - 3 * (b / 3)
+            case 10: o = (hi << 3) + hi; break;
+            case 11: lo = o - lo; break;                                          // 9 * (15 - H) - (127 - (9 H + L)) = 8 + L
+            case 12: out4 = __builtin_amdgcn_perm(0u, 0x00ff0001u, e); break;
+            case 13: hi ^= 0x08080808u; break;
+            case 14: out[0] = plane_a(hi); break;
+            case 15: out[1] = plane_b(hi); break;
+            case 16: lo ^= 0x0f0f0f0fu; break;                                    // 7 - L, 31 for L = 8
+            case 17: out[2] = plane_a(lo); break;
+            case 18: out[3] = plane_b(lo); break;
+            }
+        }
+    }
+};
 
 __device__ __forceinline__ i32x2 lds_read_tr8(unsigned addr) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -233,22 +272,20 @@ __global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) 
     load_weights(wk + WK, w1);                             // (requested after them, as in the loop: loads return in order)
     i32x4 a[CT], b[RT];
     Unpack<GW> un[RT];
-    const u16x2 minus1 = opaque_minus1();
+    constexpr int kOps = Unpack<GW>::kOps;
+    const UnpackConst uc(GW);
     // step st of making the weight operands of matrix instructions q from the raw dwords w
     auto unpack_step = [&](const i32x4 (&w)[RT], unsigned keep, int q, int st, i32x4 (&o)[RT]) {
-        const int rt = st / (GW + 1), j = st % (GW + 1);
+        const int rt = st / kOps, j = st % kOps;
         if (q >= 4) {
             if (j == 0) o[rt] = i32x4{(int)left[rt][0], (int)left[rt][1], (int)left[rt][2], (int)left[rt][3]};
-        } else if (j == 0) {
-            un[rt].start(((unsigned)w[rt][q] & keep) | (kZero & ~keep));
-        } else {
-            const int pl = un[rt].plane(minus1);
-            if (j <= 4) o[rt][j - 1] = pl;
-            else left[rt][q] = (unsigned)pl;
+            return;
         }
+        if (j == 0) un[rt].w = ((unsigned)w[rt][q] & keep) | (kZero & ~keep);
+        un[rt].op(j, uc, o[rt], left[rt][q]);
     };
 #pragma unroll
-    for (int st = 0; st < RT * (GW + 1); ++st) unpack_step(w0, keep_mask(wk), 0, st, b);
+    for (int st = 0; st < RT * kOps; ++st) unpack_step(w0, keep_mask(wk), 0, st, b);
     wg_barrier_lds();
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
@@ -274,7 +311,7 @@ __global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) 
                 load_weights(macro + 2 * WK, w);
             }
             i32x4 an[CT], bn[RT];
-            constexpr int G = CT * RT, NS = RT * (GW + 1), NR = 2 * CT;
+            constexpr int G = CT * RT, NS = RT * kOps, NR = 2 * CT;
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 __builtin_amdgcn_sched_barrier(0);
@@ -307,13 +344,15 @@ __global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) 
         if (tid < BN) *(lds_i32x4*)(unsigned)((tid >> 4) * S::kP2 + ((tid >> 3) & 1) * S::kP1 + (tid & 7) * 16) = at4;
         wg_barrier_lds();
         if (wk == 0) {
+            const UnpackConst uc4(4);
             const unsigned rd4 = (unsigned)(((lane >> 4) & 1) * S::kP2 + (lane & 1) * S::kP1 + (r8 & 3) * 4 * 8 + (r8 >> 2) * 8);
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
                 Unpack<4> u;
-                u.start(w4[rt]);
+                unsigned none;
+                u.w = w4[rt];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) b[rt][j] = u.plane(minus1);
+                for (int st = 0; st < Unpack<4>::kOps; ++st) u.op(st, uc4, b[rt], none);
             }
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
@@ -347,11 +386,11 @@ __global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) 
     for (int qd = 0; qd < Q; ++qd) {
         if (qd / kOwn != wk) continue;
         const int rt = qd / 4 / CT, ct = qd / 4 % CT, g = qd & 3;
-        int v[4] = {acc[rt][ct][4 * g], acc[rt][ct][4 * g + 1], acc[rt][ct][4 * g + 2], acc[rt][ct][4 * g + 3]};
+        int v[4] = {-acc[rt][ct][4 * g], -acc[rt][ct][4 * g + 1], -acc[rt][ct][4 * g + 2], -acc[rt][ct][4 * g + 3]};   // (planes hold -w)
 #pragma unroll
         for (int s = 0; s < WK - 1; ++s) {
             const i32x4 o = *(const lds_i32x4*)(unsigned)((((wm * Q + qd) * (WK - 1)) + s) * 1024 + lane * 16);
-            v[0] += o.x; v[1] += o.y; v[2] += o.z; v[3] += o.w;
+            v[0] -= o.x; v[1] -= o.y; v[2] -= o.z; v[3] -= o.w;
         }
         const int ml = (wm * RT + rt) * 32 + i, nl = 32 * ct + 8 * g + 4 * kb;
         const int m = mt * BM + ml, n = nt * BN + nl;
