@@ -8,6 +8,7 @@ a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional, Tuple
 
@@ -15,6 +16,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libvlut.so")
+NATIVE_PATH = os.path.join(_HERE, "_vlut_torch.so")
 
 VLUT_OK = 0
 VLUT_ERR_NULL, VLUT_ERR_SHAPE, VLUT_ERR_SMALL_BUFFER = -1, -2, -3
@@ -91,8 +93,35 @@ def lib() -> ctypes.CDLL:
         L.vlut_mpgemm_static.argtypes, L.vlut_mpgemm_static.restype = [p, cf, p, p, i64, i64, i64, p, i64, p, p], ci
         L.vlut_set_plan.argtypes, L.vlut_set_plan.restype = [ci, ci, ci, ci], ci
         L.vlut_query_plan.argtypes, L.vlut_query_plan.restype = [i64, i64, i64, ctypes.POINTER(ci)], ci
+        _load_native(L)
         _lib = L
     return _lib
+
+
+# The frequent calls as native code (csrc/torch_calls.cpp): the same arguments, outputs and library call without ctypes and without
+# torch's Python layer.  Each returns None for arguments it leaves to the Python form below it (which also raises every
+# error), an int status or the tuple of outputs.  None here: not built, or built for another torch; the Python form serves then.
+# Host time of a call, Python / native form, us (256 x 256, eight tokens; the launch alone is 2.5 to 3): mpgemm_f32 7.6 / 4.3, with y and
+# workspace given 5.5 / 3.5, quantize_act 7.9 / 5.3, mpgemm 7.6 / 4.8.
+_native = None
+_NATIVE_ORDER = ("vlut_quantize_act", "vlut_mpgemm", "vlut_workspace_bytes", "vlut_mpgemm_f32", "vlut_workspace_bytes_f32", "vlut_mpgemm_g5",
+                 "vlut_workspace_bytes_g5", "vlut_mpgemm_mixed", "vlut_workspace_bytes_mixed", "vlut_pack_weights",
+                 "vlut_packed_weight_bytes", "vlut_pack_weights_g5", "vlut_packed_weight_bytes_g5", "vlut_pack_weights_mixed",
+                 "vlut_packed_weight_bytes_mixed")
+
+
+def _load_native(L: ctypes.CDLL) -> None:
+    global _native
+    if not os.path.exists(NATIVE_PATH) or not hasattr(torch._C, "_cuda_getCurrentRawStream"):
+        return
+    try:
+        spec = importlib.util.spec_from_file_location("_vlut_torch", NATIVE_PATH)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+    except ImportError:                 # built for another torch
+        return
+    mod.bind(*[ctypes.cast(getattr(L, f), ctypes.c_void_p).value for f in _NATIVE_ORDER])
+    _native = mod
 
 
 def status_string(status: int) -> str:
@@ -115,6 +144,13 @@ if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_g
 else:
     def _stream() -> int:
         return torch.cuda.current_stream().cuda_stream
+
+
+def _outputs(r, where: str):
+    """What a native call returned: the outputs, or the status of a call that was refused."""
+    if type(r) is tuple:
+        return r
+    raise VlutError(r, where)
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -159,6 +195,10 @@ def query_plan(M: int, K: int, N: int) -> Tuple[int, int, int, int]:
 
 def pack_weights(w_ternary: torch.Tensor) -> torch.Tensor:
     """int8 [M][K] on the GPU -> packed uint8 blob (opaque tile layout) on the GPU."""
+    if _native is not None:
+        r = _native.pack_weights(w_ternary)
+        if r is not None:
+            return _outputs(r, "vlut_pack_weights")[0]
     assert w_ternary.is_cuda and w_ternary.dtype == torch.int8 and w_ternary.is_contiguous()
     M, K = w_ternary.shape
     nbytes = packed_weight_bytes(M, K)
@@ -171,6 +211,10 @@ def pack_weights(w_ternary: torch.Tensor) -> torch.Tensor:
 
 def quantize_act(x: torch.Tensor, a_q: Optional[torch.Tensor] = None, a_scale: Optional[torch.Tensor] = None):
     """fp32 [N][K] (row stride >= K) -> (int8 token-chunked [ceil(N/8)][K][8], fp32 [N])."""
+    if _native is not None:
+        r = _native.quantize_act(x, a_q, a_scale)
+        if r is not None:
+            return _outputs(r, "vlut_quantize_act")
     assert x.is_cuda and x.dtype == torch.float32 and x.dim() == 2 and x.stride(1) == 1
     N, K = x.shape
     if a_q is None:
@@ -195,6 +239,10 @@ def mpgemm(packed: torch.Tensor, w_scale: float, a_q: torch.Tensor, a_scale: tor
            y: Optional[torch.Tensor] = None, acc: Optional[torch.Tensor] = None, lut: Optional[torch.Tensor] = None,
            workspace: Optional[torch.Tensor] = None, want_acc: bool = False, mfma: bool = False):
     """Runs vlut_mpgemm (or the MFMA comparison path).  Returns (y fp32 [N][M], acc int32 [M][N] or None)."""
+    if _native is not None and lut is None and not mfma:
+        r = _native.mpgemm(packed, w_scale, a_q, a_scale, M, y, acc, want_acc, workspace)
+        if r is not None:
+            return _outputs(r, "vlut_mpgemm")
     K, N = a_q.shape[1], a_scale.shape[0]
     dev = a_q.device
     if y is None:
@@ -299,6 +347,10 @@ def mpgemm_f32(packed: torch.Tensor, w_scale, x: torch.Tensor, M: int, y: Option
                want_acc: bool = False, want_scales: bool = False, workspace: Optional[torch.Tensor] = None):
     """Runs vlut_mpgemm_f32 on fp32 activations x [N][K] (row stride >= K).  w_scale: a float, or an fp32 [M]
     tensor on the GPU with one weight scale per output row.  Returns (y [N][M], acc or None, a_scale or None)."""
+    if _native is not None:
+        r = _native.mpgemm_f32(packed, w_scale, x, M, y, want_acc, want_scales, workspace)
+        if r is not None:
+            return _outputs(r, "vlut_mpgemm_f32")
     assert x.is_cuda and x.dtype == torch.float32 and x.dim() == 2 and x.stride(1) == 1
     L = _lib or lib()
     N, K = x.shape
@@ -325,6 +377,10 @@ def mpgemm_f32(packed: torch.Tensor, w_scale, x: torch.Tensor, M: int, y: Option
 # ---- 1.60-bit packing (g = 5)
 def pack_weights_g5(w_ternary: torch.Tensor) -> torch.Tensor:
     """int8 [M][K] (K % 5 == 0) on the GPU -> 1.60-bit packed blob on the GPU."""
+    if _native is not None:
+        r = _native.pack_weights_g5(w_ternary)
+        if r is not None:
+            return _outputs(r, "vlut_pack_weights_g5")[0]
     assert w_ternary.is_cuda and w_ternary.dtype == torch.int8 and w_ternary.is_contiguous()
     M, K = w_ternary.shape
     nbytes = lib().vlut_packed_weight_bytes_g5(M, K)
@@ -337,6 +393,10 @@ def pack_weights_g5(w_ternary: torch.Tensor) -> torch.Tensor:
 
 def pack_weights_mixed(w_ternary: torch.Tensor) -> torch.Tensor:
     """int8 [M][K] (K % 4 == 0) on the GPU -> blob of the mixed 1.60-bit / 2-bit packing on the GPU."""
+    if _native is not None:
+        r = _native.pack_weights_mixed(w_ternary)
+        if r is not None:
+            return _outputs(r, "vlut_pack_weights_mixed")[0]
     assert w_ternary.is_cuda and w_ternary.dtype == torch.int8 and w_ternary.is_contiguous()
     M, K = w_ternary.shape
     nbytes = lib().vlut_packed_weight_bytes_mixed(M, K)
@@ -350,6 +410,10 @@ def pack_weights_mixed(w_ternary: torch.Tensor) -> torch.Tensor:
 def mpgemm_mixed(packed: torch.Tensor, w_scale: float, a_q: torch.Tensor, a_scale: torch.Tensor, M: int,
                  y: Optional[torch.Tensor] = None, want_acc: bool = False):
     """Runs vlut_mpgemm_mixed on a blob from pack_weights_mixed.  Returns (y [N][M], acc or None)."""
+    if _native is not None:
+        r = _native.mpgemm_mixed(packed, w_scale, a_q, a_scale, M, y, None, want_acc, None)
+        if r is not None:
+            return _outputs(r, "vlut_mpgemm_mixed")
     K, N = a_q.shape[1], a_scale.shape[0]
     dev = a_q.device
     if y is None:
@@ -374,6 +438,10 @@ def query_plan_g5(M: int, K: int, N: int) -> Tuple[int, int, int]:
 def mpgemm_g5(packed: torch.Tensor, w_scale: float, a_q: torch.Tensor, a_scale: torch.Tensor, M: int,
               y: Optional[torch.Tensor] = None, want_acc: bool = False, workspace: Optional[torch.Tensor] = None):
     """Runs vlut_mpgemm_g5.  Returns (y fp32 [N][M], acc int32 [M][N] or None)."""
+    if _native is not None:
+        r = _native.mpgemm_g5(packed, w_scale, a_q, a_scale, M, y, None, want_acc, workspace)
+        if r is not None:
+            return _outputs(r, "vlut_mpgemm_g5")
     K, N = a_q.shape[1], a_scale.shape[0]
     dev = a_q.device
     if y is None:

@@ -1,0 +1,94 @@
+"""The native form of the binding's calls against their Python form: same outputs, same refusals."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_06443_amd import binding as B
+
+
+def test_native_form_is_built_and_declines_what_it_does_not_know():
+    B.lib()
+    if torch.version.hip is None:
+        pytest.skip("built with a torch for ROCm only")
+    n = B._native
+    assert n is not None
+    x = torch.zeros(2, 8)                                     # not on the GPU: the Python form decides (and raises)
+    p = torch.zeros(64, dtype=torch.uint8)
+    assert n.quantize_act(x, None, None) is None
+    assert n.quantize_act("x", None, None) is None
+    assert n.mpgemm_f32(p, 1.0, x, 4, None, False, False, None) is None
+    assert n.mpgemm(p, 1.0, x, x, 4, None, None, False, None) is None
+    assert n.mpgemm(p) is None
+    assert n.pack_weights(torch.zeros(4, 8, dtype=torch.int8)) is None
+    with pytest.raises(AssertionError):
+        B.quantize_act(x)
+    with pytest.raises(TypeError):
+        n.bind(1)
+
+
+def _both(monkeypatch, f):
+    assert B._native is not None
+    native = f()
+    with monkeypatch.context() as m:
+        m.setattr(B, "_native", None)
+        return native, f()
+
+
+def _same(a, b):
+    assert type(a) is type(b) and len(a) == len(b)
+    for u, v in zip(a, b):
+        assert (u is None) == (v is None)
+        if u is not None:
+            assert u.dtype == v.dtype and u.shape == v.shape and u.device == v.device and torch.equal(u, v)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N", [1, 9, 70])
+@pytest.mark.parametrize("want", [False, True])
+def test_native_form_gives_what_the_python_form_gives(monkeypatch, N, want):
+    B.lib()
+    torch.manual_seed(N)
+    M, K = 203, 320
+    W = torch.randint(-1, 2, (M, K), dtype=torch.int8, device="cuda")
+    x = torch.randn(N, K + 4, device="cuda")[:, :K]            # row stride above K
+    packed, mixed = B.pack_weights(W), B.pack_weights_mixed(W)
+    for pack in (B.pack_weights, B.pack_weights_g5, B.pack_weights_mixed):
+        assert torch.equal(*_both(monkeypatch, lambda: pack(W)))
+    rows = torch.rand(M, device="cuda") + 0.5
+    q = _both(monkeypatch, lambda: B.quantize_act(x))
+    _same(*q)
+    a_q, a_s = q[0]
+    y = torch.empty(N, M + 5, device="cuda")
+    for f in (lambda: B.mpgemm(packed, 0.25, a_q, a_s, M, want_acc=want), lambda: B.mpgemm(packed, np.float32(0.25), a_q, a_s, M),
+              lambda: B.mpgemm(packed, 2, a_q, a_s, M, y=y[:, :M]), lambda: B.mpgemm_g5(B.pack_weights_g5(W), 0.5, a_q, a_s, M, want_acc=want),
+              lambda: B.mpgemm_mixed(mixed, 0.5, a_q, a_s, M, want_acc=want),
+              lambda: B.mpgemm_f32(packed, 0.25, x, M, want_acc=want, want_scales=want), lambda: B.mpgemm_f32(packed, rows, x, M)):
+        n, p = _both(monkeypatch, lambda: [t.clone() if t is not None else None for t in f()])
+        _same(n, p)
+
+
+@pytest.mark.gpu
+def test_native_form_refuses_what_the_python_form_refuses(monkeypatch):
+    B.lib()
+    M, K, N = 64, 128, 40
+    packed = B.pack_weights(torch.zeros(M, K, dtype=torch.int8, device="cuda"))
+    x = torch.randn(N, K, device="cuda")
+    a_q, a_s = B.quantize_act(x)
+    wrong = torch.full((M, K), 2, dtype=torch.int8, device="cuda")
+    small = torch.empty(4, dtype=torch.uint8, device="cuda")
+    for f in (lambda: B.mpgemm_f32(packed, 1.0, x, M, workspace=small), lambda: B.mpgemm_f32(packed, 1.0, x[:, :126], M),
+              lambda: B.mpgemm_f32(packed, 1.0, x.half(), M), lambda: B.mpgemm_f32(packed, 1.0, x.t(), M), lambda: B.mpgemm_f32(packed, 1.0, x.cpu(), M),
+              lambda: B.mpgemm_f32(packed, torch.ones(M - 1, device="cuda"), x, M), lambda: B.mpgemm_f32(packed, 1.0, x[:0], M),
+              lambda: B.mpgemm(packed[1:], 1.0, a_q, a_s, M), lambda: B.mpgemm(packed, 1.0, a_q, a_s, 0),
+              lambda: B.mpgemm(packed, 1.0, a_q, a_s, M, y=torch.empty(N, M - 1, device="cuda")), lambda: B.mpgemm(packed, None, a_q, a_s, M), lambda: B.pack_weights(wrong),
+              lambda: B.pack_weights(wrong[:, :126]), lambda: B.pack_weights_g5(wrong), lambda: B.pack_weights_mixed(wrong)):
+        def outcome():
+            try:
+                f()
+            except Exception as e:
+                return type(e), getattr(e, "status", None)
+            return None
+        n, p = _both(monkeypatch, outcome)
+        assert n is not None and n == p
