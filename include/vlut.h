@@ -335,7 +335,8 @@ int vlut_set_plan(int J, int R, int waves, int split_k);
 #define VLUT_FORM_G5 2       /* vlut_mpgemm_g5                                                                 */
 #define VLUT_FORM_MIXED 3    /* vlut_mpgemm_mixed                                                              */
 #define VLUT_KERNEL_LOOKUP 1            /* tables in LDS, the plan that vlut_query_plan or vlut_query_plan_g5 reports */
-#define VLUT_KERNEL_FEW_TOKENS 2        /* tables in LDS, one or two tokens per workgroup                      */
+#define VLUT_KERNEL_FEW_TOKENS 2        /* a few tokens: tables in LDS, one or two tokens per workgroup; from INT8 codes the
+                                           matrix cores, where one chunk's codes fit into LDS (K <= 14592, M <= 32768)  */
 #define VLUT_KERNEL_MATRIX 3            /* INT8 matrix cores                                                   */
 #define VLUT_KERNEL_MATRIX_FEW_TOKENS 4 /* INT8 matrix cores, from fp32 in one launch                          */
 int vlut_query_kernel(int form, int64_t M, int64_t K, int64_t N);
@@ -347,9 +348,9 @@ int vlut_query_kernel(int form, int64_t M, int64_t K, int64_t N);
  * vlut_mpgemm mostly runs on the matrix cores instead: vlut_query_kernel tells.
  * With few tokens and no override (N <= 2 always; 3 <= N <= 32 when ceil(N/2) copies of the row tiles are at most
  * 256 workgroups and a cost estimate favours it: few rows per workgroup, or a short K), vlut_mpgemm uses a kernel
- * of its own (two tokens per
- * workgroup, table entries of one dword, every workgroup sweeps all of K, no workspace); it is reported as
- * { 0, rows per workgroup, 1, number of workgroups }.
+ * of its own (every workgroup sweeps all of K, no workspace); what is reported is the few-token table kernel (two tokens per
+ * workgroup, table entries of one dword): { 0, rows per workgroup, 1, number of workgroups }, which up to K = 14592 and
+ * M = 32768 leaves the call to the matrix cores (workgroups of 8 or 16 tokens and 16 to 128 rows).
  */
 int vlut_query_plan(int64_t M, int64_t K, int64_t N, int* out4);
 

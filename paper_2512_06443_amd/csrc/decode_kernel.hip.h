@@ -29,11 +29,76 @@ struct DecodeParams {
     int64_t ldx;
     float w_scale;
     int M, N, K, KCn, RGtotal, ldy, macros, x_vec;
+    const int8_t* a_q;            // decode_codes_kernel: INT8 codes and their scales instead of x
+    const float* a_scale;
+    int chunks, tiles_n, tiles, per_xcd;
+    unsigned magic_n;             // 2^32 / tiles_n rounded up (tiles_n > 1)
 };
 
 constexpr int kDecodeWaves = 16;
 constexpr int kDecodeKeep = 12;                // float4 of x per lane kept between the two passes; the rest is read twice
 constexpr int decode_lds_bytes(int T, int macros) { return macros * 256 * T + kDecodeWaves * 1024 + 128; }
+
+// One lane's packed bytes: row m, tile column 4 macro + kb (rows past the last one are clamped, their sums are not stored; columns
+// past the last one are clamped and replaced by zeros when they are unpacked).
+struct DecodeWeights {
+    const uint8_t* row;
+    int kb, last;
+    __device__ __forceinline__ DecodeWeights(const DecodeParams& p, int m, int kb_)
+        : row(p.packed + (size_t)min(m >> 2, p.RGtotal - 1) * p.KCn * 64 + (m & 3) * 16), kb(kb_), last(p.KCn - 1) {}
+    __device__ __forceinline__ i32x4 load(int macro) const { return *(const i32x4*)(row + (size_t)min(4 * macro + kb, last) * 64); }
+};
+
+// Four packed bytes as the four planes of -w; the all-zero pattern where keep is 0.
+__device__ __forceinline__ i32x4 unpack_planes4(unsigned w, unsigned keep, const UnpackConst& uc) {
+    Unpack<4> un;
+    i32x4 b;
+    unsigned none;
+    un.w = (w & keep) | (kZeroIdx4 & ~keep);
+#pragma unroll
+    for (int st = 0; st < Unpack<4>::kOps; ++st) un.op(st, uc, b, none);
+    return b;
+}
+
+// The outputs tid, tid + 1024, .. of the workgroup's 16 * MT rows (from m0) x TOK tokens (from n0).  Their scales are requested ahead of
+// the weights: at the end they would cost a trip to memory of their own.
+template <int TOK, int MT>
+struct DecodeOut {
+    static constexpr int kThreads = 64 * kDecodeWaves, kRounds = (16 * MT * TOK + kThreads - 1) / kThreads;
+    int first, m0, n0;
+    float ws[kRounds], as[kRounds];
+    __device__ __forceinline__ DecodeOut(const DecodeParams& p, int tid, int m0_, int n0_) : first(tid), m0(m0_), n0(n0_) {
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const int o = tid + kThreads * r, n = n0 + o / (16 * MT), m = m0 + o % (16 * MT);
+            ws[r] = p.w_scale;
+            as[r] = 0.0f;
+            if (n < p.N && m < p.M) {
+                if (p.w_rows) ws[r] = p.w_rows[m];
+                if (p.a_scale) as[r] = p.a_scale[n];
+            }
+        }
+    }
+    // adds the parts of K (sums of -w, 16 tokens x 16 rows per wave), scales, stores; scale(n, as) is the scale of the tile's token n
+    template <class Scale>
+    __device__ __forceinline__ void store(const DecodeParams& p, unsigned sums, Scale scale) const {
+        constexpr int KP = kDecodeWaves / MT;
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const int o = first + kThreads * r, nl = o / (16 * MT), ml = o % (16 * MT);
+            const int n = n0 + nl, m = m0 + ml;
+            if (nl >= TOK || n >= p.N) break;
+            const unsigned src = sums + (unsigned)((ml >> 4) * 1024 + ((nl >> 2) * 16 + (ml & 15)) * 16 + (nl & 3) * 4);
+            int v = 0;
+#pragma unroll
+            for (int k = 0; k < KP; ++k) v -= *(const lds_i32*)(src + (unsigned)(k * MT * 1024));
+            if (m < p.M) {
+                if (p.y) p.y[(size_t)n * p.ldy + m] = (float)v * (ws[r] * scale(nl, as[r]));
+                if (p.acc) p.acc[(size_t)m * p.N + n] = v;
+            }
+        }
+    }
+};
 
 template <int T, int MT>
 __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeParams p) {
@@ -67,9 +132,9 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeP
     }
     const int rt = wave % MT, part = wave / MT;
     const int i = lane & 15, kb = lane >> 4;
-    const int m_row = (blockIdx.x * MT + rt) * 16 + i;
-    const uint8_t* wrow = p.packed + (size_t)min(m_row >> 2, p.RGtotal - 1) * p.KCn * 64 + (m_row & 3) * 16;
-    auto load_w = [&](int macro) { return *(const i32x4*)(wrow + (size_t)min(4 * macro + kb, p.KCn - 1) * 64); };
+    const DecodeWeights weights(p, (blockIdx.x * MT + rt) * 16 + i, kb);
+    auto load_w = [&](int macro) { return weights.load(macro); };
+    const DecodeOut<T, MT> out(p, tid, blockIdx.x * 16 * MT, 0);
     i32x4 w[PF];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -141,13 +206,7 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeP
                 for (int q = 0; q < 4; ++q) a[q] = *(const lds_i32x4*)(rd[q] + (unsigned)macro * (256u * T));
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    Unpack<4> un;
-                    i32x4 b;
-                    unsigned none;
-                    un.w = ((unsigned)w[j][q] & keep) | (kZeroIdx4 & ~keep);
-#pragma unroll
-                    for (int st = 0; st < Unpack<4>::kOps; ++st) un.op(st, uc, b, none);
-                    acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[q], b, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[q], unpack_planes4((unsigned)w[j][q], keep, uc), acc, 0, 0, 0);
                 }
                 w[j] = load_w(macro + KP * PF);
             }
@@ -156,19 +215,106 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeP
     // ---- lane: output row i, tokens 4 kb .. 4 kb + 3
     *(lds_i32x4*)(sums + (unsigned)(wave * 1024 + lane * 16)) = acc;
     wg_barrier_lds();
-    for (int o = tid; o < 16 * MT * p.N; o += 64 * kDecodeWaves) {
-        const int n = o / (16 * MT), ml = o % (16 * MT);
-        const unsigned src = sums + (unsigned)((ml >> 4) * 1024 + ((n >> 2) * 16 + (ml & 15)) * 16 + (n & 3) * 4);
-        int v = 0;
+    out.store(p, sums, [&](int n, float) { return *(const lds_f32*)(red + 64 + n * 4); });
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same product from INT8 codes, 8 * CH tokens per workgroup: it copies their codes over all of K to LDS as they lie in
+// memory, one 16-byte unit (two k of eight tokens) per lane, and reads its operands with the transposing reads of gemm_kernel.
+// Tile columns (64 k) are pitched 640 bytes and chunks 16 bytes beyond a multiple of 256, so that the 32 rows of half a
+// read lie in distinct banks.  What lies behind the last k in LDS meets zero weights, what lies in an absent chunk makes
+// sums that are not stored.
+// All of the codes at once, one barrier, all of the weights: a launch is little more than two trips to memory, where gemm_kernel waits
+// for one with every macro step.
+// ---------------------------------------------------------------------------------------------
+constexpr int kCodesColumn = 640;
+constexpr int decode_codes_pitch(int macros) { return macros * 4 * kCodesColumn + 16; }
+constexpr int decode_codes_lds_bytes(int ch, int macros) { return ch * decode_codes_pitch(macros) + kDecodeWaves * 1024; }
+// K that the LDS of a workgroup holds: 14592 values for one chunk, 7168 for two
+constexpr bool decode_codes_fits(int ch, int64_t K) { return K <= 14592 && decode_codes_lds_bytes(ch, (int)((K + 255) / 256)) <= 160 * 1024; }
+
+template <int CH, int MT>
+__global__ void __launch_bounds__(64 * kDecodeWaves) decode_codes_kernel(const DecodeParams p) {
+    constexpr int KP = kDecodeWaves / MT;      // parts of K
+    constexpr int PF = 4;                      // macro steps of weights in flight
+    constexpr int NU = 4;                      // units per thread and pass
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned pitch = (unsigned)decode_codes_pitch(p.macros);
+    const unsigned sums = CH * pitch;
+    // tiles as in gemm_kernel: the token tiles of a row tile next to each other, a contiguous range of the list for each XCD
+    const int tile = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
+    if (tile >= p.tiles) return;
+    const int mt = p.tiles_n == 1 ? tile : (int)__umulhi((unsigned)tile, p.magic_n), nt = tile - mt * p.tiles_n;
+    const int m0 = mt * 16 * MT;
+
+    // ---- request the codes first (they are copied while the weights are on their way), then the epilogue's scales, then weights
+    const int units = p.K >> 1;                            // of a chunk (K % 4 == 0); chunks lie one behind the other
+    const int total = CH == 2 && 2 * nt + 1 < p.chunks ? 2 * units : units;
+    const int8_t* codes = p.a_q + (size_t)nt * CH * p.K * 8;
+    i32x4 v[NU];
+    auto load_units = [&](int u0) {
 #pragma unroll
-        for (int k = 0; k < KP; ++k) v -= *(const lds_i32*)(src + (unsigned)(k * MT * 1024));
-        const int m = blockIdx.x * 16 * MT + ml;
-        if (m < p.M) {
-            const float ws = p.w_rows ? p.w_rows[m] : p.w_scale;
-            if (p.y) p.y[(size_t)n * p.ldy + m] = (float)v * (ws * *(const lds_f32*)(red + 64 + n * 4));
-            if (p.acc) p.acc[(size_t)m * p.N + n] = v;
+        for (int j = 0; j < NU; ++j)
+            if (u0 + 64 * kDecodeWaves * j + 64 * wave < total)        // (uniform)
+                v[j] = *(const i32x4*)(codes + (size_t)min(u0 + 64 * kDecodeWaves * j + tid, total - 1) * 16);
+    };
+    auto store_units = [&](int u0) {
+#pragma unroll
+        for (int j = 0; j < NU; ++j) {
+            const int u = u0 + 64 * kDecodeWaves * j + tid;
+            if (u < total) {
+                const bool second = CH == 2 && u >= units;
+                const unsigned at = (unsigned)(second ? u - units : u);
+                *(lds_i32x4*)((second ? pitch : 0u) + at * 16u + (at >> 5) * (unsigned)(kCodesColumn - 512)) = v[j];
+            }
+        }
+    };
+    load_units(0);
+    const int rt = wave % MT, part = wave / MT;
+    const int i = lane & 15, kb = lane >> 4;
+    const DecodeWeights weights(p, m0 + rt * 16 + i, kb);
+    const DecodeOut<8 * CH, MT> out(p, tid, m0, nt * 8 * CH);
+    i32x4 w[PF];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < PF; ++j) w[j] = weights.load(part + KP * j);
+    __builtin_amdgcn_sched_barrier(0);
+    store_units(0);
+    for (int u0 = 64 * kDecodeWaves * NU; u0 < total; u0 += 64 * kDecodeWaves * NU) {
+        load_units(u0);
+        store_units(u0);
+    }
+    wg_barrier_lds();
+
+    // ---- multiply: macro steps part, part + KP, ... of row tile rt.  Of a group of 16 lanes two point at each of eight rows (k in the
+    //      order of the planes), one per chunk, and lane i receives the eight values of token i
+    const int r8 = i >> 1;
+    const unsigned rd = (unsigned)(kb * kCodesColumn + (r8 & 3) * 32 + (r8 >> 2) * 8) + (CH == 2 && (lane & 1) ? pitch : 0u);
+    const UnpackConst uc(4);
+    i32x4 acc = {0, 0, 0, 0};
+    for (int s0 = part; s0 < p.macros; s0 += KP * PF) {
+#pragma unroll
+        for (int j = 0; j < PF; ++j) {
+            const int macro = s0 + KP * j;
+            if (macro < p.macros) {
+                const unsigned keep = 4 * macro + kb < p.KCn ? 0xffffffffu : 0u;
+                const unsigned at = rd + (unsigned)macro * (4u * kCodesColumn);
+                i32x4 a[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const i32x2 lo = lds_read_tr8(at + q * 128), hi = lds_read_tr8(at + q * 128 + 16);
+                    a[q] = i32x4{lo.x, lo.y, hi.x, hi.y};
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[q], unpack_planes4((unsigned)w[j][q], keep, uc), acc, 0, 0, 0);
+                w[j] = weights.load(macro + KP * PF);
+            }
         }
     }
+    *(lds_i32x4*)(sums + (unsigned)(wave * 1024 + lane * 16)) = acc;     // output row i, tokens 4 kb .. 4 kb + 3
+    wg_barrier_lds();
+    out.store(p, sums, [](int, float scale) { return scale; });
 }
 
 }  // namespace

@@ -151,7 +151,7 @@ constexpr int gemm_lds_bytes() {
 }
 
 template <int GW, int RT, int CT, int WM, int WK>
-__global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) {
+__global__ void __launch_bounds__(64 * WM * WK, 2) gemm_kernel(const GemmParams p) {
     using S = GemmShape<GW>;
     constexpr int NQ = GW;                                 // matrix instructions per macro step and 32 x 32 tile
     constexpr int BN = 32 * CT;
@@ -209,15 +209,9 @@ __global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) 
         aend[u] = row + (unsigned)(p.Kmain / 2 - 1) * 16u;
         adst[u] = (unsigned)((wk * 2) * kBuf + (c >> 1) * S::kP2 + (c & 1) * S::kP1 + unit * 16);
     }
-    auto load_acts = [&](int macro, i32x4 (&a)[kPer]) {
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) a[u] = *(const i32x4*)(abase + min(aoff[u] + (unsigned)macro * (S::kUnits * 16u), aend[u]));
-    };
-    auto store_acts = [&](int buf, const i32x4 (&a)[kPer]) {
-#pragma unroll
-        for (int u = 0; u < kPer; ++u)
-            if (kUnitsTile % kGroupThreads == 0 || u + 1 < kPer || gt + u * kGroupThreads < kUnitsTile)
-                *(lds_i32x4*)(adst[u] + buf * kBuf) = a[u];
+    auto load_act = [&](int macro, int u) { return *(const i32x4*)(abase + min(aoff[u] + (unsigned)macro * (S::kUnits * 16u), aend[u])); };
+    auto store_act = [&](int buf, int u, const i32x4 v) {
+        if (kUnitsTile % kGroupThreads == 0 || u + 1 < kPer || gt + u * kGroupThreads < kUnitsTile) *(lds_i32x4*)(adst[u] + buf * kBuf) = v;
     };
     // ---- transposing reads: lane of a group of 16 -> row r of the eight, chunk half; the four groups are tokens 0-15
     //      and 16-31 of K block 0, then of K block 1
@@ -245,7 +239,8 @@ __global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) 
     const int passes = (p.macros + WK - 1) / WK;
     i32x4 w0[RT], w1[RT], a0[kPer];
     load_weights(wk, w0);
-    load_acts(wk, a0);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) a0[u] = load_act(wk, u);
     // (mixed packing) the last < 20 values of K: at most four packed bytes per row, 16 activation rows per chunk
     i32x4 at4 = {0, 0, 0, 0};
     unsigned w4[RT];
@@ -267,8 +262,11 @@ __global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) 
     for (int j = tid; j < BN + BM; j += 64 * WM * WK)
         *(lds_i32*)(unsigned)(kScales + j * 4) = __builtin_bit_cast(
             int, j < BN ? p.a_scale[min(nt * BN + j, p.N - 1)] : (p.w_rows ? p.w_rows[min(mt * BM + j - BN, p.M - 1)] : p.w_scale));
-    store_acts(0, a0);
-    load_acts(wk + WK, a0);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        store_act(0, u, a0[u]);
+        a0[u] = load_act(wk + WK, u);
+    }
     load_weights(wk + WK, w1);                             // (requested after them, as in the loop: loads return in order)
     i32x4 a[CT], b[RT];
     Unpack<GW> un[RT];
@@ -302,10 +300,6 @@ __global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) 
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             const bool last = q + 1 == NQ;
-            if (q == 0) {
-                store_acts(buf ^ 1, a0);
-                load_acts(macro + 2 * WK, a0);
-            }
             if (last) {
                 wg_barrier_lds();
                 load_weights(macro + 2 * WK, w);
@@ -316,6 +310,12 @@ __global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) 
             for (int g = 0; g < G; ++g) {
                 __builtin_amdgcn_sched_barrier(0);
                 acc[g % RT][g / RT] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[g / RT], b[g % RT], acc[g % RT][g / RT], 0, 0, 0);
+                // (the writes spread over two groups: in one burst they hold up the reads behind them)
+#pragma unroll
+                for (int u = (q * G + g) * kPer / (2 * G); q < 2 && u < (q * G + g + 1) * kPer / (2 * G); ++u) {
+                    store_act(buf ^ 1, u, a0[u]);
+                    a0[u] = load_act(macro + 2 * WK, u);
+                }
 #pragma unroll
                 for (int r = g * NR / G; r < (g + 1) * NR / G; ++r) {
                     const i32x2 v = read_half(last ? buf ^ 1 : buf, last ? 0 : q + 1, r >> 1, r & 1);
@@ -415,23 +415,28 @@ __global__ void __launch_bounds__(64 * WM * WK) gemm_kernel(const GemmParams p) 
     }
 }
 
-// The tile shapes that are built and what a launch costs with them, in us, fitted to launches of 1 to 8 workgroups per
-// compute unit n at K = 1280 and 5120: base + n * fixed + passes of the K loop * (lat + n * pass).  First value four, second
-// five weights per byte.  `fixed` is the store of the tile (4.5 to 5 TB/s over all compute units, not overlapped: the
-// workgroups of a round end together), `pass` one macro step of every K group.
+// The tile shapes that are built and what a launch costs with them, in us, fitted (rms 2 to 4 %) to 4100 and 1700 shapes of 200 to 14336
+// rows, K = 256 to 14336 and 16 to 1024 tokens: base + n / per_unit * fixed + M * N / 10^6 * store + passes of the K loop *
+// (lat + n * pass), n workgroups per compute unit.  First value four, second five weights per byte; `pass` is one macro step of every K group.  The tile of
+// the least cost is within 0.4 % of the fastest on average (2 % of the shapes beyond 5 %, worst 19 %).
+// With one K group two workgroups of four waves share a compute unit, and one stores while the other multiplies: 13824 x 2560 x 1024
+// 45.7 -> 42.0 us; 128 rows x 64 tokens: 4096 x 14336 x 512 40.1 -> 36.0 us.
 struct GemmTile {
     int rt, ct, wm, wk;
-    double base[2], fixed[2], lat[2], pass[2];
+    int per_unit[2];               // workgroups that share a compute unit (what a workgroup costs besides its K loop overlaps)
+    double base[2], fixed[2], store[2], lat[2], pass[2];
     constexpr int rows() const { return 32 * rt * wm; }
     constexpr int tokens() const { return 32 * ct; }
 };
 constexpr GemmTile kGemmTiles[] = {
-    {2, 4, 4, 2, {4.2, 4.2}, {6.5, 7.0}, {0.00, 0.10}, {1.43, 1.90}},
-    {1, 4, 4, 2, {3.0, 3.0}, {3.8, 4.0}, {0.00, 0.03}, {0.90, 1.14}},
-    {1, 4, 2, 4, {1.9, 0.0}, {4.1, 0.0}, {0.00, 0.00}, {1.13, 0.00}},      // long K; (five weights: more LDS than there is)
-    {1, 2, 2, 4, {2.9, 2.2}, {1.3, 2.4}, {0.08, 0.00}, {0.64, 0.95}},
-    {1, 1, 2, 4, {2.8, 2.8}, {0.75, 1.1}, {0.13, 0.08}, {0.45, 0.60}},
-    {1, 1, 1, 8, {2.6, 1.5}, {1.0, 2.2}, {0.11, 0.00}, {0.54, 0.88}},
+    {2, 4, 4, 2, {1, 1}, {3.70, 4.94}, {4.43, 3.47}, {0.681, 0.760}, {0.000, 0.000}, {1.123, 1.406}},
+    {2, 4, 4, 1, {1, 1}, {9.15, 0.00}, {0.00, 0.00}, {0.710, 0.000}, {0.200, 0.000}, {0.489, 0.000}},      // (five weights: spills)
+    {1, 4, 4, 2, {1, 1}, {2.95, 3.14}, {2.54, 2.54}, {0.753, 0.834}, {0.000, 0.000}, {0.693, 0.890}},
+    {1, 4, 2, 4, {1, 1}, {2.19, 0.00}, {3.28, 0.00}, {0.785, 0.000}, {0.000, 0.000}, {0.881, 0.000}},      // long K; (five weights: more LDS than there is)
+    {2, 2, 2, 4, {1, 1}, {2.21, 0.00}, {2.85, 0.00}, {0.721, 0.000}, {0.000, 0.000}, {0.829, 0.000}},
+    {1, 2, 2, 4, {2, 1}, {3.01, 2.04}, {1.06, 2.13}, {1.036, 0.921}, {0.000, 0.000}, {0.546, 0.731}},
+    {1, 1, 2, 4, {2, 2}, {3.24, 2.78}, {0.26, 0.89}, {1.300, 1.345}, {0.045, 0.070}, {0.350, 0.486}},
+    {1, 1, 1, 8, {2, 1}, {2.93, 2.05}, {0.93, 1.81}, {2.161, 1.575}, {0.032, 0.000}, {0.452, 0.658}},
 };
 constexpr int kGemmTileCount = (int)(sizeof(kGemmTiles) / sizeof(kGemmTiles[0]));
 constexpr bool gemm_tile_built(int gw, int tile) { return gw == 4 || kGemmTiles[tile].pass[1] > 0.0; }

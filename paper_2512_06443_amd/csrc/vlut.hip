@@ -377,10 +377,9 @@ NarrowPlan narrow_plan(int64_t M, int64_t K, int64_t N) {
 //   this kernel   4.6 from fp32 activations (3.6 from INT8 ones) + c x {0.9, 1.35, 2.0, 3.4} for 32, 64, 128, 256 rows
 //                 per workgroup;
 //   lookup kernel 5.8 + 0.94 c + 0.41 x M N / 10^4 with its split-K sum, + 3.5 for the quantiser from fp32.
-// The estimate is older than gemm_kernel, which serves most calls that this rule declines.  Against that one the line is right for
-// short rows only; from INT8 codes, this kernel / the matrix cores: 640 x 1024 x 8 4.0 / 4.6 us, 640 x 2560 x 4 5.5 / 5.8, 6912 x 2560 x 1
-// 5.1 / 6.0, but 2560 x 2560 x 16 8.1 / 5.9, 100 x 8192 x 16 11.0 / 8.9, 4096 x 14336 x 4 17.9 / 13.3, 2560 x 30000 x 2 33.0 / 17.7.  Workspace sizes
-// and reported plans follow the rule, so callers know where it lies.
+// The estimate is older than the matrix-core kernels.  From INT8 codes decode_codes_kernel takes every call that this rule accepts and
+// whose K it holds (codes_plan_if_taken); beyond that the table kernel keeps what it had (2560 x 30000 x 2 33.0 us, gemm_kernel 17.7):
+// workspace sizes and reported plans follow the rule, so callers know where it lies.
 bool narrow_applies(int64_t M, int64_t K, int64_t N, const void* lut, bool from_f32) {
     if (N > kNarrowMaxN || lut != nullptr || lookup_plan_forced()) return false;
     if (N <= 2) return true;
@@ -664,7 +663,7 @@ double gemm_cost(int gw, int tile, int64_t M, int64_t macros, int64_t N) {
     const int g = gw - 4;
     const int64_t tiles = ((M + t.rows() - 1) / t.rows()) * ((N + t.tokens() - 1) / t.tokens());
     const double n = (double)((tiles + 255) / 256), passes = (double)((macros + t.wk - 1) / t.wk);
-    return t.base[g] + n * t.fixed[g] + passes * (t.lat[g] + n * t.pass[g]);
+    return t.base[g] + (double)((tiles + 256 * t.per_unit[g] - 1) / (256 * t.per_unit[g])) * t.fixed[g] + 1e-6 * (double)M * (double)N * t.store[g] + passes * (t.lat[g] + n * t.pass[g]);
 }
 
 int choose_gemm_tile(int gw, int64_t M, int64_t macros, int64_t N) {
@@ -683,6 +682,40 @@ double gemm_best_cost(int gw, int64_t M, int64_t K, int64_t N) {
     return gemm_cost(gw, choose_gemm_tile(gw, M, macros, N), M, macros, N);
 }
 
+// decode_codes_kernel for a few tokens: eight or sixteen per workgroup (ch chunks) and 16 * mt rows; ch = 0: not this kernel.  Its time in
+// us, launches back to back, fitted (rms 3.7 %) to 18000 launches over 4100 shapes of 200 to 14336 rows, K = 256 to 14336 and 16 to 1024
+// tokens: a launch and two trips to memory, then K times what a workgroup copies and unpacks, weights beyond 27 MB from further
+// away, the store; beyond one workgroup per compute unit further rounds, shorter where two of them fit one unit's LDS.
+struct CodesPlan {
+    int ch, mt;
+    double us;
+};
+CodesPlan codes_plan(int64_t M, int64_t K, int64_t N) {
+    CodesPlan best = {0, 0, 1e300};
+    if (lookup_plan_forced()) return best;
+    for (int ch = 1; ch <= 2; ++ch) {
+        if (!decode_codes_fits(ch, K) || (ch == 2 && N <= 8)) continue;
+        const bool two_per_unit = decode_codes_lds_bytes(ch, (int)((K + 255) / 256)) <= 80 * 1024;
+        for (int mt = 1; mt <= 8; mt *= 2) {
+            const int64_t wgs = ((M + 16 * mt - 1) / (16 * mt)) * ((N + 8 * ch - 1) / (8 * ch)), rounds = (wgs + 255) / 256;
+            double us = 3.45 + (double)K * (ch == 1 ? 0.51e-4 + 1.31e-4 * mt : 1.29e-4 + 1.34e-4 * mt) + 0.00073 * (double)std::min<int64_t>(wgs, 256);
+            us += 0.024 * std::max(0.0, (double)M * (double)K / 4e6 - 27.5) + 0.52e-6 * (double)M * (double)N;
+            if (rounds > 1) us = 3.06 + (double)rounds * (us - 3.06) * (two_per_unit ? 0.9 : 1.18);
+            if (us < best.us) best = {ch, mt, us};
+        }
+    }
+    return best;
+}
+// Where the few-token table kernel would run: always (beyond 32768 rows workgroups of 128 rows repeat the copy: left to that kernel).  us, table
+// kernel / this one: 256 x 256 x 1 3.43 / 3.36, 640 x 2560 x 4 5.5 / 3.7, 2560 x 6912 x 2 9.8 / 4.4, 14336 x 14336 x 1 16.3 / 14.0.
+// Else against the tiles of gemm_kernel (us, gemm_kernel / this one: 2560 x 2560 x 16 5.5 / 4.05, 2560 x 6912 x 16 7.5 / 5.3,
+// 6912 x 2560 x 32 5.6 / 5.1, but 6912 x 2560 x 64 5.9 / 6.7, 13824 x 2560 x 32 5.9 / 6.7).
+CodesPlan codes_plan_if_taken(int64_t M, int64_t K, int64_t N, bool narrow) {
+    CodesPlan pl = codes_plan(M, K, N);
+    if (narrow ? M > 256 * 128 : pl.us >= gemm_best_cost(4, M, K, N)) pl.ch = 0;
+    return pl;
+}
+
 // Time of a lookup plan (with its split-K sum) in us, in the units of gemm_cost: least squares over 869 shapes of 4 to 4096 rows,
 // K = 1024 to 65532 and 3 to 400 tokens, launches back to back (standard deviation 2.6 %, worst 12 % at 4 rows).  plan_cost above ranks plans
 // and overstates the time, by 6 % where a workgroup has several tiles and by 20 to 57 % where it has one.
@@ -697,12 +730,14 @@ double lookup_us(const Plan& pl, int64_t M, int64_t K, int64_t N) {
     return std::max(t, (double)d.tiles_n * (double)d.RGtotal * d.KCn * 64.0 / (256.0 * 24.0 * 2100.0));   // weights from L2
 }
 
-// Few rows and tokens with a long K leave the matrix-core path a handful of workgroups, while the lookup kernel can
-// split K over many (with the partial sums in the workspace): the cheaper of the two fitted times.  Measured, us, lookup / matrix
-// cores: 64 x 16384 x 128 10.9 / 14.1, 100 x 24000 x 72 13.9 / 19.4, 640 x 30000 x 33 18.9 / 23.7, 2560 x 30000 x 16 20.2 / 23.9, but
-// 256 x 14336 x 72 13.4 / 12.8, 640 x 16384 x 128 20.0 / 14.8, 2048 x 14336 x 16 15.4 / 12.9.
+// Few rows and tokens with a K that decode_codes_kernel does not hold leave the matrix-core path a handful of workgroups, while the lookup
+// kernel can split K over many (with the partial sums in the workspace).  us, lookup / gemm_kernel: 16 x 65532 x 33 23.6 / 34.1, 16 x 32768
+// x 33 14.7 / 18.7, 100 x 24000 x 72 13.8 / 15.4, 640 x 30000 x 33 18.6 / 18.3, 2560 x 20480 x 16 15.8 / 13.5.  The lookup kernel keeps a call
+// up to 1.25 times gemm_kernel's fitted time: that is where the line has been since the matrix cores took the others, and queries
+// name the kernel.
 bool matrix_cores_take(const Plan& pl, int64_t M, int64_t K, int64_t N) {
-    return !lookup_plan_forced() && lookup_us(pl, M, K, N) >= gemm_best_cost(4, M, K, N);
+    if (lookup_plan_forced()) return false;
+    return decode_codes_fits(1, K) || lookup_us(pl, M, K, N) >= 1.25 * gemm_best_cost(4, M, K, N);
 }
 bool matrix_cores_take_g5(int64_t K) { return t_forced5.R == 0 && t_forced5.S == 0 && K % 4 == 0; }
 bool matrix_cores_take_mixed() { return t_forced5.R == 0 && t_forced5.S == 0 && !lookup_plan_forced(); }
@@ -777,6 +812,45 @@ int launch_decode(const DecodeParams& p, hipStream_t stream) {
     case 4: return launch_decode_t<T, 4>(p, stream);
     default: return launch_decode_t<T, 8>(p, stream);
     }
+}
+
+// ---- a few tokens from INT8 codes (decode_codes_kernel)
+template <int CH, int MT>
+int launch_codes_t(const DecodeParams& p, hipStream_t stream) {
+    auto kfn = decode_codes_kernel<CH, MT>;
+    if (!decode_codes_fits(CH, p.K)) return VLUT_ERR_UNSUPPORTED;      // (cannot happen: codes_plan)
+    static std::atomic<unsigned> attr_done{0};   // one bit per device: the attribute belongs to the device's copy
+    if (!allow_dynamic_lds((const void*)kfn, 160 * 1024, attr_done)) return VLUT_ERR_DEVICE;
+    DecodeParams q = p;
+    q.chunks = (q.N + 7) / 8;
+    q.tiles_n = (q.chunks + CH - 1) / CH;
+    q.magic_n = q.tiles_n > 1 ? (unsigned)(((uint64_t)1 << 32) / (unsigned)q.tiles_n) + 1u : 0u;      // exact while tiles * tiles_n < 2^32
+    const int64_t tiles = (int64_t)((q.M + 16 * MT - 1) / (16 * MT)) * q.tiles_n;
+    if (tiles * q.tiles_n >= ((int64_t)1 << 32) || tiles > INT32_MAX / 2) return VLUT_ERR_UNSUPPORTED;     // (cannot happen: codes_plan)
+    q.tiles = (int)tiles;
+    q.per_xcd = (q.tiles + 7) / 8;
+    hipLaunchKernelGGL(kfn, dim3((unsigned)(8 * q.per_xcd)), dim3(64 * kDecodeWaves), decode_codes_lds_bytes(CH, q.macros), stream, q);
+    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+}
+
+template <int CH>
+int launch_codes_mt(int mt, const DecodeParams& p, hipStream_t stream) {
+    switch (mt) {
+    case 1: return launch_codes_t<CH, 1>(p, stream);
+    case 2: return launch_codes_t<CH, 2>(p, stream);
+    case 4: return launch_codes_t<CH, 4>(p, stream);
+    default: return launch_codes_t<CH, 8>(p, stream);
+    }
+}
+
+int launch_codes(const CodesPlan& pl, const uint8_t* packed, float w_scale, const float* w_rows, const int8_t* a_q, const float* a_scale, int64_t M,
+                 int64_t K, int64_t N, float* y, int64_t ldy, int32_t* acc, hipStream_t stream) {
+    DecodeParams q;
+    std::memset(&q, 0, sizeof(q));
+    q.packed = packed; q.a_q = a_q; q.a_scale = a_scale; q.w_rows = w_rows; q.y = y; q.acc = acc; q.w_scale = w_scale;
+    q.M = (int)M; q.N = (int)N; q.K = (int)K; q.KCn = (int)((K / 4 + 15) / 16); q.RGtotal = (int)((M + 3) / 4); q.ldy = (int)ldy;
+    q.macros = (q.KCn + 3) / 4;
+    return pl.ch == 1 ? launch_codes_mt<1>(pl.mt, q, stream) : launch_codes_mt<2>(pl.mt, q, stream);
 }
 
 // ---- comparison path: tokens per workgroup from N, K split so that few tiles still give every CU a few workgroups
@@ -966,6 +1040,8 @@ static int mpgemm_impl(const uint8_t* packed, float w_scale, const float* w_rows
     if (((uintptr_t)a_q) % 16 != 0) return VLUT_ERR_UNSUPPORTED;      // the [N/8][K][8] blocks are read 16 bytes at a time
     if (((uintptr_t)packed) % 16 != 0) return VLUT_ERR_UNSUPPORTED;   // packed tiles are read up to 16 bytes at a time
     if (narrow_applies(M, K, N, lut_or_null, false)) {   // a few tokens: the workgroups sweep all of K, no workspace
+        const CodesPlan cp = codes_plan_if_taken(M, K, N, true);
+        if (cp.ch) return launch_codes(cp, packed, w_scale, w_rows, a_q, a_scale, M, K, N, y, ldy, acc_or_null, (hipStream_t)stream);
         const NarrowPlan np = narrow_plan(M, K, N);
         NarrowParams q;
         std::memset(&q, 0, sizeof(q));
@@ -991,8 +1067,11 @@ static int mpgemm_impl(const uint8_t* packed, float w_scale, const float* w_rows
         if (!workspace) return VLUT_ERR_NULL;
         if (workspace_bytes < ws_need) return VLUT_ERR_SMALL_BUFFER;
     }
-    if (!lut_or_null && matrix_cores_take(pl, M, K, N))
+    if (!lut_or_null && matrix_cores_take(pl, M, K, N)) {
+        const CodesPlan cp = codes_plan_if_taken(M, K, N, false);
+        if (cp.ch) return launch_codes(cp, packed, w_scale, w_rows, a_q, a_scale, M, K, N, y, ldy, acc_or_null, (hipStream_t)stream);
         return launch_gemm(packed, w_scale, w_rows, a_q, a_scale, M, K, 0, N, y, ldy, acc_or_null, (hipStream_t)stream);
+    }
     LookupParams p;
     std::memset(&p, 0, sizeof(p));
     p.packed = packed; p.a_q = a_q; p.a_scale = a_scale; p.lut = lut_or_null;
