@@ -31,7 +31,9 @@ struct DecodeParams {
     int M, N, K, KCn, RGtotal, ldy, macros, x_vec;
     const int8_t* a_q;            // decode_codes_kernel: INT8 codes and their scales instead of x
     const float* a_scale;
-    int chunks, tiles_n, tiles, per_xcd;
+    const uint8_t* packed4;       // mixed packing: the 2-bit blob of the last K - Kmain < 20 values of K, else null
+    int Kmain, KCn4;              // values of K in `packed`
+    int chunks, tiles_n, tiles, per_xcd, pitch;
     unsigned magic_n;             // 2^32 / tiles_n rounded up (tiles_n > 1)
 };
 
@@ -219,28 +221,30 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeP
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same product from INT8 codes, 8 * CH tokens per workgroup: it copies their codes over all of K to LDS as they lie in
-// memory, one 16-byte unit (two k of eight tokens) per lane, and reads its operands with the transposing reads of gemm_kernel.
-// Tile columns (64 k) are pitched 640 bytes and chunks 16 bytes beyond a multiple of 256, so that the 32 rows of half a
-// read lie in distinct banks.  What lies behind the last k in LDS meets zero weights, what lies in an absent chunk makes
-// sums that are not stored.
+// The same product from INT8 codes, 8 * CH tokens per workgroup, four or five weights per byte: it copies their codes over all of K to LDS
+// as they lie in memory, one 16-byte unit (two k of eight tokens) per lane, and reads its operands with the transposing reads of
+// gemm_kernel.  Tile columns (64 or 80 k) are pitched 128 bytes beyond their size and chunks 16 bytes beyond a multiple of 256, so that
+// the 32 rows of half a read lie in distinct banks (five weights: nearly).  What lies behind the last k in LDS meets zero
+// weights, what lies in an absent chunk makes sums that are not stored.
 // All of the codes at once, one barrier, all of the weights: a launch is little more than two trips to memory, where gemm_kernel waits
 // for one with every macro step.
 // ---------------------------------------------------------------------------------------------
-constexpr int kCodesColumn = 640;
-constexpr int decode_codes_pitch(int macros) { return macros * 4 * kCodesColumn + 16; }
-constexpr int decode_codes_lds_bytes(int ch, int macros) { return ch * decode_codes_pitch(macros) + kDecodeWaves * 1024; }
-// K that the LDS of a workgroup holds: 14592 values for one chunk, 7168 for two
-constexpr bool decode_codes_fits(int ch, int64_t K) { return K <= 14592 && decode_codes_lds_bytes(ch, (int)((K + 255) / 256)) <= 160 * 1024; }
+constexpr int codes_column(int gw) { return 16 * gw * 8 + 128; }
+constexpr int decode_codes_pitch(int gw, int64_t K) { return (int)((K + 64 * gw - 1) / (64 * gw)) * 4 * codes_column(gw) + 16; }
+constexpr int decode_codes_lds_bytes(int gw, int ch, int64_t K) { return ch * decode_codes_pitch(gw, K) + kDecodeWaves * 1024; }
+// K that the LDS of a workgroup holds: 14592 values for one chunk, 7168 for two (five weights per byte: 14592 and 7360)
+constexpr bool decode_codes_fits(int gw, int ch, int64_t K) { return K <= 14592 && decode_codes_lds_bytes(gw, ch, K) <= 160 * 1024; }
 
-template <int CH, int MT>
+template <int GW, int CH, int MT>
 __global__ void __launch_bounds__(64 * kDecodeWaves) decode_codes_kernel(const DecodeParams p) {
     constexpr int KP = kDecodeWaves / MT;      // parts of K
     constexpr int PF = 4;                      // macro steps of weights in flight
     constexpr int NU = 4;                      // units per thread and pass
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned pitch = (unsigned)decode_codes_pitch(p.macros);
+    constexpr int kColumn = codes_column(GW);
+    constexpr unsigned kZero = GW == 4 ? kZeroIdx4 : 0x79797979u;      // four bytes of the all-zero pattern
+    const unsigned pitch = (unsigned)p.pitch;
     const unsigned sums = CH * pitch;
     // tiles as in gemm_kernel: the token tiles of a row tile next to each other, a contiguous range of the list for each XCD
     const int tile = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
@@ -266,7 +270,7 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_codes_kernel(const D
             if (u < total) {
                 const bool second = CH == 2 && u >= units;
                 const unsigned at = (unsigned)(second ? u - units : u);
-                *(lds_i32x4*)((second ? pitch : 0u) + at * 16u + (at >> 5) * (unsigned)(kCodesColumn - 512)) = v[j];
+                *(lds_i32x4*)((second ? pitch : 0u) + at * 16u + (GW == 4 ? at >> 5 : at * 52429u >> 21) * 128u) = v[j];     // at / 32 or / 40, the column
             }
         }
     };
@@ -275,6 +279,11 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_codes_kernel(const D
     const int i = lane & 15, kb = lane >> 4;
     const DecodeWeights weights(p, m0 + rt * 16 + i, kb);
     const DecodeOut<8 * CH, MT> out(p, tid, m0, nt * 8 * CH);
+    unsigned w4 = kZeroIdx4;
+    if (GW == 5 && p.packed4) {
+        const int m = m0 + rt * 16 + i;
+        w4 = *(const unsigned*)(p.packed4 + (size_t)min(m >> 2, p.RGtotal - 1) * p.KCn4 * 64 + (m & 3) * 16);
+    }
     i32x4 w[PF];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -290,8 +299,10 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_codes_kernel(const D
     // ---- multiply: macro steps part, part + KP, ... of row tile rt.  Of a group of 16 lanes two point at each of eight rows (k in the
     //      order of the planes), one per chunk, and lane i receives the eight values of token i
     const int r8 = i >> 1;
-    const unsigned rd = (unsigned)(kb * kCodesColumn + (r8 & 3) * 32 + (r8 >> 2) * 8) + (CH == 2 && (lane & 1) ? pitch : 0u);
-    const UnpackConst uc(4);
+    const unsigned second = CH == 2 && (lane & 1) ? pitch : 0u;
+    const unsigned rd = (unsigned)(kb * kColumn + (r8 & 3) * GW * 8 + (r8 >> 2) * 8) + second;
+    const unsigned rd_b = (unsigned)(kb * kColumn + (r8 & 3) * GW * 8 + (r8 >> 2) * 4 * GW * 8 + 32) + second;     // (five weights) plane 4 of two dwords
+    const UnpackConst uc(GW);
     i32x4 acc = {0, 0, 0, 0};
     for (int s0 = part; s0 < p.macros; s0 += KP * PF) {
 #pragma unroll
@@ -299,17 +310,36 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_codes_kernel(const D
             const int macro = s0 + KP * j;
             if (macro < p.macros) {
                 const unsigned keep = 4 * macro + kb < p.KCn ? 0xffffffffu : 0u;
-                const unsigned at = rd + (unsigned)macro * (4u * kCodesColumn);
-                i32x4 a[4];
+                const unsigned at = (unsigned)macro * (4u * kColumn);
+                i32x4 a[GW];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const i32x2 lo = lds_read_tr8(at + q * 128), hi = lds_read_tr8(at + q * 128 + 16);
+                for (int q = 0; q < GW; ++q) {
+                    const unsigned from = q < 4 ? rd + at + q * 4 * GW * 8 : rd_b + at;
+                    const i32x2 lo = lds_read_tr8(from), hi = lds_read_tr8(from + (q < 4 ? 16 : 2 * 4 * GW * 8));
                     a[q] = i32x4{lo.x, lo.y, hi.x, hi.y};
                 }
+                unsigned left[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[q], unpack_planes4((unsigned)w[j][q], keep, uc), acc, 0, 0, 0);
+                for (int q = 0; q < 4; ++q) {
+                    Unpack<GW> un;
+                    i32x4 b;
+                    un.w = ((unsigned)w[j][q] & keep) | (kZero & ~keep);
+#pragma unroll
+                    for (int st = 0; st < Unpack<GW>::kOps; ++st) un.op(st, uc, b, left[q]);
+                    acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[q], b, acc, 0, 0, 0);
+                }
+                if constexpr (GW == 5)
+                    acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[4], i32x4{(int)left[0], (int)left[1], (int)left[2], (int)left[3]}, acc, 0, 0, 0);
                 w[j] = weights.load(macro + KP * PF);
             }
+        }
+    }
+    if constexpr (GW == 5) {
+        if (p.packed4 && part == 0) {                      // (mixed packing) its dword of a row holds up to 16 values, planes of four weights per byte
+            const unsigned u0 = (unsigned)p.Kmain >> 1;    // their first unit; they lie in one tile column (Kmain is a multiple of 20)
+            const unsigned at = second + u0 * 16u + (u0 * 52429u >> 21) * 128u + (unsigned)((r8 & 3) * 32 + (r8 >> 2) * 8);
+            const i32x2 lo = lds_read_tr8(at), hi = lds_read_tr8(at + 16);
+            acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(i32x4{lo.x, lo.y, hi.x, hi.y}, unpack_planes4(w4, kb == 0 ? 0xffffffffu : 0u, UnpackConst(4)), acc, 0, 0, 0);
         }
     }
     *(lds_i32x4*)(sums + (unsigned)(wave * 1024 + lane * 16)) = acc;     // output row i, tokens 4 kb .. 4 kb + 3

@@ -685,21 +685,24 @@ double gemm_best_cost(int gw, int64_t M, int64_t K, int64_t N) {
 // decode_codes_kernel for a few tokens: eight or sixteen per workgroup (ch chunks) and 16 * mt rows; ch = 0: not this kernel.  Its time in
 // us, launches back to back, fitted (rms 3.7 %) to 18000 launches over 4100 shapes of 200 to 14336 rows, K = 256 to 14336 and 16 to 1024
 // tokens: a launch and two trips to memory, then K times what a workgroup copies and unpacks, weights beyond 27 MB from further
-// away, the store; beyond one workgroup per compute unit further rounds, shorter where two of them fit one unit's LDS.
+// away, the store; beyond one workgroup per compute unit further rounds, shorter where two of them fit one unit's LDS.  Five weights per
+// byte cost the same (30 shapes: the choice it makes is within 3 % of the fastest; us, gemm_kernel / this one: 4096 x 4096 x 32 mixed 6.6 / 5.8,
+// 4096 x 4000 x 16 6.5 / 4.8, 2560 x 6900 x 8 7.7 / 4.8, but 13820 x 2560 x 64 7.7 / 11.9).
 struct CodesPlan {
     int ch, mt;
     double us;
 };
-CodesPlan codes_plan(int64_t M, int64_t K, int64_t N) {
+CodesPlan codes_plan(int gw, int64_t M, int64_t K, int64_t N) {
     CodesPlan best = {0, 0, 1e300};
-    if (lookup_plan_forced()) return best;
+    if (gw == 4 && lookup_plan_forced()) return best;
+    const double mb = (double)M * (double)K / (gw * 1e6);
     for (int ch = 1; ch <= 2; ++ch) {
-        if (!decode_codes_fits(ch, K) || (ch == 2 && N <= 8)) continue;
-        const bool two_per_unit = decode_codes_lds_bytes(ch, (int)((K + 255) / 256)) <= 80 * 1024;
+        if (!decode_codes_fits(gw, ch, K) || (ch == 2 && N <= 8)) continue;
+        const bool two_per_unit = decode_codes_lds_bytes(gw, ch, K) <= 80 * 1024;
         for (int mt = 1; mt <= 8; mt *= 2) {
             const int64_t wgs = ((M + 16 * mt - 1) / (16 * mt)) * ((N + 8 * ch - 1) / (8 * ch)), rounds = (wgs + 255) / 256;
             double us = 3.45 + (double)K * (ch == 1 ? 0.51e-4 + 1.31e-4 * mt : 1.29e-4 + 1.34e-4 * mt) + 0.00073 * (double)std::min<int64_t>(wgs, 256);
-            us += 0.024 * std::max(0.0, (double)M * (double)K / 4e6 - 27.5) + 0.52e-6 * (double)M * (double)N;
+            us += 0.024 * std::max(0.0, mb - 27.5) + 0.52e-6 * (double)M * (double)N;
             if (rounds > 1) us = 3.06 + (double)rounds * (us - 3.06) * (two_per_unit ? 0.9 : 1.18);
             if (us < best.us) best = {ch, mt, us};
         }
@@ -710,9 +713,9 @@ CodesPlan codes_plan(int64_t M, int64_t K, int64_t N) {
 // kernel / this one: 256 x 256 x 1 3.43 / 3.36, 640 x 2560 x 4 5.5 / 3.7, 2560 x 6912 x 2 9.8 / 4.4, 14336 x 14336 x 1 16.3 / 14.0.
 // Else against the tiles of gemm_kernel (us, gemm_kernel / this one: 2560 x 2560 x 16 5.5 / 4.05, 2560 x 6912 x 16 7.5 / 5.3,
 // 6912 x 2560 x 32 5.6 / 5.1, but 6912 x 2560 x 64 5.9 / 6.7, 13824 x 2560 x 32 5.9 / 6.7).
-CodesPlan codes_plan_if_taken(int64_t M, int64_t K, int64_t N, bool narrow) {
-    CodesPlan pl = codes_plan(M, K, N);
-    if (narrow ? M > 256 * 128 : pl.us >= gemm_best_cost(4, M, K, N)) pl.ch = 0;
+CodesPlan codes_plan_if_taken(int gw, int64_t M, int64_t K, int64_t N, bool narrow) {
+    CodesPlan pl = codes_plan(gw, M, K, N);
+    if (narrow ? M > 256 * 128 : pl.us >= gemm_best_cost(gw, M, K, N)) pl.ch = 0;
     return pl;
 }
 
@@ -737,7 +740,7 @@ double lookup_us(const Plan& pl, int64_t M, int64_t K, int64_t N) {
 // name the kernel.
 bool matrix_cores_take(const Plan& pl, int64_t M, int64_t K, int64_t N) {
     if (lookup_plan_forced()) return false;
-    return decode_codes_fits(1, K) || lookup_us(pl, M, K, N) >= 1.25 * gemm_best_cost(4, M, K, N);
+    return decode_codes_fits(4, 1, K) || lookup_us(pl, M, K, N) >= 1.25 * gemm_best_cost(4, M, K, N);
 }
 bool matrix_cores_take_g5(int64_t K) { return t_forced5.R == 0 && t_forced5.S == 0 && K % 4 == 0; }
 bool matrix_cores_take_mixed() { return t_forced5.R == 0 && t_forced5.S == 0 && !lookup_plan_forced(); }
@@ -815,42 +818,52 @@ int launch_decode(const DecodeParams& p, hipStream_t stream) {
 }
 
 // ---- a few tokens from INT8 codes (decode_codes_kernel)
-template <int CH, int MT>
+template <int GW, int CH, int MT>
 int launch_codes_t(const DecodeParams& p, hipStream_t stream) {
-    auto kfn = decode_codes_kernel<CH, MT>;
-    if (!decode_codes_fits(CH, p.K)) return VLUT_ERR_UNSUPPORTED;      // (cannot happen: codes_plan)
+    auto kfn = decode_codes_kernel<GW, CH, MT>;
+    if (!decode_codes_fits(GW, CH, p.K)) return VLUT_ERR_UNSUPPORTED;      // (cannot happen: codes_plan)
     static std::atomic<unsigned> attr_done{0};   // one bit per device: the attribute belongs to the device's copy
     if (!allow_dynamic_lds((const void*)kfn, 160 * 1024, attr_done)) return VLUT_ERR_DEVICE;
     DecodeParams q = p;
     q.chunks = (q.N + 7) / 8;
+    q.pitch = decode_codes_pitch(GW, q.K);
     q.tiles_n = (q.chunks + CH - 1) / CH;
     q.magic_n = q.tiles_n > 1 ? (unsigned)(((uint64_t)1 << 32) / (unsigned)q.tiles_n) + 1u : 0u;      // exact while tiles * tiles_n < 2^32
     const int64_t tiles = (int64_t)((q.M + 16 * MT - 1) / (16 * MT)) * q.tiles_n;
     if (tiles * q.tiles_n >= ((int64_t)1 << 32) || tiles > INT32_MAX / 2) return VLUT_ERR_UNSUPPORTED;     // (cannot happen: codes_plan)
     q.tiles = (int)tiles;
     q.per_xcd = (q.tiles + 7) / 8;
-    hipLaunchKernelGGL(kfn, dim3((unsigned)(8 * q.per_xcd)), dim3(64 * kDecodeWaves), decode_codes_lds_bytes(CH, q.macros), stream, q);
+    hipLaunchKernelGGL(kfn, dim3((unsigned)(8 * q.per_xcd)), dim3(64 * kDecodeWaves), decode_codes_lds_bytes(GW, CH, q.K), stream, q);
     return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
 }
 
-template <int CH>
+template <int GW, int CH>
 int launch_codes_mt(int mt, const DecodeParams& p, hipStream_t stream) {
     switch (mt) {
-    case 1: return launch_codes_t<CH, 1>(p, stream);
-    case 2: return launch_codes_t<CH, 2>(p, stream);
-    case 4: return launch_codes_t<CH, 4>(p, stream);
-    default: return launch_codes_t<CH, 8>(p, stream);
+    case 1: return launch_codes_t<GW, CH, 1>(p, stream);
+    case 2: return launch_codes_t<GW, CH, 2>(p, stream);
+    case 4: return launch_codes_t<GW, CH, 4>(p, stream);
+    default: return launch_codes_t<GW, CH, 8>(p, stream);
     }
 }
 
+// K5 values of K five to a byte (0: none), the rest of K four to a byte behind them (at most 16 values if K5 > 0).
 int launch_codes(const CodesPlan& pl, const uint8_t* packed, float w_scale, const float* w_rows, const int8_t* a_q, const float* a_scale, int64_t M,
-                 int64_t K, int64_t N, float* y, int64_t ldy, int32_t* acc, hipStream_t stream) {
+                 int64_t K, int64_t K5, int64_t N, float* y, int64_t ldy, int32_t* acc, hipStream_t stream) {
     DecodeParams q;
     std::memset(&q, 0, sizeof(q));
+    const int gw = K5 > 0 ? 5 : 4;
     q.packed = packed; q.a_q = a_q; q.a_scale = a_scale; q.w_rows = w_rows; q.y = y; q.acc = acc; q.w_scale = w_scale;
-    q.M = (int)M; q.N = (int)N; q.K = (int)K; q.KCn = (int)((K / 4 + 15) / 16); q.RGtotal = (int)((M + 3) / 4); q.ldy = (int)ldy;
+    q.M = (int)M; q.N = (int)N; q.K = (int)K; q.RGtotal = (int)((M + 3) / 4); q.ldy = (int)ldy;
+    q.Kmain = (int)(K5 > 0 ? K5 : K);
+    q.KCn = (q.Kmain / gw + 15) / 16;
     q.macros = (q.KCn + 3) / 4;
-    return pl.ch == 1 ? launch_codes_mt<1>(pl.mt, q, stream) : launch_codes_mt<2>(pl.mt, q, stream);
+    if (gw == 4) return pl.ch == 1 ? launch_codes_mt<4, 1>(pl.mt, q, stream) : launch_codes_mt<4, 2>(pl.mt, q, stream);
+    if (K > K5) {
+        q.packed4 = packed + (size_t)q.RGtotal * q.KCn * 64;
+        q.KCn4 = (int)(((K - K5) / 4 + 15) / 16);
+    }
+    return pl.ch == 1 ? launch_codes_mt<5, 1>(pl.mt, q, stream) : launch_codes_mt<5, 2>(pl.mt, q, stream);
 }
 
 // ---- comparison path: tokens per workgroup from N, K split so that few tiles still give every CU a few workgroups
@@ -1040,8 +1053,8 @@ static int mpgemm_impl(const uint8_t* packed, float w_scale, const float* w_rows
     if (((uintptr_t)a_q) % 16 != 0) return VLUT_ERR_UNSUPPORTED;      // the [N/8][K][8] blocks are read 16 bytes at a time
     if (((uintptr_t)packed) % 16 != 0) return VLUT_ERR_UNSUPPORTED;   // packed tiles are read up to 16 bytes at a time
     if (narrow_applies(M, K, N, lut_or_null, false)) {   // a few tokens: the workgroups sweep all of K, no workspace
-        const CodesPlan cp = codes_plan_if_taken(M, K, N, true);
-        if (cp.ch) return launch_codes(cp, packed, w_scale, w_rows, a_q, a_scale, M, K, N, y, ldy, acc_or_null, (hipStream_t)stream);
+        const CodesPlan cp = codes_plan_if_taken(4, M, K, N, true);
+        if (cp.ch) return launch_codes(cp, packed, w_scale, w_rows, a_q, a_scale, M, K, 0, N, y, ldy, acc_or_null, (hipStream_t)stream);
         const NarrowPlan np = narrow_plan(M, K, N);
         NarrowParams q;
         std::memset(&q, 0, sizeof(q));
@@ -1068,8 +1081,8 @@ static int mpgemm_impl(const uint8_t* packed, float w_scale, const float* w_rows
         if (workspace_bytes < ws_need) return VLUT_ERR_SMALL_BUFFER;
     }
     if (!lut_or_null && matrix_cores_take(pl, M, K, N)) {
-        const CodesPlan cp = codes_plan_if_taken(M, K, N, false);
-        if (cp.ch) return launch_codes(cp, packed, w_scale, w_rows, a_q, a_scale, M, K, N, y, ldy, acc_or_null, (hipStream_t)stream);
+        const CodesPlan cp = codes_plan_if_taken(4, M, K, N, false);
+        if (cp.ch) return launch_codes(cp, packed, w_scale, w_rows, a_q, a_scale, M, K, 0, N, y, ldy, acc_or_null, (hipStream_t)stream);
         return launch_gemm(packed, w_scale, w_rows, a_q, a_scale, M, K, 0, N, y, ldy, acc_or_null, (hipStream_t)stream);
     }
     LookupParams p;
@@ -1293,8 +1306,11 @@ int vlut_mpgemm_g5(const uint8_t* packed, float w_scale, const int8_t* a_q, cons
     }
     // the matrix-core path reads both operands 16 bytes at a time, so it wants the alignment and K % 4 == 0 (two activation
     // rows of a chunk are 16 bytes) that this call does not demand
-    if (matrix_cores_take_g5(K) && (uintptr_t)packed % 16 == 0 && (uintptr_t)a_q % 16 == 0)
+    if (matrix_cores_take_g5(K) && (uintptr_t)packed % 16 == 0 && (uintptr_t)a_q % 16 == 0) {
+        const CodesPlan cp = codes_plan_if_taken(5, M, K, N, false);
+        if (cp.ch) return launch_codes(cp, packed, w_scale, nullptr, a_q, a_scale, M, K, K, N, y, ldy, acc_or_null, (hipStream_t)stream);
         return launch_gemm(packed, w_scale, nullptr, a_q, a_scale, M, K, K, N, y, ldy, acc_or_null, (hipStream_t)stream);
+    }
     Lookup5Params p;
     std::memset(&p, 0, sizeof(p));
     p.packed = packed; p.a_q = a_q; p.a_scale = a_scale; p.y = y; p.acc = acc_or_null; p.ws = (int32_t*)workspace;
@@ -1370,8 +1386,11 @@ int vlut_mpgemm_mixed(const uint8_t* packed, float w_scale, const int8_t* a_q, c
     if (!workspace) return VLUT_ERR_NULL;
     if (workspace_bytes < need) return VLUT_ERR_SMALL_BUFFER;
     hipStream_t s = (hipStream_t)stream;
-    if (matrix_cores_take_mixed() && (uintptr_t)packed % 16 == 0)
+    if (matrix_cores_take_mixed() && (uintptr_t)packed % 16 == 0) {
+        const CodesPlan cp = codes_plan_if_taken(K5 > 0 ? 5 : 4, M, K, N, false);
+        if (cp.ch) return launch_codes(cp, packed, w_scale, nullptr, a_q, a_scale, M, K, K5, N, y, ldy, acc_or_null, s);
         return launch_gemm(packed, w_scale, nullptr, a_q, a_scale, M, K, K5, N, y, ldy, acc_or_null, s);
+    }
     if (K5 > 0) {
         const Derived5 d = derive5(pl5, M, K5, N);
         Lookup5Params p;

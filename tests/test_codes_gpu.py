@@ -44,8 +44,25 @@ def test_few_tokens_from_codes(B, M, K, N):
     assert torch.equal(y, yr) and torch.all(pad[:, M:] == -7.0)
 
 
+# the 1.60-bit and the mixed packing: no, one and four groups of four behind the last twenty values, in every column position of them; the
+# sizes of a workgroup as above (the largest K of two chunks is 7360)
+@pytest.mark.parametrize("M,K,N", [(1, 20, 1), (5, 24, 3), (33, 320, 8), (203, 336, 9), (203, 1036, 16), (77, 2560, 17), (640, 2564, 33), (4097, 516, 8),
+                                   (8200, 276, 16), (16400, 136, 5), (50, 7360, 16), (50, 7364, 16), (64, 14592, 8), (40, 14596, 2), (100, 396, 70)])
+def test_few_tokens_from_codes_five_weights_per_byte(B, M, K, N):
+    print(f"codes5 case M={M} K={K} N={N}", flush=True)
+    W, s, x = wl.small_case(3500 + M + K + N, M, K, N)
+    _, _, acc_ref, y_ref = O.mpgemm(W, s, x)
+    a_q, a_s = B.quantize_act(dev(x))
+    out = [B.mpgemm_mixed(B.pack_weights_mixed(dev(W)), float(s), a_q, a_s, M, want_acc=True)]
+    if K % 20 == 0:
+        out.append(B.mpgemm_g5(B.pack_weights_g5(dev(W)), float(s), a_q, a_s, M, want_acc=True))
+    for y, acc in out:
+        assert np.array_equal(acc.cpu().numpy(), acc_ref)
+        assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - y_ref) <= REL * np.abs(y_ref))
+
+
 # every byte of both packings in every position of a dword: all pairs of digits that the byte permutes look up
-@pytest.mark.parametrize("g,N", [(4, 3), (4, 40), (5, 40)])
+@pytest.mark.parametrize("g,N", [(4, 3), (4, 40), (5, 3), (5, 40)])
 def test_every_packed_byte(B, g, N):
     values = 3 ** g
     idx = (np.arange(values)[:, None] + 37 * np.arange(16)[None, :]) % values           # row r, byte b of a tile column
