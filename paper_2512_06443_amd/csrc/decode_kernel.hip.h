@@ -1,4 +1,5 @@
-// Up to sixteen tokens from fp32 activations in one launch: quantisation, unpacking and the INT8 matrix cores.
+// A few tokens on the INT8 matrix cores: up to sixteen from fp32 activations in one launch (quantisation, unpacking, product), and
+// from INT8 codes.
 // Part of the single translation unit vlut.hip (included there, in this order).
 #pragma once
 
@@ -17,7 +18,7 @@ namespace {
 // primitives, which is the plane order, and store one dword each.  Slots are rotated by the unit, so that the 16 units of
 // a pass lie in distinct banks and the 16 tokens of an operand read do too.
 //
-// Bound by latency: launch, the rows of x, one trip to HBM for the weights, 24 instructions per four packed bytes.
+// Bound by latency: launch, the rows of x, one trip to HBM for the weights, 13 instructions per four packed bytes.
 // ---------------------------------------------------------------------------------------------
 struct DecodeParams {
     const uint8_t* packed;

@@ -6,7 +6,6 @@
 namespace {
 
 typedef int i32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
 
 // ---------------------------------------------------------------------------------------------
@@ -18,17 +17,17 @@ typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
 // its row and tile column (one 16-byte load per macro step, whole 128-byte lines per four rows) and unpacks four bytes
 // at a time into "planes": plane j holds digit j of the four bytes.  That is a fixed permutation of K inside the 16
 // (20) values of a dword, which the activations follow, so no byte is ever moved to its natural place.  Four bytes
-// cost 24 VALU instructions: as 8-bit fractions F of 3^g in 16-bit halves, the next digit is the integer part of 3 F
-// (v_pk_mad_u16 adds the -1 of the digit to the high byte on the way), one byte permute gathers a plane.
+// cost 13 VALU instructions (see Unpack).
 //
 // Activations.  The token-chunked layout [N/8][K][8] goes through LDS as it is, 16 bytes (two k of eight tokens) per
 // lane, and ds_read_b64_tr_b8 transposes it on the way to the registers: 16 lanes point at 8 rows (k) x 16 tokens, lane
 // i receives the eight values of token i.  Which k a row pointer names is free, so the plane order costs nothing.
 // Chunks of eight tokens are pitched so that the 16 eight-byte rows of a read lie in distinct banks.
 //
-// What bounds it (rates of this chip, measured): 16 ns per v_mfma_i32_32x32x32_i8 and SIMD (4.1 POP/s in all), about
-// five VALU instructions fit beside one of them; LDS serves transposing reads at 183 and writes at 71 bytes per clock.
-// With RT x CT = 2 x 4 a wave spends six unpacking instructions per matrix instruction, hence the wide token tile.
+// What bounds it (rates of this chip, measured): power.  14.2 ns per v_mfma_i32_32x32x32_i8 and SIMD on zeros, 17 to 18 on codes and
+// ternary weights (1.9 GHz, 3.8 POP/s), 20.5 with four VALU instructions beside each; LDS serves transposing reads at 183 and
+// writes at 71 bytes per clock.  With CT = 4 a wave spends 3.3 unpacking instructions per matrix instruction, hence the wide token
+// tile.  14336 x 4096 x 512: 32.7 us, of which 22 in the K loop.
 // ---------------------------------------------------------------------------------------------
 struct GemmParams {
     const uint8_t* packed;
