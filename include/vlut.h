@@ -337,9 +337,17 @@ int vlut_set_plan(int J, int R, int waves, int split_k);
 #define VLUT_KERNEL_LOOKUP 1            /* tables in LDS, the plan that vlut_query_plan or vlut_query_plan_g5 reports */
 #define VLUT_KERNEL_FEW_TOKENS 2        /* a few tokens: tables in LDS, one or two tokens per workgroup; from INT8 codes the
                                            matrix cores, where one chunk's codes fit into LDS (K <= 14592, M <= 32768)  */
-#define VLUT_KERNEL_MATRIX 3            /* INT8 matrix cores                                                   */
+#define VLUT_KERNEL_MATRIX 3            /* INT8 matrix cores (vlut_query_matrix_plan tells which workgroups)   */
 #define VLUT_KERNEL_MATRIX_FEW_TOKENS 4 /* INT8 matrix cores, from fp32 in one launch                          */
 int vlut_query_kernel(int form, int64_t M, int64_t K, int64_t N);
+
+/*
+ * The workgroups that compute the product of such a call where it runs on the matrix cores:
+ * out4 (host, 4 ints) = { rows per workgroup, tokens per workgroup, parts of K in a workgroup, number of workgroups }.
+ * Up to 16 tokens per workgroup are the kernels for a few tokens, which VLUT_KERNEL_FEW_TOKENS and VLUT_KERNEL_MATRIX both
+ * can mean from INT8 codes; from 32 on it is the tiled product.  VLUT_ERR_UNSUPPORTED where a kernel that looks up tables runs.
+ */
+int vlut_query_matrix_plan(int form, int64_t M, int64_t K, int64_t N, int* out4);
 
 /*
  * Reports the launch plan of the lookup kernel for this shape, after any vlut_set_plan override of the calling
@@ -350,7 +358,7 @@ int vlut_query_kernel(int form, int64_t M, int64_t K, int64_t N);
  * 256 workgroups and a cost estimate favours it: few rows per workgroup, or a short K), vlut_mpgemm uses a kernel
  * of its own (every workgroup sweeps all of K, no workspace); what is reported is the few-token table kernel (two tokens per
  * workgroup, table entries of one dword): { 0, rows per workgroup, 1, number of workgroups }, which up to K = 14592 and
- * M = 32768 leaves the call to the matrix cores (workgroups of 8 or 16 tokens and 16 to 128 rows).
+ * M = 32768 leaves the call to the matrix cores (vlut_query_matrix_plan: workgroups of 8 or 16 tokens and 16 to 128 rows).
  */
 int vlut_query_plan(int64_t M, int64_t K, int64_t N, int* out4);
 

@@ -33,7 +33,7 @@ EXPORTS = [
     "vlut_build_lut_token_outer", "vlut_mpgemm_token_outer",
     "vlut_mixed_k5", "vlut_packed_weight_bytes_mixed", "vlut_workspace_bytes_mixed", "vlut_pack_weights_mixed",
     "vlut_mpgemm_mixed", "vlut_static_scratch_bytes", "vlut_mpgemm_static", "vlut_query_lookup_waves",
-    "vlut_query_kernel",
+    "vlut_query_kernel", "vlut_query_matrix_plan",
 ]
 
 _lib = None
@@ -89,6 +89,7 @@ def lib() -> ctypes.CDLL:
         L.vlut_mpgemm_f32.restype = ci
         L.vlut_query_lookup_waves.argtypes, L.vlut_query_lookup_waves.restype = [i64, i64, i64], ci
         L.vlut_query_kernel.argtypes, L.vlut_query_kernel.restype = [ci, i64, i64, i64], ci
+        L.vlut_query_matrix_plan.argtypes, L.vlut_query_matrix_plan.restype = [ci, i64, i64, i64, ctypes.POINTER(ci)], ci
         L.vlut_static_scratch_bytes.argtypes, L.vlut_static_scratch_bytes.restype = [], sz
         L.vlut_mpgemm_static.argtypes, L.vlut_mpgemm_static.restype = [p, cf, p, p, i64, i64, i64, p, i64, p, p], ci
         L.vlut_set_plan.argtypes, L.vlut_set_plan.restype = [ci, ci, ci, ci], ci
@@ -274,11 +275,23 @@ _KERNELS = {1: "lookup", 2: "few_tokens", 3: "matrix", 4: "matrix_few_tokens"}
 
 def query_kernel(form: str, M: int, K: int, N: int) -> str:
     """The kernel that computes the product of `mpgemm` ("codes"), `mpgemm_f32` ("f32"), `mpgemm_g5` ("g5") or
-    `mpgemm_mixed` ("mixed"): "lookup", "few_tokens", "matrix" or "matrix_few_tokens" (VLUT_KERNEL_* of the header)."""
+    `mpgemm_mixed` ("mixed"): "lookup", "few_tokens", "matrix" or "matrix_few_tokens" (VLUT_KERNEL_* of the header).
+    From INT8 codes both "few_tokens" and "matrix" can be the matrix-core kernel for a few tokens: query_matrix_plan tells."""
     k = lib().vlut_query_kernel(_FORMS[form], M, K, N)
     if k < 0:
         raise VlutError(k, "vlut_query_kernel")
     return _KERNELS[k]
+
+
+def query_matrix_plan(form: str, M: int, K: int, N: int) -> Optional[Tuple[int, int, int, int]]:
+    """(rows, tokens, parts of K) of a workgroup and the number of workgroups of the matrix-core kernel that computes the
+    product of such a call; up to 16 tokens: a kernel for a few tokens.  None where a kernel that looks up tables runs."""
+    out = (ctypes.c_int * 4)()
+    rc = lib().vlut_query_matrix_plan(_FORMS[form], M, K, N, out)
+    if rc == VLUT_ERR_UNSUPPORTED and lib().vlut_query_kernel(_FORMS[form], M, K, N) > 0:
+        return None
+    _check(rc, "vlut_query_matrix_plan")
+    return out[0], out[1], out[2], out[3]
 
 
 def static_scratch_bytes() -> int:

@@ -475,6 +475,7 @@ bool decode_applies(int64_t M, int64_t K, int64_t N) {
     if (N > 8 && N * K >= 49152 + 12 * M && narrow_applies(M, K, N, nullptr, true) && narrow_plan(M, K, N).rows == 32) return false;
     return true;
 }
+int decode_token_slots(int64_t N) { return N <= 2 ? (int)N : (N <= 4 ? 4 : (N <= 8 ? 8 : 16)); }
 // Row tiles of 16 per workgroup: the fewest whose grid is one round of workgroups (more waves per row tile split K finer).
 int decode_row_tiles(int64_t M) { return M <= 256 * 16 ? 1 : (M <= 256 * 32 ? 2 : (M <= 256 * 64 ? 4 : 8)); }
 
@@ -677,8 +678,10 @@ int choose_gemm_tile(int gw, int64_t M, int64_t macros, int64_t N) {
     return best;
 }
 
+int gemm_macros(int gw, int64_t K) { return (int)(((K / gw + 15) / 16 + 1) / 2); }
+
 double gemm_best_cost(int gw, int64_t M, int64_t K, int64_t N) {
-    const int64_t macros = ((K / gw + 15) / 16 + 1) / 2;
+    const int macros = gemm_macros(gw, K);
     return gemm_cost(gw, choose_gemm_tile(gw, M, macros, N), M, macros, N);
 }
 
@@ -783,7 +786,7 @@ int launch_gemm(const uint8_t* packed, float w_scale, const float* w_rows, const
     p.M = (int)M; p.N = (int)N; p.Ka = (int)K; p.ldy = (int)ldy; p.RGtotal = (int)((M + 3) / 4); p.chunks = (int)((N + 7) / 8);
     p.Kmain = (int)(K5 > 0 ? K5 : K);
     p.KCn = (p.Kmain / gw + 15) / 16;
-    p.macros = (p.KCn + 1) / 2;
+    p.macros = gemm_macros(gw, p.Kmain);
     // an output beyond half of the L2s (32 MB) is not kept there: 14336 x 4096 x 512 37.4 -> 35.4 us.  Who reads y next pays about what
     // the store saves: with quantise, clamp or sigmoid behind it 47.5, 48.0, 54.1 us, 47.5, 47.9, 53.8 with ordinary stores; nine
     // shapes from 17 to 84 MB with a reader are within 2 % either way
@@ -1193,11 +1196,13 @@ int vlut_mpgemm_f32(const uint8_t* packed, float w_scale, const float* w_scale_r
         q.packed = packed; q.x = x; q.w_rows = w_rows; q.y = y; q.acc = acc_or_null; q.a_scale_out = a_scale_out_or_null;
         q.ldx = ldx; q.w_scale = w_one; q.M = (int)M; q.N = (int)N; q.K = (int)K; q.KCn = (int)((K / 4 + 15) / 16);
         q.RGtotal = (int)((M + 3) / 4); q.ldy = (int)ldy; q.macros = (q.KCn + 3) / 4; q.x_vec = x_vec;
-        if (N == 1) return launch_decode<1>(q, s);
-        if (N == 2) return launch_decode<2>(q, s);
-        if (N <= 4) return launch_decode<4>(q, s);
-        if (N <= 8) return launch_decode<8>(q, s);
-        return launch_decode<16>(q, s);
+        switch (decode_token_slots(N)) {
+        case 1: return launch_decode<1>(q, s);
+        case 2: return launch_decode<2>(q, s);
+        case 4: return launch_decode<4>(q, s);
+        case 8: return launch_decode<8>(q, s);
+        default: return launch_decode<16>(q, s);
+        }
     }
     if (L.kind == kF32Narrow) {
         const NarrowPlan np = narrow_plan(M, K, N);
@@ -1450,6 +1455,41 @@ int vlut_query_kernel(int form, int64_t M, int64_t K, int64_t N) {
     Plan p4;
     if (!mixed_plans(M, K, N, &p5, &p4)) return VLUT_ERR_UNSUPPORTED;
     return matrix_cores_take_mixed() ? VLUT_KERNEL_MATRIX : VLUT_KERNEL_LOOKUP;
+}
+
+// Of a call that the matrix cores take from INT8 codes, Kmain values of K in the main blob; `narrow` as in codes_plan_if_taken.
+static int codes_matrix_plan(int gw, int64_t M, int64_t K, int64_t Kmain, int64_t N, bool narrow, int* out4) {
+    const CodesPlan cp = codes_plan_if_taken(gw, M, K, N, narrow);
+    if (!cp.ch && narrow) return VLUT_ERR_UNSUPPORTED;       // the table kernel's
+    if (cp.ch) {
+        out4[0] = 16 * cp.mt; out4[1] = 8 * cp.ch; out4[2] = kDecodeWaves / cp.mt;
+    } else {
+        const GemmTile& t = kGemmTiles[choose_gemm_tile(gw, M, gemm_macros(gw, Kmain), N)];
+        out4[0] = t.rows(); out4[1] = t.tokens(); out4[2] = t.wk;
+    }
+    const int64_t tiles = ((M + out4[0] - 1) / out4[0]) * ((N + out4[1] - 1) / out4[1]);
+    out4[3] = (int)std::min<int64_t>(tiles, INT32_MAX);
+    return VLUT_OK;
+}
+
+int vlut_query_matrix_plan(int form, int64_t M, int64_t K, int64_t N, int* out4) {
+    if (!out4) return VLUT_ERR_NULL;
+    const int kernel = vlut_query_kernel(form, M, K, N);
+    if (kernel < 0) return kernel;
+    if (kernel == VLUT_KERNEL_LOOKUP) return VLUT_ERR_UNSUPPORTED;
+    if (form == VLUT_FORM_G5) return codes_matrix_plan(5, M, K, K, N, false, out4);
+    if (form == VLUT_FORM_MIXED) {
+        const int64_t K5 = vlut_mixed_k5(K);
+        return codes_matrix_plan(K5 > 0 ? 5 : 4, M, K, K5 > 0 ? K5 : K, N, false, out4);
+    }
+    if (kernel == VLUT_KERNEL_MATRIX_FEW_TOKENS) {
+        const int mt = decode_row_tiles(M);
+        out4[0] = 16 * mt; out4[1] = decode_token_slots(N); out4[2] = kDecodeWaves / mt;
+        out4[3] = (int)((M + out4[0] - 1) / out4[0]);
+        return VLUT_OK;
+    }
+    if (form == VLUT_FORM_F32 && f32_layout(M, K, N).kind != kF32TwoLaunches) return VLUT_ERR_UNSUPPORTED;
+    return codes_matrix_plan(4, M, K, K, N, narrow_applies(M, K, N, nullptr, false), out4);
 }
 
 size_t vlut_mfma_workspace_bytes(int64_t M, int64_t K, int64_t N) {

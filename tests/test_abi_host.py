@@ -453,3 +453,46 @@ def test_nine_to_sixteen_tokens_on_few_rows_take_the_faster_kernel(L):
     for shape, t_table, t_matrix in measured:
         assert L.vlut_query_kernel(1, *shape) == (few if t_table < t_matrix else matrix_few), shape
     assert L.vlut_query_kernel(1, 4, 8188, 8) == matrix_few                    # up to eight tokens two waves share a row: never
+
+
+def test_matrix_plan_names_the_workgroups_that_run(L):
+    """vlut_query_matrix_plan tells the kernels for a few tokens (up to 16 per workgroup) from the tiled product, which
+    vlut_query_kernel and vlut_query_plan do not from INT8 codes, and refuses where a kernel that looks up tables runs."""
+    L.vlut_query_kernel.argtypes = [ci, i64, i64, i64]
+    L.vlut_query_matrix_plan.argtypes = [ci, i64, i64, i64, ctypes.POINTER(ci)]
+    codes, f32, g5, mixed = range(4)
+    few, matrix = 2, 3
+    out = (ci * 4)()
+
+    def plan(*shape):
+        rc = L.vlut_query_matrix_plan(*shape, out)
+        if rc == 0:
+            rows, tokens, parts, workgroups = out
+            assert workgroups == -(-shape[1] // rows) * -(-shape[3] // tokens)
+            assert tokens in (32, 64, 128) or (tokens <= 16 and rows * parts == 256)       # sixteen waves: row tiles x parts of K
+        return tuple(out)[:3] if rc == 0 else rc
+
+    # one kernel behind two names, and another behind one of them
+    assert L.vlut_query_kernel(codes, 640, 2560, 4) == few and plan(codes, 640, 2560, 4) == (16, 8, 16)
+    assert L.vlut_query_kernel(codes, 2560, 6912, 16) == matrix and plan(codes, 2560, 6912, 16)[1] <= 16
+    assert L.vlut_query_kernel(codes, 13824, 2560, 1024) == matrix and plan(codes, 13824, 2560, 1024) == (256, 128, 1)
+    assert plan(f32, 2560, 6912, 16) == plan(codes, 2560, 6912, 16)                        # two launches: the same product
+    assert plan(f32, 4097, 2560, 16) == (32, 16, 8) and plan(f32, 16384, 4096, 1) == (64, 1, 4) and plan(f32, 64, 64, 3)[1] == 4
+    assert plan(g5, 4096, 4000, 16)[1] <= 16 and plan(mixed, 4096, 4096, 256)[1] >= 32 and plan(mixed, 64, 16, 8)[1] <= 16
+    # table kernels: K beyond what decode_codes_kernel holds, more rows than it repeats its copy for, K that four do not divide
+    for shape in [(codes, 2560, 30000, 2), (codes, 32769, 64, 2), (g5, 640, 2555, 4), (codes, 64, 16384, 40), (f32, 16385, 4096, 1)]:
+        assert plan(*shape) == -6, shape
+    assert plan(codes, 32768, 14592, 2)[1] == 8
+    try:
+        assert L.vlut_set_plan(16, 2, 0, 1) == 0
+        assert plan(codes, 300, 2560, 40) == plan(f32, 300, 2560, 40) == plan(mixed, 300, 2560, 40) == -6 and isinstance(plan(g5, 300, 2560, 40), tuple)
+        assert plan(f32, 4097, 2560, 16) == -6
+    finally:
+        assert L.vlut_set_plan(0, 0, 0, 0) == 0
+    assert L.vlut_query_matrix_plan(codes, 8, 8, 8, None) == -1
+    assert plan(codes, 8, 6, 8) == -2 and plan(g5, 8, 64, 8) == -2 and plan(4, 8, 64, 8) == -6
+    from paper_2512_06443_amd import binding
+    assert binding.query_matrix_plan("codes", 13824, 2560, 1024) == (256, 128, 1, 54 * 8)
+    assert binding.query_matrix_plan("codes", 2560, 30000, 2) is None
+    with pytest.raises(binding.VlutError):
+        binding.query_matrix_plan("codes", 8, 6, 8)
