@@ -688,9 +688,10 @@ double gemm_best_cost(int gw, int64_t M, int64_t K, int64_t N) {
 // decode_codes_kernel for a few tokens: eight or sixteen per workgroup (ch chunks) and 16 * mt rows; ch = 0: not this kernel.  Its time in
 // us, launches back to back, fitted (rms 3.7 %) to 18000 launches over 4100 shapes of 200 to 14336 rows, K = 256 to 14336 and 16 to 1024
 // tokens: a launch and two trips to memory, then K times what a workgroup copies and unpacks, weights beyond 27 MB from further
-// away, the store; beyond one workgroup per compute unit further rounds, shorter where two of them fit one unit's LDS.  Five weights per
-// byte cost the same (30 shapes: the choice it makes is within 3 % of the fastest; us, gemm_kernel / this one: 4096 x 4096 x 32 mixed 6.6 / 5.8,
-// 4096 x 4000 x 16 6.5 / 4.8, 2560 x 6900 x 8 7.7 / 4.8, but 13820 x 2560 x 64 7.7 / 11.9).
+// away, the store; beyond one workgroup per compute unit further rounds, shorter where two of them share a unit: their LDS fits and
+// their 16 waves each take at most 64 registers (four weights per byte: 60 to 62; five: 75 to 77, never two).  Five weights per byte cost the
+// same otherwise (us, gemm_kernel / this one: 4096 x 4096 x 32 mixed 6.6 / 5.8, 4096 x 4000 x 16 6.5 / 4.8, 2560 x 6900 x 8 7.7 / 4.8, but
+// 13820 x 2560 x 64 7.7 / 11.9, 3079 x 360 x 233 4.8 / 6.7, 8624 x 1640 x 170 11.0 / 13.9, 12659 x 2020 x 98 12.0 / 15.0).
 struct CodesPlan {
     int ch, mt;
     double us;
@@ -701,7 +702,7 @@ CodesPlan codes_plan(int gw, int64_t M, int64_t K, int64_t N) {
     const double mb = (double)M * (double)K / (gw * 1e6);
     for (int ch = 1; ch <= 2; ++ch) {
         if (!decode_codes_fits(gw, ch, K) || (ch == 2 && N <= 8)) continue;
-        const bool two_per_unit = decode_codes_lds_bytes(gw, ch, K) <= 80 * 1024;
+        const bool two_per_unit = gw == 4 && decode_codes_lds_bytes(gw, ch, K) <= 80 * 1024;
         for (int mt = 1; mt <= 8; mt *= 2) {
             const int64_t wgs = ((M + 16 * mt - 1) / (16 * mt)) * ((N + 8 * ch - 1) / (8 * ch)), rounds = (wgs + 255) / 256;
             double us = 3.45 + (double)K * (ch == 1 ? 0.51e-4 + 1.31e-4 * mt : 1.29e-4 + 1.34e-4 * mt) + 0.00073 * (double)std::min<int64_t>(wgs, 256);

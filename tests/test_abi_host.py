@@ -496,3 +496,17 @@ def test_matrix_plan_names_the_workgroups_that_run(L):
     assert binding.query_matrix_plan("codes", 2560, 30000, 2) is None
     with pytest.raises(binding.VlutError):
         binding.query_matrix_plan("codes", 8, 6, 8)
+
+
+def test_several_rounds_of_five_weights_per_byte_take_the_faster_kernel(L):
+    """1.60-bit packing, more workgroups of the kernel for a few tokens than compute units: one of them fills a unit (registers), so
+    the side of the rule on which the measured times (us, tiled product / a few tokens) put a shape is the tiled product's."""
+    L.vlut_query_kernel.argtypes = [ci, i64, i64, i64]
+    out = (ci * 4)()
+    measured = [((3079, 360, 233), 4.85, 6.67), ((8624, 1640, 170), 10.96, 13.86), ((12659, 2020, 98), 11.96, 14.99), ((4391, 1320, 219), 7.11, 8.99),
+                ((9743, 900, 92), 6.10, 7.39), ((2943, 340, 216), 4.71, 6.46), ((11837, 340, 97), 6.97, 9.12),
+                ((4096, 4000, 16), 6.5, 4.8), ((2560, 6900, 8), 7.7, 4.8)]
+    for shape, t_tiles, t_few in measured:
+        for form in (2, 3):
+            assert L.vlut_query_matrix_plan(form, *shape, out) == 0
+            assert (out[1] <= 16) == (t_few < t_tiles), (form, shape)
