@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
@@ -21,8 +22,8 @@ HIPCC_FLAGS = [
 
 
 def build(force: bool = True) -> str:
-    """Compiles the library and the native form of the binding's calls; returns the library's path.  force=False only builds
-    what is missing or stale."""
+    """Compiles the library and, where it can, the native form of the binding's calls; returns the library's path.  force=False
+    only builds what is missing or stale."""
     csrc = os.path.dirname(SRC)         # vlut.hip includes the kernel headers next to it
     sources = [os.path.join(csrc, f) for f in os.listdir(csrc)] + [os.path.join(INCLUDE, "vlut.h")]
     newest = max(os.path.getmtime(f) for f in sources)
@@ -33,10 +34,25 @@ def build(force: bool = True) -> str:
     if stale(LIB):
         hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
         _run([hipcc, *HIPCC_FLAGS, "-I", INCLUDE, SRC, "-o", LIB])
-    cmd = torch_command()
-    if cmd and stale(TORCH_LIB):
-        _run(cmd)
+    if stale(TORCH_LIB):
+        _build_native()
     return LIB
+
+
+def _build_native() -> None:
+    """TORCH_LIB, if torch, its headers and a C++ compiler are there.  The calls have a Python form, so that a failure is a warning; a
+    file of older sources does not outlive it."""
+    try:
+        cmd = torch_command()
+        if cmd:
+            _run(cmd)
+            return
+        why = "torch was not built for ROCm"
+    except (ImportError, OSError, RuntimeError) as e:
+        why = str(e)
+    if os.path.exists(TORCH_LIB):
+        os.remove(TORCH_LIB)
+    warnings.warn(f"{os.path.basename(TORCH_LIB)} is not built, the binding's calls run in their Python form: {why}", RuntimeWarning, stacklevel=3)
 
 
 def torch_command():
