@@ -68,3 +68,14 @@ def test_only_what_is_missing_or_stale_is_built(scratch):
         os.remove(b.TORCH_LIB)
         b.build(force=False)
     assert (scratch / "lib.so").read_text() == "kept" and (scratch / "torch.so").exists()
+
+
+def test_compiler_may_be_given_with_arguments(monkeypatch, scratch):
+    torch = pytest.importorskip("torch")
+    if torch.version.hip is None:
+        pytest.skip("built with a torch for ROCm only")
+    monkeypatch.setenv("CXX", f"env CONTENT=wrapped '{scratch}/compiler'")
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        b.build()
+    assert (scratch / "torch.so").read_text().strip() == "wrapped"
