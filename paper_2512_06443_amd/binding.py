@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes
 import importlib.util
 import os
+import sys
 from typing import Optional, Tuple
 
 import torch
@@ -111,6 +112,11 @@ _NATIVE_ORDER = ("vlut_quantize_act", "vlut_mpgemm", "vlut_workspace_bytes", "vl
                  "vlut_packed_weight_bytes_mixed")
 
 
+def built_for() -> str:
+    """What NATIVE_PATH is compiled against: it holds layouts and key numbers of torch's headers, and a file for others may load all the same."""
+    return f"torch {torch.__version__} {getattr(torch.version, 'git_version', '')} python {sys.version_info[0]}.{sys.version_info[1]}"
+
+
 def _load_native(L: ctypes.CDLL) -> None:
     global _native
     if not os.path.exists(NATIVE_PATH) or not hasattr(torch._C, "_cuda_getCurrentRawStream"):
@@ -120,6 +126,8 @@ def _load_native(L: ctypes.CDLL) -> None:
         mod = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(mod)
     except ImportError:                 # built for another torch
+        return
+    if getattr(mod, "built_for", None) != built_for():      # (whose symbols are all here)
         return
     mod.bind(*[ctypes.cast(getattr(L, f), ctypes.c_void_p).value for f in _NATIVE_ORDER])
     _native = mod

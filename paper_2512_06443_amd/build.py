@@ -35,9 +35,22 @@ def build(force: bool = True) -> str:
     if stale(LIB):
         hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
         _run([hipcc, *HIPCC_FLAGS, "-I", INCLUDE, SRC, "-o", LIB])
-    if stale(TORCH_LIB):
+    if stale(TORCH_LIB) or not _built_for_this_torch():
         _build_native()
     return LIB
+
+
+def _built_for() -> str:
+    from .binding import built_for      # (needs torch)
+    return built_for()
+
+
+def _built_for_this_torch() -> bool:
+    try:
+        with open(TORCH_LIB, "rb") as f:
+            return _built_for().encode() in f.read()
+    except ImportError:
+        return False
 
 
 def _build_native() -> None:
@@ -47,10 +60,9 @@ def _build_native() -> None:
         cmd = torch_command()
         if cmd:
             _run(cmd)
-            return
-        why = "torch was not built for ROCm"
+        return
     except (ImportError, OSError, RuntimeError) as e:
-        why = str(e)
+        why = e
     if os.path.exists(TORCH_LIB):
         os.remove(TORCH_LIB)
     warnings.warn(f"{os.path.basename(TORCH_LIB)} is not built, the binding's calls run in their Python form: {why}", RuntimeWarning, stacklevel=3)
@@ -69,7 +81,7 @@ def torch_command():
            os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
     # (host code only; torch's libraries are found as the ones that are already loaded)
     return [*shlex.split(os.environ.get("CXX", "g++")), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *["-I" + d for d in inc], TORCH_SRC, "-o", TORCH_LIB,
+            f'-DVLUT_BUILT_FOR="{_built_for()}"', f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *["-I" + d for d in inc], TORCH_SRC, "-o", TORCH_LIB,
             "-L" + os.path.join(base, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
 
 

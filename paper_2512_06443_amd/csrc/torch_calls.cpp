@@ -260,4 +260,9 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_vlut_torch", nullptr, -1, kMetho
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__vlut_torch(void) { return PyModule_Create(&kModule); }
+// built_for: the torch and the Python of the headers above (binding.built_for); binding.py uses no module that was built for others
+PyMODINIT_FUNC PyInit__vlut_torch(void) {
+    PyObject* m = PyModule_Create(&kModule);
+    if (m && PyModule_AddStringConstant(m, "built_for", VLUT_BUILT_FOR) != 0) Py_CLEAR(m);
+    return m;
+}

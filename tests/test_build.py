@@ -67,7 +67,13 @@ def test_only_what_is_missing_or_stale_is_built(scratch):
         (scratch / "lib.so").write_text("kept")
         os.remove(b.TORCH_LIB)
         b.build(force=False)
-    assert (scratch / "lib.so").read_text() == "kept" and (scratch / "torch.so").exists()
+        assert (scratch / "lib.so").read_text() == "kept" and (scratch / "torch.so").exists()
+        (scratch / "torch.so").write_text("kept, " + b._built_for())
+        b.build(force=False)
+        assert (scratch / "torch.so").read_text().startswith("kept")
+        (scratch / "torch.so").write_text("for another torch")
+        b.build(force=False)
+    assert (scratch / "torch.so").read_text().strip() == "new" and (scratch / "lib.so").read_text() == "kept"
 
 
 def test_compiler_may_be_given_with_arguments(monkeypatch, scratch):

@@ -28,6 +28,22 @@ def test_native_form_is_built_and_declines_what_it_does_not_know():
         n.bind(1)
 
 
+def test_native_form_of_another_torch_is_not_used(monkeypatch):
+    """A file whose symbols all resolve can hold the layouts of another torch's headers."""
+    L = B.lib()
+    if torch.version.hip is None:
+        pytest.skip("built with a torch for ROCm only")
+    monkeypatch.setattr(B, "_native", None)
+    B._load_native(L)
+    assert B._native is not None and B._native.built_for == B.built_for()
+    for name, value in (("__version__", "2.99.0"), ("version.git_version", "0" * 40)):
+        with monkeypatch.context() as m:
+            m.setattr("torch." + name, value)
+            m.setattr(B, "_native", None)
+            B._load_native(L)
+            assert B._native is None
+
+
 def _both(monkeypatch, f):
     assert B._native is not None
     native = f()
