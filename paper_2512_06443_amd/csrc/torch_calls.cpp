@@ -112,15 +112,16 @@ PyObject* guarded(F f) {
         Py_RETURN_NONE;
     }
 }
-// Other threads run Python during the call of the library, as they do during a ctypes call.
+// Other threads run Python during the allocations and the call of the library, as they do during torch.empty and a ctypes call: an
+// allocation may wait for the device.  Taken back on the way out of an exception too.
 struct WithoutGil {
     PyThreadState* const state = PyEval_SaveThread();
     ~WithoutGil() { PyEval_RestoreThread(state); }
 };
-template <class F, class... A>
-int call_library(F fn, A... args) {
+template <class F>
+void without_gil(F f) {
     const WithoutGil released;
-    return fn(args...);
+    f();
 }
 
 // quantize_act(x, a_q, a_scale)
@@ -129,9 +130,15 @@ PyObject* py_quantize_act(PyObject*, PyObject* const* o, Py_ssize_t n) {
         const at::Tensor *x, *given_q, *given_s;
         if (!ordinary(n, 3) || !matrix(x = plain(o[0]), at::kFloat) || !optional(o[1], given_q) || !optional(o[2], given_s)) Py_RETURN_NONE;
         const int64_t N = x->size(0), K = x->size(1);
-        const at::Tensor a_q = given_q ? *given_q : make({(N + 7) / 8, K, 8}, at::kChar, x->device());
-        const at::Tensor a_s = given_s ? *given_s : make({N}, at::kFloat, x->device());
-        const int rc = call_library(g_api.quantize_act, ptr<float>(*x), N, K, x->stride(0), ptr<int8_t>(a_q), ptr<float>(a_s), stream());
+        at::Tensor a_q, a_s;
+        if (given_q) a_q = *given_q;
+        if (given_s) a_s = *given_s;
+        int rc;
+        without_gil([&] {
+            if (!given_q) a_q = make({(N + 7) / 8, K, 8}, at::kChar, x->device());
+            if (!given_s) a_s = make({N}, at::kFloat, x->device());
+            rc = g_api.quantize_act(ptr<float>(*x), N, K, x->stride(0), ptr<int8_t>(a_q), ptr<float>(a_s), stream());
+        });
         return result(rc, a_q, a_s);
     });
 }
@@ -149,17 +156,21 @@ PyObject* product(PyObject* const* o, size_t least, Bytes workspace_bytes, Call 
         const int64_t K = q->size(1), N = s->size(0);
         const int want = PyObject_IsTrue(o[7]);
         if (want < 0) { PyErr_Clear(); Py_RETURN_NONE; }
-        const at::Tensor y = gy ? *gy : make({N, M}, at::kFloat, q->device());
-        at::Tensor acc, ws;
+        at::Tensor y, acc, ws;
+        if (gy) y = *gy;
         if (gacc) acc = *gacc;
-        else if (want) acc = make({M, N}, at::kInt, q->device());
         if (gws) ws = *gws;
-        else {
-            const size_t need = workspace_bytes(M, K, N);
-            if (need || least) ws = make({(int64_t)(need > least ? need : least)}, at::kByte, q->device());
-        }
-        const int rc = call_library(call, ptr<uint8_t>(*packed), w_scale, ptr<int8_t>(*q), ptr<float>(*s), M, K, N, ptr<float>(y), y.stride(0),
-                                    ptr<int32_t>(acc), ptr<void>(ws), ws.defined() ? bytes_of(ws) : 0, stream());
+        int rc;
+        without_gil([&] {
+            if (!gy) y = make({N, M}, at::kFloat, q->device());
+            if (!gacc && want) acc = make({M, N}, at::kInt, q->device());
+            if (!gws) {
+                const size_t need = workspace_bytes(M, K, N);
+                if (need || least) ws = make({(int64_t)(need > least ? need : least)}, at::kByte, q->device());
+            }
+            rc = call(ptr<uint8_t>(*packed), w_scale, ptr<int8_t>(*q), ptr<float>(*s), M, K, N, ptr<float>(y), y.stride(0), ptr<int32_t>(acc),
+                      ptr<void>(ws), ws.defined() ? bytes_of(ws) : 0, stream());
+        });
         return result(rc, y, acc);
     });
 }
@@ -193,15 +204,21 @@ PyObject* py_mpgemm_f32(PyObject*, PyObject* const* o, Py_ssize_t n) {
         const int want_acc = PyObject_IsTrue(o[5]), want_scales = PyObject_IsTrue(o[6]);
         if (want_acc < 0 || want_scales < 0) { PyErr_Clear(); Py_RETURN_NONE; }
         const int64_t N = x->size(0), K = x->size(1);
-        const at::Tensor y = gy ? *gy : make({N, M}, at::kFloat, x->device());
-        at::Tensor acc, scales, ws;
-        if (want_acc) acc = make({M, N}, at::kInt, x->device());
-        if (want_scales) scales = make({N}, at::kFloat, x->device());
-        size_t bytes = 0;
-        if (gws) bytes = bytes_of(ws = *gws);
-        else if ((bytes = g_api.workspace_bytes_f32(M, K, N)) != 0) ws = make({(int64_t)bytes}, at::kByte, x->device());
-        const int rc = call_library(g_api.mpgemm_f32, ptr<uint8_t>(*packed), w_scale, rows ? ptr<float>(*rows) : nullptr, ptr<float>(*x), x->stride(0),
-                                    M, K, N, ptr<float>(y), y.stride(0), ptr<int32_t>(acc), ptr<float>(scales), ptr<void>(ws), bytes, stream());
+        at::Tensor y, acc, scales, ws, w_rows;
+        if (gy) y = *gy;
+        if (gws) ws = *gws;
+        if (rows) w_rows = *rows;
+        int rc;
+        without_gil([&] {
+            if (!gy) y = make({N, M}, at::kFloat, x->device());
+            if (want_acc) acc = make({M, N}, at::kInt, x->device());
+            if (want_scales) scales = make({N}, at::kFloat, x->device());
+            size_t bytes = 0;
+            if (gws) bytes = bytes_of(ws);
+            else if ((bytes = g_api.workspace_bytes_f32(M, K, N)) != 0) ws = make({(int64_t)bytes}, at::kByte, x->device());
+            rc = g_api.mpgemm_f32(ptr<uint8_t>(*packed), w_scale, ptr<float>(w_rows), ptr<float>(*x), x->stride(0), M, K, N, ptr<float>(y), y.stride(0),
+                                  ptr<int32_t>(acc), ptr<float>(scales), ptr<void>(ws), bytes, stream());
+        });
         return result(rc, y, acc, scales);
     });
 }
@@ -215,8 +232,13 @@ PyObject* pack(PyObject* const* o, Py_ssize_t n, Bytes packed_bytes, Call call) 
         const int64_t M = w->size(0), K = w->size(1);
         const size_t bytes = packed_bytes(M, K);
         if (bytes == 0) Py_RETURN_NONE;
-        const at::Tensor packed = make({(int64_t)bytes}, at::kByte, w->device());
-        return result(call_library(call, ptr<int8_t>(*w), M, K, ptr<uint8_t>(packed), bytes, stream()), packed);
+        at::Tensor packed;
+        int rc;
+        without_gil([&] {
+            packed = make({(int64_t)bytes}, at::kByte, w->device());
+            rc = call(ptr<int8_t>(*w), M, K, ptr<uint8_t>(packed), bytes, stream());
+        });
+        return result(rc, packed);
     });
 }
 PyObject* py_pack_weights(PyObject*, PyObject* const* o, Py_ssize_t n) { return pack(o, n, g_api.packed_weight_bytes, g_api.pack_weights); }

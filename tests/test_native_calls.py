@@ -44,6 +44,90 @@ def test_native_form_of_another_torch_is_not_used(monkeypatch):
             assert B._native is None
 
 
+# The native form as it is, on CPU tensors: in place of the GPU tests of its arguments, of torch's allocator and of the stream are ones that
+# count, and functions of the library that count.  Counted is whether the thread holds the interpreter's lock.
+ON_CPU = r"""
+#include <Python.h>
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/core/Tensor.h>
+#include <ATen/ops/empty.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/autograd/python_variable.h>
+#include <stdexcept>
+#include "vlut.h"
+#define SHOWN extern "C" __attribute__((visibility("default")))
+static int allocations_, calls_, held_, fail_at_;
+static int called() { ++calls_; held_ += PyGILState_Check(); return 0; }
+namespace at {
+static Tensor counted_empty(c10::IntArrayRef size, TensorOptions o) {
+    held_ += PyGILState_Check();
+    if (++allocations_ == fail_at_) throw std::runtime_error("no memory");
+    return at::empty(size, o);
+}
+}
+namespace c10 { namespace hip { struct NoStream { void* stream() { return nullptr; } }; static NoStream no_stream() { return {}; } } }
+static int quantize(const float*, int64_t, int64_t, int64_t, int8_t*, float*, void*) { return called(); }
+static int mpgemm(const uint8_t*, float, const int8_t*, const float*, const int16_t*, int64_t, int64_t, int64_t, float*, int64_t, int32_t*, void*,
+                  size_t, void*) { return called(); }
+static int mpgemm5(const uint8_t*, float, const int8_t*, const float*, int64_t, int64_t, int64_t, float*, int64_t, int32_t*, void*, size_t,
+                   void*) { return called(); }
+static int mpgemm_f32(const uint8_t*, float, const float*, const float*, int64_t, int64_t, int64_t, int64_t, float*, int64_t, int32_t*, float*,
+                      void*, size_t, void*) { return called(); }
+static int pack(const int8_t*, int64_t, int64_t, uint8_t*, size_t, void*) { return called(); }
+static size_t bytes3(int64_t, int64_t, int64_t) { return 64; }
+static size_t bytes2(int64_t, int64_t) { return 64; }
+SHOWN void* address(int i) {
+    void* const a[] = {(void*)quantize, (void*)mpgemm, (void*)bytes3, (void*)mpgemm_f32, (void*)bytes3, (void*)mpgemm5, (void*)bytes3,
+                       (void*)mpgemm5, (void*)bytes3, (void*)pack, (void*)bytes2, (void*)pack, (void*)bytes2, (void*)pack, (void*)bytes2};
+    return a[i];
+}
+SHOWN void start(int fail_at) { allocations_ = calls_ = held_ = 0; fail_at_ = fail_at; }
+SHOWN int allocations() { return allocations_; }
+SHOWN int calls() { return calls_; }
+SHOWN int held() { return held_; }
+#define is_cuda is_cpu
+#define empty counted_empty
+#define getCurrentHIPStream no_stream
+#include "torch_calls.cpp"
+"""
+
+
+def test_native_form_allocates_and_calls_with_the_interpreter_released(tmp_path):
+    """An allocation may wait for the device, as the call may: other threads run Python meanwhile, as they do in the Python form.  An
+    allocation that fails leaves the call to that form, with the lock taken back."""
+    import ctypes
+    import importlib.util
+    import os
+
+    from paper_2512_06443_amd import build
+    if torch.version.hip is None:
+        pytest.skip("built with a torch for ROCm only")
+    (tmp_path / "on_cpu.cpp").write_text(ON_CPU)
+    path = str(tmp_path / "_vlut_torch.so")
+    own = {build.TORCH_SRC: str(tmp_path / "on_cpu.cpp"), build.TORCH_LIB: path, "-O2": "-O0"}
+    build._run([own.get(a, a) for a in build.torch_command()] + ["-I" + os.path.dirname(build.TORCH_SRC)])
+    lib = ctypes.CDLL(path)
+    lib.address.restype = ctypes.c_void_p
+    spec = importlib.util.spec_from_file_location("_vlut_torch", path)
+    n = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(n)
+    n.bind(*[lib.address(i) for i in range(len(B._NATIVE_ORDER))])
+    M, K, N = 8, 16, 3
+    w, x, p = torch.zeros(M, K, dtype=torch.int8), torch.zeros(N, K), torch.zeros(64, dtype=torch.uint8)
+    q, s = torch.zeros(1, K, 8, dtype=torch.int8), torch.zeros(N)
+    product = (p, 0.5, q, s, M, None, None, True, None)
+    for f, args, allocations in ((n.quantize_act, (x, None, None), 2), (n.mpgemm, product, 3), (n.mpgemm_g5, product, 3), (n.mpgemm_mixed, product, 3),
+                                 (n.mpgemm_f32, (p, 0.5, x, M, None, True, True, None), 4), (n.pack_weights, (w,), 1), (n.pack_weights_g5, (w,), 1),
+                                 (n.pack_weights_mixed, (w,), 1)):
+        lib.start(0)
+        out = f(*args)
+        assert isinstance(out, tuple) and all(isinstance(t, torch.Tensor) for t in out), f
+        assert (lib.allocations(), lib.calls(), lib.held()) == (allocations, 1, 0), f
+        lib.start(allocations)
+        assert f(*args) is None and lib.calls() == 0, f
+    assert ctypes.PyDLL(path).calls() == 0 and ctypes.pythonapi.PyGILState_Check() == 1
+
+
 def _both(monkeypatch, f):
     assert B._native is not None
     native = f()
