@@ -192,3 +192,74 @@ def test_native_form_refuses_what_the_python_form_refuses(monkeypatch):
             return None
         n, p = _both(monkeypatch, outcome)
         assert n is not None and n == p
+
+
+@pytest.mark.gpu
+def test_native_form_leaves_modes_and_subclasses_to_the_python_form():
+    from torch.overrides import TorchFunctionMode
+    B.lib()
+    n = B._native
+    M, K, N = 64, 128, 5
+    W = torch.randint(-1, 2, (M, K), dtype=torch.int8, device="cuda")
+    x = torch.randn(N, K, device="cuda")
+    packed = B.pack_weights(W)
+    a_q, a_s = B.quantize_act(x)
+    args = {"quantize_act": (x, None, None), "pack_weights": (W,), "mpgemm": (packed, 0.5, a_q, a_s, M, None, None, False, None),
+            "mpgemm_f32": (packed, 0.5, x, M, None, False, False, None)}
+    want = B.mpgemm_f32(packed, 0.5, x, M)[0]
+
+    class Seen(TorchFunctionMode):
+        functions = []
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            self.functions.append(func)
+            return func(*args, **(kwargs or {}))
+
+    class Sub(torch.Tensor):
+        pass
+
+    for name, a in args.items():
+        assert getattr(n, name)(*a) is not None
+        with Seen():
+            assert getattr(n, name)(*a) is None, name
+        for i, t in enumerate(a):
+            if isinstance(t, torch.Tensor):
+                assert getattr(n, name)(*a[:i], t.as_subclass(Sub), *a[i + 1:]) is None, (name, i)
+    with Seen() as mode:
+        y = B.mpgemm_f32(packed, 0.5, x, M)[0]
+    assert torch.empty in mode.functions and torch.equal(y, want)
+    assert torch.equal(B.mpgemm_f32(packed, 0.5, x.as_subclass(Sub), M)[0], want)
+    assert torch.equal(B.mpgemm_f32(torch.nn.Parameter(packed, requires_grad=False), 0.5, x, M)[0], want)
+
+
+@pytest.mark.gpu
+def test_native_form_from_two_threads_and_streams():
+    import threading
+    B.lib()
+    M, K = 640, 2560
+    packed = B.pack_weights(torch.randint(-1, 2, (M, K), dtype=torch.int8, device="cuda"))
+    xs = [torch.randn(N, K, device="cuda") for N in (5, 40)]
+    want = [B.mpgemm_f32(packed, 0.5, x, M, want_acc=True, want_scales=True) for x in xs]
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(i):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                for _ in range(100):
+                    got = B.mpgemm_f32(packed, 0.5, xs[i], M, want_acc=True, want_scales=True)
+                    a_q, a_s = B.quantize_act(xs[i])
+                    y, acc = B.mpgemm(packed, 0.5, a_q, a_s, M, want_acc=True)
+                    stream.synchronize()
+                    if not (all(torch.equal(u, v) for u, v in zip(got, want[i])) and torch.equal(y, got[0]) and torch.equal(acc, got[1])):
+                        bad.append(i)
+        except Exception as e:
+            bad.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
