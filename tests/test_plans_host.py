@@ -1,0 +1,56 @@
+"""The sizes of the GPU tests against the plans that the library makes for them: each runs the workgroup that it is there for, and the
+tests run every workgroup that is built."""
+import os
+import re
+
+import pytest
+
+from tests.conftest import ROOT
+
+pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def B(vlut_lib_path):
+    from paper_2512_06443_amd import binding
+    binding.lib()
+    return binding
+
+
+def built_tiles():
+    """(rows, tokens, parts of K) of every row of kGemmTiles, and of those that are built for five weights per byte."""
+    text = open(os.path.join(ROOT, "paper_2512_06443_amd", "csrc", "gemm_kernel.hip.h")).read()
+    table = re.search(r"kGemmTiles\[\] = \{\n(.*?)\n\};", text, flags=re.S).group(1)
+    four, five = set(), set()
+    for line in table.splitlines():
+        numbers = [float(v) for v in re.findall(r"[0-9.]+", line.split("//")[0])]
+        rt, ct, wm, wk = (int(v) for v in numbers[:4])
+        four.add((32 * rt * wm, 32 * ct, wk))
+        if numbers[-1] > 0.0:
+            five.add((32 * rt * wm, 32 * ct, wk))
+    return four, five
+
+
+def test_gpu_tests_run_every_workgroup(B):
+    from tests import test_codes_gpu as G
+    few = {(16 * mt, 8 * ch, 16 // mt) for mt in (1, 2, 4, 8) for ch in (1, 2)}
+    four, five = built_tiles()
+    assert len(four) == 8 and len(five) == 5
+    for form, M, K, N, workgroup in G.WORKGROUPS:
+        assert B.query_matrix_plan(form, M, K, N)[:3] == workgroup, (form, M, K, N)
+        assert M % workgroup[0] and N % workgroup[1], (form, M, K, N)
+    run = {form: {w for f, _, _, _, w in G.WORKGROUPS if f == form} for form in ("codes", "g5", "mixed")}
+    assert run["codes"] == few | four and run["g5"] == few | five and run["mixed"] >= five
+    # the tile without parts of K, also at sizes whose outputs are stored past the caches
+    assert any(w == (256, 128, 1) and 4 * M * N >= 16 << 20 for _, M, _, N, w in G.WORKGROUPS)
+
+
+def test_gpu_tests_run_two_chunks_up_to_their_largest_k(B):
+    from tests import test_codes_gpu as G
+    for shapes, form, largest in ((G.FEW_TOKENS, "codes", 7168), (G.FEW_TOKENS_FIVE, "mixed", 7360)):
+        plans = {s: B.query_matrix_plan(form, *s) for s in shapes}
+        two = [s for s, p in plans.items() if p and p[1] == 16]
+        assert largest - 4 <= max(K for _, K, _ in two) <= largest and largest in {K for _, K, _ in two}
+        assert any(largest < K <= largest + 4 and N > 8 and plans[M, K, N][1] == 8 for M, K, N in shapes)      # one beyond: one chunk
+        assert any(K >= largest - 4 and (N + 7) // 8 % 2 == 0 and N % 8 for _, K, N in two)                    # a partly filled second chunk
+        assert any((N + 7) // 8 % 2 == 1 for _, _, N in two)                                                    # an absent one
