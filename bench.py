@@ -115,6 +115,9 @@ class Case:
         self.ws32 = torch.empty(max(L.vlut_workspace_bytes_f32(self.M, self.K, self.N), 16), dtype=torch.uint8, device="cuda")
         self.plan32 = B.query_plan_f32(self.M, self.K, self.N)
         self.kernel32 = B.query_kernel("f32", self.M, self.K, self.N)
+        plan = B.query_matrix_plan("f32", self.M, self.K, self.N)
+        if plan and plan[1] <= 16 and self.kernel32 != "matrix_few_tokens":      # behind the quantiser (either name can mean it)
+            self.kernel32 = "matrix_few_codes"
         rows_ptr = None if self.w_rows is None else self.w_rows.data_ptr()
         self._fargs = [(pk.data_ptr(), self.w_scale, rows_ptr, self.x.data_ptr(), self.x.stride(0), self.M, self.K, self.N,
                         self.y.data_ptr(), self.y.stride(0), None, None, self.ws32.data_ptr(), self.ws32.numel())
@@ -460,6 +463,7 @@ def main():
         g5 = {"what": "vlut_mpgemm_mixed on the same weights (first 20*floor(K/20) features 5 per byte, the rest 4 per byte)",
               "ms": ms_mx, "packed_weight_bytes": case.poolx[0].numel(), "time_over_2bit": ms_mx / ms_gemm}
     kernel_name = {"matrix_few_tokens": "decode_kernel (few tokens: quantisation, unpacking, INT8 matrix cores and scale in one launch)",
+                   "matrix_few_codes": "decode_codes_kernel (few tokens from INT8 codes: unpacking, INT8 matrix cores and scale)",
                    "matrix": "gemm_kernel (packed bytes unpacked in registers, INT8 matrix cores, scale)",
                    "few_tokens": "narrow_kernel (few tokens: table build, lookups and scale)",
                    "lookup": "lookup_kernel (LDS table build, lookup-accumulate, scale)"}[head["kernel"]]

@@ -24,10 +24,10 @@ typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
 // i receives the eight values of token i.  Which k a row pointer names is free, so the plane order costs nothing.
 // Chunks of eight tokens are pitched so that the 16 eight-byte rows of a read lie in distinct banks.
 //
-// What bounds it (rates of this chip, measured): power.  14.2 ns per v_mfma_i32_32x32x32_i8 and SIMD on zeros, 17 to 18 on codes and
-// ternary weights (1.9 GHz, 3.8 POP/s), 20.5 with four VALU instructions beside each; LDS serves transposing reads at 183 and
-// writes at 71 bytes per clock.  With CT = 4 a wave spends 3.3 unpacking instructions per matrix instruction, hence the wide token
-// tile.  14336 x 4096 x 512: 32.7 us, of which 22 in the K loop.
+// What bounds it (rates of this chip, measured): power.  13.5 ns per v_mfma_i32_32x32x32_i8 and SIMD on zeros (2.38 GHz), 16.8 on codes and
+// ternary weights (1.95 GHz, 4.0 POP/s), 18.5 with four byte permutes beside each (1.88 GHz, 3.6 POP/s); LDS serves transposing reads at
+// 183 and writes at 71 bytes per clock.  With CT = 4 a wave spends 3.3 unpacking instructions per matrix instruction, hence the wide
+// token tile.  14336 x 4096 x 512: 32.7 us, of which 22 in the K loop.
 // ---------------------------------------------------------------------------------------------
 struct GemmParams {
     const uint8_t* packed;
@@ -414,12 +414,18 @@ __global__ void __launch_bounds__(64 * WM * WK, 2) gemm_kernel(const GemmParams 
     }
 }
 
-// The tile shapes that are built and what a launch costs with them, in us, fitted (rms 2 to 4 %) to 4100 and 1700 shapes of 200 to 14336
-// rows, K = 256 to 14336 and 16 to 1024 tokens: base + n / per_unit * fixed + M * N / 10^6 * store + passes of the K loop *
-// (lat + n * pass), n workgroups per compute unit.  First value four, second five weights per byte; `pass` is one macro step of every K group.  The tile of
-// the least cost is within 0.4 % of the fastest on average (2 % of the shapes beyond 5 %, worst 19 %).
+// The tile shapes that are built and what a launch costs with them, in us, fitted (rms 2 to 4 %) to launches back to back of 4100 and 1700
+// shapes of 200 to 14336 rows, K = 256 to 14336 and 16 to 1024 tokens: base + n / per_unit * fixed + M * N / 10^6 * store + passes of the K
+// loop * (lat + n * pass), n workgroups per compute unit.  First value four, second five weights per byte; `pass` is one macro step of every
+// K group.  The tile of the least cost is within 0.4 % of the fastest on average (2 % of the shapes beyond 5 %, worst 19 %).  It ranks tiles;
+// as a time it is less good than the fit: against graph replays, whose launches are shorter, of 185 other shapes 7 % too long on average (rms
+// 11 %), 8 % too short above 5 * 10^9 weights times tokens (4096 x 14336 x 512: 29.8 for 36.0), and its terms are a fit's, not a model's
+// (256 rows without parts of K: all of the launch in `base`, none of the store in `fixed`).
 // With one K group two workgroups of four waves share a compute unit, and one stores while the other multiplies: 13824 x 2560 x 1024
 // 45.7 -> 42.0 us; 128 rows x 64 tokens: 4096 x 14336 x 512 40.1 -> 36.0 us.
+// Five weights per byte take more registers than four: 64 x 64 133 per lane, so that one workgroup has a unit to itself (per_unit), 256 x 128
+// all 256 and 20 bytes of scratch (at most 2 % of a launch: 13620 x 260 x 281 11.4 -> 11.5 us against the unpacking before, which did
+// without; 8 % faster than with that on average of 31 shapes).
 struct GemmTile {
     int rt, ct, wm, wk;
     int per_unit[2];               // workgroups that share a compute unit (what a workgroup costs besides its K loop overlaps)
@@ -431,7 +437,7 @@ constexpr GemmTile kGemmTiles[] = {
     {2, 4, 4, 2, {1, 1}, {3.70, 4.94}, {4.43, 3.47}, {0.681, 0.760}, {0.000, 0.000}, {1.123, 1.406}},
     {2, 4, 4, 1, {1, 1}, {9.15, 0.00}, {0.00, 0.00}, {0.710, 0.000}, {0.200, 0.000}, {0.489, 0.000}},      // (five weights: spills)
     {1, 4, 4, 2, {1, 1}, {2.95, 3.14}, {2.54, 2.54}, {0.753, 0.834}, {0.000, 0.000}, {0.693, 0.890}},
-    {1, 4, 2, 4, {1, 1}, {2.19, 0.00}, {3.28, 0.00}, {0.785, 0.000}, {0.000, 0.000}, {0.881, 0.000}},      // long K; (five weights: more LDS than there is)
+    {1, 4, 2, 4, {1, 1}, {2.19, 0.00}, {3.28, 0.00}, {0.785, 0.000}, {0.000, 0.000}, {0.881, 0.000}},      // few shapes (one in 10^4): long K; (five weights: more LDS than there is)
     {2, 2, 2, 4, {1, 1}, {2.21, 0.00}, {2.85, 0.00}, {0.721, 0.000}, {0.000, 0.000}, {0.829, 0.000}},
     {1, 2, 2, 4, {2, 1}, {3.01, 2.04}, {1.06, 2.13}, {1.036, 0.921}, {0.000, 0.000}, {0.546, 0.731}},
     {1, 1, 2, 4, {2, 2}, {3.24, 2.78}, {0.26, 0.89}, {1.300, 1.345}, {0.045, 0.070}, {0.350, 0.486}},

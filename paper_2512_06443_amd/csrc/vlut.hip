@@ -686,9 +686,9 @@ double gemm_best_cost(int gw, int64_t M, int64_t K, int64_t N) {
 }
 
 // decode_codes_kernel for a few tokens: eight or sixteen per workgroup (ch chunks) and 16 * mt rows; ch = 0: not this kernel.  Its time in
-// us, launches back to back, fitted (rms 3.7 %) to 18000 launches over 4100 shapes of 200 to 14336 rows, K = 256 to 14336 and 16 to 1024
-// tokens: a launch and two trips to memory, then K times what a workgroup copies and unpacks, weights beyond 27 MB from further
-// away, the store; beyond one workgroup per compute unit further rounds, shorter where two of them share a unit: their LDS fits and
+// us, launches back to back in a stream (graph replays: 0.5 to 0.9 less), fitted (rms 3.7 %) to 18000 launches over 4100 shapes of 200 to 14336
+// rows, K = 256 to 14336 and 16 to 1024 tokens: a launch and two trips to memory, then K times what a workgroup copies and unpacks,
+// weights beyond 27 MB from further away, the store; beyond one workgroup per compute unit further rounds, shorter where two of them share a unit: their LDS fits and
 // their 16 waves each take at most 64 registers (four weights per byte: 60 to 62; five: 75 to 77, never two).  Five weights per byte cost the
 // same otherwise (us, gemm_kernel / this one: 4096 x 4096 x 32 mixed 6.6 / 5.8, 4096 x 4000 x 16 6.5 / 4.8, 2560 x 6900 x 8 7.7 / 4.8, but
 // 13820 x 2560 x 64 7.7 / 11.9, 3079 x 360 x 233 4.8 / 6.7, 8624 x 1640 x 170 11.0 / 13.9, 12659 x 2020 x 98 12.0 / 15.0).
@@ -738,10 +738,10 @@ double lookup_us(const Plan& pl, int64_t M, int64_t K, int64_t N) {
 }
 
 // Few rows and tokens with a K that decode_codes_kernel does not hold leave the matrix-core path a handful of workgroups, while the lookup
-// kernel can split K over many (with the partial sums in the workspace).  us, lookup / gemm_kernel: 16 x 65532 x 33 23.6 / 34.1, 16 x 32768
-// x 33 14.7 / 18.7, 100 x 24000 x 72 13.8 / 15.4, 640 x 30000 x 33 18.6 / 18.3, 2560 x 20480 x 16 15.8 / 13.5.  The lookup kernel keeps a call
-// up to 1.25 times gemm_kernel's fitted time: that is where the line has been since the matrix cores took the others, and queries
-// name the kernel.
+// kernel can split K over many (with the partial sums in the workspace).  us, lookup / gemm_kernel: 16 x 65532 x 33 23.3 / 33.5, 16 x 32768
+// x 33 14.3 / 18.4, 64 x 16384 x 128 10.3 / 10.7, 100 x 24000 x 72 13.4 / 14.7; but 640 x 30000 x 33 18.5 / 17.9, 2048 x 36000 x 20 22.8 / 20.8,
+// 1280 x 65532 x 64 43.3 / 39.0, 2560 x 20480 x 16 15.0 / 12.6.  The lookup kernel keeps a call up to 1.25 times gemm_kernel's fitted time: that
+// is where the line was before gemm_kernel unpacked by permutes, and from about 500 rows on it is now up to a fifth too far out.
 bool matrix_cores_take(const Plan& pl, int64_t M, int64_t K, int64_t N) {
     if (lookup_plan_forced()) return false;
     return decode_codes_fits(4, 1, K) || lookup_us(pl, M, K, N) >= 1.25 * gemm_best_cost(4, M, K, N);

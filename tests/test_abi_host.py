@@ -419,8 +419,9 @@ def test_bench_line_is_one_line_that_fits(L):
 
 
 def test_long_rows_of_few_outputs_take_the_faster_kernel(L):
-    """INT8 codes with a long K: the side of the rule on which the measured times (us, lookup kernel with split-K / matrix
-    cores) put a shape, on both sides of 4096 outputs."""
+    """INT8 codes with a long K: the side of the rule on which the times measured when its line was drawn (us, lookup kernel with
+    split-K / matrix cores) put a shape, on both sides of 4096 outputs.  gemm_kernel has become faster since: the comment at the rule
+    has both sides as they are now."""
     L.vlut_query_kernel.argtypes = [ci, i64, i64, i64]
     lookup, matrix = 1, 3
     measured = [((16, 65532, 33), 23.8, 45.0), ((64, 16384, 40), 10.8, 14.0), ((64, 16384, 128), 10.85, 14.06), ((200, 16384, 48), 11.94, 14.15),
