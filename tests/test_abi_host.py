@@ -446,7 +446,8 @@ def test_one_token_on_many_rows_takes_the_table_kernel(L):
 
 
 def test_nine_to_sixteen_tokens_on_few_rows_take_the_faster_kernel(L):
-    """From fp32: the side of the rule on which the measured times (us, table kernel / matrix cores) put a shape."""
+    """From fp32: the side of the rule on which the measured times (us, table kernel / matrix cores in one launch) put a shape.  The
+    rule does not weigh two launches: the comment at it has their times."""
     L.vlut_query_kernel.argtypes = [ci, i64, i64, i64]
     few, matrix_few = 2, 4
     measured = [((4, 6552, 9), 10.57, 11.52), ((100, 4680, 14), 9.52, 10.3), ((100, 4096, 16), 8.79, 9.15), ((640, 4680, 14), 9.65, 10.39),
