@@ -186,6 +186,22 @@ int vlut_mpgemm(const uint8_t* packed, float w_scale, const int8_t* a_q, const f
                 int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * vlut_mpgemm, vlut_mpgemm_g5 and vlut_mpgemm_mixed (below) for callers that allocate a workspace for each call: the same calls with
+ * the same numbers and errors, except that the workspace may be NULL where the kernel that serves the call leaves it alone.
+ * vlut_workspace_used* tells how many of the bytes of vlut_workspace_bytes* are used (operands aligned to 16 bytes): all or none.
+ * A workspace that is handed over has to have the full size.
+ */
+size_t vlut_workspace_used(int64_t M, int64_t K, int64_t N);
+size_t vlut_workspace_used_g5(int64_t M, int64_t K, int64_t N);
+size_t vlut_workspace_used_mixed(int64_t M, int64_t K, int64_t N);
+int vlut_mpgemm_lean(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, const int16_t* lut_or_null, int64_t M, int64_t K,
+                     int64_t N, float* y, int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream);
+int vlut_mpgemm_g5_lean(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K, int64_t N, float* y,
+                        int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream);
+int vlut_mpgemm_mixed_lean(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K, int64_t N, float* y,
+                           int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * vlut_mpgemm for callers that cannot allocate device memory or hand over a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels, same numbers as vlut_mpgemm with
  * lut_or_null == NULL; the split-K partial sums go to a scratch array that is part of the library's device image

@@ -34,7 +34,8 @@ EXPORTS = [
     "vlut_build_lut_token_outer", "vlut_mpgemm_token_outer",
     "vlut_mixed_k5", "vlut_packed_weight_bytes_mixed", "vlut_workspace_bytes_mixed", "vlut_pack_weights_mixed",
     "vlut_mpgemm_mixed", "vlut_static_scratch_bytes", "vlut_mpgemm_static", "vlut_query_lookup_waves",
-    "vlut_query_kernel", "vlut_query_matrix_plan",
+    "vlut_query_kernel", "vlut_query_matrix_plan", "vlut_workspace_used", "vlut_workspace_used_g5", "vlut_workspace_used_mixed",
+    "vlut_mpgemm_lean", "vlut_mpgemm_g5_lean", "vlut_mpgemm_mixed_lean",
 ]
 
 _lib = None
@@ -68,6 +69,11 @@ def lib() -> ctypes.CDLL:
         gemm_args = [p, cf, p, p, p, i64, i64, i64, p, i64, p, p, sz, p]
         L.vlut_mpgemm.argtypes, L.vlut_mpgemm.restype = gemm_args, ci
         L.vlut_mpgemm_mfma.argtypes, L.vlut_mpgemm_mfma.restype = gemm_args, ci
+        L.vlut_mpgemm_lean.argtypes, L.vlut_mpgemm_lean.restype = gemm_args, ci
+        for f in (L.vlut_workspace_used, L.vlut_workspace_used_g5, L.vlut_workspace_used_mixed):
+            f.argtypes, f.restype = [i64, i64, i64], sz
+        for f in (L.vlut_mpgemm_g5_lean, L.vlut_mpgemm_mixed_lean):
+            f.argtypes, f.restype = [p, cf, p, p, i64, i64, i64, p, i64, p, p, sz, p], ci
         L.vlut_mpgemm_rows.argtypes, L.vlut_mpgemm_rows.restype = [p, p] + list(gemm_args[2:]), ci
         L.vlut_packed_weight_bytes_g5.argtypes, L.vlut_packed_weight_bytes_g5.restype = [i64, i64], sz
         L.vlut_packed_offset_g5.argtypes, L.vlut_packed_offset_g5.restype = [i64, i64, i64, i64], sz
@@ -103,11 +109,13 @@ def lib() -> ctypes.CDLL:
 # The frequent calls as native code (csrc/torch_calls.cpp): the same arguments, outputs and library call without ctypes and without
 # torch's Python layer.  Each returns None for arguments it leaves to the Python form below it (which also raises every
 # error), an int status or the tuple of outputs.  None here: not built, or built for another torch; the Python form serves then.
-# Host time of a call, Python / native form, us (256 x 256, eight tokens; the launch alone is 2.5 to 3): mpgemm_f32 7.6 / 4.3, with y and
-# workspace given 5.5 / 3.5, quantize_act 7.9 / 5.3, mpgemm 7.6 / 4.8.
+# The products take the lean form of the call: no workspace is allocated where the kernel leaves it alone (0.75 us each).
+# Host time of a call, Python / native form, us (640 x 2560, four tokens; the launch alone is 2.2): quantize_act 7.9 / 4.9,
+# mpgemm 7.6 / 4.4, with y and workspace given 5.5 / 3.4, mpgemm_g5 and mpgemm_mixed 4.5, mpgemm_f32 7.6 / 4.4; with a workspace for
+# each call, a launch by <<< >>> and the rules worked out anew 5.3, 4.6, 3.6, 5.9 and 4.5.
 _native = None
-_NATIVE_ORDER = ("vlut_quantize_act", "vlut_mpgemm", "vlut_workspace_bytes", "vlut_mpgemm_f32", "vlut_workspace_bytes_f32", "vlut_mpgemm_g5",
-                 "vlut_workspace_bytes_g5", "vlut_mpgemm_mixed", "vlut_workspace_bytes_mixed", "vlut_pack_weights",
+_NATIVE_ORDER = ("vlut_quantize_act", "vlut_mpgemm_lean", "vlut_workspace_used", "vlut_mpgemm_f32", "vlut_workspace_bytes_f32", "vlut_mpgemm_g5_lean",
+                 "vlut_workspace_used_g5", "vlut_mpgemm_mixed_lean", "vlut_workspace_used_mixed", "vlut_pack_weights",
                  "vlut_packed_weight_bytes", "vlut_pack_weights_g5", "vlut_packed_weight_bytes_g5", "vlut_pack_weights_mixed",
                  "vlut_packed_weight_bytes_mixed")
 

@@ -22,14 +22,14 @@ namespace {
 
 struct Api {                                   // addresses inside the loaded libvlut.so, in the order of binding._NATIVE_ORDER
     decltype(&vlut_quantize_act) quantize_act;
-    decltype(&vlut_mpgemm) mpgemm;
-    decltype(&vlut_workspace_bytes) workspace_bytes;
+    decltype(&vlut_mpgemm_lean) mpgemm;
+    decltype(&vlut_workspace_used) workspace;
     decltype(&vlut_mpgemm_f32) mpgemm_f32;
     decltype(&vlut_workspace_bytes_f32) workspace_bytes_f32;
-    decltype(&vlut_mpgemm_g5) mpgemm_g5;
-    decltype(&vlut_workspace_bytes_g5) workspace_bytes_g5;
-    decltype(&vlut_mpgemm_mixed) mpgemm_mixed;
-    decltype(&vlut_workspace_bytes_mixed) workspace_bytes_mixed;
+    decltype(&vlut_mpgemm_g5_lean) mpgemm_g5;
+    decltype(&vlut_workspace_used_g5) workspace_g5;
+    decltype(&vlut_mpgemm_mixed_lean) mpgemm_mixed;
+    decltype(&vlut_workspace_used_mixed) workspace_mixed;
     decltype(&vlut_pack_weights) pack_weights;
     decltype(&vlut_packed_weight_bytes) packed_weight_bytes;
     decltype(&vlut_pack_weights_g5) pack_weights_g5;
@@ -143,15 +143,16 @@ PyObject* py_quantize_act(PyObject*, PyObject* const* o, Py_ssize_t n) {
     });
 }
 
-// What mpgemm, mpgemm_g5 and mpgemm_mixed have in common: (packed, w_scale, a_q, a_scale, M, y, acc or None, want_acc, workspace or None)
+// What mpgemm, mpgemm_g5 and mpgemm_mixed have in common: (packed, w_scale, a_q, a_scale, M, y, acc or None, want_acc, workspace or None).
+// `used` tells what the call needs of operands aligned to 16 bytes; others are left to the Python form.
 template <class Bytes, class Call>
-PyObject* product(PyObject* const* o, size_t least, Bytes workspace_bytes, Call call) {
+PyObject* product(PyObject* const* o, Bytes used, Call call) {
     return guarded([&]() -> PyObject* {
         const at::Tensor *packed = plain(o[0]), *q = plain(o[2]), *s = plain(o[3]), *gy, *gacc, *gws;
         float w_scale;
         int64_t M;
         if (!packed || !q || !s || q->dim() < 2 || s->dim() < 1 || !real(o[1], w_scale) || !whole(o[4], M) || M < 0 || !output(o[5], gy) ||
-            !optional(o[6], gacc) || !optional(o[8], gws))
+            !optional(o[6], gacc) || !optional(o[8], gws) || ((uintptr_t)packed->data_ptr() | (uintptr_t)q->data_ptr()) % 16 != 0)
             Py_RETURN_NONE;
         const int64_t K = q->size(1), N = s->size(0);
         const int want = PyObject_IsTrue(o[7]);
@@ -165,8 +166,8 @@ PyObject* product(PyObject* const* o, size_t least, Bytes workspace_bytes, Call 
             if (!gy) y = make({N, M}, at::kFloat, q->device());
             if (!gacc && want) acc = make({M, N}, at::kInt, q->device());
             if (!gws) {
-                const size_t need = workspace_bytes(M, K, N);
-                if (need || least) ws = make({(int64_t)(need > least ? need : least)}, at::kByte, q->device());
+                const size_t need = used(M, K, N);
+                if (need) ws = make({(int64_t)need}, at::kByte, q->device());
             }
             rc = call(ptr<uint8_t>(*packed), w_scale, ptr<int8_t>(*q), ptr<float>(*s), M, K, N, ptr<float>(y), y.stride(0), ptr<int32_t>(acc),
                       ptr<void>(ws), ws.defined() ? bytes_of(ws) : 0, stream());
@@ -177,18 +178,18 @@ PyObject* product(PyObject* const* o, size_t least, Bytes workspace_bytes, Call 
 
 PyObject* py_mpgemm(PyObject*, PyObject* const* o, Py_ssize_t n) {
     if (!ordinary(n, 9)) Py_RETURN_NONE;
-    return product(o, 0, g_api.workspace_bytes, [](const uint8_t* p, float w, const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N, float* y,
+    return product(o, g_api.workspace, [](const uint8_t* p, float w, const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N, float* y,
                                                    int64_t ldy, int32_t* acc, void* ws, size_t bytes, void* st) {
         return g_api.mpgemm(p, w, q, s, nullptr, M, K, N, y, ldy, acc, ws, bytes, st);
     });
 }
 PyObject* py_mpgemm_g5(PyObject*, PyObject* const* o, Py_ssize_t n) {
     if (!ordinary(n, 9)) Py_RETURN_NONE;
-    return product(o, 0, g_api.workspace_bytes_g5, g_api.mpgemm_g5);
+    return product(o, g_api.workspace_g5, g_api.mpgemm_g5);
 }
 PyObject* py_mpgemm_mixed(PyObject*, PyObject* const* o, Py_ssize_t n) {
     if (!ordinary(n, 9)) Py_RETURN_NONE;
-    return product(o, 16, g_api.workspace_bytes_mixed, g_api.mpgemm_mixed);
+    return product(o, g_api.workspace_mixed, g_api.mpgemm_mixed);
 }
 
 // mpgemm_f32(packed, w_scale, x, M, y, want_acc, want_scales, workspace)

@@ -82,6 +82,18 @@ bool allow_dynamic_lds(const void* kfn, int bytes, std::atomic<unsigned>& done_m
     return true;
 }
 
+// A launch by the runtime's call itself: <<< >>> (hipLaunchKernelGGL) hands the same arguments over through a thread's stack of
+// configurations first, 2.35 us of the host against 2.15.
+template <class T>
+struct AsIs { using type = T; };
+template <class... Args>
+int launch(void (*kfn)(Args...), dim3 grid, int threads, int lds, hipStream_t stream, typename AsIs<Args>::type... args) {
+    void* list[] = {(void*)&args...};
+    if (hipLaunchKernel((const void*)kfn, grid, dim3((unsigned)threads), list, (size_t)lds, stream) == hipSuccess) return VLUT_OK;
+    (void)hipGetLastError();                     // (reported here: not once more to whoever asks next)
+    return VLUT_ERR_DEVICE;
+}
+
 struct Plan {
     int Jlog, R, S;
     int BW;      // build waves of the 16-wave workgroup (4, 2 or 1); the other 16 - BW waves look up
@@ -281,8 +293,7 @@ int launch_lookup_t(const LookupParams& p, hipStream_t stream) {
     else q.out_vec = !q.y || (((uintptr_t)q.y % 16 == 0) && (q.ldy % 4 == 0));
     q.magic_S = q.S > 1 ? (unsigned)((1ull << 32) / (unsigned)q.S) : 0xffffffffu;
     q.magic_tiles_n = q.tiles_n > 1 ? (unsigned)((1ull << 32) / (unsigned)q.tiles_n) : 0xffffffffu;
-    hipLaunchKernelGGL(kfn, dim3(grid), dim3(kThreads), lds, stream, q);
-    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+    return launch(kfn, dim3(grid), kThreads, lds, stream, q);
 }
 
 // Which instances of the lookup kernel are compiled: the streamed kernels for every supported R (the INT32-widening
@@ -329,11 +340,7 @@ int launch_splitk_reduce(const int32_t* ws, int S, int64_t M, int64_t N, float w
                      (!w_rows || (uintptr_t)w_rows % 16 == 0);
     const size_t total = (size_t)(vec ? M / 4 : M) * (size_t)N;
     const dim3 grid((unsigned)((total + 255) / 256));
-    if (vec) hipLaunchKernelGGL(splitk_reduce_kernel<4>, grid, dim3(256), 0, s, ws, S, (int)M, (int)N, w_scale, w_rows,
-                                a_scale, y, ldy, acc);
-    else hipLaunchKernelGGL(splitk_reduce_kernel<1>, grid, dim3(256), 0, s, ws, S, (int)M, (int)N, w_scale, w_rows,
-                            a_scale, y, ldy, acc);
-    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+    return launch(vec ? splitk_reduce_kernel<4> : splitk_reduce_kernel<1>, grid, 256, 0, s, ws, S, (int)M, (int)N, w_scale, w_rows, a_scale, y, ldy, acc);
 }
 
 int check_mpgemm_args(const uint8_t* packed, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K,
@@ -400,8 +407,7 @@ int launch_narrow_t(const NarrowParams& p, int grid, hipStream_t stream) {
     if (lds > max_lds) return VLUT_ERR_UNSUPPORTED;
     static std::atomic<unsigned> attr_done{0};   // one bit per device: the attribute belongs to the device's copy
     if (!allow_dynamic_lds((const void*)kfn, max_lds, attr_done)) return VLUT_ERR_DEVICE;
-    hipLaunchKernelGGL(kfn, dim3(grid), dim3(kThreads), lds, stream, p);
-    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+    return launch(kfn, dim3(grid), kThreads, lds, stream, p);
 }
 
 template <int NTOK, bool FUSED>
@@ -432,9 +438,7 @@ template <int GW>
 int launch_pack(const int8_t* w, int64_t M, int64_t ldw, int64_t K, uint8_t* packed, hipStream_t s) {
     const int G = (int)(K / GW), KCn = (G + 15) / 16, RGtotal = (int)((M + 3) / 4);
     const size_t threads = (size_t)RGtotal * KCn * 16;
-    hipLaunchKernelGGL(pack_kernel<GW>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, w, (int)M, ldw, G, KCn, RGtotal,
-                       (unaligned_u32*)packed, g_pack_flag);
-    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+    return launch(pack_kernel<GW>, dim3((unsigned)((threads + 255) / 256)), 256, 0, s, w, (int)M, ldw, G, KCn, RGtotal, (unaligned_u32*)packed, g_pack_flag);
 }
 
 // The first K5 values of every row five to a byte, the others four to a byte behind them; then waits for the flag of the
@@ -493,7 +497,7 @@ struct F32Layout {
 
 size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-F32Layout f32_layout(int64_t M, int64_t K, int64_t N) {
+F32Layout work_out_f32_layout(int64_t M, int64_t K, int64_t N) {
     F32Layout L;
     std::memset(&L, 0, sizeof(L));
     L.decode = decode_applies(M, K, N);
@@ -524,6 +528,19 @@ F32Layout f32_layout(int64_t M, int64_t K, int64_t N) {
     L.plan = pl;
     L.total = L.off_ws + (pl.S > 1 ? (size_t)pl.S * (size_t)M * (size_t)N * sizeof(int32_t) : 0);
     return L;
+}
+
+// (kept per shape like the routes from codes: asked for twice per call)
+struct F32Entry {
+    int64_t M, K, N;
+    F32Layout layout;
+};
+constexpr int kF32Entries = 16;
+thread_local F32Entry t_f32[kF32Entries];
+const F32Layout& f32_layout(int64_t M, int64_t K, int64_t N) {
+    F32Entry& e = t_f32[(unsigned)(M * 5 + K * 3 + N * 7 + (M >> 5) + (K >> 5)) % kF32Entries];
+    if (e.M != M || e.K != K || e.N != N) e = {M, K, N, work_out_f32_layout(M, K, N)};
+    return e.layout;
 }
 
 // ---- 1.60-bit (g = 5) host side
@@ -597,8 +614,7 @@ int launch_lookup5_t(const Lookup5Params& p, int grid, hipStream_t stream) {
     Lookup5Params q = p;
     if (q.S > 1 || q.partial) q.out_vec = ((uintptr_t)q.ws % 16 == 0) && (q.M % 4 == 0);
     else q.out_vec = !q.y || (((uintptr_t)q.y % 16 == 0) && (q.ldy % 4 == 0));
-    hipLaunchKernelGGL(kfn, dim3(grid), dim3(kThreads), kLds5Bytes, stream, q);
-    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+    return launch(kfn, dim3(grid), kThreads, kLds5Bytes, stream, q);
 }
 
 template <bool NEED32>
@@ -635,30 +651,27 @@ int launch_lookup5_r(int R, const Lookup5Params& p, int grid, hipStream_t stream
 template <bool VEC>
 int launch_quantize(const float* x, int64_t N, int64_t K, int64_t ldx, int8_t* a_q, float* a_scale, int chunks, hipStream_t s) {
     const unsigned blocks8 = (unsigned)((chunks + 7) / 8);       // groups of eight chunks, one per XCD
-    auto launch = [&](auto kfn, unsigned grid, int threads) -> int {
-        hipLaunchKernelGGL(kfn, dim3(grid), dim3(threads), 0, s, x, (int)N, (int)K, ldx, a_q, a_scale, chunks);
-        return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
-    };
-    if (K <= 256) return launch(quantize_token_kernel<64, 1, VEC>, blocks8 * 64, 64);
-    if (K <= 1024) return launch(quantize_token_kernel<256, 1, VEC>, blocks8 * 64, 256);
+    auto run = [&](auto kfn, unsigned grid, int threads) { return launch(kfn, dim3(grid), threads, 0, s, x, (int)N, (int)K, ldx, a_q, a_scale, chunks); };
+    if (K <= 256) return run(quantize_token_kernel<64, 1, VEC>, blocks8 * 64, 64);
+    if (K <= 1024) return run(quantize_token_kernel<256, 1, VEC>, blocks8 * 64, 256);
     if (N < (K <= 3072 ? 1536 : 768)) {
         constexpr int T = kTokThreads;
-        if (K <= 4096) return launch(quantize_token_kernel<T, 2, VEC>, blocks8 * 64, T);
-        if (K <= 8192) return launch(quantize_token_kernel<T, 4, VEC>, blocks8 * 64, T);
-        if (K <= 16384) return launch(quantize_token_kernel<T, 8, VEC>, blocks8 * 64, T);
-        return launch(quantize_token_kernel<T, 0, VEC>, blocks8 * 64, T);
+        if (K <= 4096) return run(quantize_token_kernel<T, 2, VEC>, blocks8 * 64, T);
+        if (K <= 8192) return run(quantize_token_kernel<T, 4, VEC>, blocks8 * 64, T);
+        if (K <= 16384) return run(quantize_token_kernel<T, 8, VEC>, blocks8 * 64, T);
+        return run(quantize_token_kernel<T, 0, VEC>, blocks8 * 64, T);
     }
     if (N >= 3584 && K <= 3072) {
-        if (K <= 1536) return launch(quantize_kernel<8, 3, VEC>, (unsigned)chunks, kQuantThreads);
-        if (K <= 2048) return launch(quantize_kernel<8, 4, VEC>, (unsigned)chunks, kQuantThreads);
-        return launch(quantize_kernel<8, 6, VEC>, (unsigned)chunks, kQuantThreads);
+        if (K <= 1536) return run(quantize_kernel<8, 3, VEC>, (unsigned)chunks, kQuantThreads);
+        if (K <= 2048) return run(quantize_kernel<8, 4, VEC>, (unsigned)chunks, kQuantThreads);
+        return run(quantize_kernel<8, 6, VEC>, (unsigned)chunks, kQuantThreads);
     }
-    if (K <= 2048) return launch(quantize_kernel<4, 2, VEC>, blocks8 * 16, kQuantThreads);
-    if (K <= 3072) return launch(quantize_kernel<4, 3, VEC>, blocks8 * 16, kQuantThreads);
-    if (K <= 4096) return launch(quantize_kernel<4, 4, VEC>, blocks8 * 16, kQuantThreads);
-    if (K <= 8192) return launch(quantize_kernel<4, 8, VEC>, blocks8 * 16, kQuantThreads);
-    if (K <= 14336) return launch(quantize_kernel<4, 14, VEC>, blocks8 * 16, kQuantThreads);
-    return launch(quantize_kernel<4, 0, VEC>, blocks8 * 16, kQuantThreads);
+    if (K <= 2048) return run(quantize_kernel<4, 2, VEC>, blocks8 * 16, kQuantThreads);
+    if (K <= 3072) return run(quantize_kernel<4, 3, VEC>, blocks8 * 16, kQuantThreads);
+    if (K <= 4096) return run(quantize_kernel<4, 4, VEC>, blocks8 * 16, kQuantThreads);
+    if (K <= 8192) return run(quantize_kernel<4, 8, VEC>, blocks8 * 16, kQuantThreads);
+    if (K <= 14336) return run(quantize_kernel<4, 14, VEC>, blocks8 * 16, kQuantThreads);
+    return run(quantize_kernel<4, 0, VEC>, blocks8 * 16, kQuantThreads);
 }
 
 // ---- matrix-core path (gemm_kernel): products with streamed tables, unless a plan of the lookup kernels is forced or a rule below says otherwise
@@ -764,8 +777,7 @@ int launch_gemm_t(const GemmParams& p, hipStream_t stream) {
     q.tiles_n = (q.N + t.tokens() - 1) / t.tokens();
     q.tiles = (q.M + t.rows() - 1) / t.rows() * q.tiles_n;
     q.per_xcd = (q.tiles + 7) / 8;
-    hipLaunchKernelGGL(kfn, dim3(8 * q.per_xcd), dim3(64 * t.wm * t.wk), lds, stream, q);
-    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+    return launch(kfn, dim3(8 * q.per_xcd), 64 * t.wm * t.wk, lds, stream, q);
 }
 
 template <int GW, int I = 0>
@@ -782,7 +794,7 @@ int launch_gemm_tile(int tile, const GemmParams& p, hipStream_t stream) {
 
 // K5 values of K five to a byte (0: none), the rest of K four to a byte behind them (at most 16 values if K5 > 0).
 int launch_gemm(const uint8_t* packed, float w_scale, const float* w_rows, const int8_t* a_q, const float* a_scale, int64_t M,
-                int64_t K, int64_t K5, int64_t N, float* y, int64_t ldy, int32_t* acc, hipStream_t stream) {
+                int64_t K, int64_t K5, int64_t N, float* y, int64_t ldy, int32_t* acc, hipStream_t stream, int tile) {
     GemmParams p;
     std::memset(&p, 0, sizeof(p));
     const int gw = K5 > 0 ? 5 : 4;
@@ -799,7 +811,6 @@ int launch_gemm(const uint8_t* packed, float w_scale, const float* w_rows, const
         p.packed4 = packed + (size_t)p.RGtotal * p.KCn * 64;
         p.KCn4 = (int)(((K - K5) / 4 + 15) / 16);
     }
-    const int tile = choose_gemm_tile(gw, M, p.macros, N);
     return gw == 5 ? launch_gemm_tile<5>(tile, p, stream) : launch_gemm_tile<4>(tile, p, stream);
 }
 
@@ -810,8 +821,7 @@ int launch_decode_t(const DecodeParams& p, hipStream_t stream) {
     if (lds > 160 * 1024) return VLUT_ERR_UNSUPPORTED;      // (cannot happen within decode_applies)
     static std::atomic<unsigned> attr_done{0};   // one bit per device: the attribute belongs to the device's copy
     if (!allow_dynamic_lds((const void*)kfn, 160 * 1024, attr_done)) return VLUT_ERR_DEVICE;
-    hipLaunchKernelGGL(kfn, dim3((unsigned)((p.M + 16 * MT - 1) / (16 * MT))), dim3(64 * kDecodeWaves), lds, stream, p);
-    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+    return launch(kfn, dim3((unsigned)((p.M + 16 * MT - 1) / (16 * MT))), 64 * kDecodeWaves, lds, stream, p);
 }
 
 template <int T>
@@ -840,8 +850,7 @@ int launch_codes_t(const DecodeParams& p, hipStream_t stream) {
     if (tiles * q.tiles_n >= ((int64_t)1 << 32) || tiles > INT32_MAX / 2) return VLUT_ERR_UNSUPPORTED;     // (cannot happen: codes_plan)
     q.tiles = (int)tiles;
     q.per_xcd = (q.tiles + 7) / 8;
-    hipLaunchKernelGGL(kfn, dim3((unsigned)(8 * q.per_xcd)), dim3(64 * kDecodeWaves), decode_codes_lds_bytes(GW, CH, q.K), stream, q);
-    return hipGetLastError() == hipSuccess ? VLUT_OK : VLUT_ERR_DEVICE;
+    return launch(kfn, dim3((unsigned)(8 * q.per_xcd)), 64 * kDecodeWaves, decode_codes_lds_bytes(GW, CH, q.K), stream, q);
 }
 
 template <int GW, int CH>
@@ -871,6 +880,99 @@ int launch_codes(const CodesPlan& pl, const uint8_t* packed, float w_scale, cons
         q.KCn4 = (int)(((K - K5) / 4 + 15) / 16);
     }
     return pl.ch == 1 ? launch_codes_mt<5, 1>(pl.mt, q, stream) : launch_codes_mt<5, 2>(pl.mt, q, stream);
+}
+
+// ---- what a product from INT8 codes runs and demands, worked out once per shape: the rules above and the plans of the lookup kernels
+// cost 0.4 us (2-bit) to 2 us (five weights per byte: its plan search twice) of a call of 5, so the last answers are kept per thread,
+// found by their shape, until a plan is forced or released.
+enum { kRouteTables = 0, kRouteCodes = 1, kRouteGemm = 2 };
+struct Route {
+    int64_t M, K, N;                             // M = 0: none kept here
+    int form, status;                            // status: VLUT_ERR_UNSUPPORTED where an override does not fit the shape
+    int kernel, tile;                            // tile of gemm_kernel
+    bool narrow;                                 // (2-bit) the few-token rule holds
+    CodesPlan codes;
+    Plan plan;                                   // of the lookup kernel (mixed: of the 2-bit part)
+    Plan5 plan5;
+    size_t demanded;                             // bytes of workspace that the call wants to see
+    size_t used() const { return kernel == kRouteTables ? demanded : 0; }
+};
+constexpr int kRoutes = 32;
+thread_local Route t_routes[kRoutes];
+void forget_routes() {
+    for (Route& r : t_routes) r.M = 0;
+    for (F32Entry& e : t_f32) e.M = 0;
+}
+
+bool mixed_plans(int64_t M, int64_t K, int64_t N, Plan5* p5, Plan* p4);
+
+// gw weights per byte in the main blob of Kmain values
+void matrix_route(Route& r, int gw, int64_t Kmain) {
+    r.codes = codes_plan_if_taken(gw, r.M, r.K, r.N, false);
+    r.kernel = r.codes.ch ? kRouteCodes : kRouteGemm;
+    if (!r.codes.ch) r.tile = choose_gemm_tile(gw, r.M, gemm_macros(gw, Kmain), r.N);
+}
+
+const Route& find_route(int form, int64_t M, int64_t K, int64_t N) {
+    Route& r = t_routes[(unsigned)(M * 5 + K * 3 + N * 7 + form + (M >> 5) + (K >> 5)) % kRoutes];
+    if (r.M == M && r.K == K && r.N == N && r.form == form) return r;
+    r = Route{};
+    r.M = M; r.K = K; r.N = N; r.form = form;
+    const size_t sums = (size_t)M * (size_t)N * sizeof(int32_t);
+    if (form == VLUT_FORM_CODES) {
+        r.narrow = narrow_applies(M, K, N, nullptr, false);
+        if (r.narrow) {
+            r.codes = codes_plan_if_taken(4, M, K, N, true);
+            r.kernel = r.codes.ch ? kRouteCodes : kRouteTables;
+            return r;
+        }
+        r.plan = choose_plan(M, K, N);
+        if (r.plan.R == 0) r.status = VLUT_ERR_UNSUPPORTED;
+        else if (matrix_cores_take(r.plan, M, K, N)) matrix_route(r, 4, K);
+        r.demanded = r.plan.S > 1 ? (size_t)r.plan.S * sums : 0;
+    } else if (form == VLUT_FORM_G5) {
+        r.plan5 = choose_plan5(M, K, N);
+        if (!plan5_valid(r.plan5, M, K, N)) r.status = VLUT_ERR_UNSUPPORTED;
+        else if (matrix_cores_take_g5(K)) matrix_route(r, 5, K);
+        r.demanded = r.plan5.S > 1 ? (size_t)r.plan5.S * sums : 0;
+    } else {
+        const int64_t K5 = (K / 20) * 20;
+        if (!mixed_plans(M, K, N, &r.plan5, &r.plan)) {
+            r.status = VLUT_ERR_UNSUPPORTED;
+            return r;
+        }
+        r.demanded = (size_t)(r.plan5.S + r.plan.S) * sums;
+        if (matrix_cores_take_mixed()) matrix_route(r, K5 > 0 ? 5 : 4, K5 > 0 ? K5 : K);
+    }
+    return r;
+}
+
+// The mixed packing as launches of the lookup kernels in partial-sum mode, then one exact INT32 sum + scale step.
+// Workspace: [S5 + S4][N][M] INT32.
+bool mixed_plans(int64_t M, int64_t K, int64_t N, Plan5* p5, Plan* p4) {
+    const int64_t K5 = (K / 20) * 20, K4 = K - K5;
+    if (K5 > 0) {
+        *p5 = choose_plan5(M, K5, N);
+        if (!plan5_valid(*p5, M, K5, N)) return false;
+    } else {
+        *p5 = Plan5{0, 0};
+    }
+    *p4 = K4 > 0 ? choose_plan(M, K4, N) : Plan{0, 0, 0, 0};
+    if (K4 > 0 && p4->R == 0) return false;              // the override of vlut_set_plan does not fit the 2-bit part
+    return true;
+}
+
+// The workspace of a call that demands r.demanded bytes (lean: r.used() if none is handed over)
+int check_workspace(const Route& r, const void* workspace, size_t bytes, bool lean) {
+    const size_t need = lean && !workspace ? r.used() : r.demanded;
+    if (need == 0) return VLUT_OK;
+    return !workspace ? VLUT_ERR_NULL : bytes < need ? VLUT_ERR_SMALL_BUFFER : VLUT_OK;
+}
+
+int launch_matrix_route(const Route& r, const uint8_t* packed, float w_scale, const float* w_rows, const int8_t* a_q, const float* a_scale, int64_t K5,
+                        float* y, int64_t ldy, int32_t* acc, hipStream_t s) {
+    if (r.kernel == kRouteCodes) return launch_codes(r.codes, packed, w_scale, w_rows, a_q, a_scale, r.M, r.K, K5, r.N, y, ldy, acc, s);
+    return launch_gemm(packed, w_scale, w_rows, a_q, a_scale, r.M, r.K, K5, r.N, y, ldy, acc, s, r.tile);
 }
 
 // ---- comparison path: tokens per workgroup from N, K split so that few tiles still give every CU a few workgroups
@@ -944,9 +1046,11 @@ size_t vlut_workspace_bytes(int64_t M, int64_t K, int64_t N) {
     if (!shape_ok(M, K, N)) return 0;
     // Where the few-token kernel serves the streamed path (no workspace), the materialised-table variant runs a
     // plan without split-K, so this one size serves both variants.
-    if (narrow_applies(M, K, N, nullptr, false)) return 0;
-    const Plan pl = choose_plan(M, K, N);
-    return pl.S > 1 ? (size_t)pl.S * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
+    return find_route(VLUT_FORM_CODES, M, K, N).demanded;
+}
+
+size_t vlut_workspace_used(int64_t M, int64_t K, int64_t N) {
+    return shape_ok(M, K, N) ? find_route(VLUT_FORM_CODES, M, K, N).used() : 0;
 }
 
 int vlut_set_plan(int J, int R, int waves, int split_k) {
@@ -964,6 +1068,7 @@ int vlut_set_plan(int J, int R, int waves, int split_k) {
     t_cache_next = 0;
     t_fcache_used = 0;
     t_fcache_next = 0;
+    forget_routes();
     return VLUT_OK;
 }
 
@@ -1054,44 +1159,46 @@ int vlut_mpgemm_token_outer(const uint8_t* packed, float w_scale, const float* a
 
 static int mpgemm_impl(const uint8_t* packed, float w_scale, const float* w_rows, const int8_t* a_q, const float* a_scale,
                        const int16_t* lut_or_null, int64_t M, int64_t K, int64_t N, float* y, int64_t ldy,
-                       int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream) {
+                       int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream, bool lean = false) {
     int rc = check_mpgemm_args(packed, a_q, a_scale, M, K, N, y, ldy, acc_or_null);
     if (rc != VLUT_OK) return rc;
     if (((uintptr_t)a_q) % 16 != 0) return VLUT_ERR_UNSUPPORTED;      // the [N/8][K][8] blocks are read 16 bytes at a time
     if (((uintptr_t)packed) % 16 != 0) return VLUT_ERR_UNSUPPORTED;   // packed tiles are read up to 16 bytes at a time
-    if (narrow_applies(M, K, N, lut_or_null, false)) {   // a few tokens: the workgroups sweep all of K, no workspace
-        const CodesPlan cp = codes_plan_if_taken(4, M, K, N, true);
-        if (cp.ch) return launch_codes(cp, packed, w_scale, w_rows, a_q, a_scale, M, K, 0, N, y, ldy, acc_or_null, (hipStream_t)stream);
-        const NarrowPlan np = narrow_plan(M, K, N);
-        NarrowParams q;
-        std::memset(&q, 0, sizeof(q));
-        q.packed = packed; q.a_q = a_q; q.a_scale = a_scale; q.w_rows = w_rows; q.y = y; q.acc = acc_or_null;
-        q.w_scale = w_scale; q.M = (int)M; q.K = (int)K; q.N = (int)N; q.G = (int)(K / 4);
-        q.KCn = (int)((K / 4 + 15) / 16); q.RGtotal = (int)((M + 3) / 4); q.ldy = (int)ldy; q.chunks = np.chunks;
-        return launch_narrow<false>(np, q, (hipStream_t)stream);
+    hipStream_t s = (hipStream_t)stream;
+    Plan pl;
+    if (!lut_or_null) {
+        const Route& r = find_route(VLUT_FORM_CODES, M, K, N);
+        if (r.status != VLUT_OK) return r.status;                     // the override of vlut_set_plan does not fit this shape
+        rc = check_workspace(r, workspace, workspace_bytes, lean);
+        if (rc != VLUT_OK) return rc;
+        if (r.kernel != kRouteTables) return launch_matrix_route(r, packed, w_scale, w_rows, a_q, a_scale, 0, y, ldy, acc_or_null, s);
+        if (r.narrow) {                                  // a few tokens: the workgroups sweep all of K, no workspace
+            const NarrowPlan np = narrow_plan(M, K, N);
+            NarrowParams q;
+            std::memset(&q, 0, sizeof(q));
+            q.packed = packed; q.a_q = a_q; q.a_scale = a_scale; q.w_rows = w_rows; q.y = y; q.acc = acc_or_null;
+            q.w_scale = w_scale; q.M = (int)M; q.K = (int)K; q.N = (int)N; q.G = (int)(K / 4);
+            q.KCn = (int)((K / 4 + 15) / 16); q.RGtotal = (int)((M + 3) / 4); q.ldy = (int)ldy; q.chunks = np.chunks;
+            return launch_narrow<false>(np, q, s);
+        }
+        pl = r.plan;
+    } else {
+        // A materialised table where the streamed path would take the few-token kernel (and vlut_workspace_bytes says
+        // 0): a plan without split-K, so that no workspace is needed here either.
+        const int max_S = narrow_applies(M, K, N, nullptr, false) ? 1 : 16;
+        pl = max_S == 1 ? search_plan(M, K, N, 1) : choose_plan(M, K, N);
+        if (pl.R != 0 && pl.BW != 4) pl = search_plan(M, K, N, max_S, true);
+        if (pl.R == 0) return VLUT_ERR_UNSUPPORTED;      // the override of vlut_set_plan does not fit this shape
+        pl.R = pl.R >= 4 ? 4 : (pl.R >= 2 ? 2 : 1);      // the materialised-table variant is built for these R and four build waves only
+        pl.BW = 4;
+        if (pl.S > 1) {
+            if (!workspace) return VLUT_ERR_NULL;
+            if (workspace_bytes < (size_t)pl.S * (size_t)M * (size_t)N * sizeof(int32_t)) return VLUT_ERR_SMALL_BUFFER;
+        }
     }
-    // A materialised table where the streamed path would take the few-token kernel (and vlut_workspace_bytes says
-    // 0): a plan without split-K, so that no workspace is needed here either.
-    Plan pl = (lut_or_null && narrow_applies(M, K, N, nullptr, false)) ? search_plan(M, K, N, 1) : choose_plan(M, K, N);
-    if (lut_or_null && pl.R != 0 && pl.BW != 4) pl = search_plan(M, K, N, narrow_applies(M, K, N, nullptr, false) ? 1 : 16, true);
-    if (pl.R == 0) return VLUT_ERR_UNSUPPORTED;          // the override of vlut_set_plan does not fit this shape
     const bool al = lut_or_null && (N % 8 == 0) && (((uintptr_t)lut_or_null) % 16 == 0);
     const int mode = lut_or_null ? kFromGlobal : kFast;
-    if (mode != kFast) {   // the materialised-table variant is built for these R and four build waves only
-        pl.R = pl.R >= 4 ? 4 : (pl.R >= 2 ? 2 : 1);
-        pl.BW = 4;
-    }
-    Derived d = derive(pl, M, K, N);
-    size_t ws_need = pl.S > 1 ? (size_t)pl.S * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
-    if (ws_need > 0) {
-        if (!workspace) return VLUT_ERR_NULL;
-        if (workspace_bytes < ws_need) return VLUT_ERR_SMALL_BUFFER;
-    }
-    if (!lut_or_null && matrix_cores_take(pl, M, K, N)) {
-        const CodesPlan cp = codes_plan_if_taken(4, M, K, N, false);
-        if (cp.ch) return launch_codes(cp, packed, w_scale, w_rows, a_q, a_scale, M, K, 0, N, y, ldy, acc_or_null, (hipStream_t)stream);
-        return launch_gemm(packed, w_scale, w_rows, a_q, a_scale, M, K, 0, N, y, ldy, acc_or_null, (hipStream_t)stream);
-    }
+    const Derived d = derive(pl, M, K, N);
     LookupParams p;
     std::memset(&p, 0, sizeof(p));
     p.packed = packed; p.a_q = a_q; p.a_scale = a_scale; p.lut = lut_or_null;
@@ -1102,7 +1209,6 @@ static int mpgemm_impl(const uint8_t* packed, float w_scale, const float* w_rows
     p.total_tiles = d.total; p.per_xcd = d.per_xcd;
     p.aligned8 = al ? 1 : 0;
     p.Ka = (int)K;
-    hipStream_t s = (hipStream_t)stream;
     rc = d.need32 ? launch_lookup_r<true>(pl.R, pl.BW, mode, p, s) : launch_lookup_r<false>(pl.R, pl.BW, mode, p, s);
     if (rc != VLUT_OK) return rc;
     if (pl.S > 1)
@@ -1115,6 +1221,11 @@ int vlut_mpgemm(const uint8_t* packed, float w_scale, const int8_t* a_q, const f
                 int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream) {
     return mpgemm_impl(packed, w_scale, nullptr, a_q, a_scale, lut_or_null, M, K, N, y, ldy, acc_or_null, workspace,
                        workspace_bytes, stream);
+}
+
+int vlut_mpgemm_lean(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, const int16_t* lut_or_null, int64_t M, int64_t K,
+                     int64_t N, float* y, int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream) {
+    return mpgemm_impl(packed, w_scale, nullptr, a_q, a_scale, lut_or_null, M, K, N, y, ldy, acc_or_null, workspace, workspace_bytes, stream, true);
 }
 
 size_t vlut_static_scratch_bytes(void) { return (size_t)VLUT_STATIC_SCRATCH_BYTES; }
@@ -1272,8 +1383,11 @@ int vlut_pack_weights_g5(const int8_t* w_ternary, int64_t M, int64_t K, uint8_t*
 
 size_t vlut_workspace_bytes_g5(int64_t M, int64_t K, int64_t N) {
     if (!shape5_ok(M, K, N)) return 0;
-    Plan5 pl = choose_plan5(M, K, N);
-    return pl.S > 1 ? (size_t)pl.S * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
+    return find_route(VLUT_FORM_G5, M, K, N).demanded;
+}
+
+size_t vlut_workspace_used_g5(int64_t M, int64_t K, int64_t N) {
+    return shape5_ok(M, K, N) ? find_route(VLUT_FORM_G5, M, K, N).used() : 0;
 }
 
 int vlut_set_plan_g5(int R, int split_k) {
@@ -1284,6 +1398,7 @@ int vlut_set_plan_g5(int R, int split_k) {
     }
     if (split_k < 0 || split_k > 16) return VLUT_ERR_UNSUPPORTED;
     t_forced5 = {R, split_k};
+    forget_routes();
     return VLUT_OK;
 }
 
@@ -1297,29 +1412,23 @@ int vlut_query_plan_g5(int64_t M, int64_t K, int64_t N, int* out3) {
     return VLUT_OK;
 }
 
-int vlut_mpgemm_g5(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K,
-                   int64_t N, float* y, int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes,
-                   void* stream) {
+static int mpgemm_g5_impl(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K, int64_t N, float* y,
+                          int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream, bool lean) {
     if (!shape5_ok(M, K, N)) return VLUT_ERR_SHAPE;
     if (!packed || !a_q || !a_scale) return VLUT_ERR_NULL;
     if (!y && !acc_or_null) return VLUT_ERR_NULL;
     if (y && (ldy < M || ldy > INT32_MAX)) return VLUT_ERR_SHAPE;
     if (((uintptr_t)a_q) % 8 != 0) return VLUT_ERR_UNSUPPORTED;       // 5 rows x 8 tokens are read 8 bytes at a time
-    Plan5 pl = choose_plan5(M, K, N);
-    if (!plan5_valid(pl, M, K, N)) return VLUT_ERR_UNSUPPORTED;
-    Derived5 d = derive5(pl, M, K, N);
-    size_t ws_need = pl.S > 1 ? (size_t)pl.S * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
-    if (ws_need > 0) {
-        if (!workspace) return VLUT_ERR_NULL;
-        if (workspace_bytes < ws_need) return VLUT_ERR_SMALL_BUFFER;
-    }
+    const Route& r = find_route(VLUT_FORM_G5, M, K, N);
+    if (r.status != VLUT_OK) return r.status;
     // the matrix-core path reads both operands 16 bytes at a time, so it wants the alignment and K % 4 == 0 (two activation
     // rows of a chunk are 16 bytes) that this call does not demand
-    if (matrix_cores_take_g5(K) && (uintptr_t)packed % 16 == 0 && (uintptr_t)a_q % 16 == 0) {
-        const CodesPlan cp = codes_plan_if_taken(5, M, K, N, false);
-        if (cp.ch) return launch_codes(cp, packed, w_scale, nullptr, a_q, a_scale, M, K, K, N, y, ldy, acc_or_null, (hipStream_t)stream);
-        return launch_gemm(packed, w_scale, nullptr, a_q, a_scale, M, K, K, N, y, ldy, acc_or_null, (hipStream_t)stream);
-    }
+    const bool matrix = r.kernel != kRouteTables && (uintptr_t)packed % 16 == 0 && (uintptr_t)a_q % 16 == 0;
+    const int rc_ws = check_workspace(r, workspace, workspace_bytes, lean && matrix);
+    if (rc_ws != VLUT_OK) return rc_ws;
+    if (matrix) return launch_matrix_route(r, packed, w_scale, nullptr, a_q, a_scale, K, y, ldy, acc_or_null, (hipStream_t)stream);
+    const Plan5 pl = r.plan5;
+    const Derived5 d = derive5(pl, M, K, N);
     Lookup5Params p;
     std::memset(&p, 0, sizeof(p));
     p.packed = packed; p.a_q = a_q; p.a_scale = a_scale; p.y = y; p.acc = acc_or_null; p.ws = (int32_t*)workspace;
@@ -1336,6 +1445,17 @@ int vlut_mpgemm_g5(const uint8_t* packed, float w_scale, const int8_t* a_q, cons
     if (pl.S > 1)
         return launch_splitk_reduce((const int32_t*)workspace, pl.S, M, N, w_scale, nullptr, a_scale, y, ldy, acc_or_null, s);
     return VLUT_OK;
+}
+
+int vlut_mpgemm_g5(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K,
+                   int64_t N, float* y, int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes,
+                   void* stream) {
+    return mpgemm_g5_impl(packed, w_scale, a_q, a_scale, M, K, N, y, ldy, acc_or_null, workspace, workspace_bytes, stream, false);
+}
+
+int vlut_mpgemm_g5_lean(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K, int64_t N, float* y,
+                        int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream) {
+    return mpgemm_g5_impl(packed, w_scale, a_q, a_scale, M, K, N, y, ldy, acc_or_null, workspace, workspace_bytes, stream, true);
 }
 
 // ---- mixed 1.60-bit / 2-bit packing (Sec. 3.3 "Flexible sub-2-bit weight packing")
@@ -1358,48 +1478,30 @@ int vlut_pack_weights_mixed(const int8_t* w_ternary, int64_t M, int64_t K, uint8
     return pack_parts(w_ternary, M, K, vlut_mixed_k5(K), packed, stream);
 }
 
-// The two parts as launches of the kernels above in partial-sum mode, then one exact INT32 sum + scale step.
-// Workspace: [S5 + S4][N][M] INT32.
-static bool mixed_plans(int64_t M, int64_t K, int64_t N, Plan5* p5, Plan* p4) {
-    const int64_t K5 = vlut_mixed_k5(K), K4 = K - K5;
-    if (K5 > 0) {
-        *p5 = choose_plan5(M, K5, N);
-        if (!plan5_valid(*p5, M, K5, N)) return false;
-    } else {
-        *p5 = Plan5{0, 0};
-    }
-    *p4 = K4 > 0 ? choose_plan(M, K4, N) : Plan{0, 0, 0, 0};
-    if (K4 > 0 && p4->R == 0) return false;              // the override of vlut_set_plan does not fit the 2-bit part
-    return true;
-}
 
 size_t vlut_workspace_bytes_mixed(int64_t M, int64_t K, int64_t N) {
-    if (!shape_ok(M, K, N)) return 0;
-    Plan5 p5;
-    Plan p4;
-    if (!mixed_plans(M, K, N, &p5, &p4)) return 0;
-    return (size_t)(p5.S + p4.S) * (size_t)M * (size_t)N * sizeof(int32_t);
+    return shape_ok(M, K, N) ? find_route(VLUT_FORM_MIXED, M, K, N).demanded : 0;
 }
 
-int vlut_mpgemm_mixed(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K,
-                      int64_t N, float* y, int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes,
-                      void* stream) {
+size_t vlut_workspace_used_mixed(int64_t M, int64_t K, int64_t N) {
+    return shape_ok(M, K, N) ? find_route(VLUT_FORM_MIXED, M, K, N).used() : 0;
+}
+
+static int mpgemm_mixed_impl(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K, int64_t N, float* y,
+                             int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream, bool lean) {
     int rc = check_mpgemm_args(packed, a_q, a_scale, M, K, N, y, ldy, acc_or_null);
     if (rc != VLUT_OK) return rc;
     if (((uintptr_t)a_q) % 16 != 0) return VLUT_ERR_UNSUPPORTED;
     const int64_t K5 = vlut_mixed_k5(K), K4 = K - K5;
-    Plan5 pl5;
-    Plan pl4;
-    if (!mixed_plans(M, K, N, &pl5, &pl4)) return VLUT_ERR_UNSUPPORTED;
-    const size_t need = (size_t)(pl5.S + pl4.S) * (size_t)M * (size_t)N * sizeof(int32_t);
-    if (!workspace) return VLUT_ERR_NULL;
-    if (workspace_bytes < need) return VLUT_ERR_SMALL_BUFFER;
+    const Route& r = find_route(VLUT_FORM_MIXED, M, K, N);
+    if (r.status != VLUT_OK) return r.status;
+    const bool matrix = r.kernel != kRouteTables && (uintptr_t)packed % 16 == 0;
+    rc = check_workspace(r, workspace, workspace_bytes, lean && matrix);
+    if (rc != VLUT_OK) return rc;
     hipStream_t s = (hipStream_t)stream;
-    if (matrix_cores_take_mixed() && (uintptr_t)packed % 16 == 0) {
-        const CodesPlan cp = codes_plan_if_taken(K5 > 0 ? 5 : 4, M, K, N, false);
-        if (cp.ch) return launch_codes(cp, packed, w_scale, nullptr, a_q, a_scale, M, K, K5, N, y, ldy, acc_or_null, s);
-        return launch_gemm(packed, w_scale, nullptr, a_q, a_scale, M, K, K5, N, y, ldy, acc_or_null, s);
-    }
+    if (matrix) return launch_matrix_route(r, packed, w_scale, nullptr, a_q, a_scale, K5, y, ldy, acc_or_null, s);
+    const Plan5 pl5 = r.plan5;
+    const Plan pl4 = r.plan;
     if (K5 > 0) {
         const Derived5 d = derive5(pl5, M, K5, N);
         Lookup5Params p;
@@ -1431,6 +1533,17 @@ int vlut_mpgemm_mixed(const uint8_t* packed, float w_scale, const int8_t* a_q, c
     }
     return launch_splitk_reduce((const int32_t*)workspace, pl5.S + pl4.S, M, N, w_scale, nullptr, a_scale, y, ldy,
                                 acc_or_null, s);
+}
+
+int vlut_mpgemm_mixed(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K,
+                      int64_t N, float* y, int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes,
+                      void* stream) {
+    return mpgemm_mixed_impl(packed, w_scale, a_q, a_scale, M, K, N, y, ldy, acc_or_null, workspace, workspace_bytes, stream, false);
+}
+
+int vlut_mpgemm_mixed_lean(const uint8_t* packed, float w_scale, const int8_t* a_q, const float* a_scale, int64_t M, int64_t K, int64_t N, float* y,
+                           int64_t ldy, int32_t* acc_or_null, void* workspace, size_t workspace_bytes, void* stream) {
+    return mpgemm_mixed_impl(packed, w_scale, a_q, a_scale, M, K, N, y, ldy, acc_or_null, workspace, workspace_bytes, stream, true);
 }
 
 static int codes_kernel(int64_t M, int64_t K, int64_t N) {

@@ -512,3 +512,33 @@ def test_several_rounds_of_five_weights_per_byte_take_the_faster_kernel(L):
         for form in (2, 3):
             assert L.vlut_query_matrix_plan(form, *shape, out) == 0
             assert (out[1] <= 16) == (t_few < t_tiles), (form, shape)
+
+
+def test_lean_calls_demand_the_workspace_that_is_used(L):
+    """No device call: every refusal comes first.  A workspace that the matrix cores leave alone may be NULL in the lean form and only
+    there, one that is handed over has to have its size, and what a shape runs is asked for anew when a plan is forced or released."""
+    d = 0x1000
+    forms = {"": (0, L.vlut_mpgemm_lean, L.vlut_mpgemm, (None,)), "_g5": (2, L.vlut_mpgemm_g5_lean, L.vlut_mpgemm_g5, ()),
+             "_mixed": (3, L.vlut_mpgemm_mixed_lean, L.vlut_mpgemm_mixed, ())}
+    for suffix, (form, lean, full, lut) in forms.items():
+        used, demanded = getattr(L, "vlut_workspace_used" + suffix), getattr(L, "vlut_workspace_bytes" + suffix)
+        used.argtypes, used.restype = [i64, i64, i64], sz
+        demanded.argtypes, demanded.restype = [i64, i64, i64], sz
+        args = [vp, cf, vp, vp] + ([vp] if lut else []) + [i64, i64, i64, vp, i64, vp, vp, sz, vp]
+        for f in (lean, full):
+            f.argtypes, f.restype = args, ci
+        shape = (640, 2560, 77)
+        need = demanded(*shape)
+        assert need > 0 and used(*shape) == 0
+        call = lambda f, ws, size: f(d, 1.0, d, d, *lut, *shape, d, 640, None, ws, size, None)   # noqa: E731
+        assert call(full, None, 0) == -1 and call(full, d, need - 1) == call(lean, d, need - 1) == -3
+        force, release = (L.vlut_set_plan_g5, (0, 0)) if form == 2 else (L.vlut_set_plan, (0, 0, 0, 0))
+        try:
+            assert force(*((2, 3) if form == 2 else (16, 2, 0, 3))) == 0
+            assert used(*shape) == demanded(*shape) >= 3 * 640 * 77 * 4            # the lookup kernel, K in three parts
+            assert call(lean, None, 0) == call(full, None, 0) == -1
+        finally:
+            assert force(*release) == 0
+        assert used(*shape) == 0 and demanded(*shape) == need
+        assert used(8, 6, 8) == demanded(8, 6, 8) == 0
+    assert L.vlut_workspace_used(64, 16384, 40) == L.vlut_workspace_bytes(64, 16384, 40) > 0     # the lookup kernel's
