@@ -27,7 +27,7 @@ typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
 // What bounds it (rates of this chip, measured): power.  13.5 ns per v_mfma_i32_32x32x32_i8 and SIMD on zeros (2.38 GHz), 16.8 on codes and
 // ternary weights (1.95 GHz, 4.0 POP/s), 18.5 with four byte permutes beside each (1.88 GHz, 3.6 POP/s); LDS serves transposing reads at
 // 183 and writes at 71 bytes per clock.  With CT = 4 a wave spends 3.3 unpacking instructions per matrix instruction, hence the wide
-// token tile.  14336 x 4096 x 512: 32.7 us, of which 22 in the K loop.
+// token tile.  The larger tiles with four weights per byte are gemm_ring_kernel's.
 // ---------------------------------------------------------------------------------------------
 struct GemmParams {
     const uint8_t* packed;
@@ -141,6 +141,146 @@ __device__ __forceinline__ i32x2 lds_read_tr8(unsigned addr) {
 #endif
 }
 
+// How the outputs leave.  A compute unit takes some 16 cycles for a store whether a lane gives one dword or four: dword by dword the
+// 256 x 128 tile took 3.6 us of 32, and 6.2 with one K group; together 1.6 and 2.0.
+//   kStoreTogether   the rows of lanes i and i + 16 and of the two row tiles are neighbours (gemm_row); one lane swap leaves every lane
+//                    with 2 RT consecutive outputs of one token.  For weights that come from LDS: loads from memory want four neighbouring
+//                    lanes in the four rows of a packed tile (otherwise the K loop is 4 to 14 % longer).
+//   kStorePairs      rows in their order; neighbouring lanes exchange one of two tokens and have two consecutive outputs each.
+//                    256 x 128 2.7 us, 64 x 128 1.15 -> 0.87.
+//   kStoreDwords     for tiles of up to 64 tokens, where pairs gain 0.1 us of stores and lose as much to longer code (3203 x 3116 x 77, 64 x 32
+//                    tiles: 5.97 us, pairs 6.04).
+enum { kStoreDwords, kStorePairs, kStoreTogether };
+template <int RT, int STORE>
+__device__ __forceinline__ int gemm_row(int i, int rt) {      // output row, of the 32 * RT of a wave, of lane i in row tile rt
+    return STORE == kStoreTogether ? 2 * RT * (i & 15) + 2 * rt + (i >> 4) : 32 * rt + i;
+}
+// Lanes 2 j and 2 j + 1 with (a0, b0), (a1, b1) -> (a0, a1), (b0, b1)
+__device__ __forceinline__ void swap_neighbours(float& a, float& b, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto other = [](float v) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, false)); };
+    const float oa = other(a), ob = other(b);
+    const float x = lane & 1 ? ob : a, y = lane & 1 ? b : oa;
+    a = x;
+    b = y;
+    asm volatile("" : "+v"(a), "+v"(b));                   // (by all lanes, whoever stores)
+#else
+    (void)a; (void)b; (void)lane;
+#endif
+}
+// Of a pair of registers: rows of 16 lanes (a0 a1 a2 a3), (b0 b1 b2 b3) -> (a0 b0 a2 b2), (a1 b1 a3 b3).  Two pairs per call.  Written out:
+// from the builtin the compiler made code that took the first result for both (a test with two tokens found it).  The
+// instruction wants two wait states behind the vector instruction that wrote its operands.
+__device__ __forceinline__ void swap_rows16(float& a, float& b, float& c, float& d) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\tv_permlane16_swap_b32 %2, %3" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+#else
+    (void)a; (void)b; (void)c; (void)d;
+#endif
+}
+// (y and its rows may start at any float: global memory takes vectors aligned to a dword)
+typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// The end of a tiled product: the K groups' sums meet in LDS (overwritten from its start; the caller has passed a barrier since its last
+// use), scales, stores.  A lane holds, of each 32 x 32 product, one output row (gemm_row) and the tokens 8 g + 4 kb + 0..3 in registers
+// 4 g .. 4 g + 3: "quad" g.  The quads are dealt out over the WK groups, those of the RT row tiles together; a group adds the other
+// groups' sums to its own.  scales: LDS address of the tile's token scales, its row scales behind them.
+template <int RT, int CT, int WM, int WK, int STORE>
+__device__ __forceinline__ void gemm_store(const GemmParams& p, const i32x16 (&acc)[RT][CT], int lane, int wm, int wk, int mt, int nt, unsigned scales) {
+    constexpr int BN = 32 * CT, BM = 32 * RT * WM;
+    constexpr int Q = RT * CT * 4;
+    constexpr int kOwn = (Q + WK - 1) / WK;                // quads per group
+    static_assert(kOwn % RT == 0, "the row tiles of a quad belong to one group");
+    const int i = lane & 31, kb = lane >> 5;
+    auto quad = [&](int qd) {
+        const i32x16& v = acc[qd % RT][qd / RT / 4];
+        const int g = qd / RT & 3;
+        return i32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+    };
+    if (WK > 1) {
+#pragma unroll
+        for (int qd = 0; qd < Q; ++qd) {
+            const int owner = qd / kOwn;
+            if (owner != wk) {
+                const int slot = wk - (wk > owner ? 1 : 0);
+                *(lds_i32x4*)(unsigned)((((wm * Q + qd) * (WK - 1)) + slot) * 1024 + lane * 16) = quad(qd);
+            }
+        }
+        wg_barrier_lds();
+    }
+    const int m_wave = mt * BM + wm * 32 * RT;
+    float ws[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) ws[rt] = __builtin_bit_cast(float, *(const lds_i32*)(scales + (unsigned)((BN + wm * 32 * RT + gemm_row<RT, STORE>(i, rt)) * 4)));
+    // (tokens of a store: 4 kb + a bit of the lane, then a number that all lanes share)
+    constexpr bool kTogether = STORE == kStoreTogether;
+    const int n_lane = nt * BN + 4 * kb + (kTogether ? (lane >> 4) & 1 : STORE == kStorePairs ? lane & 1 : 0);
+    const int m_lane = m_wave + (kTogether ? 2 * RT * (i & 15) : STORE == kStorePairs ? i & ~1 : i);
+    float* const y_lane = p.y + (size_t)n_lane * p.ldy + m_lane;
+    auto store_quads = [&](auto inside) {                  // inside: only y is wanted and no output lies past M or N
+        constexpr bool kInside = decltype(inside)::value;
+#pragma unroll
+        for (int q0 = 0; q0 < Q; q0 += RT) {
+            if (q0 / kOwn != wk) continue;
+            const int nq = 32 * (q0 / RT / 4) + 8 * (q0 / RT & 3), n = nt * BN + nq + 4 * kb;
+            const i32x4 sc = *(const lds_i32x4*)(scales + (unsigned)((nq + 4 * kb) * 4));
+            float out[RT][4];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                i32x4 v = -quad(q0 + rt);                  // (planes hold -w)
+#pragma unroll
+                for (int s = 0; s < WK - 1; ++s) v -= *(const lds_i32x4*)(unsigned)((((wm * Q + q0 + rt) * (WK - 1)) + s) * 1024 + lane * 16);
+                if (!kInside && p.acc) {
+                    const int m = m_wave + gemm_row<RT, STORE>(i, rt);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (m < p.M && n + e < p.N) p.acc[(size_t)m * p.N + n + e] = v[e];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) out[rt][e] = (float)v[e] * (ws[rt] * __builtin_bit_cast(float, (int)sc[e]));
+            }
+            if (!kInside && !p.y) continue;
+            auto put = [&](int m, int n, auto v) {         // from m_lane and n_lane on
+                constexpr int kWidth = sizeof(v) / 4;
+                if (!kInside && n_lane + nq + n >= p.N) return;
+                float* const dst = y_lane + (size_t)(nq + n) * p.ldy + m;
+                if (kInside || m_lane + m + kWidth <= p.M) {
+                    if (p.stream_out) __builtin_nontemporal_store(v, (decltype(v)*)dst);
+                    else *(decltype(v)*)dst = v;
+                } else if constexpr (kWidth > 1) {
+#pragma unroll
+                    for (int j = 0; j + 1 < kWidth; ++j)
+                        if (m_lane + m + j < p.M) dst[j] = v[j];
+                }
+            };
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                if constexpr (kTogether) swap_rows16(out[rt][0], out[rt][1], out[rt][2], out[rt][3]);
+                if constexpr (STORE == kStorePairs) swap_neighbours(out[rt][0], out[rt][1], lane), swap_neighbours(out[rt][2], out[rt][3], lane);
+            }
+            if constexpr (STORE == kStoreDwords) {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) put(32 * rt, e, out[rt][e]);
+            } else {
+#pragma unroll
+                for (int h = 0; h < 4; h += 2) {
+                    if constexpr (kTogether && RT == 2) {
+                        put(0, h, f32x4_any{out[0][h], out[0][h + 1], out[1][h], out[1][h + 1]});
+                    } else {
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) put(32 * rt, h, f32x2_any{out[rt][h], out[rt][h + 1]});
+                    }
+                }
+            }
+        }
+    };
+    if (STORE != kStoreDwords && p.y && !p.acc && m_wave + 32 * RT <= p.M && (nt + 1) * BN <= p.N) store_quads(std::true_type{});
+    else store_quads(std::false_type{});
+}
+
 // LDS bytes of one workgroup: the double-buffered activation tiles of the WK groups, later the sums they exchange;
 // behind them the scales of the tile's tokens and rows.
 template <int GW, int RT, int CT, int WM, int WK>
@@ -184,8 +324,8 @@ __global__ void __launch_bounds__(64 * WM * WK, 2) gemm_kernel(const GemmParams 
     unsigned woff[RT], wend[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-        const int rgl = min((wm * RT + rt) * 8 + (i >> 2), p.RGtotal - 1 - rg0);
-        const unsigned row = (unsigned)rgl * (unsigned)p.KCn * 64u + (unsigned)((i & 3) * 16);
+        const int r = wm * 32 * RT + gemm_row<RT, kStorePairs>(i, rt);
+        const unsigned row = (unsigned)min(r >> 2, p.RGtotal - 1 - rg0) * (unsigned)p.KCn * 64u + (unsigned)((r & 3) * 16);
         woff[rt] = row + (unsigned)(kb * 64);
         wend[rt] = row + (unsigned)(p.KCn - 1) * 64u;
     }
@@ -253,7 +393,7 @@ __global__ void __launch_bounds__(64 * WM * WK, 2) gemm_kernel(const GemmParams 
         if (wk == 0 && kb == 0) {
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
-                const int row = m_wave + 32 * rt + i;
+                const int row = m_wave + gemm_row<RT, kStorePairs>(i, rt);
                 w4[rt] = *(const unsigned*)(p.packed4 + (size_t)min(row >> 2, p.RGtotal - 1) * p.KCn4 * 64 + (row & 3) * 16);
             }
         }
@@ -364,54 +504,7 @@ __global__ void __launch_bounds__(64 * WM * WK, 2) gemm_kernel(const GemmParams 
         wg_barrier_lds();
     }
 
-    // ---- epilogue.  A lane holds, of each 32 x 32 product, output row i and the tokens 8 g + 4 kb + 0..3 in registers 4 g
-    //      .. 4 g + 3: "quad" g.  The quads are dealt out over the WK groups, which add the other groups' sums and store.
-    constexpr int Q = RT * CT * 4;
-    constexpr int kOwn = (Q + WK - 1) / WK;                // quads per group
-    if (WK > 1) {
-#pragma unroll
-        for (int qd = 0; qd < Q; ++qd) {
-            const int owner = qd / kOwn;
-            if (owner != wk) {
-                const i32x16& v = acc[qd / 4 / CT][qd / 4 % CT];
-                const int g = qd & 3;
-                const int slot = wk - (wk > owner ? 1 : 0);
-                *(lds_i32x4*)(unsigned)((((wm * Q + qd) * (WK - 1)) + slot) * 1024 + lane * 16) = i32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
-            }
-        }
-        wg_barrier_lds();
-    }
-#pragma unroll
-    for (int qd = 0; qd < Q; ++qd) {
-        if (qd / kOwn != wk) continue;
-        const int rt = qd / 4 / CT, ct = qd / 4 % CT, g = qd & 3;
-        int v[4] = {-acc[rt][ct][4 * g], -acc[rt][ct][4 * g + 1], -acc[rt][ct][4 * g + 2], -acc[rt][ct][4 * g + 3]};   // (planes hold -w)
-#pragma unroll
-        for (int s = 0; s < WK - 1; ++s) {
-            const i32x4 o = *(const lds_i32x4*)(unsigned)((((wm * Q + qd) * (WK - 1)) + s) * 1024 + lane * 16);
-            v[0] -= o.x; v[1] -= o.y; v[2] -= o.z; v[3] -= o.w;
-        }
-        const int ml = (wm * RT + rt) * 32 + i, nl = 32 * ct + 8 * g + 4 * kb;
-        const int m = mt * BM + ml, n = nt * BN + nl;
-        if (m >= p.M) continue;
-        if (p.y) {
-            const i32x4 sc = *(const lds_i32x4*)(unsigned)(kScales + nl * 4);
-            const float ws = __builtin_bit_cast(float, *(const lds_i32*)(unsigned)(kScales + (BN + ml) * 4));
-            float* dst = p.y + (size_t)n * p.ldy + m;
-#pragma unroll
-            for (int e = 0; e < 4; ++e, dst += p.ldy)
-                if (n + e < p.N) {
-                    const float out = (float)v[e] * (ws * __builtin_bit_cast(float, (int)sc[e]));
-                    if (p.stream_out) __builtin_nontemporal_store(out, dst);
-                    else *dst = out;
-                }
-        }
-        if (p.acc) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (n + e < p.N) p.acc[(size_t)m * p.N + n + e] = v[e];
-        }
-    }
+    gemm_store<RT, CT, WM, WK, (CT > 2 ? kStorePairs : kStoreDwords)>(p, acc, lane, wm, wk, mt, nt, kScales);
 }
 
 // The tile shapes that are built and what a launch costs with them, in us, fitted (rms 2 to 4 %) to launches back to back of 4100 and 1700
@@ -420,11 +513,13 @@ __global__ void __launch_bounds__(64 * WM * WK, 2) gemm_kernel(const GemmParams 
 // K group.  The tile of the least cost is within 0.4 % of the fastest on average (2 % of the shapes beyond 5 %, worst 19 %).  It ranks tiles;
 // as a time it is less good than the fit: against graph replays, whose launches are shorter, of 185 other shapes 7 % too long on average (rms
 // 11 %), 8 % too short above 5 * 10^9 weights times tokens (4096 x 14336 x 512: 29.8 for 36.0), and its terms are a fit's, not a model's
-// (256 rows without parts of K: all of the launch in `base`, none of the store in `fixed`).
+// (256 rows without parts of K: all of the launch in `base`, none of the store in `fixed`).  Fitted before tiles were loaded straight to LDS
+// and stored wide, which makes the larger ones 7 to 19 % faster: of 450 shapes timed with that the tile of the least cost is still within 0.4 % of
+// the fastest on average (3 % of them beyond 5 %), and constants fitted to the new times rank no better.
 // With one K group two workgroups of four waves share a compute unit, and one stores while the other multiplies: 13824 x 2560 x 1024
-// 45.7 -> 42.0 us; 128 rows x 64 tokens: 4096 x 14336 x 512 40.1 -> 36.0 us.
+// 45.7 -> 42.0 us (34.1 now); 128 rows x 64 tokens: 4096 x 14336 x 512 40.1 -> 36.0 us (31.4 now).
 // Five weights per byte take more registers than four: 64 x 64 133 per lane, so that one workgroup has a unit to itself (per_unit), 256 x 128
-// all 256 and 20 bytes of scratch (at most 2 % of a launch: 13620 x 260 x 281 11.4 -> 11.5 us against the unpacking before, which did
+// all 256 and 12 bytes of scratch (at most 2 % of a launch: 13620 x 260 x 281 11.4 -> 11.5 us against the unpacking before, which did
 // without; 8 % faster than with that on average of 31 shapes).
 struct GemmTile {
     int rt, ct, wm, wk;

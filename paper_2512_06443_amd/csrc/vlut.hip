@@ -34,6 +34,7 @@
 #include "mfma_kernel.hip.h"
 #include "lookup5_kernel.hip.h"
 #include "gemm_kernel.hip.h"
+#include "gemm_ring_kernel.hip.h"
 #include "decode_kernel.hip.h"
 #include "narrow_kernel.hip.h"
 #include "small_kernels.hip.h"
@@ -768,8 +769,11 @@ bool matrix_cores_take_mixed() { return t_forced5.R == 0 && t_forced5.S == 0 && 
 template <int GW, int I>
 int launch_gemm_t(const GemmParams& p, hipStream_t stream) {
     constexpr GemmTile t = kGemmTiles[I];
-    auto kfn = gemm_kernel<GW, t.rt, t.ct, t.wm, t.wk>;
-    constexpr int lds = gemm_lds_bytes<GW, t.rt, t.ct, t.wm, t.wk>();
+    constexpr bool ring = gemm_ring_built(GW, t.rt, t.ct, t.wm, t.wk);
+    void (*kfn)(GemmParams);
+    if constexpr (ring) kfn = gemm_ring_kernel<t.rt, t.ct, t.wm, t.wk>;
+    else kfn = gemm_kernel<GW, t.rt, t.ct, t.wm, t.wk>;
+    constexpr int lds = ring ? ring_lds_bytes<t.rt, t.ct, t.wm, t.wk>() : gemm_lds_bytes<GW, t.rt, t.ct, t.wm, t.wk>();
     static_assert(lds <= 160 * 1024, "LDS of a workgroup");
     static std::atomic<unsigned> attr_done{0};   // one bit per device: the attribute belongs to the device's copy
     if (!allow_dynamic_lds((const void*)kfn, lds, attr_done)) return VLUT_ERR_DEVICE;

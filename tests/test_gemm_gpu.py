@@ -222,3 +222,33 @@ def test_one_token_on_many_rows(B, M, K, kernel):
                                           (1000, 4680, 14, "few_tokens"), (1000, 4096, 14, "matrix_few_tokens"), (33, 3072, 16, "matrix_few_tokens")])
 def test_nine_to_sixteen_tokens_on_few_rows(B, M, K, N, kernel):
     check_f32(B, *wl.small_case(1900 + M + N, M, K, N), kernel)
+
+
+# The tiles whose operands are loaded straight to LDS: one to eight passes of the K loop (three slots, two register sets), K that ends
+# anywhere in a step, tiles that the matrix fills (stored without checks, past the caches from 16 MB on) and cuts.
+@pytest.mark.parametrize("M,K,N,workgroup", [
+    (3328, 4, 640, (128, 128, 2)), (8307, 260, 238, (128, 128, 2)), (8448, 516, 256, (128, 128, 2)), (11187, 780, 167, (128, 128, 2)),
+    (3328, 1300, 640, (128, 128, 2)), (2816, 1540, 768, (128, 128, 2)), (11008, 4, 384, (256, 128, 2)), (11266, 260, 384, (256, 128, 2)),
+    (11008, 516, 384, (256, 128, 2)), (10924, 1324, 325, (256, 128, 2)), (9628, 4, 793, (256, 128, 1)), (14592, 132, 640, (256, 128, 1)),
+    (11264, 388, 768, (256, 128, 1)), (13429, 812, 518, (256, 128, 1)), (3840, 520, 384, (128, 64, 4)), (14336, 1032, 67, (128, 64, 4)),
+    (8448, 2592, 128, (128, 64, 4)), (11261, 3944, 65, (128, 64, 4))])
+def test_tiles_loaded_to_lds(B, M, K, N, workgroup):
+    assert B.query_matrix_plan("codes", M, K, N)[:3] == workgroup
+    print(f"tile case {workgroup} M={M} K={K} N={N}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + K + N)
+    W = torch.randint(-1, 2, (M, K), dtype=torch.int8, generator=gen, device="cuda")
+    a_q, a_s = B.quantize_act(torch.randn(N, K, generator=gen, device="cuda"))
+    packed = B.pack_weights(W)
+    acc_ref = W.float().cpu() @ B.act_chunked_to_kn(a_q, N).float().cpu()      # whole numbers below 2^24: exact in fp32
+    rows = torch.rand(M, device="cuda") + 0.5
+    def right(y, scale):                                     # two fp32 roundings of the exact product
+        want = acc_ref.double().t() * scale.cpu().double() * a_s.cpu().double()[:, None]
+        return bool(torch.all((y.cpu().double() - want).abs() <= REL * want.abs()))
+    y, _ = B.mpgemm(packed, 0.375, a_q, a_s, M)
+    assert right(y, torch.full((M,), 0.375))
+    pad = torch.full((N, M + 7), -7.0, device="cuda")        # rows that start at any float, and what lies beside them
+    y, acc = B.mpgemm_rows(packed, rows, a_q, a_s, M, y=pad[:, 3:M + 3], want_acc=True)
+    assert torch.equal(acc.cpu(), acc_ref.to(torch.int32)) and right(y, rows)
+    B.mpgemm_rows(packed, rows, a_q, a_s, M, y=pad[:, 3:M + 3])
+    assert right(pad[:, 3:M + 3], rows) and torch.all(pad[:, :3] == -7.0) and torch.all(pad[:, M + 3:] == -7.0)
