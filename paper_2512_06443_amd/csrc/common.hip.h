@@ -70,6 +70,24 @@ __device__ __forceinline__ unsigned lds_base_of(void* p) {
 #endif
 }
 
+// Memory behind a descriptor: 32-bit offsets from a base that the wave shares, and a length beyond which loads return zeros.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef __amdgpu_buffer_rsrc_t buffer_rsrc;
+// The `left` bytes from base on: loads beyond them return zeros (left < 0: none).
+__device__ __forceinline__ buffer_rsrc make_buffer(const void* base, int64_t left) {
+    const unsigned hi = (unsigned)(left >> 32), n = (int)hi < 0 ? 0u : (hi ? 0xffffffffu : (unsigned)left);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)n, 0x00027000);
+}
+// 16 bytes from offset `at` on (any multiple of four: vectors from memory are aligned to a dword)
+__device__ __forceinline__ i32x4 buffer_load128(buffer_rsrc r, unsigned at) {
+    return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)at, 0, 0));
+}
+#else
+typedef int buffer_rsrc;
+inline __device__ buffer_rsrc make_buffer(const void*, int64_t) { return 0; }
+inline __device__ i32x4 buffer_load128(buffer_rsrc, unsigned) { return i32x4{0, 0, 0, 0}; }
+#endif
+
 // addr is a byte address inside LDS; OFF16 is a compile-time offset in units of 16 bytes, kept apart so that it
 // lands in the instruction's immediate offset field instead of costing a VALU add.
 template <int OFF16>

@@ -29,7 +29,7 @@ struct DecodeParams {
     float* a_scale_out;
     int64_t ldx;
     float w_scale;
-    int M, N, K, KCn, RGtotal, ldy, macros, x_vec;
+    int M, N, K, KCn, RGtotal, ldy, macros;
     const int8_t* a_q;            // decode_codes_kernel: INT8 codes and their scales instead of x
     const float* a_scale;
     const uint8_t* packed4;       // mixed packing: the 2-bit blob of the last K - Kmain < 20 values of K, else null
@@ -42,14 +42,19 @@ constexpr int kDecodeWaves = 16;
 constexpr int kDecodeKeep = 12;                // float4 of x per lane kept between the two passes; the rest is read twice
 constexpr int decode_lds_bytes(int T, int macros) { return macros * 256 * T + kDecodeWaves * 1024 + 128; }
 
-// One lane's packed bytes: row m, tile column 4 macro + kb (rows past the last one are clamped, their sums are not stored; columns
-// past the last one are clamped and replaced by zeros when they are unpacked).
+// One lane's packed bytes: row m of the workgroup's rows from m0 on, tile column 4 macro + kb (rows past the last one read zeros, their sums
+// are not stored; columns past the last one are clamped and replaced by zeros when they are unpacked).  A workgroup's rows span less than
+// 2^31 bytes.
 struct DecodeWeights {
-    const uint8_t* row;
-    int kb, last;
-    __device__ __forceinline__ DecodeWeights(const DecodeParams& p, int m, int kb_)
-        : row(p.packed + (size_t)min(m >> 2, p.RGtotal - 1) * p.KCn * 64 + (m & 3) * 16), kb(kb_), last(p.KCn - 1) {}
-    __device__ __forceinline__ i32x4 load(int macro) const { return *(const i32x4*)(row + (size_t)min(4 * macro + kb, last) * 64); }
+    buffer_rsrc from;
+    unsigned at, end;
+    __device__ __forceinline__ DecodeWeights(const DecodeParams& p, int m0, int m, int kb)
+        : from(make_buffer(p.packed + (size_t)(m0 >> 2) * p.KCn * 64, (int64_t)(p.RGtotal - (m0 >> 2)) * p.KCn * 64)) {
+        const unsigned row = (unsigned)((m >> 2) * p.KCn) * 64u + (unsigned)((m & 3) * 16);
+        at = row + (unsigned)(kb * 64);
+        end = row + (unsigned)(p.KCn - 1) * 64u;
+    }
+    __device__ __forceinline__ i32x4 load(int macro) const { return buffer_load128(from, min(at + (unsigned)macro * 256u, end)); }
 };
 
 // Four packed bytes as the four planes of -w; the all-zero pattern where keep is 0.
@@ -103,6 +108,21 @@ struct DecodeOut {
     }
 };
 
+// f(0), f(1), .. for the first `steps` (uniform) of the kDecodeKeep steps.  Nested, so that few steps are few branches, and with something
+// in each that the compiler cannot run ahead of its branch: it turned twelve short steps into twelve selections (one token: +0.2 us).
+template <int I, class F>
+__device__ __forceinline__ void first_steps(int steps, F f) {
+    if constexpr (I < kDecodeKeep) {
+        if (I < steps) {
+#if defined(__HIP_DEVICE_COMPILE__)
+            asm volatile("");
+#endif
+            f(I);
+            first_steps<I + 1>(steps, f);
+        }
+    }
+}
+
 template <int T, int MT>
 __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeParams p) {
     constexpr int KP = kDecodeWaves / MT;      // parts of K
@@ -118,24 +138,15 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeP
     // ---- request the rows of x first, then the first weights (loads return in order, and x is needed first)
     const int tok = wave / WPT, sub = wave % WPT;
     const bool live = tok < p.N;
-    const float* row = p.x + (size_t)(live ? tok : 0) * p.ldx;
-    const int nquad = p.K >> 2;
-    auto load4 = [&](int macro) -> f32x4 {
-        const int qi = macro * 64 + lane;
-        if (qi >= nquad) return f32x4{0.f, 0.f, 0.f, 0.f};
-        const float* src = row + 4 * (size_t)qi;
-        if (p.x_vec) return *(const f32x4*)src;
-        return f32x4{src[0], src[1], src[2], src[3]};
-    };
+    const buffer_rsrc row = make_buffer(p.x + (size_t)(live ? tok : 0) * p.ldx, (int64_t)p.K * 4);
+    const unsigned at = (unsigned)(sub * 1024 + lane * 16);              // the wave's macro steps are sub + WPT * it
+    const int steps = live ? max(p.macros - sub + WPT - 1, 0) / WPT : 0;
+    auto load4 = [&](int it) { return __builtin_bit_cast(f32x4, buffer_load128(row, at + (unsigned)it * (WPT * 1024u))); };
     f32x4 xv[kDecodeKeep];
-    if (live) {
-#pragma unroll
-        for (int it = 0; it < kDecodeKeep; ++it)
-            if (sub + WPT * it < p.macros) xv[it] = load4(sub + WPT * it);
-    }
+    first_steps<0>(steps, [&](int it) { xv[it] = load4(it); });
     const int rt = wave % MT, part = wave / MT;
     const int i = lane & 15, kb = lane >> 4;
-    const DecodeWeights weights(p, (blockIdx.x * MT + rt) * 16 + i, kb);
+    const DecodeWeights weights(p, blockIdx.x * 16 * MT, rt * 16 + i, kb);
     auto load_w = [&](int macro) { return weights.load(macro); };
     const DecodeOut<T, MT> out(p, tid, blockIdx.x * 16 * MT, 0);
     i32x4 w[PF];
@@ -144,19 +155,29 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeP
     for (int j = 0; j < PF; ++j) w[j] = load_w(part + KP * j);
     __builtin_amdgcn_sched_barrier(0);
 
-    // ---- quantise: absmax over the row, then codes (the decisions of quant_codes4, IEEE divisions)
-    auto absmax4 = [](float m, const f32x4 v) { return fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w))); };
+    // ---- quantise: absmax over the row, then codes (the decisions of quant_codes4, IEEE divisions).  Maxima that let a NaN through take two
+    //      values per instruction; a wave that meets one reads its values again.  18 instructions per four values instead of 32: with
+    //      16 tokens a wave quantises a whole row and the vector units are what it waits for.  The four linears of a 2560-wide layer, us in a
+    //      stream: 16 tokens 29.0 -> 26.3; one token, where it is the branches around loads that go, 17.0 -> 16.3.
     float amax = 0.0f;
-    if (live) {
-#pragma unroll
-        for (int it = 0; it < kDecodeKeep; ++it)
-            if (sub + WPT * it < p.macros) amax = absmax4(amax, xv[it]);
-        for (int m0 = sub + WPT * kDecodeKeep; m0 < p.macros; m0 += WPT * 4) {
+    bool odd = false;                                                    // (uniform)
+    auto rest = [&](int first, auto take) {                              // values that no register holds, four steps at a time
+        for (int it = first; it < steps; it += 4) {
             f32x4 tv[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) tv[c] = m0 + WPT * c < p.macros ? load4(m0 + WPT * c) : f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int c = 0; c < 4; ++c) tv[c] = load4(it + c);           // (zeros past the end of the row)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) amax = absmax4(amax, tv[c]);
+            for (int c = 0; c < 4; ++c) take(it + c, tv[c]);
+        }
+    };
+    if (live) {
+        auto absmax4 = [&](int, const f32x4 v) { amax = nan_max(nan_max(nan_max(nan_max(amax, fabsf(v.x)), fabsf(v.y)), fabsf(v.z)), fabsf(v.w)); };
+        first_steps<0>(steps, [&](int it) { absmax4(it, xv[it]); });
+        rest(kDecodeKeep, absmax4);
+        odd = __builtin_amdgcn_ballot_w64(amax != amax) != 0;
+        if (odd) {
+            amax = 0.0f;
+            rest(0, [&](int, const f32x4 v) { amax = fmaxf(fmaxf(amax, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w))); });
         }
         amax = wave_max_f32(amax);
     }
@@ -174,20 +195,13 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_kernel(const DecodeP
             if (p.a_scale_out && blockIdx.x == 0) p.a_scale_out[tok] = sc;
         }
         const int u = lane >> 2;
-        const unsigned dst = (unsigned)(((u * T) + ((tok + (u >> kShift)) & (T - 1))) * 16 + (lane & 3) * 4);
-        auto emit = [&](int macro, const f32x4 v) {
-            *(lds_i32*)(dst + (unsigned)macro * (256u * T)) = (int)quad_transpose_codes(quant_codes4(v, inv), lane);
-        };
-#pragma unroll
-        for (int it = 0; it < kDecodeKeep; ++it)
-            if (sub + WPT * it < p.macros) emit(sub + WPT * it, xv[it]);
-        for (int m0 = sub + WPT * kDecodeKeep; m0 < p.macros; m0 += WPT * 4) {
-            f32x4 tv[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) tv[c] = m0 + WPT * c < p.macros ? load4(m0 + WPT * c) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (m0 + WPT * c < p.macros) emit(m0 + WPT * c, tv[c]);
+        const unsigned dst = (unsigned)(((u * T) + ((tok + (u >> kShift)) & (T - 1))) * 16 + (lane & 3) * 4) + (unsigned)sub * (256u * T);
+        auto put = [&](int it, unsigned codes) { *(lds_i32*)(dst + (unsigned)it * (WPT * 256u * T)) = (int)quad_transpose_codes(codes, lane); };
+        if (!odd && __builtin_amdgcn_readfirstlane((int)quant_in_range(amax))) {
+            first_steps<0>(steps, [&](int it) { put(it, quant_codes4<false>(xv[it], inv)); });
+            rest(kDecodeKeep, [&](int it, const f32x4 v) { if (it < steps) put(it, quant_codes4<false>(v, inv)); });
+        } else {
+            rest(0, [&](int it, const f32x4 v) { if (it < steps) put(it, quant_codes4<true>(v, inv)); });
         }
     }
     wg_barrier_lds();
@@ -278,7 +292,7 @@ __global__ void __launch_bounds__(64 * kDecodeWaves) decode_codes_kernel(const D
     load_units(0);
     const int rt = wave % MT, part = wave / MT;
     const int i = lane & 15, kb = lane >> 4;
-    const DecodeWeights weights(p, m0 + rt * 16 + i, kb);
+    const DecodeWeights weights(p, m0, rt * 16 + i, kb);
     const DecodeOut<8 * CH, MT> out(p, tid, m0, nt * 8 * CH);
     unsigned w4 = kZeroIdx4;
     if (GW == 5 && p.packed4) {

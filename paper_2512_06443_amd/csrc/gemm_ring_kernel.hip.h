@@ -27,12 +27,6 @@ namespace {
 // of the first stage and stored to LDS behind the loop, when every load has been waited for.
 // ---------------------------------------------------------------------------------------------
 #if defined(__HIP_DEVICE_COMPILE__)
-typedef __amdgpu_buffer_rsrc_t buffer_rsrc;
-// The `left` bytes from base on: loads beyond them return zeros (left < 0: none).
-__device__ __forceinline__ buffer_rsrc make_buffer(const void* base, int64_t left) {
-    const unsigned hi = (unsigned)(left >> 32), n = (int)hi < 0 ? 0u : (hi ? 0xffffffffu : (unsigned)left);
-    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)n, 0x00027000);
-}
 // 16 bytes per lane from offset `at` to LDS, lane after lane from `to` on
 __device__ __forceinline__ void load_to_lds(buffer_rsrc r, unsigned at, unsigned to) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(at), "s"(r) : "memory", "m0");
@@ -40,8 +34,6 @@ __device__ __forceinline__ void load_to_lds(buffer_rsrc r, unsigned at, unsigned
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 #else
-typedef int buffer_rsrc;
-inline __device__ buffer_rsrc make_buffer(const void*, int64_t) { return 0; }
 inline __device__ void load_to_lds(buffer_rsrc, unsigned, unsigned) {}
 template <int N>
 inline __device__ void wait_loads() {}

@@ -93,30 +93,43 @@ __global__ void __launch_bounds__(256) pack_kernel(const int8_t* __restrict__ w,
 constexpr int kQuantThreads = 1024;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// The larger value, NaN where either is one.  (fmaxf drops NaNs, for which the compiler first rewrites every operand.)
+__device__ __forceinline__ float nan_max(float a, float b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_elementwise_maximum(a, b);
+#else
+    (void)b;
+    return a;
+#endif
+}
+
 // Absmax quantiser of one token row, decided in fp32: inv = 127 / amax (IEEE division, 0 for an all-zero row),
 // code = clamp(rint(x * inv), -127, 127) with ties to even.
 // Four values at once, code of v[c] in byte c.  Adding 1.5 * 2^23 to the product (rounded to fp32 first: there is no
 // contraction here) rounds it to an integer with ties to even and leaves that integer, two's complement, in the low byte of
 // the sum.  The clamp comes before the rounding, which gives the same code; it only matters where 127 / amax overflows
-// (rows below 4e-37): -inf and NaN become -127, +inf 127.
+// (rows below 4e-37) or x has an infinity or a NaN: -inf and NaN become -127, +inf 127.  CLAMP false: the caller has ruled these out
+// (the product of |x| <= amax and 127 / amax is at most 127 * (1 + 2^-23), which rounds to 127).
+template <bool CLAMP = true>
 __device__ __forceinline__ unsigned quant_codes4(const f32x4 v, float inv) {
     unsigned u[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) u[c] = __builtin_bit_cast(unsigned, __builtin_amdgcn_fmed3f(v[c] * inv, -127.0f, 127.0f) + 12582912.0f);
+    for (int c = 0; c < 4; ++c) {
+        const float t = v[c] * inv;
+        u[c] = __builtin_bit_cast(unsigned, (CLAMP ? __builtin_amdgcn_fmed3f(t, -127.0f, 127.0f) : t) + 12582912.0f);
+    }
     return __builtin_amdgcn_perm(u[1], u[0], 0x0c0c0400u) | __builtin_amdgcn_perm(u[3], u[2], 0x04000c0cu);
 }
+// Rows that need no clamp, from the greatest magnitude of their values without NaN.
+__device__ __forceinline__ bool quant_in_range(float amax) { return (amax >= 4e-37f && amax < INFINITY) || amax == 0.0f; }
+
 // The lane holds the codes of k = 4q .. 4q+3 of token `tok` (byte c = k offset c); the four lanes of a quad hold
 // four consecutive tokens of the same q.  Returns, for the lane with tok % 4 == c, the codes of those four tokens
-// at k = 4q + c (byte e = token 4*(tok/4) + e).
+// at k = 4q + c (byte e = token 4*(tok/4) + e).  Two exchanges: bytes with the neighbour, halves with the other pair.
 __device__ __forceinline__ unsigned quad_transpose_codes(unsigned d, int tok) {
-    const unsigned d0 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)d, 0x00, 0xF, 0xF, false);
-    const unsigned d1 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)d, 0x55, 0xF, 0xF, false);
-    const unsigned d2 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)d, 0xAA, 0xF, 0xF, false);
-    const unsigned d3 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)d, 0xFF, 0xF, 0xF, false);
-    const unsigned c = (unsigned)tok & 3u;
-    const unsigned lo = __builtin_amdgcn_perm(d1, d0, 0x0c0c0000u | ((4u + c) << 8) | c);
-    const unsigned hi = __builtin_amdgcn_perm(d3, d2, 0x00000c0cu | ((4u + c) << 24) | (c << 16));
-    return lo | hi;
+    const unsigned pair = (tok & 1) ? 0x03070105u : 0x06020400u, half = (tok & 2) ? 0x03020706u : 0x05040100u;
+    const unsigned e = __builtin_amdgcn_perm((unsigned)lane_xor16<1>((int)d), d, pair);
+    return __builtin_amdgcn_perm((unsigned)lane_xor16<2>((int)e), e, half);
 }
 
 template <int TOK, int NV, bool VEC>

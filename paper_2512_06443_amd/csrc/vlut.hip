@@ -1314,7 +1314,7 @@ int vlut_mpgemm_f32(const uint8_t* packed, float w_scale, const float* w_scale_r
         std::memset(&q, 0, sizeof(q));
         q.packed = packed; q.x = x; q.w_rows = w_rows; q.y = y; q.acc = acc_or_null; q.a_scale_out = a_scale_out_or_null;
         q.ldx = ldx; q.w_scale = w_one; q.M = (int)M; q.N = (int)N; q.K = (int)K; q.KCn = (int)((K / 4 + 15) / 16);
-        q.RGtotal = (int)((M + 3) / 4); q.ldy = (int)ldy; q.macros = (q.KCn + 3) / 4; q.x_vec = x_vec;
+        q.RGtotal = (int)((M + 3) / 4); q.ldy = (int)ldy; q.macros = (q.KCn + 3) / 4;
         switch (decode_token_slots(N)) {
         case 1: return launch_decode<1>(q, s);
         case 2: return launch_decode<2>(q, s);
