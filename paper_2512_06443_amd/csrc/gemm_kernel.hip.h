@@ -539,6 +539,27 @@ constexpr GemmTile kGemmTiles[] = {
     {1, 1, 1, 8, {2, 1}, {2.93, 2.05}, {0.93, 1.81}, {2.161, 1.575}, {0.032, 0.000}, {0.452, 0.658}},
 };
 constexpr int kGemmTileCount = (int)(sizeof(kGemmTiles) / sizeof(kGemmTiles[0]));
-constexpr bool gemm_tile_built(int gw, int tile) { return gw == 4 || kGemmTiles[tile].pass[1] > 0.0; }
+
+// More tiles for four weights per byte, considered from ten macro steps on (below, the choice among the others stays as it was, although 128 x 64
+// in two groups is often the faster one there too: 7117 x 328 x 569 10.5 / 8.7 us).  Fitted on the scale of the others to graph replays of 150
+// shapes of 400 to 14336 rows, K = 256 to 14336 and 48 to 1024 tokens.  In us:
+//   128 x 64 in two K groups: 78 KB of LDS and 90 registers, so that two workgroups share a unit; 6912 x 2560 x 256 9.6 -> 9.3, 4870 x 1892 x 821 16.5 -> 13.8
+//   128 x 64 in four groups of one wave (gemm_private_kernel), long K: 4096 x 14336 x 512 32.1 -> 30.7, 4864 x 7552 x 225 17.4 -> 17.3
+//   160 x 64 so (gemm_private_kernel), where it fills the units as the others don't: 2560 x 6912 x 1024 25.2 -> 22.2
+constexpr GemmTile kGemmTilesLong[] = {
+    {1, 2, 4, 2, {2, 1}, {3.32, 0.00}, {0.33, 0.00}, {1.020, 0.000}, {0.121, 0.000}, {0.385, 0.000}},
+    {4, 2, 1, 4, {1, 1}, {2.27, 0.00}, {3.49, 0.00}, {0.638, 0.000}, {0.000, 0.000}, {0.838, 0.000}},
+    {5, 2, 1, 4, {1, 1}, {2.46, 0.00}, {3.88, 0.00}, {0.740, 0.000}, {0.000, 0.000}, {1.002, 0.000}},
+};
+constexpr int kGemmTilesLongCount = (int)(sizeof(kGemmTilesLong) / sizeof(kGemmTilesLong[0])), kGemmTilesLongMacros = 10;
+constexpr GemmTile gemm_tile(int tile) { return tile < kGemmTileCount ? kGemmTiles[tile] : kGemmTilesLong[tile - kGemmTileCount]; }
+constexpr bool gemm_tile_built(int gw, int tile) { return gw == 4 || gemm_tile(tile).pass[1] > 0.0; }
+// 128 x 64 in four groups of two waves (64 rows each) is left out where these three are considered: of the 103 shapes with ten macro steps or
+// more the tile of the least cost is then within 0.6 % of the fastest on average (with it 0.7 %, without the three 2.9 %).
+constexpr bool gemm_tile_considered(int gw, int tile, int64_t macros) {
+    const bool more = gw == 4 && macros >= kGemmTilesLongMacros;
+    const GemmTile t = gemm_tile(tile);
+    return gemm_tile_built(gw, tile) && (tile < kGemmTileCount ? !(more && t.rt == 2 && t.ct == 2) : more);
+}
 
 }  // namespace

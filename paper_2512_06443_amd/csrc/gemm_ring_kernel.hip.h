@@ -27,14 +27,14 @@ namespace {
 // of the first stage and stored to LDS behind the loop, when every load has been waited for.
 // ---------------------------------------------------------------------------------------------
 #if defined(__HIP_DEVICE_COMPILE__)
-// 16 bytes per lane from offset `at` to LDS, lane after lane from `to` on
-__device__ __forceinline__ void load_to_lds(buffer_rsrc r, unsigned at, unsigned to) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(at), "s"(r) : "memory", "m0");
+// 16 bytes per lane from offset `at` + `from` to LDS, lane after lane from `to` on
+__device__ __forceinline__ void load_to_lds(buffer_rsrc r, unsigned at, unsigned from, unsigned to) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(to), "v"(at), "s"(r), "s"(from) : "memory", "m0");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 #else
-inline __device__ void load_to_lds(buffer_rsrc, unsigned, unsigned) {}
+inline __device__ void load_to_lds(buffer_rsrc, unsigned, unsigned, unsigned) {}
 template <int N>
 inline __device__ void wait_loads() {}
 #endif
@@ -94,17 +94,18 @@ __global__ void __launch_bounds__(64 * WM * WK, 2) gemm_ring_kernel(const GemmPa
     for (int u = 0; u < kActLoads; ++u) aat[u] = (unsigned)(u * WM + wm) * (unsigned)p.Ka * 8u + (unsigned)(lane * 16);
     const unsigned group = (unsigned)(wk * kRingSlots * kStep);
     const unsigned weights = group + 2 * CT * S::kP2 + (unsigned)(wm * RT * 1024);
-    struct Step { buffer_rsrc act, weights; };
-    auto step_at = [&](int t) {                            // pass t of this K group; empty past the last one
-        const int64_t macro = wk + (int64_t)t * WK;
-        return Step{make_buffer(abase + macro * kChunk, t < passes ? aleft - macro * kChunk : 0), make_buffer(wbase + macro * 128, t < passes ? wleft - macro * 128 : 0)};
+    const buffer_rsrc act_from = make_buffer(abase, aleft), weights_from = make_buffer(wbase, wleft);
+    struct Step { unsigned act, weights; };
+    auto step_at = [&](int t) {                            // pass t of this K group; past the last one the last step of K, which nobody reads
+        const unsigned macro = (unsigned)min(wk + t * WK, p.macros - 1);
+        return Step{macro * (unsigned)kChunk, macro * 128u};
     };
     auto load = [&](const Step& from, int slot, int op) {
         if (op < kActLoads) {
             const int c = op * WM + wm;
-            load_to_lds(from.act, aat[op], group + (unsigned)(slot * kStep + (c >> 1) * S::kP2 + (c & 1) * S::kP1));
+            load_to_lds(act_from, aat[op], from.act, group + (unsigned)(slot * kStep + (c >> 1) * S::kP2 + (c & 1) * S::kP1));
         } else {
-            load_to_lds(from.weights, wat[op - kActLoads], weights + (unsigned)(slot * kStep + (op - kActLoads) * 1024));
+            load_to_lds(weights_from, wat[op - kActLoads], from.weights, weights + (unsigned)(slot * kStep + (op - kActLoads) * 1024));
         }
     };
 #pragma unroll
@@ -204,7 +205,7 @@ __global__ void __launch_bounds__(64 * WM * WK, 2) gemm_ring_kernel(const GemmPa
     gemm_store<RT, CT, WM, WK, kStoreTogether>(p, acc, lane, wm, wk, mt, nt, kScales);
 }
 
-// The tiles of kGemmTiles that this kernel serves: those that are 64 rows per wave, or 128 x 128.
-constexpr bool gemm_ring_built(int gw, int rt, int ct, int wm, int wk) { return gw == 4 && (rt == 2 || (ct == 4 && wm == 4 && wk == 2)); }
+// The tiles that this kernel serves: those that are 64 rows per wave, 128 x 128, and 128 x 64 in two K groups.
+constexpr bool gemm_ring_built(int gw, int rt, int ct, int wm, int wk) { return gw == 4 && (rt == 2 || (ct > 1 && wm == 4 && wk == 2)); }
 
 }  // namespace

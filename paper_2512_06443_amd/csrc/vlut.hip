@@ -35,6 +35,7 @@
 #include "lookup5_kernel.hip.h"
 #include "gemm_kernel.hip.h"
 #include "gemm_ring_kernel.hip.h"
+#include "gemm_private_kernel.hip.h"
 #include "decode_kernel.hip.h"
 #include "narrow_kernel.hip.h"
 #include "small_kernels.hip.h"
@@ -677,7 +678,7 @@ int launch_quantize(const float* x, int64_t N, int64_t K, int64_t ldx, int8_t* a
 
 // ---- matrix-core path (gemm_kernel): products with streamed tables, unless a plan of the lookup kernels is forced or a rule below says otherwise
 double gemm_cost(int gw, int tile, int64_t M, int64_t macros, int64_t N) {
-    const GemmTile& t = kGemmTiles[tile];
+    const GemmTile t = gemm_tile(tile);
     const int g = gw - 4;
     const int64_t tiles = ((M + t.rows() - 1) / t.rows()) * ((N + t.tokens() - 1) / t.tokens());
     const double n = (double)((tiles + 255) / 256), passes = (double)((macros + t.wk - 1) / t.wk);
@@ -687,8 +688,8 @@ double gemm_cost(int gw, int tile, int64_t M, int64_t macros, int64_t N) {
 int choose_gemm_tile(int gw, int64_t M, int64_t macros, int64_t N) {
     int best = -1;
     double best_cost = 1e300;
-    for (int i = 0; i < kGemmTileCount; ++i) {
-        if (!gemm_tile_built(gw, i)) continue;
+    for (int i = 0; i < kGemmTileCount + kGemmTilesLongCount; ++i) {
+        if (!gemm_tile_considered(gw, i, macros)) continue;
         const double c = gemm_cost(gw, i, M, macros, N);
         if (c < best_cost) { best_cost = c; best = i; }
     }
@@ -768,12 +769,13 @@ bool matrix_cores_take_mixed() { return t_forced5.R == 0 && t_forced5.S == 0 && 
 
 template <int GW, int I>
 int launch_gemm_t(const GemmParams& p, hipStream_t stream) {
-    constexpr GemmTile t = kGemmTiles[I];
-    constexpr bool ring = gemm_ring_built(GW, t.rt, t.ct, t.wm, t.wk);
+    constexpr GemmTile t = gemm_tile(I);
+    constexpr bool own = gemm_private_built(GW, t.wm, t.wk), ring = gemm_ring_built(GW, t.rt, t.ct, t.wm, t.wk);
     void (*kfn)(GemmParams);
-    if constexpr (ring) kfn = gemm_ring_kernel<t.rt, t.ct, t.wm, t.wk>;
+    if constexpr (own) kfn = gemm_private_kernel<t.rt, t.ct, t.wk>;
+    else if constexpr (ring) kfn = gemm_ring_kernel<t.rt, t.ct, t.wm, t.wk>;
     else kfn = gemm_kernel<GW, t.rt, t.ct, t.wm, t.wk>;
-    constexpr int lds = ring ? ring_lds_bytes<t.rt, t.ct, t.wm, t.wk>() : gemm_lds_bytes<GW, t.rt, t.ct, t.wm, t.wk>();
+    constexpr int lds = own ? PrivateShape<t.rt, t.ct, t.wk>::kLds : ring ? ring_lds_bytes<t.rt, t.ct, t.wm, t.wk>() : gemm_lds_bytes<GW, t.rt, t.ct, t.wm, t.wk>();
     static_assert(lds <= 160 * 1024, "LDS of a workgroup");
     static std::atomic<unsigned> attr_done{0};   // one bit per device: the attribute belongs to the device's copy
     if (!allow_dynamic_lds((const void*)kfn, lds, attr_done)) return VLUT_ERR_DEVICE;
@@ -786,7 +788,7 @@ int launch_gemm_t(const GemmParams& p, hipStream_t stream) {
 
 template <int GW, int I = 0>
 int launch_gemm_tile(int tile, const GemmParams& p, hipStream_t stream) {
-    if constexpr (I >= kGemmTileCount) {
+    if constexpr (I >= kGemmTileCount + kGemmTilesLongCount) {
         return VLUT_ERR_UNSUPPORTED;
     } else {
         if constexpr (gemm_tile_built(GW, I)) {
@@ -1585,7 +1587,7 @@ static int codes_matrix_plan(int gw, int64_t M, int64_t K, int64_t Kmain, int64_
     if (cp.ch) {
         out4[0] = 16 * cp.mt; out4[1] = 8 * cp.ch; out4[2] = kDecodeWaves / cp.mt;
     } else {
-        const GemmTile& t = kGemmTiles[choose_gemm_tile(gw, M, gemm_macros(gw, Kmain), N)];
+        const GemmTile t = gemm_tile(choose_gemm_tile(gw, M, gemm_macros(gw, Kmain), N));
         out4[0] = t.rows(); out4[1] = t.tokens(); out4[2] = t.wk;
     }
     const int64_t tiles = ((M + out4[0] - 1) / out4[0]) * ((N + out4[1] - 1) / out4[1]);
