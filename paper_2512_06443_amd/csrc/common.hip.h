@@ -74,10 +74,24 @@ __device__ __forceinline__ unsigned lds_base_of(void* p) {
 #if defined(__HIP_DEVICE_COMPILE__)
 typedef __amdgpu_buffer_rsrc_t buffer_rsrc;
 // The `left` bytes from base on: loads beyond them return zeros (left < 0: none).
-__device__ __forceinline__ buffer_rsrc make_buffer(const void* base, int64_t left) {
-    const unsigned hi = (unsigned)(left >> 32), n = (int)hi < 0 ? 0u : (hi ? 0xffffffffu : (unsigned)left);
-    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)n, 0x00027000);
+__device__ __forceinline__ unsigned buffer_bytes(int64_t left) {
+    const unsigned hi = (unsigned)(left >> 32);
+    return (int)hi < 0 ? 0u : (hi ? 0xffffffffu : (unsigned)left);
 }
+__device__ __forceinline__ buffer_rsrc make_buffer(const void* base, int64_t left) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)buffer_bytes(left), 0x00027000);
+}
+// Memory whose part from a moving start on is read: at(off) is the descriptor of what lies `off` bytes (at most `bytes`) further and ends
+// where the memory ends.  The scalar offset of a load would do the same in one instruction less, but whether the length is checked
+// against an offset with or without it is described both ways.
+struct BufferSpan {
+    const uint8_t* base;
+    unsigned bytes;
+    __device__ __forceinline__ BufferSpan(const void* base_, int64_t left) : base((const uint8_t*)base_), bytes(buffer_bytes(left)) {}
+    __device__ __forceinline__ buffer_rsrc at(unsigned off) const {
+        return __builtin_amdgcn_make_buffer_rsrc((void*)(base + off), 0, (int)(bytes - off), 0x00027000);
+    }
+};
 // 16 bytes from offset `at` on (any multiple of four: vectors from memory are aligned to a dword)
 __device__ __forceinline__ i32x4 buffer_load128(buffer_rsrc r, unsigned at) {
     return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)at, 0, 0));
@@ -85,6 +99,10 @@ __device__ __forceinline__ i32x4 buffer_load128(buffer_rsrc r, unsigned at) {
 #else
 typedef int buffer_rsrc;
 inline __device__ buffer_rsrc make_buffer(const void*, int64_t) { return 0; }
+struct BufferSpan {
+    inline __device__ BufferSpan(const void*, int64_t) {}
+    inline __device__ buffer_rsrc at(unsigned) const { return 0; }
+};
 inline __device__ i32x4 buffer_load128(buffer_rsrc, unsigned) { return i32x4{0, 0, 0, 0}; }
 #endif
 

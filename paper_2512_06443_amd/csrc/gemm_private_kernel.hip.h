@@ -61,17 +61,17 @@ __global__ void __launch_bounds__(64 * WK, 1) gemm_private_kernel(const GemmPara
 #pragma unroll
     for (int c = 0; c < kActLoads; ++c) aat[c] = (unsigned)c * (unsigned)p.Ka * 8u + (unsigned)(lane * 16);
     const unsigned group = (unsigned)(wk * P::kGroup), weights = group + P::kActSlots * P::kAct;
-    const buffer_rsrc act_from = make_buffer(abase, aleft), weights_from = make_buffer(wbase, wleft);
-    struct Step { unsigned act, weights; };
-    auto step_at = [&](int t) {                            // pass t of this wave; past the last one the last step of K, which nobody reads
+    const BufferSpan act_from(abase, aleft), weights_from(wbase, wleft);
+    struct Step { buffer_rsrc act, weights; };
+    auto step_at = [&](int t) {                            // pass t of this wave; past K the last step again (unread or, in the last pass, against zeros)
         const unsigned macro = (unsigned)min(wk + t * WK, p.macros - 1);
-        return Step{macro * (unsigned)kChunk, macro * 128u};
+        return Step{act_from.at(macro * (unsigned)kChunk), weights_from.at(macro * 128u)};
     };
     auto load = [&](const Step& from, int slot, int set, int op) {      // weights first: they come from further away
-        if (op < RT) load_to_lds(weights_from, wat[op], from.weights, weights + (unsigned)(set * P::kWeights + op * 1024));
+        if (op < RT) load_to_lds(from.weights, wat[op], weights + (unsigned)(set * P::kWeights + op * 1024));
         else {
             const int c = op - RT;
-            load_to_lds(act_from, aat[c], from.act, group + (unsigned)(slot * P::kAct + (c >> 1) * S::kP2 + (c & 1) * S::kP1));
+            load_to_lds(from.act, aat[c], group + (unsigned)(slot * P::kAct + (c >> 1) * S::kP2 + (c & 1) * S::kP1));
         }
     };
 #pragma unroll

@@ -22,19 +22,24 @@ namespace {
 //
 // The loads are single instructions written out (no result register; the LDS address in M0): the compiler, when it issues them itself,
 // waits for all of them before every LDS read that follows.  Waits are counted by hand: each stage is exactly kLoads of them per wave, also past the
-// end of K, where the descriptors are empty, so that vmcnt(kLoads) before the barrier of step t stands for "the loads of step t + 1 are
+// end of K, where the last step is loaded again, so that vmcnt(kLoads) before the barrier of step t stands for "the loads of step t + 1 are
 // done": behind them only those of step t + 2 have been issued.  Nothing else in the loop touches memory.  The scales are loaded ahead
 // of the first stage and stored to LDS behind the loop, when every load has been waited for.
+//
+// What keeps the reads inside the tensors: a stage's descriptors start at its step and end with the tensor (BufferSpan), so that rows and chunks
+// past the last one, and the rest of the last row group's and the last chunk's step, are zeros.  Inside the tensor a step that K ends in
+// reads on into the next row group or chunk, and a K group whose share of the last pass lies past K multiplies the last step once more:
+// both meet weights that keep has set to zero.
 // ---------------------------------------------------------------------------------------------
 #if defined(__HIP_DEVICE_COMPILE__)
-// 16 bytes per lane from offset `at` + `from` to LDS, lane after lane from `to` on
-__device__ __forceinline__ void load_to_lds(buffer_rsrc r, unsigned at, unsigned from, unsigned to) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(to), "v"(at), "s"(r), "s"(from) : "memory", "m0");
+// 16 bytes per lane from offset `at` on to LDS, lane after lane from `to` on
+__device__ __forceinline__ void load_to_lds(buffer_rsrc r, unsigned at, unsigned to) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(at), "s"(r) : "memory", "m0");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 #else
-inline __device__ void load_to_lds(buffer_rsrc, unsigned, unsigned, unsigned) {}
+inline __device__ void load_to_lds(buffer_rsrc, unsigned, unsigned) {}
 template <int N>
 inline __device__ void wait_loads() {}
 #endif
@@ -75,8 +80,7 @@ __global__ void __launch_bounds__(64 * WM * WK, 2) gemm_ring_kernel(const GemmPa
     auto load_scale = [&](int j) { return j < BN ? p.a_scale[min(nt * BN + j, p.N - 1)] : (p.w_rows ? p.w_rows[min(mt * BM + j - BN, p.M - 1)] : p.w_scale); };
     const float scale0 = load_scale(min(tid, BN + BM - 1)), scale1 = load_scale(min(tid + kThreads_, BN + BM - 1));
 
-    // ---- loads.  Descriptors reach from the tile's first byte (of this step) to the end of the tensor; offsets inside the tile are constant.
-    //      What lies past the end of K is another chunk's or row's data and meets zero weights (keep, below).
+    // ---- loads.  Descriptors reach from the tile's first byte of a step to the end of the tensor; offsets inside the tile are constant.
     const int rg0 = mt * (BM / 4), chunk0 = nt * (BN / 8);
     const uint8_t* wbase = p.packed + (size_t)rg0 * p.KCn * 64;
     const int8_t* abase = p.a_q + (size_t)chunk0 * p.Ka * 8;
@@ -94,18 +98,18 @@ __global__ void __launch_bounds__(64 * WM * WK, 2) gemm_ring_kernel(const GemmPa
     for (int u = 0; u < kActLoads; ++u) aat[u] = (unsigned)(u * WM + wm) * (unsigned)p.Ka * 8u + (unsigned)(lane * 16);
     const unsigned group = (unsigned)(wk * kRingSlots * kStep);
     const unsigned weights = group + 2 * CT * S::kP2 + (unsigned)(wm * RT * 1024);
-    const buffer_rsrc act_from = make_buffer(abase, aleft), weights_from = make_buffer(wbase, wleft);
-    struct Step { unsigned act, weights; };
-    auto step_at = [&](int t) {                            // pass t of this K group; past the last one the last step of K, which nobody reads
+    const BufferSpan act_from(abase, aleft), weights_from(wbase, wleft);
+    struct Step { buffer_rsrc act, weights; };
+    auto step_at = [&](int t) {                            // pass t of this K group; past K the last step again (unread or, in the last pass, against zeros)
         const unsigned macro = (unsigned)min(wk + t * WK, p.macros - 1);
-        return Step{macro * (unsigned)kChunk, macro * 128u};
+        return Step{act_from.at(macro * (unsigned)kChunk), weights_from.at(macro * 128u)};
     };
     auto load = [&](const Step& from, int slot, int op) {
         if (op < kActLoads) {
             const int c = op * WM + wm;
-            load_to_lds(act_from, aat[op], from.act, group + (unsigned)(slot * kStep + (c >> 1) * S::kP2 + (c & 1) * S::kP1));
+            load_to_lds(from.act, aat[op], group + (unsigned)(slot * kStep + (c >> 1) * S::kP2 + (c & 1) * S::kP1));
         } else {
-            load_to_lds(weights_from, wat[op - kActLoads], from.weights, weights + (unsigned)(slot * kStep + (op - kActLoads) * 1024));
+            load_to_lds(from.weights, wat[op - kActLoads], weights + (unsigned)(slot * kStep + (op - kActLoads) * 1024));
         }
     };
 #pragma unroll
