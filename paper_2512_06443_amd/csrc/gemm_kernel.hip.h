@@ -178,9 +178,25 @@ __device__ __forceinline__ void swap_rows16(float& a, float& b, float& c, float&
     (void)a; (void)b; (void)c; (void)d;
 #endif
 }
-// (y and its rows may start at any float: global memory takes vectors aligned to a dword)
+// One, two or four consecutive floats.  y and its rows may start at any float, and global memory takes vectors aligned to a dword: the
+// store says so (by a type that is named here: one that a template deduces has lost its alignment).
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <class V>
+__device__ __forceinline__ void store_floats(float* dst, V v, bool past_the_caches) {
+    constexpr int kWidth = sizeof(V) / 4;
+    if constexpr (kWidth == 4) {
+        if (past_the_caches) __builtin_nontemporal_store(v, (f32x4_any*)dst);
+        else *(f32x4_any*)dst = v;
+    } else if constexpr (kWidth == 2) {
+        if (past_the_caches) __builtin_nontemporal_store(v, (f32x2_any*)dst);
+        else *(f32x2_any*)dst = v;
+    } else {
+        if (past_the_caches) __builtin_nontemporal_store(v, dst);
+        else *dst = v;
+    }
+}
 
 // The end of a tiled product: the K groups' sums meet in LDS (overwritten from its start; the caller has passed a barrier since its last
 // use), scales, stores.  A lane holds, of each 32 x 32 product, one output row (gemm_row) and the tokens 8 g + 4 kb + 0..3 in registers
@@ -246,8 +262,7 @@ __device__ __forceinline__ void gemm_store(const GemmParams& p, const i32x16 (&a
                 if (!kInside && n_lane + nq + n >= p.N) return;
                 float* const dst = y_lane + (size_t)(nq + n) * p.ldy + m;
                 if (kInside || m_lane + m + kWidth <= p.M) {
-                    if (p.stream_out) __builtin_nontemporal_store(v, (decltype(v)*)dst);
-                    else *(decltype(v)*)dst = v;
+                    store_floats(dst, v, p.stream_out);
                 } else if constexpr (kWidth > 1) {
 #pragma unroll
                     for (int j = 0; j + 1 < kWidth; ++j)
@@ -268,10 +283,10 @@ __device__ __forceinline__ void gemm_store(const GemmParams& p, const i32x16 (&a
 #pragma unroll
                 for (int h = 0; h < 4; h += 2) {
                     if constexpr (kTogether && RT == 2) {
-                        put(0, h, f32x4_any{out[0][h], out[0][h + 1], out[1][h], out[1][h + 1]});
+                        put(0, h, f32x4{out[0][h], out[0][h + 1], out[1][h], out[1][h + 1]});
                     } else {
 #pragma unroll
-                        for (int rt = 0; rt < RT; ++rt) put(32 * rt, h, f32x2_any{out[rt][h], out[rt][h + 1]});
+                        for (int rt = 0; rt < RT; ++rt) put(32 * rt, h, f32x2{out[rt][h], out[rt][h + 1]});
                     }
                 }
             }
