@@ -144,7 +144,8 @@ PyObject* py_quantize_act(PyObject*, PyObject* const* o, Py_ssize_t n) {
 }
 
 // What mpgemm, mpgemm_g5 and mpgemm_mixed have in common: (packed, w_scale, a_q, a_scale, M, y, acc or None, want_acc, workspace or None).
-// `used` tells what the call needs of operands aligned to 16 bytes; others are left to the Python form.
+// `used` tells what the call needs of operands aligned to 16 bytes; others are left to the Python form, and so is a workspace without
+// memory, which the lean call would take for one that was not given.
 template <class Bytes, class Call>
 PyObject* product(PyObject* const* o, Bytes used, Call call) {
     return guarded([&]() -> PyObject* {
@@ -152,7 +153,7 @@ PyObject* product(PyObject* const* o, Bytes used, Call call) {
         float w_scale;
         int64_t M;
         if (!packed || !q || !s || q->dim() < 2 || s->dim() < 1 || !real(o[1], w_scale) || !whole(o[4], M) || M < 0 || !output(o[5], gy) ||
-            !optional(o[6], gacc) || !optional(o[8], gws) || ((uintptr_t)packed->data_ptr() | (uintptr_t)q->data_ptr()) % 16 != 0)
+            !optional(o[6], gacc) || !optional(o[8], gws) || (gws && !gws->data_ptr()) || ((uintptr_t)packed->data_ptr() | (uintptr_t)q->data_ptr()) % 16 != 0)
             Py_RETURN_NONE;
         const int64_t K = q->size(1), N = s->size(0);
         const int want = PyObject_IsTrue(o[7]);

@@ -92,9 +92,9 @@ SHOWN int held() { return held_; }
 """
 
 
-def test_native_form_allocates_and_calls_with_the_interpreter_released(tmp_path):
-    """An allocation may wait for the device, as the call may: other threads run Python meanwhile, as they do in the Python form.  An
-    allocation that fails leaves the call to that form, with the lock taken back."""
+@pytest.fixture(scope="module")
+def on_cpu(tmp_path_factory):
+    """(the module, its counting library, the library's path)"""
     import ctypes
     import importlib.util
     import os
@@ -102,6 +102,7 @@ def test_native_form_allocates_and_calls_with_the_interpreter_released(tmp_path)
     from paper_2512_06443_amd import build
     if torch.version.hip is None:
         pytest.skip("built with a torch for ROCm only")
+    tmp_path = tmp_path_factory.mktemp("on_cpu")
     (tmp_path / "on_cpu.cpp").write_text(ON_CPU)
     path = str(tmp_path / "_vlut_torch.so")
     own = {build.TORCH_SRC: str(tmp_path / "on_cpu.cpp"), build.TORCH_LIB: path, "-O2": "-O0"}
@@ -112,6 +113,14 @@ def test_native_form_allocates_and_calls_with_the_interpreter_released(tmp_path)
     n = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(n)
     n.bind(*[lib.address(i) for i in range(len(B._NATIVE_ORDER))])
+    return n, lib, path
+
+
+def test_native_form_allocates_and_calls_with_the_interpreter_released(on_cpu):
+    """An allocation may wait for the device, as the call may: other threads run Python meanwhile, as they do in the Python form.  An
+    allocation that fails leaves the call to that form, with the lock taken back."""
+    import ctypes
+    n, lib, path = on_cpu
     M, K, N = 8, 16, 3
     w, x, p = torch.zeros(M, K, dtype=torch.int8), torch.zeros(N, K), torch.zeros(64, dtype=torch.uint8)
     q, s = torch.zeros(1, K, 8, dtype=torch.int8), torch.zeros(N)
@@ -126,6 +135,18 @@ def test_native_form_allocates_and_calls_with_the_interpreter_released(tmp_path)
         lib.start(allocations)
         assert f(*args) is None and lib.calls() == 0, f
     assert ctypes.PyDLL(path).calls() == 0 and ctypes.pythonapi.PyGILState_Check() == 1
+
+
+def test_native_form_leaves_a_workspace_without_memory_to_the_python_form(on_cpu):
+    """The Python form hands it over and the call refuses it; the lean call would run without one."""
+    n, lib, _ = on_cpu
+    M, K, N = 8, 16, 3
+    p, q, s = torch.zeros(64, dtype=torch.uint8), torch.zeros(1, K, 8, dtype=torch.int8), torch.zeros(N)
+    for f in (n.mpgemm, n.mpgemm_g5, n.mpgemm_mixed):
+        lib.start(0)
+        assert f(p, 0.5, q, s, M, None, None, False, torch.empty(0, dtype=torch.uint8)) is None
+        assert (lib.allocations(), lib.calls()) == (0, 0)
+        assert f(p, 0.5, q, s, M, None, None, False, torch.empty(64, dtype=torch.uint8)) is not None and lib.calls() == 1
 
 
 def _both(monkeypatch, f):
