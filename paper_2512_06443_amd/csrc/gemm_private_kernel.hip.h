@@ -36,7 +36,7 @@ __global__ void __launch_bounds__(64 * WK, 1) gemm_private_kernel(const GemmPara
     constexpr int NG = 4 * CT;                             // activation operands of a step: q = 0..3, CT each
     constexpr int AR = 2;                                  // of them in registers ahead of use
     constexpr int kReady = NG - AR - 1;                    // operand behind which the next step's loads are waited for
-    constexpr int kIssue = CT == 1 ? 1 : 3;                // the loads of the step after that stand behind the first operands
+    constexpr int kIssue = 3;                              // the loads of the step after that stand behind the first operands
     static_assert(kReady < 3 * CT && kIssue <= kReady && BN + BM <= 2 * kThreads_, "");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wk = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -161,8 +161,7 @@ __global__ void __launch_bounds__(64 * WK, 1) gemm_private_kernel(const GemmPara
         if (t + 4 < passes) macro_step(0, 1, t + 4);
         if (t + 5 < passes) macro_step(1, 2, t + 5);
     }
-    wait_loads<0>();
-    wg_barrier_lds();                                      // (scales and sums lie where other waves' slots are)
+    wait_loads<0>();                                       // (scales lie behind every slot, the sums of gemm_store where they are)
     *(lds_i32*)(unsigned)(P::kScales + min(tid, BN + BM - 1) * 4) = __builtin_bit_cast(int, scale0);
     if (tid + kThreads_ < BN + BM) *(lds_i32*)(unsigned)(P::kScales + (tid + kThreads_) * 4) = __builtin_bit_cast(int, scale1);
     wg_barrier_lds();
