@@ -1553,20 +1553,16 @@ int vlut_mpgemm_mixed_lean(const uint8_t* packed, float w_scale, const int8_t* a
 }
 
 static int codes_kernel(int64_t M, int64_t K, int64_t N) {
-    if (narrow_applies(M, K, N, nullptr, false)) return VLUT_KERNEL_FEW_TOKENS;
-    const Plan pl = choose_plan(M, K, N);
-    if (pl.R == 0) return VLUT_ERR_UNSUPPORTED;
-    return matrix_cores_take(pl, M, K, N) ? VLUT_KERNEL_MATRIX : VLUT_KERNEL_LOOKUP;
+    const Route& r = find_route(VLUT_FORM_CODES, M, K, N);
+    if (r.narrow) return VLUT_KERNEL_FEW_TOKENS;
+    if (r.status != VLUT_OK) return r.status;
+    return r.kernel == kRouteTables ? VLUT_KERNEL_LOOKUP : VLUT_KERNEL_MATRIX;
 }
 
+// (the queries answer from the routes that the calls take)
 int vlut_query_kernel(int form, int64_t M, int64_t K, int64_t N) {
-    if (form == VLUT_FORM_G5) {
-        if (!shape5_ok(M, K, N)) return VLUT_ERR_SHAPE;
-        if (!plan5_valid(choose_plan5(M, K, N), M, K, N)) return VLUT_ERR_UNSUPPORTED;
-        return matrix_cores_take_g5(K) ? VLUT_KERNEL_MATRIX : VLUT_KERNEL_LOOKUP;
-    }
-    if (form != VLUT_FORM_CODES && form != VLUT_FORM_F32 && form != VLUT_FORM_MIXED) return VLUT_ERR_UNSUPPORTED;
-    if (!shape_ok(M, K, N)) return VLUT_ERR_SHAPE;
+    if (form != VLUT_FORM_CODES && form != VLUT_FORM_F32 && form != VLUT_FORM_MIXED && form != VLUT_FORM_G5) return VLUT_ERR_UNSUPPORTED;
+    if (form == VLUT_FORM_G5 ? !shape5_ok(M, K, N) : !shape_ok(M, K, N)) return VLUT_ERR_SHAPE;
     if (form == VLUT_FORM_CODES) return codes_kernel(M, K, N);
     if (form == VLUT_FORM_F32) {
         const F32Layout L = f32_layout(M, K, N);
@@ -1574,25 +1570,9 @@ int vlut_query_kernel(int form, int64_t M, int64_t K, int64_t N) {
         if (L.kind == kF32Narrow) return VLUT_KERNEL_FEW_TOKENS;
         return L.kind == kF32Fused ? VLUT_KERNEL_LOOKUP : codes_kernel(M, K, N);
     }
-    Plan5 p5;
-    Plan p4;
-    if (!mixed_plans(M, K, N, &p5, &p4)) return VLUT_ERR_UNSUPPORTED;
-    return matrix_cores_take_mixed() ? VLUT_KERNEL_MATRIX : VLUT_KERNEL_LOOKUP;
-}
-
-// Of a call that the matrix cores take from INT8 codes, Kmain values of K in the main blob; `narrow` as in codes_plan_if_taken.
-static int codes_matrix_plan(int gw, int64_t M, int64_t K, int64_t Kmain, int64_t N, bool narrow, int* out4) {
-    const CodesPlan cp = codes_plan_if_taken(gw, M, K, N, narrow);
-    if (!cp.ch && narrow) return VLUT_ERR_UNSUPPORTED;       // the table kernel's
-    if (cp.ch) {
-        out4[0] = 16 * cp.mt; out4[1] = 8 * cp.ch; out4[2] = kDecodeWaves / cp.mt;
-    } else {
-        const GemmTile t = gemm_tile(choose_gemm_tile(gw, M, gemm_macros(gw, Kmain), N));
-        out4[0] = t.rows(); out4[1] = t.tokens(); out4[2] = t.wk;
-    }
-    const int64_t tiles = ((M + out4[0] - 1) / out4[0]) * ((N + out4[1] - 1) / out4[1]);
-    out4[3] = (int)std::min<int64_t>(tiles, INT32_MAX);
-    return VLUT_OK;
+    const Route& r = find_route(form, M, K, N);
+    if (r.status != VLUT_OK) return r.status;
+    return r.kernel == kRouteTables ? VLUT_KERNEL_LOOKUP : VLUT_KERNEL_MATRIX;
 }
 
 int vlut_query_matrix_plan(int form, int64_t M, int64_t K, int64_t N, int* out4) {
@@ -1600,11 +1580,6 @@ int vlut_query_matrix_plan(int form, int64_t M, int64_t K, int64_t N, int* out4)
     const int kernel = vlut_query_kernel(form, M, K, N);
     if (kernel < 0) return kernel;
     if (kernel == VLUT_KERNEL_LOOKUP) return VLUT_ERR_UNSUPPORTED;
-    if (form == VLUT_FORM_G5) return codes_matrix_plan(5, M, K, K, N, false, out4);
-    if (form == VLUT_FORM_MIXED) {
-        const int64_t K5 = vlut_mixed_k5(K);
-        return codes_matrix_plan(K5 > 0 ? 5 : 4, M, K, K5 > 0 ? K5 : K, N, false, out4);
-    }
     if (kernel == VLUT_KERNEL_MATRIX_FEW_TOKENS) {
         const int mt = decode_row_tiles(M);
         out4[0] = 16 * mt; out4[1] = decode_token_slots(N); out4[2] = kDecodeWaves / mt;
@@ -1612,7 +1587,17 @@ int vlut_query_matrix_plan(int form, int64_t M, int64_t K, int64_t N, int* out4)
         return VLUT_OK;
     }
     if (form == VLUT_FORM_F32 && f32_layout(M, K, N).kind != kF32TwoLaunches) return VLUT_ERR_UNSUPPORTED;
-    return codes_matrix_plan(4, M, K, K, N, narrow_applies(M, K, N, nullptr, false), out4);
+    const Route& r = find_route(form == VLUT_FORM_F32 ? VLUT_FORM_CODES : form, M, K, N);
+    if (r.kernel == kRouteTables) return VLUT_ERR_UNSUPPORTED;       // few tokens: the table kernel's
+    if (r.kernel == kRouteCodes) {
+        out4[0] = 16 * r.codes.mt; out4[1] = 8 * r.codes.ch; out4[2] = kDecodeWaves / r.codes.mt;
+    } else {
+        const GemmTile t = gemm_tile(r.tile);
+        out4[0] = t.rows(); out4[1] = t.tokens(); out4[2] = t.wk;
+    }
+    const int64_t tiles = ((M + out4[0] - 1) / out4[0]) * ((N + out4[1] - 1) / out4[1]);
+    out4[3] = (int)std::min<int64_t>(tiles, INT32_MAX);
+    return VLUT_OK;
 }
 
 size_t vlut_mfma_workspace_bytes(int64_t M, int64_t K, int64_t N) {

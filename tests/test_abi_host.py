@@ -542,3 +542,29 @@ def test_lean_calls_demand_the_workspace_that_is_used(L):
         assert used(*shape) == 0 and demanded(*shape) == need
         assert used(8, 6, 8) == demanded(8, 6, 8) == 0
     assert L.vlut_workspace_used(64, 16384, 40) == L.vlut_workspace_bytes(64, 16384, 40) > 0     # the lookup kernel's
+
+
+def test_shapes_that_take_turns_keep_their_own_routes(L):
+    """What a shape runs is kept in a table in which shapes replace each other (those of a decoder layer among them): every one is answered
+    as if it had been asked for alone."""
+    shapes = [(3840, 2560), (2560, 2560), (13824, 2560), (2560, 6912), (640, 2560), (4096, 4096), (14336, 4096), (4096, 14336), (64, 16384)]
+    L.vlut_query_kernel.argtypes = [ci, i64, i64, i64]
+    L.vlut_query_matrix_plan.argtypes = [ci, i64, i64, i64, ctypes.POINTER(ci)]
+    out = (ci * 4)()
+
+    def answer(form, suffix, M, K, N):
+        used, demanded = getattr(L, "vlut_workspace_used" + suffix), getattr(L, "vlut_workspace_bytes" + suffix)
+        for f in (used, demanded, L.vlut_workspace_bytes_f32):
+            f.argtypes, f.restype = [i64, i64, i64], sz
+        rc = L.vlut_query_matrix_plan(form, M, K, N, out)
+        return L.vlut_query_kernel(form, M, K, N), rc, tuple(out), used(M, K, N), demanded(M, K, N), L.vlut_workspace_bytes_f32(M, K, N)
+    cases = [(form, suffix, M, K // 20 * 20 if form == 2 else K, N) for N in (1, 16, 64, 1024) for M, K in shapes
+             for form, suffix in ((0, ""), (2, "_g5"), (3, "_mixed"))]
+    alone = {}
+    for c in cases:
+        assert L.vlut_set_plan(0, 0, 0, 0) == 0              # (empties the table)
+        alone[c] = answer(*c)
+    assert any(a[3] for a in alone.values()) and len(set(alone.values())) > 20
+    for _ in range(3):
+        for c in cases:
+            assert answer(*c) == alone[c], c
