@@ -326,31 +326,31 @@ def test_degenerate_shapes_through_every_entry_point(B, M, K, N):
     check_y(y1.cpu().numpy(), y_ref)
 
 
-@pytest.mark.parametrize("K", [4, 252, 1028, 3076, 4000])
-@pytest.mark.parametrize("N", [1, 2, 3, 8, 9, 16])
+# The last K of each N: more than the twelve steps of a wave whose values stay in registers.
+@pytest.mark.parametrize("N,K", [(N, K) for N, Ks in ((1, (4, 252, 3076, 61444)), (2, (4, 252, 1028, 29700)), (3, (252, 1028, 14900)),
+                                                      (8, (4, 252, 3076, 7940)), (9, (252, 1028, 4000)), (16, (4, 1028, 3076))) for K in Ks])
 def test_few_tokens_with_values_that_need_the_clamp(B, N, K):
-    """One launch for a few tokens against the quantiser alone: NaN, infinities, rows where 127 / absmax overflows, zeros."""
-    if N * K > 65536:
-        K = 65536 // N // 4 * 4
+    """One launch for a few tokens against the quantiser alone: rows with NaN, with infinities, where 127 / absmax overflows, of zeros, of
+    nothing but NaN and of none of these, each alone (one token) and beside the others."""
+    assert B.query_kernel("f32", 70, K, N) == "matrix_few_tokens"
     rng = np.random.default_rng(100 * K + N)
     W = rng.integers(-1, 2, size=(70, K)).astype(np.int8)
-    x = rng.standard_normal((N, K)).astype(np.float32)
-    special = [np.nan, np.inf, -np.inf, 1e-39]
-    for n in range(N):
-        kind = (n + K) % 6
-        if kind < 4:
-            x[n, rng.integers(0, K, size=2)] = special[kind]
-        elif kind == 4:
-            x[n] *= np.float32(1e-38)
-        else:
-            x[n] = 0.0
-    x[N - 1, K - 1] = np.float32(np.nan)
-    rows = torch.zeros(N * (K + 1) + 1, device="cuda")[1:].view(N, K + 1)[:, :K]      # rows start at any float
-    rows.copy_(torch.from_numpy(x))
     packed = B.pack_weights(dev(W))
-    a_q, scales = B.quantize_act(dev(x))
-    _, want = B.mpgemm(packed, 0.5, a_q, scales, 70, want_acc=True)
-    for t in (dev(x), rows):
-        _, acc, sc = B.mpgemm_f32(packed, 0.5, t, 70, want_acc=True, want_scales=True)
-        assert torch.equal(acc, want)
-        assert torch.equal(sc.view(torch.int32), scales.view(torch.int32))
+    rows = torch.zeros(N * (K + 1) + 1, device="cuda")[1:].view(N, K + 1)[:, :K]      # rows start at any float
+    for first in range(7):
+        print(f"clamp case N={N} K={K} first kind {first}", flush=True)
+        x = rng.standard_normal((N, K)).astype(np.float32)
+        for n in range(N):
+            at = [K - 1, int(rng.integers(0, K))]
+            kind = (first + n) % 7
+            if kind < 3:
+                x[n, at] = np.float32([np.nan, np.inf, -np.inf][kind])
+            elif kind < 6:
+                x[n] *= np.float32([1e-38, 0.0, np.nan][kind - 3])
+        a_q, scales = B.quantize_act(dev(x))
+        _, want = B.mpgemm(packed, 0.5, a_q, scales, 70, want_acc=True)
+        rows.copy_(torch.from_numpy(x))
+        for t in (dev(x), rows):
+            _, acc, sc = B.mpgemm_f32(packed, 0.5, t, 70, want_acc=True, want_scales=True)
+            assert torch.equal(acc, want)
+            assert torch.equal(sc.view(torch.int32), scales.view(torch.int32))
