@@ -226,13 +226,16 @@ def test_nine_to_sixteen_tokens_on_few_rows(B, M, K, N, kernel):
 
 # The tiles whose operands are loaded straight to LDS: one to eight passes of the K loop (three slots, two register sets), K that ends
 # anywhere in a step, tiles that the matrix fills (stored without checks, past the caches from 16 MB on) and cuts.
-@pytest.mark.parametrize("M,K,N,workgroup", [
+TILES_LOADED_TO_LDS = [
     (3328, 4, 640, (128, 128, 2)), (8307, 260, 238, (128, 128, 2)), (8448, 516, 256, (128, 128, 2)), (11187, 780, 167, (128, 128, 2)),
     (3840, 1300, 1024, (128, 128, 2)), (3840, 1544, 1000, (128, 128, 2)), (11008, 4, 384, (256, 128, 2)), (11266, 260, 384, (256, 128, 2)),
     (11008, 516, 384, (256, 128, 2)), (14336, 1540, 512, (256, 128, 2)), (9628, 4, 793, (256, 128, 1)), (14592, 132, 640, (256, 128, 1)),
     (11264, 388, 768, (256, 128, 1)), (13429, 812, 518, (256, 128, 1)), (3840, 520, 384, (128, 64, 4)), (14336, 1032, 67, (128, 64, 4)),
     (10888, 1156, 65, (128, 64, 2)), (8448, 2592, 128, (128, 64, 2)), (11261, 3944, 65, (128, 64, 2)), (9804, 4920, 100, (128, 64, 4)),
-    (4096, 9220, 512, (128, 64, 4)), (2052, 1336, 1000, (160, 64, 4)), (2560, 2560, 1024, (160, 64, 4)), (10881, 2180, 190, (160, 64, 4))])
+    (4096, 9220, 512, (128, 64, 4)), (2052, 1336, 1000, (160, 64, 4)), (2560, 2560, 1024, (160, 64, 4)), (10881, 2180, 190, (160, 64, 4))]
+
+
+@pytest.mark.parametrize("M,K,N,workgroup", TILES_LOADED_TO_LDS)
 def test_tiles_loaded_to_lds(B, M, K, N, workgroup):
     assert B.query_matrix_plan("codes", M, K, N)[:3] == workgroup
     print(f"tile case {workgroup} M={M} K={K} N={N}", flush=True)

@@ -18,24 +18,26 @@ def B(vlut_lib_path):
 
 
 def built_tiles():
-    """(rows, tokens, parts of K) of every row of kGemmTiles, and of those that are built for five weights per byte."""
+    """(rows, tokens, parts of K) of every row of kGemmTiles, of those that are built for five weights per byte, and of kGemmTilesLong."""
     text = open(os.path.join(ROOT, "paper_2512_06443_amd", "csrc", "gemm_kernel.hip.h")).read()
-    table = re.search(r"kGemmTiles\[\] = \{\n(.*?)\n\};", text, flags=re.S).group(1)
-    four, five = set(), set()
-    for line in table.splitlines():
-        numbers = [float(v) for v in re.findall(r"[0-9.]+", line.split("//")[0])]
-        rt, ct, wm, wk = (int(v) for v in numbers[:4])
-        four.add((32 * rt * wm, 32 * ct, wk))
-        if numbers[-1] > 0.0:
-            five.add((32 * rt * wm, 32 * ct, wk))
-    return four, five
+    four, five, long_k = set(), set(), set()
+    for name, tiles in (("kGemmTiles", four), ("kGemmTilesLong", long_k)):
+        table = re.search(name + r"\[\] = \{\n(.*?)\n\};", text, flags=re.S).group(1)
+        for line in table.splitlines():
+            numbers = [float(v) for v in re.findall(r"[0-9.]+", line.split("//")[0])]
+            rt, ct, wm, wk = (int(v) for v in numbers[:4])
+            tiles.add((32 * rt * wm, 32 * ct, wk))
+            if numbers[-1] > 0.0:
+                five.add((32 * rt * wm, 32 * ct, wk))
+    return four, five, long_k
 
 
 def test_gpu_tests_run_every_workgroup(B):
     from tests import test_codes_gpu as G
+    from tests import test_gemm_gpu as T
     few = {(16 * mt, 8 * ch, 16 // mt) for mt in (1, 2, 4, 8) for ch in (1, 2)}
-    four, five = built_tiles()
-    assert len(four) == 8 and len(five) == 5
+    four, five, long_k = built_tiles()
+    assert len(four) == 8 and len(five) == 5 and len(long_k) == 3
     for form, M, K, N, workgroup in G.WORKGROUPS:
         assert B.query_matrix_plan(form, M, K, N)[:3] == workgroup, (form, M, K, N)
         assert M % workgroup[0] and N % workgroup[1], (form, M, K, N)
@@ -43,6 +45,10 @@ def test_gpu_tests_run_every_workgroup(B):
     assert run["codes"] == few | four and run["g5"] == few | five and run["mixed"] >= five
     # the tile without parts of K, also at sizes whose outputs are stored past the caches
     assert any(w == (256, 128, 1) and 4 * M * N >= 16 << 20 for _, M, _, N, w in G.WORKGROUPS)
+    # the tiles from ten macro steps of 128 on: where they divide nothing, and the last step neither
+    for M, K, N, workgroup in T.TILES_LOADED_TO_LDS:
+        assert B.query_matrix_plan("codes", M, K, N)[:3] == workgroup, (M, K, N)
+    assert long_k == {w for M, K, N, w in T.TILES_LOADED_TO_LDS if K > 9 * 128 and M % w[0] and N % w[1] and K % 128}
 
 
 def test_gpu_tests_run_two_chunks_up_to_their_largest_k(B):
