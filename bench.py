@@ -42,8 +42,15 @@ MFMA_INT8_PEAK_TOPS = 5000.0                              # dense INT8 matrix-co
 
 # HBM bytes per launch of the product's kernel measured with rocprofv3 --pmc (FETCH_SIZE, WRITE_SIZE), see profiles/
 MEASURED_TRAFFIC_BYTES = {
-    "llama8b_linears/gateup/512": 45.3e6,  # profiles/gemm_kernel_llama8b_gateup_n512_sq_counters_hbm_traffic.md
+    "llama8b_linears/gateup/512": 45.3e6,  # profiles/tiles_loaded_to_lds_llama8b_gateup_down_n512_sq_counters_hbm_traffic.md
 }
+
+
+def tiled_kernel(rows, tokens, parts, K):
+    """The kernel of a tiled product from four weights per byte, by its workgroup."""
+    if (rows, tokens, parts) in ((128, 64, 4), (160, 64, 4)) and -(-K // 128) >= 10:
+        return "gemm_private_kernel"
+    return "gemm_ring_kernel" if rows >= 128 else "gemm_kernel"
 
 
 def parse_args():
@@ -462,9 +469,11 @@ def main():
             sys.exit(4)
         g5 = {"what": "vlut_mpgemm_mixed on the same weights (first 20*floor(K/20) features 5 per byte, the rest 4 per byte)",
               "ms": ms_mx, "packed_weight_bytes": case.poolx[0].numel(), "time_over_2bit": ms_mx / ms_gemm}
+    plan = B.query_matrix_plan("f32", M, K, N)
     kernel_name = {"matrix_few_tokens": "decode_kernel (few tokens: quantisation, unpacking, INT8 matrix cores and scale in one launch)",
                    "matrix_few_codes": "decode_codes_kernel (few tokens from INT8 codes: unpacking, INT8 matrix cores and scale)",
-                   "matrix": "gemm_kernel (packed bytes unpacked in registers, INT8 matrix cores, scale)",
+                   "matrix": f"{tiled_kernel(*plan[:3], K)} ({plan[0]} x {plan[1]} tiles, K in {plan[2]} parts: packed bytes unpacked in registers, INT8 "
+                             "matrix cores, scale)" if plan else None,
                    "few_tokens": "narrow_kernel (few tokens: table build, lookups and scale)",
                    "lookup": "lookup_kernel (LDS table build, lookup-accumulate, scale)"}[head["kernel"]]
     ops = 2.0 * M * K * N

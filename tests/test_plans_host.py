@@ -60,3 +60,24 @@ def test_gpu_tests_run_two_chunks_up_to_their_largest_k(B):
         assert any(largest < K <= largest + 4 and N > 8 and plans[M, K, N][1] == 8 for M, K, N in shapes)      # one beyond: one chunk
         assert any(K >= largest - 4 and (N + 7) // 8 % 2 == 0 and N % 8 for _, K, N in two)                    # a partly filled second chunk
         assert any((N + 7) // 8 % 2 == 1 for _, _, N in two)                                                    # an absent one
+
+
+def test_bench_names_the_kernel_of_a_tile():
+    """bench.py against the two conditions that choose the kernel (gemm_ring_built, gemm_private_built) for every tile and K it is considered at."""
+    import bench
+    csrc = os.path.join(ROOT, "paper_2512_06443_amd", "csrc")
+    tables = open(os.path.join(csrc, "gemm_kernel.hip.h")).read()
+
+    def condition(name):
+        text = open(os.path.join(csrc, f"gemm_{name}_kernel.hip.h")).read()
+        c = re.search(rf"gemm_{name}_built\(.*?\) {{ return (.*?); }}", text).group(1)
+        return c.replace("&&", "and").replace("||", "or")
+    ring, private = condition("ring"), condition("private")
+    for name, first, last in (("kGemmTiles", 4, 14336), ("kGemmTilesLong", 1156, 14336)):
+        table = re.search(name + r"\[\] = \{\n(.*?)\n\};", tables, flags=re.S).group(1)
+        for line in table.splitlines():
+            rt, ct, wm, wk = (int(v) for v in re.findall(r"\d+", line)[:4])
+            tile = {"gw": 4, "rt": rt, "ct": ct, "wm": wm, "wk": wk}
+            want = "gemm_private_kernel" if eval(private, {}, tile) else "gemm_ring_kernel" if eval(ring, {}, tile) else "gemm_kernel"
+            for K in (first, last) if (rt, ct) != (2, 2) else (first, 1152):      # 128 x 64 in four parts: two kernels, by K
+                assert bench.tiled_kernel(32 * rt * wm, 32 * ct, wk, K) == want, (rt, ct, wm, wk, K)
