@@ -326,13 +326,8 @@ def test_degenerate_shapes_through_every_entry_point(B, M, K, N):
     check_y(y1.cpu().numpy(), y_ref)
 
 
-# The last K of each N: more than the twelve steps of a wave whose values stay in registers.
-@pytest.mark.parametrize("N,K", [(N, K) for N, Ks in ((1, (4, 252, 3076, 61444)), (2, (4, 252, 1028, 29700)), (3, (252, 1028, 14900)),
-                                                      (8, (4, 252, 3076, 7940)), (9, (252, 1028, 4000)), (16, (4, 1028, 3076))) for K in Ks])
-def test_few_tokens_with_values_that_need_the_clamp(B, N, K):
-    """One launch for a few tokens against the quantiser alone: rows with NaN, with infinities, where 127 / absmax overflows, of zeros, of
-    nothing but NaN and of none of these, each alone (one token) and beside the others."""
-    assert B.query_kernel("f32", 70, K, N) == "matrix_few_tokens"
+def few_tokens_with_values_that_need_the_clamp(B, N, K, kernel):
+    assert B.query_kernel("f32", 70, K, N) == kernel
     rng = np.random.default_rng(100 * K + N)
     W = rng.integers(-1, 2, size=(70, K)).astype(np.int8)
     packed = B.pack_weights(dev(W))
@@ -354,3 +349,17 @@ def test_few_tokens_with_values_that_need_the_clamp(B, N, K):
             _, acc, sc = B.mpgemm_f32(packed, 0.5, t, 70, want_acc=True, want_scales=True)
             assert torch.equal(acc, want)
             assert torch.equal(sc.view(torch.int32), scales.view(torch.int32))
+
+
+@pytest.mark.parametrize("K", [4, 252, 1028, 3076, 4000])
+@pytest.mark.parametrize("N", [1, 2, 3, 8, 9, 16])
+def test_few_tokens_with_values_that_need_the_clamp(B, N, K):
+    """One launch for a few tokens against the quantiser alone: rows with NaN, with infinities, where 127 / absmax overflows, of zeros, of
+    nothing but NaN and of none of these, each alone (one token) and beside the others."""
+    few_tokens_with_values_that_need_the_clamp(B, N, K, "few_tokens" if (N, K) == (16, 4000) else "matrix_few_tokens")
+
+
+@pytest.mark.parametrize("N,K", [(1, 61444), (2, 29700), (3, 14900), (8, 7940), (16, 3112)])
+def test_few_tokens_with_values_that_need_the_clamp_beyond_the_registers(B, N, K):
+    """More than the twelve steps of K whose values a wave keeps (from nine tokens on: more than 3072 values)."""
+    few_tokens_with_values_that_need_the_clamp(B, N, K, "matrix_few_tokens")
