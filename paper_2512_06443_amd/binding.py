@@ -112,7 +112,8 @@ def lib() -> ctypes.CDLL:
 # The products take the lean form of the call: no workspace is allocated where the kernel leaves it alone (0.75 us each).
 # Host time of a call, Python / native form, us (640 x 2560, four tokens; the launch alone is 2.2): quantize_act 7.9 / 4.9,
 # mpgemm 7.6 / 4.4, with y and workspace given 5.5 / 3.4, mpgemm_g5 and mpgemm_mixed 4.5, mpgemm_f32 7.6 / 4.4; with a workspace for
-# each call, a launch by <<< >>> and the rules worked out anew 5.3, 4.6, 3.6, 5.9 and 4.5.
+# each call, a launch by <<< >>> and the rules worked out anew 5.3, 4.6, 3.6, 5.9 and 4.5 (hosts differ: the native forms 4.5, 3.8, 2.9, 3.9
+# and 3.8 on another; with a layer's four matrices in turn within 0.2 of that).
 _native = None
 _NATIVE_ORDER = ("vlut_quantize_act", "vlut_mpgemm_lean", "vlut_workspace_used", "vlut_mpgemm_f32", "vlut_workspace_bytes_f32", "vlut_mpgemm_g5_lean",
                  "vlut_workspace_used_g5", "vlut_mpgemm_mixed_lean", "vlut_workspace_used_mixed", "vlut_pack_weights",

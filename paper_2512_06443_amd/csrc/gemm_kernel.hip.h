@@ -27,7 +27,7 @@ typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
 // What bounds it (rates of this chip, measured): power.  13.5 ns per v_mfma_i32_32x32x32_i8 and SIMD on zeros (2.38 GHz), 16.8 on codes and
 // ternary weights (1.95 GHz, 4.0 POP/s), 18.5 with four byte permutes beside each (1.88 GHz, 3.6 POP/s); LDS serves transposing reads at
 // 183 and writes at 71 bytes per clock.  With CT = 4 a wave spends 3.3 unpacking instructions per matrix instruction, hence the wide
-// token tile.  The larger tiles with four weights per byte are gemm_ring_kernel's.
+// token tile.  The larger tiles with four weights per byte are gemm_ring_kernel's and gemm_private_kernel's.
 // ---------------------------------------------------------------------------------------------
 struct GemmParams {
     const uint8_t* packed;
@@ -532,9 +532,9 @@ __global__ void __launch_bounds__(64 * WM * WK, 2) gemm_kernel(const GemmParams 
 // and stored wide, which makes the larger ones 7 to 19 % faster: of 450 shapes timed with that the tile of the least cost is still within 0.4 % of
 // the fastest on average (3 % of them beyond 5 %), and constants fitted to the new times rank no better.
 // With one K group two workgroups of four waves share a compute unit, and one stores while the other multiplies: 13824 x 2560 x 1024
-// 45.7 -> 42.0 us (34.1 now); 128 rows x 64 tokens: 4096 x 14336 x 512 40.1 -> 36.0 us (31.4 now).
+// 45.7 -> 42.0 us; 128 rows x 64 tokens: 4096 x 14336 x 512 40.1 -> 36.0 us (both of gemm_kernel, which runs neither now).
 // Five weights per byte take more registers than four: 64 x 64 133 per lane, so that one workgroup has a unit to itself (per_unit), 256 x 128
-// all 256 and 12 bytes of scratch (at most 2 % of a launch: 13620 x 260 x 281 11.4 -> 11.5 us against the unpacking before, which did
+// all 256 and three in scratch (at most 2 % of a launch: 13620 x 260 x 281 11.4 -> 11.5 us against the unpacking before, which did
 // without; 8 % faster than with that on average of 31 shapes).
 struct GemmTile {
     int rt, ct, wm, wk;
@@ -555,9 +555,11 @@ constexpr GemmTile kGemmTiles[] = {
 };
 constexpr int kGemmTileCount = (int)(sizeof(kGemmTiles) / sizeof(kGemmTiles[0]));
 
-// More tiles for four weights per byte, considered from ten macro steps on (below, the choice among the others stays as it was, although 128 x 64
-// in two groups is often the faster one there too: 7117 x 328 x 569 10.5 / 8.7 us).  Fitted on the scale of the others to graph replays of 150
-// shapes of 400 to 14336 rows, K = 256 to 14336 and 48 to 1024 tokens.  In us:
+// More tiles for four weights per byte, considered from ten macro steps on.  Fitted on the scale of the others to graph replays of 150
+// shapes of 400 to 14336 rows, K = 256 to 14336 and 48 to 1024 tokens.  Of the 47 with fewer steps the tile of the least cost among kGemmTiles is 7 % behind
+// the fastest of all on average (43 % of them beyond 5 %, worst 28 %: 7117 x 328 x 569 10.5 / 8.7 us); with 128 x 64 in two groups among them it
+// would be 2 % (15 %, worst 23 %: 12800 x 256 x 528 9.5 / 11.7 us, where it would displace 256 x 128).  The line is where its constants rank without
+// such losses; one fitted for short K does not exist yet.  In us:
 //   128 x 64 in two K groups: 78 KB of LDS and 90 registers, so that two workgroups share a unit; 6912 x 2560 x 256 9.6 -> 9.3, 4870 x 1892 x 821 16.5 -> 13.8
 //   128 x 64 in four groups of one wave (gemm_private_kernel), long K: 4096 x 14336 x 512 32.1 -> 30.7, 4864 x 7552 x 225 17.4 -> 17.3
 //   160 x 64 so (gemm_private_kernel), where it fills the units as the others don't: 2560 x 6912 x 1024 25.2 -> 22.2

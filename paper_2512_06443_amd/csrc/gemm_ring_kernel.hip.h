@@ -14,9 +14,10 @@ namespace {
 //   - raw weights (private to the wave) are read once per step, 16 bytes per lane, into the register set that is not in use.
 // The loop is unrolled over slots and register sets, so that every LDS address is a register and a constant (addresses worked out per
 // step cost 9 %: 1470 -> 1610 cycles).  Cycles per pass, gemm_kernel /
-// this one: 256 x 128 2800 / 2500 (one K group 1950 / 1660), 128 x 128 1762 / 1500, 128 x 64 2240 / 1900.  us per launch back to back, gemm_kernel
-// storing dword by dword / this one: 14336 x 4096 x 512 32.4 / 28.7, 13824 x 2560 x 1024 42.0 / 34.1, 2560 x 6912 x 1024 27.2 / 23.2, 2560 x 2560
-// x 1024 14.1 / 12.5, 4096 x 14336 x 512 36.5 / 31.4.  What is left of a pass beyond the matrix cores is LDS reads and the power limit (1.8 to 2.1
+// this one: 256 x 128 2800 / 2450 to 2490 (one K group 1950 / 1480 to 1500), 128 x 128 1762 / 1400 to 1430, 128 x 64 in four K groups 2240 / 1760 to 1850.  us
+// per launch back to back on one card, gemm_kernel storing dword by dword / this one: 14336 x 4096 x 512 32.4 / 28.7, 13824 x 2560 x 1024 42.0 / 34.1,
+// 2560 x 6912 x 1024 27.2 / 23.2, 2560 x 2560 x 1024 14.1 / 12.5, 4096 x 14336 x 512 36.5 / 31.4 (other cards are up to a tenth slower: the first
+// 29 to 32).  What is left of a pass beyond the matrix cores is LDS reads and the power limit (1.8 to 2.1
 // GHz where every unit works).  v_mfma_i32_16x16x64_i8 draws less (14.5 ns for the work of 16.5) but takes twice the
 // issue slots beside 3.3 unpacking instructions: 2 to 3 % faster than this loop at 256 x 128, 7 % slower at 128 x 128: not taken.
 //

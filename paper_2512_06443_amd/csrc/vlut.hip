@@ -532,7 +532,7 @@ F32Layout work_out_f32_layout(int64_t M, int64_t K, int64_t N) {
     return L;
 }
 
-// (kept per shape like the routes from codes: asked for twice per call)
+// (kept like the routes from codes, in a smaller table with the same kind of places; asked for twice per call)
 struct F32Entry {
     int64_t M, K, N;
     F32Layout layout;
@@ -888,9 +888,11 @@ int launch_codes(const CodesPlan& pl, const uint8_t* packed, float w_scale, cons
     return pl.ch == 1 ? launch_codes_mt<5, 1>(pl.mt, q, stream) : launch_codes_mt<5, 2>(pl.mt, q, stream);
 }
 
-// ---- what a product from INT8 codes runs and demands, worked out once per shape: the rules above and the plans of the lookup kernels
-// cost 0.4 us (2-bit) to 2 us (five weights per byte: its plan search twice) of a call of 5, so the last answers are kept per thread,
-// found by their shape, until a plan is forced or released.
+// ---- what a product from INT8 codes runs and demands: the rules above and the plans of the lookup kernels, which a call asks for twice (the
+// size of the workspace, then the launch).  The last answers are kept per thread until a plan is forced or released, in a table where every
+// shape has one place.  Shapes that fall on the same place replace each other: of a layer's four stacked matrices (3840, 2560, 13824 x 2560 and
+// 2560 x 6912) the first and the last share one and the others another, so that in turn each is worked out once per call, which
+// costs 0.03 to 0.2 us (2-bit), 0.6 (mixed) or 0.9 (1.60-bit, whose plans are searched anew) of a call of 4 to 5; repeated shapes are found.
 enum { kRouteTables = 0, kRouteCodes = 1, kRouteGemm = 2 };
 struct Route {
     int64_t M, K, N;                             // M = 0: none kept here
