@@ -474,9 +474,10 @@ int pack_parts(const int8_t* w, int64_t M, int64_t K, int64_t K5, uint8_t* packe
 //      spreads the tokens over workgroups; its time grows with their number, hence with M.  The line between them is fitted to
 //      M = 4 to 1000 (decode / table: 100 x 4096 x 12 8.2 / 8.7 us, 100 x 4680 x 14 10.3 / 9.5, 4 x 6552 x 9 11.5 / 10.6; 1000 x 4096 x 16
 //      level): within 3 % of the faster one, 5 % at M = 4.
-//      All of this is older than decode_codes_kernel behind the quantiser, which these rules don't weigh: graph replays, one launch / two,
-//      100 x 4680 x 14 8.7 / 6.3 us, 1000 x 4680 x 14 9.2 / 6.4, 100 x 4096 x 12 7.1 / 5.8, 2560 x 6912 x 8 8.6 / 7.0, 2560 x 2560 x 16 6.3 / 6.0,
-//      13824 x 2560 x 16 7.6 / 7.2, but 640 x 2560 x 8 5.0 / 5.3, 13824 x 2560 x 1 4.7 / 6.3.
+//      All of this is older than decode_codes_kernel behind the quantiser, which these rules don't weigh, and than the shorter quantisation in
+//      decode_kernel.  Graph replays, one launch / two, now: table kernel 100 x 4680 x 14 8.5 / 6.3 us, 1000 x 4680 x 14 8.8 / 6.3; decode_kernel
+//      100 x 4096 x 12 5.7 / 5.65, 2560 x 6912 x 8 7.1 / 6.9, but 2560 x 2560 x 16 5.0 / 5.8, 13824 x 2560 x 16 6.2 / 6.9, 640 x 2560 x 8
+//      4.1 / 5.3, 13824 x 2560 x 1 4.5 / 6.2.
 constexpr int64_t kDecodeMaxValues = 65536;
 bool decode_applies(int64_t M, int64_t K, int64_t N) {
     if (lookup_plan_forced() || N > 16 || N * K > kDecodeMaxValues || M > 256 * 128) return false;
